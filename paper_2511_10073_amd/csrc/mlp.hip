@@ -21,9 +21,9 @@
 // tiles fill them (slots 8g..8g+3 hold hidden units 32p+4g..+3, slots
 // 8g+4..8g+7 hold 32p+16+4g..+3), and the weights are loaded into the A
 // operand with the same permutation of K, so no data moves between lanes.  Training runs forward and
-// backward in float32 with the same bfloat16 rounding points (weights,
-// features and hidden activations), gradients straight through the
-// rounding, accumulated per workgroup in a fixed order and reduced in a
+// backward with the same bfloat16 rounding points (weights, features and
+// hidden activations) and float32 accumulation, gradients straight through
+// the rounding, accumulated per workgroup in a fixed order and reduced in a
 // fixed order.
 #include <algorithm>
 
@@ -47,6 +47,8 @@ typedef short v4s __attribute__((ext_vector_type(4)));
 typedef short v8s __attribute__((ext_vector_type(8)));
 typedef __bf16 v8bf __attribute__((ext_vector_type(8)));
 typedef float v4f __attribute__((ext_vector_type(4)));
+typedef int v2i __attribute__((ext_vector_type(2)));
+typedef int v4i __attribute__((ext_vector_type(4)));
 
 // Hidden unit of K slot q (0..31) of chunk p in the layers contracting over
 // the hidden units (see above).
@@ -425,17 +427,305 @@ __global__ void __launch_bounds__(kBT) k_colstat_final(LearnArgs a, const double
 // ---------------------------------------------------------------- training
 
 constexpr int kTS = 32;           // samples per tile
-constexpr int kGradGrid = 240;    // workgroups (fixed: fixes the summation order)
+constexpr int kGradGrid = 240;    // workgroups of the float32-operand form (fixed: fixes the summation order)
+constexpr int kGradMax = 512;     // most workgroups of the matrix-core form: two per CU, its occupancy
 
-// Q: the inference's bfloat16 rounding points (weights, features, hidden
-// activations); without, float32 operands throughout.
-template <bool Q>
-__device__ __forceinline__ float qround(float x) {
-    if constexpr (Q) return bf16_round(x);
-    else return x;
+// The gradient with the inference's bfloat16 rounding points, on the matrix
+// cores.  A wave takes 32 samples at a time.  Every product below has
+// operands that are bfloat16 exactly (or float32 on the float32 matrix
+// instruction), so nothing is rounded that the float32 form keeps:
+//   z1, z2, o      weights, features and hidden activations are bfloat16 by
+//                  the rounding points; b1 rides in layer 1's unused K slots
+//                  as its three bfloat16 parts (x = hi + mid + lo holds all
+//                  24 bits of a float32).
+//   dz1            = [z1 > 0] do u,  u = W2^T (w3 [z2 > 0]): w3 masked is bfloat16.
+//   gW2[h][k]      = w3_h sum_s [z2 > 0] do_s a1_sk: do_s as its three
+//                  bfloat16 parts, one product each; gb2 the same without a1,
+//                  gw3 = sum_s do_s a2 likewise.
+//   gW1, gb1       sum over samples of dz1 (float32) times the features and a
+//                  column of ones, with v_mfma_f32_16x16x4_f32.
+// Contractions over hidden units need a lane to hold hidden units of one
+// sample, contractions over samples need samples of one hidden unit.  A tile
+// product gives one or the other by the order of its operands (the same
+// registers), so z1 and z2 are formed both ways and nothing moves between
+// lanes.  The weights' operands sit in LDS in fragment order.
+//
+// What bounds it: the matrix instructions, about 1,450 SIMD cycles per 16
+// samples (three quarters of them in gW2 and gW1), beside about as many
+// cycles of vector work (masks, packing).  1.6M samples take 0.166 ms where
+// the LDS tiles in float32 took 13.28 (5,000: 39 against 89 us with Adam);
+// the gradient's error against 64 bits went from 7.5e-7 to 4.5e-7.
+// bfloat16 of relu(z), NaN -> 0: the median of z, 0 and infinity (inf: a
+// register, since with a constant the compiler takes two instructions).  The
+// empty asm keeps the packed words as they are: the compiler otherwise
+// converts each half again for the masks taken from them.
+__device__ __forceinline__ v4s relu_pack(v4f z, float inf) {
+    auto relu = [&](float x) { return __builtin_amdgcn_fmed3f(x, 0.f, inf); };
+    v2i w = {__builtin_bit_cast(int, __builtin_convertvector((v2f{relu(z[0]), relu(z[1])}), v2bf)),
+             __builtin_bit_cast(int, __builtin_convertvector((v2f{relu(z[2]), relu(z[3])}), v2bf))};
+    asm("" : "+v"(w));
+    return __builtin_bit_cast(v4s, w);
 }
 
-template <bool Q>
+__device__ __forceinline__ v8s join(v4s a, v4s b) { return __builtin_shufflevector(a, b, 0, 1, 2, 3, 4, 5, 6, 7); }
+
+// All ones in the halves whose (non-negative) bfloat16 is not zero.
+__device__ __forceinline__ v4i nonzero(v8s a) {
+    const v4i w = __builtin_bit_cast(v4i, a);
+    v4i m;
+#pragma unroll
+    for (int k = 0; k < 4; ++k) {
+        const int x = w[k];
+        m[k] = __builtin_bit_cast(int, v2s{0, 0} - __builtin_elementwise_min(__builtin_bit_cast(v2s, x), v2s{1, 1}));
+    }
+    return m;
+}
+
+__device__ __forceinline__ v8s masked(v4i m, v8s a) {
+    v4i w = m & __builtin_bit_cast(v4i, a);
+    asm("" : "+v"(w));      // (whole words: the compiler otherwise ands the halves)
+    return __builtin_bit_cast(v8s, w);
+}
+
+// x = hi + mid + lo, each bfloat16 (exact for finite x whose parts are normal).
+__device__ __forceinline__ void split3(v2f x, v2s (&p)[3]) {
+#pragma unroll
+    for (int c = 0; c < 3; ++c) {
+        const v2bf h = __builtin_convertvector(x, v2bf);
+        p[c] = __builtin_bit_cast(v2s, h);
+        x -= __builtin_convertvector(h, v2f);
+    }
+}
+
+// A wave's 32 samples on their way to LDS: feature floats l, l + 64, ... and
+// (lanes below 32) one target; zeros past sample n.
+struct GradTile {
+    float x[4], t;
+};
+
+__device__ __forceinline__ void load_grad_tile(const float* __restrict__ feats, const float* __restrict__ target,
+                                               int64_t s0, int64_t n, GradTile& T) {
+    const int l = lane_id();
+    const int64_t left = n - s0;                 // >= 1
+    const int nf = left < kTS ? static_cast<int>(left) * kFP : kTS * kFP;
+#pragma unroll
+    for (int q = 0; q < 4; ++q) {
+        const int e = l + kWave * q;
+        T.x[q] = feats[s0 * kFP + (e < nf ? e : nf - 1)];
+        if (e >= nf) T.x[q] = 0.f;
+    }
+    T.t = target[s0 + (l < left ? l % kTS : 0)];
+}
+
+__global__ void __launch_bounds__(kBT, 2) k_mlp_grad_mfma(const float* __restrict__ P, const float* __restrict__ feats,
+                                                          const float* __restrict__ target, int64_t n, float inv_n,
+                                                          float* __restrict__ part, double* __restrict__ loss_part) {
+    __shared__ v8s w2f[8][kWave];        // W2 rows as operands (output 16n+i, K slots over the inputs), index 2n + p
+    __shared__ v8s w2tf[8][kWave];       // W2 columns (input 16n+i, K slots over the outputs)
+    __shared__ __attribute__((aligned(16))) float b2s[kH];
+    // each wave's samples: 8 features (bfloat16 values), a one, zeros; the
+    // row stride keeps gW1's reads (lane group g at rows 4g) off each other's banks
+    constexpr int kXS = 20;
+    __shared__ __attribute__((aligned(16))) float xs[kBT / kWave][kTS][kXS], ts[kBT / kWave][kTS];
+    __shared__ float sum[kNP];
+    __shared__ double lsum[kBT / kWave];
+    const int t = threadIdx.x, l = lane_id(), i = l & 15, g = l >> 4;
+    for (int e = t; e < 8 * kWave; e += kBT) {
+        const int q = e / kWave, el = e % kWave, ei = el & 15, eg = el >> 4, row = 16 * (q >> 1) + ei;
+        v8s a, b;
+#pragma unroll
+        for (int j = 0; j < 8; ++j) {
+            const int h = hid(q & 1, 8 * eg + j);
+            a[j] = bf16_bits(P[oW2 + row * kH + h]);
+            b[j] = bf16_bits(P[oW2 + h * kH + row]);
+        }
+        w2f[q][el] = a;
+        w2tf[q][el] = b;
+    }
+    if (t < kH) b2s[t] = P[oB2 + t];
+    for (int e = t; e < kNP; e += kBT) sum[e] = 0.f;
+    for (int e = t; e < kBT / kWave * kTS * kXS; e += kBT)
+        (&xs[0][0][0])[e] = e % kXS == kFP ? 1.f : 0.f;
+    float inf = INFINITY;
+    asm("" : "+s"(inf));
+    // K slots of layer 1: the 8 features, then b1's three parts against ones
+    v4s w1[4];
+    v8s w3[2];
+    float b2n[4];
+    const float b3 = P[oB3];
+#pragma unroll
+    for (int m = 0; m < 4; ++m) {
+        v2s bp[3];
+        split3(v2f{P[oB1 + 16 * m + i], 0.f}, bp);
+#pragma unroll
+        for (int j = 0; j < 4; ++j) {
+            const short wv = bf16_bits(P[oW1 + (16 * m + i) * kFP + 4 * (g & 1) + j]);
+            w1[m][j] = g < 2 ? wv : g == 2 && j < 3 ? bp[j < 3 ? j : 0][0] : static_cast<short>(0);
+        }
+        b2n[m] = P[oB2 + 16 * m + i];
+    }
+#pragma unroll
+    for (int p = 0; p < 2; ++p)
+#pragma unroll
+        for (int j = 0; j < 8; ++j) w3[p][j] = bf16_bits(P[oW3 + hid(p, 8 * g + j)]);
+    const short kOne = 0x3F80;           // bfloat16 1.0
+    const v4s ones = {g == 2 ? kOne : short(0), g == 2 ? kOne : short(0), g == 2 ? kOne : short(0), 0};
+    const v4f zero = {0.f, 0.f, 0.f, 0.f};
+    v4f gw2[4][4], gw1[4], gv[4];        // gv: columns 0..2 gw3, 4..6 gb2 (one per part of do)
+#pragma unroll
+    for (int m = 0; m < 4; ++m) {
+        gw1[m] = gv[m] = zero;
+#pragma unroll
+        for (int k = 0; k < 4; ++k) gw2[m][k] = zero;
+    }
+    float gb3 = 0.f;
+    double loss = 0;
+    __syncthreads();
+    const int64_t npairs = (n + kTS - 1) / kTS;
+    const int64_t waves = static_cast<int64_t>(gridDim.x) * (kBT / kWave);
+    int64_t pair = static_cast<int64_t>(blockIdx.x) * (kBT / kWave) + wave_id();
+    GradTile cur;
+    if (pair < npairs) load_grad_tile(feats, target, pair * kTS, n, cur);
+    float (*X)[kXS] = xs[wave_id()];
+    float* T = ts[wave_id()];
+    for (; pair < npairs; pair += waves) {
+#pragma unroll
+        for (int q = 0; q < 4; ++q) X[(l + kWave * q) / kFP][l % kFP] = bf16_round(cur.x[q]);
+        if (l < kTS) T[l] = cur.t;
+        // (LDS serves a wave's accesses in order; the compiler keeps them so)
+        __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+        __builtin_amdgcn_wave_barrier();
+        const int left = n - pair * kTS < kTS ? static_cast<int>(n - pair * kTS) : kTS;
+        if (pair + waves < npairs) load_grad_tile(feats, target, (pair + waves) * kTS, n, cur);
+        v4s a1n[2][4], a2n[2][4];        // samples 4g..4g+3 of hidden unit 16m+i
+        v4s dp[2][3];                    // the parts of do of samples 4g..4g+3
+#pragma unroll
+        for (int u = 0; u < 2; ++u) {
+            const v4f xt = *reinterpret_cast<const v4f*>(&X[16 * u + i][4 * (g & 1)]);
+            const v2bf x01 = __builtin_convertvector((v2f{xt[0], xt[1]}), v2bf);
+            const v2bf x23 = __builtin_convertvector((v2f{xt[2], xt[3]}), v2bf);
+            v4s x = __builtin_shufflevector(__builtin_bit_cast(v2s, x01), __builtin_bit_cast(v2s, x23), 0, 1, 2, 3);
+            x = g < 2 ? x : ones;
+            v4s h1[4], h2[4];
+#pragma unroll
+            for (int m = 0; m < 4; ++m)
+                h1[m] = relu_pack(__builtin_amdgcn_mfma_f32_16x16x16bf16_1k(w1[m], x, zero, 0, 0, 0), inf);
+            const v8s a1t[2] = {join(h1[0], h1[1]), join(h1[2], h1[3])};
+#pragma unroll
+            for (int m = 0; m < 4; ++m) {
+                const v8s wa = w2f[2 * m][l], wb = w2f[2 * m + 1][l];
+                v4f zt = *reinterpret_cast<const v4f*>(&b2s[16 * m + 4 * g]);
+                v4f zn = {b2n[m], b2n[m], b2n[m], b2n[m]};
+                zt = mfma32(wa, a1t[0], zt);
+                zn = mfma32(a1t[0], wa, zn);
+                zt = mfma32(wb, a1t[1], zt);
+                zn = mfma32(a1t[1], wb, zn);
+                h2[m] = relu_pack(zt, inf);
+                a2n[u][m] = relu_pack(zn, inf);
+            }
+            const v8s a2t[2] = {join(h2[0], h2[1]), join(h2[2], h2[3])};
+            __builtin_amdgcn_sched_barrier(0);
+            // o of samples 4g..4g+3, the same in every column
+            v4f o = {b3, b3, b3, b3};
+            o = mfma32(a2t[0], w3[0], o);
+            o = mfma32(a2t[1], w3[1], o);
+            const v4f want = *reinterpret_cast<const v4f*>(&T[16 * u + 4 * g]);
+            v4f dO;
+#pragma unroll
+            for (int j = 0; j < 4; ++j) {
+                const float e = 16 * u + 4 * g + j < left ? o[j] - want[j] : 0.f;
+                dO[j] = 2.f * e * inv_n;
+                loss += static_cast<double>(e) * e;
+                gb3 += dO[j];
+            }
+            v2s p01[3], p23[3];
+            split3(v2f{dO[0], dO[1]}, p01);
+            split3(v2f{dO[2], dO[3]}, p23);
+#pragma unroll
+            for (int c = 0; c < 3; ++c) dp[u][c] = __builtin_shufflevector(p01[c], p23[c], 0, 1, 2, 3);
+            // dz1 = [z1 > 0] do u, then gW1 and gb1
+            const v8s q0 = masked(nonzero(a2t[0]), w3[0]), q1 = masked(nonzero(a2t[1]), w3[1]);
+            float xb[4];
+#pragma unroll
+            for (int j = 0; j < 4; ++j) xb[j] = X[16 * u + 4 * g + j][i];
+#pragma unroll
+            for (int m = 0; m < 4; ++m) {
+                v4f uz = mfma32(q0, w2tf[2 * m][l], zero);
+                uz = mfma32(q1, w2tf[2 * m + 1][l], uz);
+                const v4f z1 = __builtin_amdgcn_mfma_f32_16x16x16bf16_1k(x, w1[m], zero, 0, 0, 0);
+                a1n[u][m] = relu_pack(z1, inf);
+#pragma unroll
+                for (int j = 0; j < 4; ++j) {
+                    const float dz = z1[j] > 0.f ? dO[j] * uz[j] : 0.f;
+                    gw1[m] = __builtin_amdgcn_mfma_f32_16x16x4f32(dz, xb[j], gw1[m], 0, 0, 0);
+                }
+            }
+        }
+        __builtin_amdgcn_sched_barrier(0);
+        // contractions over the 32 samples: slots 8g..8g+3 hold tile 0's
+        // samples 4g..4g+3, slots 8g+4..8g+7 tile 1's
+        v8s d[3];
+#pragma unroll
+        for (int c = 0; c < 3; ++c) d[c] = join(dp[0][c], dp[1][c]);
+        const v8s dsel = (i & 3) == 0 ? d[0] : (i & 3) == 1 ? d[1] : d[2];
+        const v8s none = {0, 0, 0, 0, 0, 0, 0, 0};
+        const v8s d3 = i < 3 ? dsel : none, d2 = i >= 4 && i < 7 ? dsel : none;
+        v8s a1[4];
+#pragma unroll
+        for (int k = 0; k < 4; ++k) a1[k] = join(a1n[0][k], a1n[1][k]);
+#pragma unroll
+        for (int m = 0; m < 4; ++m) {
+            const v8s a2 = join(a2n[0][m], a2n[1][m]);
+            const v4i mask = nonzero(a2);
+            const v8s unit = {kOne, kOne, kOne, kOne, kOne, kOne, kOne, kOne};
+            gv[m] = mfma32(a2, d3, gv[m]);
+            gv[m] = mfma32(masked(mask, unit), d2, gv[m]);
+#pragma unroll
+            for (int c = 0; c < 3; ++c) {
+                const v8s md = masked(mask, d[c]);
+#pragma unroll
+                for (int k = 0; k < 4; ++k) gw2[m][k] = mfma32(md, a1[k], gw2[m][k]);
+            }
+        }
+    }
+    // the workgroup's sums: its waves one after the other
+#pragma unroll
+    for (int o = 16; o < kWave; o <<= 1) {
+        gb3 += __shfl_xor(gb3, o);
+        loss += __shfl_xor(loss, o);
+    }
+    for (int w = 0; w < kBT / kWave; ++w) {
+        if (wave_id() == w) {
+#pragma unroll
+            for (int m = 0; m < 4; ++m)
+#pragma unroll
+                for (int j = 0; j < 4; ++j) {
+                    const int h = 16 * m + 4 * g + j;
+#pragma unroll
+                    for (int k = 0; k < 4; ++k) sum[oW2 + h * kH + 16 * k + i] += gw2[m][k][j];
+                    if (i < kFP) sum[oW1 + h * kFP + i] += gw1[m][j];
+                    if (i == kFP) sum[oB1 + h] += gw1[m][j];
+                    const float v = gv[m][j] + __shfl_down(gv[m][j], 1) + __shfl_down(gv[m][j], 2);
+                    if (i == 0) sum[oW3 + h] += v;
+                    if (i == 4) sum[oB2 + h] += v;
+                }
+            if (l == 0) {        // (every lane of a group holds the group's samples' values)
+                sum[oB3] += gb3;
+                lsum[w] = loss;
+            }
+        }
+        __syncthreads();
+    }
+    float* pb = part + static_cast<int64_t>(blockIdx.x) * kNP;
+    for (int e = t; e < kNP; e += kBT) {
+        const int h = e >= oW2 && e < oB2 ? (e - oW2) / kH : e >= oB2 && e < oW3 ? e - oB2 : -1;
+        pb[e] = h >= 0 ? sum[e] * bf16_round(P[oW3 + h]) : sum[e];
+    }
+    if (t == 0) loss_part[blockIdx.x] = ((lsum[0] + lsum[1]) + lsum[2]) + lsum[3];
+}
+
+// The gradient with float32 operands throughout (no rounding points), for
+// checking it against a float64 reference: LDS tiles of 32 samples.
 __global__ void __launch_bounds__(kBT) k_mlp_grad(const float* __restrict__ P, const float* __restrict__ feats,
                                                   const float* __restrict__ target, int64_t n, float inv_n,
                                                   float* __restrict__ part, double* __restrict__ loss_part) {
@@ -445,10 +735,10 @@ __global__ void __launch_bounds__(kBT) k_mlp_grad(const float* __restrict__ P, c
     __shared__ float dO[kTS];
     __shared__ double red[kBT / kWave];
     const int t = threadIdx.x;
-    for (int e = t; e < kH * kFP; e += kBT) W1q[e] = qround<Q>(P[oW1 + e]);
-    for (int e = t; e < kH * kH; e += kBT) W2q[e] = qround<Q>(P[oW2 + e]);
+    for (int e = t; e < kH * kFP; e += kBT) W1q[e] = P[oW1 + e];
+    for (int e = t; e < kH * kH; e += kBT) W2q[e] = P[oW2 + e];
     if (t < kH) {
-        w3q[t] = qround<Q>(P[oW3 + t]);
+        w3q[t] = P[oW3 + t];
         b1[t] = P[oB1 + t];
         b2[t] = P[oB2 + t];
     }
@@ -464,7 +754,7 @@ __global__ void __launch_bounds__(kBT) k_mlp_grad(const float* __restrict__ P, c
         {
             int s = t / kFP, f = t % kFP;
             int64_t smp = s0 + s;
-            X[s][f] = smp < n ? qround<Q>(feats[smp * kFP + f]) : 0.f;
+            X[s][f] = smp < n ? feats[smp * kFP + f] : 0.f;
         }
         __syncthreads();
         for (int q = 0; q < 8; ++q) {
@@ -472,7 +762,7 @@ __global__ void __launch_bounds__(kBT) k_mlp_grad(const float* __restrict__ P, c
             float z = b1[h];
             for (int f = 0; f < kFP; ++f) z = __fmaf_rn(X[s][f], W1q[h * kFP + f], z);
             Z1[s][h] = z;
-            A1[s][h] = qround<Q>(z > 0.f ? z : 0.f);
+            A1[s][h] = (z > 0.f ? z : 0.f);
         }
         __syncthreads();
         for (int q = 0; q < 8; ++q) {
@@ -487,7 +777,7 @@ __global__ void __launch_bounds__(kBT) k_mlp_grad(const float* __restrict__ P, c
             float o = b3;
             for (int h = 0; h < kH; ++h) {
                 float z = Z2[t][h];
-                o = __fmaf_rn(qround<Q>(z > 0.f ? z : 0.f), w3q[h], o);
+                o = __fmaf_rn((z > 0.f ? z : 0.f), w3q[h], o);
             }
             if (smp < n) {
                 float e = o - target[smp];
@@ -515,7 +805,7 @@ __global__ void __launch_bounds__(kBT) k_mlp_grad(const float* __restrict__ P, c
             int h = t - 2 * kH;
             for (int s = 0; s < kTS; ++s) {
                 float z = Z2[s][h];
-                gv = __fmaf_rn(dO[s], qround<Q>(z > 0.f ? z : 0.f), gv);
+                gv = __fmaf_rn(dO[s], (z > 0.f ? z : 0.f), gv);
             }
         } else if (t == 3 * kH) {
             for (int s = 0; s < kTS; ++s) gv += dO[s];
@@ -550,18 +840,33 @@ __global__ void __launch_bounds__(kBT) k_mlp_grad(const float* __restrict__ P, c
     if (t == 0) loss_part[blockIdx.x] = ls;
 }
 
-__global__ void k_mlp_grad_final(const float* __restrict__ part, const double* __restrict__ loss_part, double inv_n,
-                                 float* __restrict__ grad, double* __restrict__ loss) {
-    int p = blockIdx.x * blockDim.x + threadIdx.x;
-    if (p < kNP) {
-        float a = 0.f;
-        for (int b = 0; b < kGradGrid; ++b) a += part[static_cast<int64_t>(b) * kNP + p];
-        grad[p] = a;
+// Sums the workgroups' partials in a fixed order: 16 interleaved slices of
+// them per parameter, then the slices.  nb workgroups wrote partials.
+constexpr int kFinalP = 64, kFinalS = 16;
+
+__global__ void __launch_bounds__(kFinalP * kFinalS) k_mlp_grad_final(const float* __restrict__ part,
+                                                                      const double* __restrict__ loss_part, int nb,
+                                                                      double inv_n, float* __restrict__ grad,
+                                                                      double* __restrict__ loss) {
+    __shared__ float slice[kFinalS][kFinalP];
+    const int p0 = blockIdx.x * kFinalP + threadIdx.x % kFinalP, p = p0 < kNP ? p0 : kNP - 1;
+    const int q = threadIdx.x / kFinalP;
+    float a = 0.f;
+#pragma unroll 8
+    for (int b = q; b < nb; b += kFinalS) a += part[static_cast<int64_t>(b) * kNP + p];
+    slice[q][threadIdx.x % kFinalP] = a;
+    __syncthreads();
+    if (threadIdx.x < kFinalP && p0 < kNP) {
+        float v = 0.f;
+#pragma unroll
+        for (int k = 0; k < kFinalS; ++k) v += slice[k][threadIdx.x];
+        grad[p0] = v;
     }
-    if (p == 0 && loss) {
+    if (blockIdx.x == 0 && threadIdx.x / kWave == 1 && loss) {
         double s = 0;
-        for (int b = 0; b < kGradGrid; ++b) s += loss_part[b];
-        *loss = s * inv_n;
+        for (int b = lane_id(); b < nb; b += kWave) s += loss_part[b];
+        s = wave_sum(s);
+        if (lane_id() == 0) *loss = s * inv_n;
     }
 }
 
@@ -666,18 +971,17 @@ void mlp_loss_grad(const float* params, const float* feats, const float* target,
                    double* loss, bool rounding, hipStream_t s) {
     DevBuf<float> part;
     DevBuf<double> lpart;
-    part.ensure(static_cast<size_t>(kGradGrid) * kNP, s);
-    lpart.ensure(kGradGrid, s);
+    // one wave per 32 samples until the grid is full
+    const int64_t need = (n + 4 * kTS - 1) / (4 * kTS);
+    const int nb = !rounding ? kGradGrid : static_cast<int>(std::max<int64_t>(1, std::min<int64_t>(need, kGradMax)));
+    part.ensure(static_cast<size_t>(nb) * kNP, s);
+    lpart.ensure(nb, s);
     const float inv_n = n > 0 ? 1.f / static_cast<float>(n) : 0.f;
-    if (rounding)
-        hipLaunchKernelGGL(k_mlp_grad<true>, dim3(kGradGrid), dim3(kBT), 0, s, params, feats, target, n, inv_n,
-                           part.p, lpart.p);
-    else
-        hipLaunchKernelGGL(k_mlp_grad<false>, dim3(kGradGrid), dim3(kBT), 0, s, params, feats, target, n, inv_n,
-                           part.p, lpart.p);
+    hipLaunchKernelGGL((rounding ? k_mlp_grad_mfma : k_mlp_grad), dim3(nb), dim3(kBT), 0, s, params, feats, target, n,
+                       inv_n, part.p, lpart.p);
     AHR_LAUNCHED("k_mlp_grad");
-    hipLaunchKernelGGL(k_mlp_grad_final, dim3(grid_for(kNP, kBT)), dim3(kBT), 0, s, part.p, lpart.p,
-                       n > 0 ? 1.0 / static_cast<double>(n) : 0.0, grad, loss);
+    hipLaunchKernelGGL(k_mlp_grad_final, dim3(grid_for(kNP, kFinalP)), dim3(kFinalP * kFinalS), 0, s, part.p, lpart.p,
+                       nb, n > 0 ? 1.0 / static_cast<double>(n) : 0.0, grad, loss);
     AHR_LAUNCHED("k_mlp_grad_final");
     part.release(s);
     lpart.release(s);
