@@ -345,16 +345,24 @@ size_t graph_workspace_bytes(const ahr_netlist& nl, const ahr_hint_params& hp, i
 size_t graph_workspace_floor(const ahr_netlist& nl, int32_t ncols);
 // netlist_build.hip
 void build_netlist(Graph& g, hipStream_t s);
-// Stable bucket sort: list = indices i in [0, n) with key[i] >= 0, grouped by
-// key, ascending within a key; start[k] = first position of key k
-// (start[nkeys] = count).  nkeys <= 16384.  list holds n entries.  Returns
-// the count when read_total (one synchronisation), else -1.
-int32_t bucket_sort(Graph& g, const int32_t* key, int32_t n, int nkeys, DevBuf<int32_t>& list,
-                    DevBuf<int32_t>& start, hipStream_t s, bool read_total = true);
+// sort.hip.  Element i in [0, n) stands for value v = idx[i] (i without idx)
+// and has the key (key[i] >> shift) & mask, or none where key[i] < 0.
+struct SortKeys {
+    const int32_t* key;
+    const int32_t* idx = nullptr;
+    int shift = 0;
+    int32_t mask = INT32_MAX;
+    int32_t* inverse = nullptr;    // inverse[v] = the position of v in the list
+    int32_t* sorted = nullptr;     // sorted[position] = key[i], for a next pass over the list
+};
+// Stable bucket sort: list = the values of the elements with a key, grouped
+// by key, in element order within a key; start[k] = first position of key k
+// (start[nkeys] = count).  nkeys <= 16384.  list holds n entries.
+void bucket_sort(Graph& g, const SortKeys& k, int32_t n, int nkeys, DevBuf<int32_t>& list, DevBuf<int32_t>& start,
+                 hipStream_t s);
 // The same with its scratch given (i32a, i32b, scan_tmp: grown as needed).
-int32_t bucket_sort(const int32_t* key, int32_t n, int nkeys, DevBuf<int32_t>& list, DevBuf<int32_t>& start,
-                    DevBuf<int32_t>& i32a, DevBuf<int32_t>& i32b, DevBuf<int64_t>& scan_tmp, hipStream_t s,
-                    bool read_total = true);
+void bucket_sort(const SortKeys& k, int32_t n, int nkeys, DevBuf<int32_t>& list, DevBuf<int32_t>& start,
+                 DevBuf<int32_t>& i32a, DevBuf<int32_t>& i32b, DevBuf<int64_t>& scan_tmp, hipStream_t s);
 // Exact entry counts of g, read from its row pointers when not known yet.
 int32_t net_count(const Graph& g, hipStream_t s);
 int32_t hint_count(const Graph& g, hipStream_t s);

@@ -16,9 +16,6 @@ namespace ahr {
 namespace {
 
 constexpr int kBT = 256;
-constexpr int kMaxBins = 16384;
-constexpr int kTileIters = 32;                 // bucket sort: 64-lane tiles of 32 x 64 cells
-constexpr int kTileCells = kTileIters * kWave;
 constexpr double kAreaQ = 268435456.0;         // bin areas in units of 2^-28 (exact integer sums)
 
 struct Grid {
@@ -159,92 +156,6 @@ __global__ void __launch_bounds__(kBT) k_cell_bins(Grid gr, const float* __restr
         for (int b = threadIdx.x; b < nbins; b += kBT)
             if (area_lds[b]) atomicAdd(&area_q[b], area_lds[b]);
     }
-}
-
-// Stable bucket sort, pass 1: hint cells per (bin, tile), bin-major.
-__global__ void __launch_bounds__(kWave) k_bucket_count(const int32_t* __restrict__ cell_bin, int32_t n, int nbins,
-                                                        int32_t ntiles, int32_t* __restrict__ hist) {
-    extern __shared__ int32_t h[];     // nbins counters (dynamic: occupancy follows the key count)
-    for (int b = threadIdx.x; b < nbins; b += kWave) h[b] = 0;
-    __syncthreads();
-    int64_t base = static_cast<int64_t>(blockIdx.x) * kTileCells;
-    int key[kTileIters];       // the tile's keys, all loads in flight together
-#pragma unroll
-    for (int t = 0; t < kTileIters; ++t) {
-        int64_t i = base + t * kWave + threadIdx.x;
-        key[t] = i < n ? cell_bin[i] : -1;
-    }
-#pragma unroll
-    for (int t = 0; t < kTileIters; ++t)
-        if (key[t] >= 0) atomicAdd(&h[key[t]], 1);
-    __syncthreads();
-    // tile-major: this tile's counters are one contiguous row
-    for (int b = threadIdx.x; b < nbins; b += kWave) hist[static_cast<int64_t>(blockIdx.x) * nbins + b] = h[b];
-}
-
-// out[c][r] = in[r][c] for an rows x cols int32 matrix, through 32 x 32 LDS tiles.
-constexpr int kTr = 32;
-__global__ void __launch_bounds__(kTr * 8) k_transpose_i32(const int32_t* __restrict__ in, int64_t rows,
-                                                            int64_t cols, int32_t* __restrict__ out) {
-    __shared__ int32_t t[kTr][kTr + 1];
-    const int64_t c0 = static_cast<int64_t>(blockIdx.x) * kTr, r0 = static_cast<int64_t>(blockIdx.y) * kTr;
-    const int tx = threadIdx.x % kTr, ty = threadIdx.x / kTr;
-    for (int k = ty; k < kTr; k += 8) {
-        const int64_t r = r0 + k, c = c0 + tx;
-        if (r < rows && c < cols) t[k][tx] = in[r * cols + c];
-    }
-    __syncthreads();
-    for (int k = ty; k < kTr; k += 8) {
-        const int64_t c = c0 + k, r = r0 + tx;
-        if (r < rows && c < cols) out[c * rows + r] = t[tx][k];
-    }
-}
-
-// Pass 2: place every hint cell at offset(bin, tile) + rank among the
-// tile's earlier cells of the same bin (lanes in id order, tiles in order);
-// off is tile-major, like the counts.
-__global__ void __launch_bounds__(kWave) k_bucket_scatter(const int32_t* __restrict__ cell_bin, int32_t n, int nbins,
-                                                          int bits, int32_t ntiles, const int32_t* __restrict__ off,
-                                                          int32_t* __restrict__ out) {
-    extern __shared__ int32_t run[];   // nbins cursors (dynamic)
-    for (int b = threadIdx.x; b < nbins; b += kWave) run[b] = off[static_cast<int64_t>(blockIdx.x) * nbins + b];
-    __syncthreads();
-    int l = threadIdx.x;
-    uint64_t lt = l ? (~0ull >> (kWave - l)) : 0ull;
-    uint64_t gt = (l == kWave - 1) ? 0ull : (~0ull << (l + 1));
-    int64_t base = static_cast<int64_t>(blockIdx.x) * kTileCells;
-    int key[kTileIters];       // the tile's keys, all loads in flight together
-#pragma unroll
-    for (int t = 0; t < kTileIters; ++t) {
-        int64_t i = base + t * kWave + l;
-        key[t] = i < n ? cell_bin[i] : -1;
-    }
-#pragma unroll
-    for (int t = 0; t < kTileIters; ++t) {
-        int64_t i = base + t * kWave + l;
-        int b = key[t];
-        bool valid = b >= 0;
-        uint64_t peer = __ballot(valid);
-        for (int k = 0; k < bits; ++k) {
-            bool bit = valid && ((b >> k) & 1);
-            uint64_t m = __ballot(bit);
-            peer &= bit ? m : ~m;
-        }
-        if (valid) {
-            int rank = __popcll(peer & lt);
-            out[run[b] + rank] = static_cast<int32_t>(i);
-        }
-        __syncthreads();
-        if (valid && (peer & gt) == 0) run[b] += __popcll(peer);
-        __syncthreads();
-    }
-}
-
-__global__ void k_bin_start(const int32_t* __restrict__ off, int nbins, int32_t ntiles,
-                            const int32_t* __restrict__ total, int32_t* __restrict__ bin_start) {
-    int b = blockIdx.x * blockDim.x + threadIdx.x;
-    if (b < nbins) bin_start[b] = off[static_cast<int64_t>(b) * ntiles];
-    if (b == nbins) bin_start[b] = *total;
 }
 
 __device__ __forceinline__ float outward(float c, float h) {
@@ -685,11 +596,6 @@ __global__ void __launch_bounds__(kBT) k_bin_side_fill(HintArgs a, const int32_t
     }
 }
 
-__global__ void k_bin_rank(int32_t n, const int32_t* __restrict__ bin_cells, int32_t* __restrict__ rank) {
-    int64_t t = static_cast<int64_t>(blockIdx.x) * blockDim.x + threadIdx.x;
-    if (t < n) rank[bin_cells[t]] = static_cast<int32_t>(t);
-}
-
 // wpre[b][slot]: entries of bin row b before window slot `slot` (row-major,
 // out-of-grid slots empty).
 __global__ void k_window_prefix(HintArgs a, int32_t* __restrict__ wpre) {
@@ -741,50 +647,6 @@ __global__ void k_fill_u64(unsigned long long* p, int64_t n) {
 }
 
 }  // namespace
-
-int32_t bucket_sort(const int32_t* key, int32_t n, int nkeys, DevBuf<int32_t>& list, DevBuf<int32_t>& start,
-                    DevBuf<int32_t>& i32a, DevBuf<int32_t>& i32b, DevBuf<int64_t>& scan_tmp, hipStream_t s,
-                    bool read_total) {
-    if (nkeys > kMaxBins) throw Error{AHR_EUNSUPPORTED, "too many buckets (at most 16384 bins or macros)"};
-    list.ensure(static_cast<size_t>(n) + 1, s);
-    start.ensure(static_cast<size_t>(nkeys) + 1, s);
-    if (n == 0) {
-        fill_i32(start.p, nkeys + 1, 0, s);
-        return 0;
-    }
-    int32_t ntiles = static_cast<int32_t>((static_cast<int64_t>(n) + kTileCells - 1) / kTileCells);
-    int64_t hn = static_cast<int64_t>(nkeys) * ntiles;
-    i32a.ensure(static_cast<size_t>(hn) + 1, s);
-    i32b.ensure(static_cast<size_t>(hn) + 1, s);
-    const size_t lds = static_cast<size_t>(nkeys) * sizeof(int32_t);
-    // counts tile-major (i32a) -> bucket-major (i32b) -> exclusive scan in
-    // bucket-then-tile order (i32a, total at [hn]) -> tile-major offsets (i32b)
-    hipLaunchKernelGGL(k_bucket_count, dim3(ntiles), dim3(kWave), lds, s, key, n, nkeys, ntiles, i32a.p);
-    AHR_LAUNCHED("k_bucket_count");
-    hipLaunchKernelGGL(k_transpose_i32, dim3((nkeys + kTr - 1) / kTr, (ntiles + kTr - 1) / kTr), dim3(kTr * 8), 0, s,
-                       i32a.p, static_cast<int64_t>(ntiles), static_cast<int64_t>(nkeys), i32b.p);
-    AHR_LAUNCHED("k_transpose_i32");
-    scan_tmp.ensure(scan_tmp_elems(hn), s);
-    scan_i32_to_i32(i32b.p, i32a.p, hn, scan_tmp.p, s);
-    hipLaunchKernelGGL(k_transpose_i32, dim3((ntiles + kTr - 1) / kTr, (nkeys + kTr - 1) / kTr), dim3(kTr * 8), 0, s,
-                       i32a.p, static_cast<int64_t>(nkeys), static_cast<int64_t>(ntiles), i32b.p);
-    AHR_LAUNCHED("k_transpose_i32");
-    int bits = 0;
-    while ((1 << bits) < nkeys) ++bits;
-    hipLaunchKernelGGL(k_bucket_scatter, dim3(ntiles), dim3(kWave), lds, s, key, n, nkeys, bits, ntiles, i32b.p,
-                       list.p);
-    AHR_LAUNCHED("k_bucket_scatter");
-    hipLaunchKernelGGL(k_bin_start, dim3(grid_for(nkeys + 1, kBT)), dim3(kBT), 0, s, i32a.p, nkeys, ntiles,
-                       i32a.p + hn, start.p);
-    AHR_LAUNCHED("k_bin_start");
-    if (!read_total) return -1;
-    return read_i32(start.p + nkeys, s);
-}
-
-int32_t bucket_sort(Graph& g, const int32_t* key, int32_t n, int nkeys, DevBuf<int32_t>& list,
-                    DevBuf<int32_t>& start, hipStream_t s, bool read_total) {
-    return bucket_sort(key, n, nkeys, list, start, g.i32a, g.i32b, g.scan_tmp, s, read_total);
-}
 
 namespace {
 
@@ -913,7 +775,11 @@ void build_hints(Graph& g, const float* pos, int32_t ncols, hipStream_t s, bool 
     AHR_LAUNCHED("k_cell_bins");
 
     // 2. hint cells grouped by bin, ascending execution rows (stable bucket sort)
-    bucket_sort(g, g.cell_bin.p, n_inst, nbins, g.bin_cells, g.bin_start, s, false);
+    // (with each cell's place, which the cell fill of unpruned rows needs)
+    g.bin_rank.ensure(static_cast<size_t>(n_inst) + 1, s);
+    SortKeys by_bin{g.cell_bin.p};
+    by_bin.inverse = g.bin_rank.p;
+    bucket_sort(g, by_bin, n_inst, nbins, g.bin_cells, g.bin_start, s);
 
     // 3. macros: footprints, spans, areas; phi
     const int32_t n_macro = g.n_macro;
@@ -1057,7 +923,7 @@ void build_hints(Graph& g, const float* pos, int32_t ncols, hipStream_t s, bool 
         AHR_LAUNCHED("k_cell_count pairs");
     }
     // pairs grouped by macro, ascending row: the macro virtual rows
-    if (use_macros) bucket_sort(g, g.pair_mac.p, n_pairs, n_macro, g.mlist, g.mstart, s, false);
+    if (use_macros) bucket_sort(g, {g.pair_mac.p}, n_pairs, n_macro, g.mlist, g.mstart, s);
 
     // 6. row counts and offsets (execution order)
     {
@@ -1090,12 +956,7 @@ void build_hints(Graph& g, const float* pos, int32_t ncols, hipStream_t s, bool 
 
     // 7. entries: cell rows first (their weights are reused), then virtual rows
     if (bin_hints) {
-        g.bin_rank.ensure(static_cast<size_t>(n_inst) + 1, s);
         g.wpre.ensure(static_cast<size_t>(nbins) * wslots + 1, s);
-        if (g.n_hint_cells && !direct_prune)
-            hipLaunchKernelGGL(k_bin_rank, dim3(grid_for(g.n_hint_cells, kBT)), dim3(kBT), 0, s, g.n_hint_cells,
-                               g.bin_cells.p, g.bin_rank.p);
-        AHR_LAUNCHED("k_bin_rank");
         hipLaunchKernelGGL(k_window_prefix, dim3(grid_for(nbins, kBT)), dim3(kBT), 0, s, a, g.wpre.p);
         AHR_LAUNCHED("k_window_prefix");
     }

@@ -92,7 +92,7 @@ __device__ __forceinline__ float2 pin_pos(const KeyArgs& a, int p) {
 
 // Sort key of node i < first_mvirt: its range above the Hilbert index of
 // its position.
-__global__ void k_layout_keys(KeyArgs a, int32_t* __restrict__ key, int32_t* __restrict__ lo) {
+__global__ void k_layout_keys(KeyArgs a, int32_t* __restrict__ key) {
     int64_t i = static_cast<int64_t>(blockIdx.x) * blockDim.x + threadIdx.x;
     if (i >= a.first_mvirt) return;
     float2 q;
@@ -112,23 +112,7 @@ __global__ void k_layout_keys(KeyArgs a, int32_t* __restrict__ key, int32_t* __r
     float fy = floorf((q.y - a.yl) * a.sy);
     int gx = !(fx > 0.f) ? 0 : (fx >= static_cast<float>(m) ? m : static_cast<int>(fx));
     int gy = !(fy > 0.f) ? 0 : (fy >= static_cast<float>(m) ? m : static_cast<int>(fy));
-    const int k = (range << (2 * kGridBits)) | hilbert_index(gx, gy);
-    key[i] = k;
-    lo[i] = k & ((1 << kDigitBits) - 1);
-}
-
-// Second digit pass: the high digit of the key of each element of the
-// first pass's order.
-__global__ void k_high_digit(int32_t n, const int32_t* __restrict__ key, const int32_t* __restrict__ order,
-                             int32_t* __restrict__ hi) {
-    int64_t j = static_cast<int64_t>(blockIdx.x) * blockDim.x + threadIdx.x;
-    if (j < n) hi[j] = key[order[j]] >> kDigitBits;
-}
-
-__global__ void k_compose(int32_t n, const int32_t* __restrict__ first, const int32_t* __restrict__ second,
-                          int32_t* __restrict__ perm) {
-    int64_t r = static_cast<int64_t>(blockIdx.x) * blockDim.x + threadIdx.x;
-    if (r < n) perm[r] = first[second[r]];
+    key[i] = (range << (2 * kGridBits)) | hilbert_index(gx, gy);
 }
 
 // Stable sort of each aligned window of kLenWindow positions of `in` by the
@@ -464,21 +448,17 @@ __global__ void k_cm_append(int32_t n, const int32_t* __restrict__ flag, const i
 // Sort keys of the netlist order (24 bits: range above the rank): an
 // instance's own rank, a macro pin's or star's lowest instance-neighbour
 // rank (n_inst if none; one wave per such row); low 12 bits to `lo`.
-__global__ void k_cm_keys(int32_t n_inst, const int32_t* __restrict__ rank, int32_t* __restrict__ key,
-                          int32_t* __restrict__ lo) {
+__global__ void k_cm_keys(int32_t n_inst, const int32_t* __restrict__ rank, int32_t* __restrict__ key) {
     const int64_t v = static_cast<int64_t>(blockIdx.x) * blockDim.x + threadIdx.x;
-    if (v >= n_inst) return;
-    const int k = rank[v];
-    key[v] = k;
-    lo[v] = k & 0xfff;
+    if (v < n_inst) key[v] = rank[v];
 }
 
 __global__ void __launch_bounds__(kBT) k_cm_keys_aux(int32_t n_inst, int32_t np, int32_t first_star,
                                                      const int64_t* __restrict__ off,
                                                      const int32_t* __restrict__ len,
                                                      const int32_t* __restrict__ col,
-                                                     const int32_t* __restrict__ rank, int32_t* __restrict__ key,
-                                                     int32_t* __restrict__ lo) {
+                                                     const int32_t* __restrict__ rank,
+                                                     int32_t* __restrict__ key) {
     const int64_t v = n_inst + (static_cast<int64_t>(blockIdx.x) * blockDim.x + threadIdx.x) / kWave;
     if (v >= np) return;                                   // wave-uniform
     const int64_t o = off[v];
@@ -489,17 +469,7 @@ __global__ void __launch_bounds__(kBT) k_cm_keys_aux(int32_t n_inst, int32_t np,
         if (c < n_inst) r = rank[c] < r ? rank[c] : r;
     }
     r = wave_min(r);
-    if (lane_id() == 0) {
-        const int k = ((v < first_star ? 1 : 2) << 22) | r;
-        key[v] = k;
-        lo[v] = k & 0xfff;
-    }
-}
-
-__global__ void k_hi12(int32_t n, const int32_t* __restrict__ key, const int32_t* __restrict__ order,
-                       int32_t* __restrict__ hi) {
-    const int64_t j = static_cast<int64_t>(blockIdx.x) * blockDim.x + threadIdx.x;
-    if (j < n) hi[j] = key[order[j]] >> 12;
+    if (lane_id() == 0) key[v] = ((v < first_star ? 1 : 2) << 22) | r;
 }
 
 // Locality of a layout: of a sample of instance rows (every kSample-th
@@ -556,34 +526,35 @@ __global__ void __launch_bounds__(kBT) k_loc_flag(const int64_t* __restrict__ pa
 
 static void exec_net_copy(Graph& g, int32_t N, hipStream_t s2);
 
-// Two stable LSD passes over np keys (low digit `digit`, then key >> lo_bits
-// of that order) into `out`; ties keep node order.
-static void sort_keys(Graph& g, DevBuf<int32_t>& key, DevBuf<int32_t>& digit, int32_t np, int lo_bits, int hi_bits,
-                      hipStream_t s) {
-    DevBuf<int32_t> first, second;
-    bucket_sort(g, digit.p, np, 1 << lo_bits, first, g.lay_start, s, false);
-    if (lo_bits == kDigitBits)
-        hipLaunchKernelGGL(k_high_digit, dim3(grid_for(np, kBT)), dim3(kBT), 0, s, np, key.p, first.p, digit.p);
-    else
-        hipLaunchKernelGGL(k_hi12, dim3(grid_for(np, kBT)), dim3(kBT), 0, s, np, key.p, first.p, digit.p);
-    AHR_LAUNCHED("k_high_digit");
-    bucket_sort(g, digit.p, np, 1 << hi_bits, second, g.lay_start, s, false);
-    hipLaunchKernelGGL(k_compose, dim3(grid_for(np, kBT)), dim3(kBT), 0, s, np, first.p, second.p, key.p);
-    AHR_LAUNCHED("k_compose");
+// Two stable LSD passes over np keys (the low digit, then key >> lo_bits of
+// that order) into `order`; ties keep node order.
+static void sort_keys(Graph& g, const DevBuf<int32_t>& key, int32_t np, int lo_bits, int hi_bits,
+                      DevBuf<int32_t>& order, hipStream_t s) {
+    DevBuf<int32_t> first, sorted;
+    sorted.ensure(static_cast<size_t>(np) + 1, s);
+    SortKeys lo{key.p};
+    lo.mask = (1 << lo_bits) - 1;
+    lo.sorted = sorted.p;
+    bucket_sort(g, lo, np, 1 << lo_bits, first, g.lay_start, s);
+    SortKeys hi{sorted.p};
+    hi.idx = first.p;
+    hi.shift = lo_bits;
+    hi.mask = (1 << hi_bits) - 1;
+    bucket_sort(g, hi, np, 1 << hi_bits, order, g.lay_start, s);
     first.release(s);
-    second.release(s);
+    sorted.release(s);
 }
 
-// perm from the sorted order in `key` (instance windows by row length,
+// perm from the sorted order (instance windows by row length,
 // macro pins and stars as sorted), then iperm.
-static void finish_perm(Graph& g, DevBuf<int32_t>& key, hipStream_t s) {
+static void finish_perm(Graph& g, const DevBuf<int32_t>& order, hipStream_t s) {
     const int32_t n = g.n_inst, N = g.n_tot, np = g.first_mvirt;
     g.perm.ensure(static_cast<size_t>(N) + 1, s);
-    hipLaunchKernelGGL(k_window_sort, dim3(grid_for(n, kLenWindow)), dim3(kLenWindow), 0, s, n, key.p, g.net_len.p,
+    hipLaunchKernelGGL(k_window_sort, dim3(grid_for(n, kLenWindow)), dim3(kLenWindow), 0, s, n, order.p, g.net_len.p,
                        g.perm.p);
     AHR_LAUNCHED("k_window_sort");
     if (np > n)
-        AHR_HIP(hipMemcpyAsync(g.perm.p + n, key.p + n, static_cast<size_t>(np - n) * sizeof(int32_t),
+        AHR_HIP(hipMemcpyAsync(g.perm.p + n, order.p + n, static_cast<size_t>(np - n) * sizeof(int32_t),
                                hipMemcpyDeviceToDevice, s));
     g.iperm.ensure(static_cast<size_t>(N) + 1, s);
     hipLaunchKernelGGL(k_iperm, dim3(grid_for(N, kBT)), dim3(kBT), 0, s, g.perm.p, np, N, g.iperm.p);
@@ -593,9 +564,8 @@ static void finish_perm(Graph& g, DevBuf<int32_t>& key, hipStream_t s) {
 // The Hilbert order of the placement's positions.
 static void position_order(Graph& g, const float* pos, int32_t ncols, hipStream_t s) {
     const int32_t n = g.n_inst, np = g.first_mvirt;
-    DevBuf<int32_t> key, digit;
+    DevBuf<int32_t> key, order;
     key.ensure(static_cast<size_t>(np) + 1, s);
-    digit.ensure(static_cast<size_t>(np) + 1, s);
     const float side = static_cast<float>(1 << kGridBits);
     KeyArgs ka;
     ka.pos = pos;
@@ -613,13 +583,13 @@ static void position_order(Graph& g, const float* pos, int32_t ncols, hipStream_
     ka.yl = g.nl.die[1];
     ka.sx = side / (g.nl.die[2] - g.nl.die[0]);
     ka.sy = side / (g.nl.die[3] - g.nl.die[1]);
-    hipLaunchKernelGGL(k_layout_keys, dim3(grid_for(np, kBT)), dim3(kBT), 0, s, ka, key.p, digit.p);
+    hipLaunchKernelGGL(k_layout_keys, dim3(grid_for(np, kBT)), dim3(kBT), 0, s, ka, key.p);
     AHR_LAUNCHED("k_layout_keys");
     // the range bits keep the instances, macro pins and stars in their own id ranges
-    sort_keys(g, key, digit, np, kDigitBits, kKeyBits - kDigitBits, s);
-    finish_perm(g, key, s);
+    sort_keys(g, key, np, kDigitBits, kKeyBits - kDigitBits, order, s);
+    finish_perm(g, order, s);
     key.release(s);
-    digit.release(s);
+    order.release(s);
 }
 
 // The locality test of the current layout, left on the device (g.loc_flag):
@@ -703,21 +673,20 @@ static void netlist_order(Graph& g, hipStream_t s) {
     scn.release(s);
     bnd.release(s);
     // sort keys: range, then rank (24 bits, two 12-bit passes)
-    DevBuf<int32_t> skey, digit;
+    DevBuf<int32_t> skey, sorted;
     skey.ensure(static_cast<size_t>(np) + 1, s);
-    digit.ensure(static_cast<size_t>(np) + 1, s);
-    hipLaunchKernelGGL(k_cm_keys, dim3(grid_for(n, kBT)), dim3(kBT), 0, s, n, rank.p, skey.p, digit.p);
+    hipLaunchKernelGGL(k_cm_keys, dim3(grid_for(n, kBT)), dim3(kBT), 0, s, n, rank.p, skey.p);
     AHR_LAUNCHED("k_cm_keys");
     if (np > n) {
         hipLaunchKernelGGL(k_cm_keys_aux, dim3(grid_for(static_cast<int64_t>(np - n) * kWave, kBT)), dim3(kBT), 0,
-                           s, n, np, g.first_star, g.net_off.p, g.net_len.p, g.net_col.p, rank.p, skey.p, digit.p);
+                           s, n, np, g.first_star, g.net_off.p, g.net_len.p, g.net_col.p, rank.p, skey.p);
         AHR_LAUNCHED("k_cm_keys_aux");
     }
     rank.release(s);
-    sort_keys(g, skey, digit, np, 12, 12, s);
-    finish_perm(g, skey, s);
+    sort_keys(g, skey, np, 12, 12, sorted, s);
+    finish_perm(g, sorted, s);
     skey.release(s);
-    digit.release(s);
+    sorted.release(s);
 }
 
 void set_layout(Graph& g, const float* pos, int32_t ncols, hipStream_t s) {

@@ -676,7 +676,7 @@ void build_netlist(Graph& g, hipStream_t s) {
     ckey.ensure(static_cast<size_t>(N) + 1, s);
     hipLaunchKernelGGL(k_class_keys, dim3(grid_for(N, kBT)), dim3(kBT), 0, s, cnt.p, N, ckey.p);
     AHR_LAUNCHED("k_class_keys");
-    bucket_sort(g, ckey.p, N, K, lists, cstart, s, false);
+    bucket_sort(g, {ckey.p}, N, K, lists, cstart, s);
     ckey.release(s);
     int64_t w[K + 2];
     read_words({{rp.p + N, 1}, {cstart.p, 0}, {cstart.p + 1, 0}, {cstart.p + 2, 0}, {cstart.p + 3, 0},

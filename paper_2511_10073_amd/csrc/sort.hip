@@ -1,0 +1,251 @@
+// Stable bucket sort of small integer keys (bins, macros, row classes, the
+// digits of the layout's keys).  Every position comes from integer counts,
+// so the order is exact and the same from run to run.
+//
+// A workgroup of W waves takes a tile of W x I x 64 consecutive elements,
+// each wave one contiguous part of it, and each wave ranks its elements with
+// ballots against a counter array of its own in LDS.  The serial chain (a
+// counter read and written per 64 elements) is what bounds the scatter, so
+// the tile is spread over W waves instead of run through one: 64 elements at
+// a time by one wave, 32 times over, took 43 us a sort at 2.2M elements and
+// 1,024 keys (24 us at 210,000, and 33 us at 2,000 with 2,048 keys).  The
+// larger tiles also make the table of (key, tile) counts an eighth as long,
+// so it is written and read in key order without the two transposes.
+// Sorting 1,024 keys now takes 17 + 10 + 31 us (count, scan, scatter) at 2.2M
+// elements where count, transposes, scan and scatter took 13 + 16 + 20 + 42,
+// 4.6 + 7 + 5.7 at 210,000 (5 + 8 + 8 + 25), and 9 at 2,000 (54 in seven
+// launches).
+#include <algorithm>
+
+#include "ahr_internal.hpp"
+#include "device_util.hpp"
+
+namespace ahr {
+
+namespace {
+
+constexpr int kMaxKeys = 16384;
+constexpr int kMaxWaves = 8;
+constexpr int kMaxIters = 16;
+// Counter words of a workgroup: 128 KB of LDS.  Above 4,096 keys that means
+// fewer waves; half of it (and half the waves) took 49 against 35 us in the
+// scatter of 0.7M elements with 8,000 keys.
+constexpr int kLdsWords = 32768;
+// Up to kSmallIters x 64 elements a wave one workgroup of up to 16 waves does
+// the whole sort, in one launch instead of four.
+constexpr int kSmallIters = 16;
+constexpr int kSmallWaves = 16;
+
+__device__ __forceinline__ int sort_key(const SortKeys& k, int64_t i) {
+    const int v = k.key[i];
+    return v < 0 ? -1 : (v >> k.shift) & k.mask;
+}
+
+__device__ __forceinline__ void wave_lds_order() {
+    // LDS serves a wave's accesses in order; the compiler keeps them so
+    __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+    __builtin_amdgcn_wave_barrier();
+}
+
+// The 64 keys b of a wave take their places (run[key] = the key's next
+// place): returns the lane's place, or -1 without a key.
+__device__ __forceinline__ int place_keys(int b, int bits, int32_t* run) {
+    const int l = lane_id();
+    const uint64_t lt = l ? (~0ull >> (kWave - l)) : 0ull;
+    const uint64_t gt = (l == kWave - 1) ? 0ull : (~0ull << (l + 1));
+    const bool valid = b >= 0;
+    uint64_t peer = __ballot(valid);
+    for (int k = 0; k < bits; ++k) {
+        const bool bit = valid && ((b >> k) & 1);
+        const uint64_t m = __ballot(bit);
+        peer &= bit ? m : ~m;
+    }
+    int at = -1;
+    if (valid) at = run[b] + __popcll(peer & lt);
+    wave_lds_order();
+    if (valid && (peer & gt) == 0) run[b] = at + 1;
+    wave_lds_order();
+    return at;
+}
+
+__device__ __forceinline__ void put(const SortKeys& k, int64_t i, int at, int32_t* list) {
+    if (at < 0) return;
+    const int32_t v = k.idx ? k.idx[i] : static_cast<int32_t>(i);
+    list[at] = v;
+    if (k.inverse) k.inverse[v] = at;
+    if (k.sorted) k.sorted[at] = k.key[i];
+}
+
+// Elements of each key in each tile, key by key: hist[key][tile].
+template <int I>
+__global__ void __launch_bounds__(kMaxWaves * kWave) k_bucket_count(SortKeys k, int32_t n, int nkeys, int32_t ntiles,
+                                                                    int32_t* __restrict__ hist) {
+    extern __shared__ int32_t h[];
+    for (int b = threadIdx.x; b < nkeys; b += blockDim.x) h[b] = 0;
+    __syncthreads();
+    const int64_t base = static_cast<int64_t>(blockIdx.x) * I * blockDim.x;
+    int key[I];       // the tile's keys, all loads in flight together
+#pragma unroll
+    for (int t = 0; t < I; ++t) {
+        const int64_t i = base + static_cast<int64_t>(t) * blockDim.x + threadIdx.x;
+        key[t] = sort_key(k, i < n ? i : n - 1);
+        if (i >= n) key[t] = -1;
+    }
+#pragma unroll
+    for (int t = 0; t < I; ++t)
+        if (key[t] >= 0) atomicAdd(&h[key[t]], 1);
+    __syncthreads();
+    for (int b = threadIdx.x; b < nkeys; b += blockDim.x)
+        hist[static_cast<int64_t>(b) * ntiles + blockIdx.x] = h[b];
+}
+
+// Places every element: off[key][tile] (the scanned counts), plus the key's
+// count in the tile's earlier waves, plus its rank in its wave.
+template <int I>
+__global__ void __launch_bounds__(kMaxWaves * kWave) k_bucket_scatter(SortKeys k, int32_t n, int nkeys, int bits,
+                                                                      int32_t ntiles, const int32_t* __restrict__ off,
+                                                                      int32_t* __restrict__ list,
+                                                                      int32_t* __restrict__ start) {
+    extern __shared__ int32_t run[];     // [wave][key]
+    const int W = blockDim.x / kWave;
+    for (int b = threadIdx.x; b < W * nkeys; b += blockDim.x) run[b] = 0;
+    __syncthreads();
+    int32_t* mine = run + wave_id() * nkeys;
+    const int64_t base = static_cast<int64_t>(blockIdx.x) * I * blockDim.x +
+                         static_cast<int64_t>(wave_id()) * I * kWave + lane_id();
+    int key[I];
+#pragma unroll
+    for (int t = 0; t < I; ++t) {
+        const int64_t i = base + t * kWave;
+        key[t] = sort_key(k, i < n ? i : n - 1);
+        if (i >= n) key[t] = -1;
+    }
+#pragma unroll
+    for (int t = 0; t < I; ++t)
+        if (key[t] >= 0) atomicAdd(&mine[key[t]], 1);
+    __syncthreads();
+    for (int b = threadIdx.x; b < nkeys; b += blockDim.x) {
+        const int first = off[static_cast<int64_t>(b) * ntiles + blockIdx.x];
+        if (blockIdx.x == 0) start[b] = first;
+        int acc = first;
+        for (int w = 0; w < W; ++w) {
+            const int c = run[w * nkeys + b];
+            run[w * nkeys + b] = acc;
+            acc += c;
+        }
+    }
+    if (blockIdx.x == 0 && threadIdx.x == 0) start[nkeys] = off[static_cast<int64_t>(nkeys) * ntiles];
+    __syncthreads();
+#pragma unroll
+    for (int t = 0; t < I; ++t) put(k, base + t * kWave, place_keys(key[t], bits, mine), list);
+}
+
+// The whole sort by one workgroup: every wave counts and places one
+// contiguous part; between the two the counters are scanned key by key,
+// waves in order within a key.
+__global__ void __launch_bounds__(kSmallWaves * kWave) k_bucket_small(SortKeys k, int32_t n, int nkeys, int bits,
+                                                                      int32_t* __restrict__ list,
+                                                                      int32_t* __restrict__ start) {
+    extern __shared__ int32_t run[];     // [wave][key]
+    __shared__ int64_t red[kSmallWaves];
+    __shared__ int64_t carry;
+    const int W = blockDim.x / kWave;
+    for (int b = threadIdx.x; b < W * nkeys; b += blockDim.x) run[b] = 0;
+    if (threadIdx.x < kSmallWaves) red[threadIdx.x] = 0;     // (the waves that are not there)
+    if (threadIdx.x == 0) carry = 0;
+    __syncthreads();
+    int32_t* mine = run + wave_id() * nkeys;
+    const int per = (n + static_cast<int>(blockDim.x) - 1) / static_cast<int>(blockDim.x);      // <= kSmallIters
+    const int64_t base = static_cast<int64_t>(wave_id()) * per * kWave + lane_id();
+    int key[kSmallIters];
+#pragma unroll
+    for (int t = 0; t < kSmallIters; ++t) {
+        const int64_t i = base + t * kWave;
+        key[t] = sort_key(k, i < n ? i : n - 1);
+        if (i >= n || t >= per) key[t] = -1;
+    }
+#pragma unroll
+    for (int t = 0; t < kSmallIters; ++t)
+        if (key[t] >= 0) atomicAdd(&mine[key[t]], 1);
+    __syncthreads();
+    for (int b0 = 0; b0 < nkeys; b0 += static_cast<int>(blockDim.x)) {
+        const int b = b0 + static_cast<int>(threadIdx.x);
+        int64_t c = 0, tot;
+        if (b < nkeys)
+            for (int w = 0; w < W; ++w) c += run[w * nkeys + b];
+        int acc = static_cast<int>(carry + block_exclusive_scan_i64<kSmallWaves * kWave>(c, red, &tot));
+        if (b < nkeys) {
+            start[b] = acc;
+            for (int w = 0; w < W; ++w) {
+                const int q = run[w * nkeys + b];
+                run[w * nkeys + b] = acc;
+                acc += q;
+            }
+        }
+        __syncthreads();
+        if (threadIdx.x == 0) carry += tot;
+        __syncthreads();
+    }
+    if (threadIdx.x == 0) start[nkeys] = static_cast<int32_t>(carry);
+#pragma unroll
+    for (int t = 0; t < kSmallIters; ++t)
+        if (t < per) put(k, base + t * kWave, place_keys(key[t], bits, mine), list);
+}
+
+template <int I>
+void sort_tiles(const SortKeys& k, int32_t n, int nkeys, int bits, int waves, int32_t* list, int32_t* start,
+                DevBuf<int32_t>& i32a, DevBuf<int32_t>& i32b, DevBuf<int64_t>& scan_tmp, hipStream_t s) {
+    const int32_t ntiles = static_cast<int32_t>(grid_for(n, I * waves * kWave));
+    const int64_t hn = static_cast<int64_t>(nkeys) * ntiles;
+    i32a.ensure(static_cast<size_t>(hn) + 1, s);
+    i32b.ensure(static_cast<size_t>(hn) + 1, s);
+    hipLaunchKernelGGL(k_bucket_count<I>, dim3(ntiles), dim3(waves * kWave), nkeys * sizeof(int32_t), s, k, n, nkeys,
+                       ntiles, i32a.p);
+    AHR_LAUNCHED("k_bucket_count");
+    scan_tmp.ensure(scan_tmp_elems(hn), s);
+    scan_i32_to_i32(i32a.p, i32b.p, hn, scan_tmp.p, s);
+    hipLaunchKernelGGL(k_bucket_scatter<I>, dim3(ntiles), dim3(waves * kWave),
+                       static_cast<size_t>(waves) * nkeys * sizeof(int32_t), s, k, n, nkeys, bits, ntiles, i32b.p, list,
+                       start);
+    AHR_LAUNCHED("k_bucket_scatter");
+}
+
+}  // namespace
+
+void bucket_sort(const SortKeys& k, int32_t n, int nkeys, DevBuf<int32_t>& list, DevBuf<int32_t>& start,
+                 DevBuf<int32_t>& i32a, DevBuf<int32_t>& i32b, DevBuf<int64_t>& scan_tmp, hipStream_t s) {
+    if (nkeys > kMaxKeys) throw Error{AHR_EUNSUPPORTED, "too many buckets (at most 16384 bins or macros)"};
+    list.ensure(static_cast<size_t>(n) + 1, s);
+    start.ensure(static_cast<size_t>(nkeys) + 1, s);
+    if (n == 0) {
+        fill_i32(start.p, nkeys + 1, 0, s);
+        return;
+    }
+    int bits = 0;
+    while ((1 << bits) < nkeys) ++bits;
+    const int small_waves =
+        std::min({kSmallWaves, kLdsWords / nkeys, static_cast<int>(std::min(grid_for(n, kWave), 16u))});
+    if (n <= small_waves * kSmallIters * kWave) {
+        const int waves = small_waves;
+        hipLaunchKernelGGL(k_bucket_small, dim3(1), dim3(waves * kWave),
+                           static_cast<size_t>(waves) * nkeys * sizeof(int32_t), s, k, n, nkeys, bits, list.p, start.p);
+        AHR_LAUNCHED("k_bucket_small");
+        return;
+    }
+    const int waves = std::min(kMaxWaves, kLdsWords / nkeys);
+    // the shortest tile whose (key, tile) table stays within 2^18 counters:
+    // short tiles give the scatter more waves, but every tile reads and writes
+    // its column of the table with a line an entry (2.2M elements, 1,024 keys:
+    // tiles of 8,192, 4,096 and 2,048 take 30, 39 and 74 us in the scatter)
+    int iters = 2;
+    while (iters < kMaxIters && static_cast<int64_t>(nkeys) * grid_for(n, iters * waves * kWave) > (1 << 18)) iters *= 2;
+    auto f = iters == 2 ? sort_tiles<2> : iters == 4 ? sort_tiles<4> : iters == 8 ? sort_tiles<8> : sort_tiles<16>;
+    f(k, n, nkeys, bits, waves, list.p, start.p, i32a, i32b, scan_tmp, s);
+}
+
+void bucket_sort(Graph& g, const SortKeys& k, int32_t n, int nkeys, DevBuf<int32_t>& list, DevBuf<int32_t>& start,
+                 hipStream_t s) {
+    bucket_sort(k, n, nkeys, list, start, g.i32a, g.i32b, g.scan_tmp, s);
+}
+
+}  // namespace ahr

@@ -588,7 +588,8 @@ ahr_status ahr_wl_create(const ahr_netlist* nl, void* stream, ahr_wl** out) {
                 ahr::list_rows(flag.p, rank.p, nl->n_nets, w->big.p, s);
                 flag.release(s);
                 rank.release(s);
-                w->n_small = ahr::bucket_sort(key.p, nl->n_nets, ahr::kWave + 1, w->small, start, a, b, tmp, s);
+                ahr::bucket_sort({key.p}, nl->n_nets, ahr::kWave + 1, w->small, start, a, b, tmp, s);
+                w->n_small = ahr::read_i32(start.p + ahr::kWave + 1, s);
                 key.release(s);
                 start.release(s);
                 a.release(s);
