@@ -186,6 +186,7 @@ struct RowClasses {
     DevBuf<int32_t> chunk_row;    // [n_chunks] long-row index of each chunk
     DevBuf<double> partial;       // [n_chunks * 8]
     DevBuf<int4> rb;              // [2 n_rb] row blocks: (r0, r1, net_lo, net_hi), (hint_lo, hint_hi, -, -)
+    DevBuf<int32_t> counts;       // counts of the scans that make them
     int32_t n_long = 0, n_long_inst = 0;      // long rows, those below n_inst
     int32_t n_chunks = 0, n_chunks_inst = 0;  // chunks, those of long rows below n_inst
     int32_t n_rb = 0, n_rb_inst = 0;          // row blocks, those below n_inst
@@ -198,8 +199,15 @@ struct RowClasses {
         chunk_row.release(s);
         partial.release(s);
         rb.release(s);
+        counts.release(s);
     }
 };
+
+// Bin areas in units of 2^-28 (exact integer sums), and the classes of an
+// instance: not a movable standard cell, one without nets, one with nets (a
+// hint cell).
+constexpr double kAreaQ = 268435456.0;
+constexpr int64_t kCellOther = 0, kCellStd = 1, kCellHint = 2;
 
 struct Graph {
     Arena* arena = nullptr;    // the caller's workspace all device memory comes from (null: the pool)
@@ -244,7 +252,8 @@ struct Graph {
     DevBuf<int32_t> net_col;      // [nnz_cap]
     DevBuf<int64_t> net_q;        // [nnz_cap]
     DevBuf<int64_t> qdeg;         // [n_tot]
-    DevBuf<double> base_w;        // [n_inst] baseWeight
+    DevBuf<int32_t> long_nodes;   // nodes of more than 64 raw netlist entries
+    int32_t n_long_nodes = 0;
     DevBuf<int32_t> big_nets;     // nets with more than a wave's worth of pins (HPWL)
     int32_t n_big_nets = 0;
     DevBuf<int32_t> big_stars;    // star indices (0-based) of nets with more than kStarMid pins
@@ -254,14 +263,13 @@ struct Graph {
     DevBuf<int32_t> cell_bin;     // [n_inst] by execution row: bin of a hint cell, -1 otherwise
     DevBuf<int32_t> bin_start;    // [n_bins+1]
     DevBuf<int32_t> bin_cells;    // [n_hint_cells] execution rows of hint cells by bin, ascending
-    DevBuf<int64_t> bin_area_q;   // [n_bins] fixed-point area (2^-28 units)
-    DevBuf<int64_t> macro_area_q; // [n_bins] the macros' part of bin_area_q (kept for the next round)
+    DevBuf<int64_t> bin_area_q;   // [n_bins] the cells' fixed-point area (2^-28 units)
+    DevBuf<int64_t> macro_area_q; // [n_bins] the macros' (kept for the next round)
     DevBuf<double> phi;           // [n_bins]
     DevBuf<int32_t> bm_start;     // [n_bins+1] macros whose bin span covers a bin
     DevBuf<int32_t> bm_list;
     DevBuf<int4> macro_span;      // [n_macro] bin span bx0, by0, bx1, by1 of the cells it can hold
     DevBuf<float4> macro_rect;    // [n_macro] cx, cy, w/2, h/2 (float32)
-    DevBuf<int32_t> hint_cnt;     // [n_tot]
     DevBuf<int32_t> nmac, nwin;   // [n_inst] per execution row: macros holding the cell, window size
     DevBuf<int32_t> pair_off;     // [n_inst+1] first (cell, macro) pair of each row
     DevBuf<int32_t> pair_row, pair_mac;
@@ -270,14 +278,13 @@ struct Graph {
     DevBuf<int32_t> wpre;         // [n_bins * window slots] offsets of the slots in bin rows
     DevBuf<unsigned long long> keep_mask;  // [n_inst] per execution row: window slots whose bin edge is kept
     DevBuf<int32_t> kept;         // [n_bins * window slots] cells of a bin keeping the edge to each window slot
-    DevBuf<int64_t> xcell;        // [n_inst] per execution row: cell area (2^-28 units) * 4 + cell class
+    DevBuf<int64_t> xcell;        // [n_inst] per execution row: cell area (2^-28 units) * 4 + cell class (kCell*)
     DevBuf<double> xbase_w;       // [n_inst] per execution row: baseWeight
     DevBuf<float2> xpos;          // [n_inst] per execution row: the current placement's (x, y)
     DevBuf<double> xhabs;         // [n_inst] per execution row: sum of |hint weight| (hint_version habs_version)
     DevBuf<float> xhsg;           // [n_inst] per execution row: signed sum of the hint weights
     int32_t habs_version = -1;
     DevBuf<double> gmax;          // first-hop Gershgorin maxima (per workgroup, then per long row)
-    int32_t has_xcell = 0;
     int32_t n_movable_macro = 0;  // macros without AHR_NODE_FIXED
     int32_t macro_cache = 0;      // macro_rect/_span, bm_start/_list and macro_area_q hold the fixed macros' values
 
@@ -488,8 +495,9 @@ struct ChainView {
 // Row classes of an operator with rows [0, N), instance rows first: the
 // long rows (more than kLongRow entries) with their chunks and a
 // partial-sum buffer for C <= 8 columns.  Resets the row blocks.
-void row_classes(const int32_t* net_rp, const int32_t* hint_rp, int32_t N, int32_t n_inst, RowClasses& rc,
-                 DevBuf<int64_t>& scan_tmp, hipStream_t s);
+// max_entries: a bound on the operator's entries (it sizes the lists).
+void row_classes(const int32_t* net_rp, const int32_t* hint_rp, int32_t N, int32_t n_inst, int64_t max_entries,
+                 RowClasses& rc, DevBuf<int64_t>& scan_tmp, hipStream_t s);
 // The row blocks of the short rows (for the row-block hop), if not built.
 void row_blocks(const int32_t* net_rp, const int32_t* hint_rp, int32_t N, int32_t n_inst, RowClasses& rc,
                 DevBuf<int64_t>& scan_tmp, hipStream_t s);

@@ -40,9 +40,9 @@ Graph::~Graph() {
     if (stream_uses > 1) (void)hipDeviceSynchronize();
     if (xnet_ready) (void)hipStreamWaitEvent(s, xnet_ready, 0);   // the side stream's copy
     DevBuf<int32_t>* i32[] = {&pin_node_x, &mpin_owner, &mpin_pin, &star_net, &macro_ids, &net_len, &net_col,
-                              &big_nets, &cell_bin, &bin_start, &bin_cells, &bm_start, &bm_list, &hint_cnt,
+                              &big_nets, &cell_bin, &bin_start, &bin_cells, &bm_start, &bm_list,
                               &nmac, &nwin, &bin_rank, &wpre, &pair_off, &pair_row, &pair_mac, &mlist, &mstart,
-                              &big_stars, &i32a, &i32b, &counter, &kept, &loc_flag};
+                              &big_stars, &long_nodes, &i32a, &i32b, &counter, &kept, &loc_flag};
     for (auto* b : i32) b->release(s);
     loc_part.release(s);
     keep_mask.release(s);
@@ -59,7 +59,6 @@ Graph::~Graph() {
     xhint_ent.release(s);
     lay_start.release(s);
     qdeg.release(s);
-    base_w.release(s);
     xcell.release(s);
     xbase_w.release(s);
     xpos.release(s);

@@ -427,7 +427,7 @@ void batch_assemble(Batch& b, hipStream_t s) {
     b.scale.ensure(static_cast<size_t>(b.n_tot) + 1, s);
     b.coef.ensure(static_cast<size_t>(b.n_tot) + 1, s);
     b.op_version.assign(n, -1);
-    row_classes(b.net_rp.p, b.hint_rp.p, b.n_tot, b.n_inst, b.rc, b.scan_tmp, s);
+    row_classes(b.net_rp.p, b.hint_rp.p, b.n_tot, b.n_inst, b.nnz_net + b.nnz_hint, b.rc, b.scan_tmp, s);
     std::vector<int32_t> blk(n + 1, 0), sblk(n + 1, 0);
     for (size_t i = 0; i < n; ++i) {
         blk[i + 1] = blk[i] + static_cast<int32_t>(grid_for(b.g[i]->n_tot, kBT));

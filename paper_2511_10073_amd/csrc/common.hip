@@ -6,6 +6,7 @@
 
 #include "ahr_internal.hpp"
 #include "device_util.hpp"
+#include "scan.hpp"
 
 namespace ahr {
 
@@ -508,9 +509,36 @@ static void scan_launch(const Tin* in, Tout* out, int64_t n, int64_t* tmp, int64
     AHR_LAUNCHED("k_tile_scan");
 }
 
+// An array's scan by one workgroup, for the inputs of at most kScanSmall items.
+template <class Tin, class Tout>
+struct PlainScan {
+    static constexpr int K = 1;
+    static constexpr bool kTotal = false, kHeavy = false;
+    using Raw = Pack<1>;
+    __device__ Pack<1> pack(const Pack<1>& p) const { return p; }
+    const Tin* in;
+    Tout* out;
+    int64_t n;
+    int64_t* sum;
+    __device__ Pack<1> first(int64_t i) const { return {{static_cast<int64_t>(in[i])}}; }
+    __device__ Pack<1> again(int64_t i) const { return first(i); }
+    __device__ void item(int64_t i, const Pack<1>&, const Pack<1>& before, const Pack<1>&) const {
+        out[i] = static_cast<Tout>(before.v[0]);
+    }
+    __device__ void done(const Pack<1>& total) const {
+        out[n] = static_cast<Tout>(total.v[0]);
+        *sum = total.v[0];
+    }
+};
+
 template <class Tin, class Tout>
 static void scan_impl(const Tin* in, Tout* out, int64_t n, int64_t* tmp, hipStream_t s) {
     int64_t ntiles = (n + kScanTile - 1) / kScanTile;   // n > 0
+    if (n <= kScanSmall) {
+        DevBuf<int64_t> none;
+        run_scans(scan_job(PlainScan<Tin, Tout>{in, out, n, tmp + ntiles}, n), none, s);
+        return;
+    }
     hipLaunchKernelGGL((k_tile_sums<Tin>), dim3(ntiles), dim3(kScanThreads), 0, s, in, n, tmp);
     AHR_LAUNCHED("k_tile_sums");
     // 16-byte accesses when both arrays allow them (the offsets inside a

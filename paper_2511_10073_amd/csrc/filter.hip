@@ -19,8 +19,11 @@
 // after the hop in a fixed order -- deterministic for any schedule.
 #include <hip/hip_ext.h>
 
+#include <algorithm>
+
 #include "ahr_internal.hpp"
 #include "device_util.hpp"
+#include "scan.hpp"
 
 namespace ahr {
 
@@ -97,39 +100,43 @@ __device__ __forceinline__ Floats<W> load_floats(const float* p) {
 
 // ---------------------------------------------------------------- row classes
 
-__global__ void k_row_len(int32_t n, const int32_t* __restrict__ net_rp, const int32_t* __restrict__ hint_rp,
-                          int32_t* __restrict__ is_long) {
-    int64_t r = static_cast<int64_t>(blockIdx.x) * blockDim.x + threadIdx.x;
-    if (r >= n) return;
-    int len = (net_rp[r + 1] - net_rp[r]) + (hint_rp[r + 1] - hint_rp[r]);
-    is_long[r] = len > kLongRow ? 1 : 0;
-}
-
-// Long-row flag and chunk count of every row (0 for short rows).
-__global__ void k_row_chunks(int32_t n, const int32_t* __restrict__ net_rp, const int32_t* __restrict__ hint_rp,
-                             int32_t* __restrict__ is_long, int32_t* __restrict__ nch) {
-    int64_t r = static_cast<int64_t>(blockIdx.x) * blockDim.x + threadIdx.x;
-    if (r >= n) return;
-    int len = (net_rp[r + 1] - net_rp[r]) + (hint_rp[r + 1] - hint_rp[r]);
-    bool lg = len > kLongRow;
-    is_long[r] = lg ? 1 : 0;
-    nch[r] = lg ? (len + kChunk - 1) / kChunk : 0;
-}
-
-// First chunk of each long row from the row-indexed chunk offsets; the
-// entry past the last row holds the chunk total.
-__global__ void k_long_chunk0(int32_t n_long, const int32_t* __restrict__ rows, const int32_t* __restrict__ cscan,
-                              int32_t n_chunks, int32_t* __restrict__ chunk0) {
-    int i = blockIdx.x * blockDim.x + threadIdx.x;
-    if (i < n_long) chunk0[i] = cscan[rows[i]];
-    if (i == n_long) chunk0[i] = n_chunks;
-}
-
-__global__ void k_chunk_rows(int32_t n_long, const int32_t* __restrict__ chunk0, int32_t* __restrict__ chunk_row) {
-    int i = blockIdx.x;
-    if (i >= n_long) return;
-    for (int c = chunk0[i] + threadIdx.x; c < chunk0[i + 1]; c += blockDim.x) chunk_row[c] = i;
-}
+// The long rows with their chunks, in row order: long_rows[k] the k-th long
+// row, chunk0[k] its first chunk (the entry past the last row: the total),
+// chunk_row[c] the long row of chunk c; and the counts of those below n_inst.
+struct LongRowScan {
+    static constexpr int K = 1;
+    static constexpr bool kTotal = false, kHeavy = false;
+    using Raw = Pack<1>;
+    __device__ Pack<1> pack(const Pack<1>& p) const { return p; }
+    const int32_t* net_rp;
+    const int32_t* hint_rp;
+    int32_t n_inst;
+    int32_t* long_rows;
+    int32_t* chunk0;
+    int32_t* chunk_row;
+    int32_t* counts;       // long rows, those below n_inst, chunks, those below n_inst
+    __device__ Pack<1> first(int64_t r) const {
+        const int len = (net_rp[r + 1] - net_rp[r]) + (hint_rp[r + 1] - hint_rp[r]);
+        return {{len > kLongRow ? pack2(1, (len + kChunk - 1) / kChunk) : 0}};
+    }
+    __device__ Pack<1> again(int64_t r) const { return first(r); }
+    __device__ void item(int64_t r, const Pack<1>& own, const Pack<1>& before, const Pack<1>&) const {
+        const int32_t k = pack_lo(before.v[0]), c0 = pack_hi(before.v[0]), nc = pack_hi(own.v[0]);
+        if (r == n_inst) {
+            counts[1] = k;
+            counts[3] = c0;
+        }
+        if (!nc) return;
+        long_rows[k] = static_cast<int32_t>(r);
+        chunk0[k] = c0;
+        for (int c = 0; c < nc; ++c) chunk_row[c0 + c] = k;
+    }
+    __device__ void done(const Pack<1>& total) const {
+        counts[0] = pack_lo(total.v[0]);
+        counts[2] = pack_hi(total.v[0]);
+        chunk0[counts[0]] = counts[2];
+    }
+};
 
 struct RowRef {
     const int32_t* net_rp;
@@ -151,29 +158,47 @@ __device__ __forceinline__ bool rb_break(int32_t r, int32_t n_inst, const int32_
     return r == n_inst || c1 / kRbEntries != c0 / kRbEntries || r / kRbRows != (r - 1) / kRbRows;
 }
 
-__global__ void k_rb_marks(int32_t n, int32_t n_inst, const int32_t* __restrict__ net_rp,
-                           const int32_t* __restrict__ hint_rp, const int32_t* __restrict__ is_long,
-                           int32_t* __restrict__ start, int32_t* __restrict__ end) {
-    int64_t r64 = static_cast<int64_t>(blockIdx.x) * blockDim.x + threadIdx.x;
-    if (r64 >= n) return;
-    const int32_t r = static_cast<int32_t>(r64);
-    int32_t st = 0, en = 0;
-    if (!is_long[r]) {
-        st = (r == 0 || is_long[r - 1] || rb_break(r, n_inst, net_rp, hint_rp)) ? 1 : 0;
-        en = (r == n - 1 || is_long[r + 1] || rb_break(r + 1, n_inst, net_rp, hint_rp)) ? 1 : 0;
-    }
-    start[r] = st;
-    end[r] = en;
+__device__ __forceinline__ bool is_long_row(int32_t r, const int32_t* net_rp, const int32_t* hint_rp) {
+    return (net_rp[r + 1] - net_rp[r]) + (hint_rp[r + 1] - hint_rp[r]) > kLongRow;
 }
 
-__global__ void k_rb_desc(int32_t n_rb, const int32_t* __restrict__ starts, const int32_t* __restrict__ ends,
-                          const int32_t* __restrict__ net_rp, const int32_t* __restrict__ hint_rp, int4* __restrict__ rb) {
-    int64_t k = static_cast<int64_t>(blockIdx.x) * blockDim.x + threadIdx.x;
-    if (k >= n_rb) return;
-    const int32_t r0 = starts[k], r1 = ends[k] + 1;
-    rb[2 * k] = make_int4(r0, r1, net_rp[r0], net_rp[r1]);
-    rb[2 * k + 1] = make_int4(hint_rp[r0], hint_rp[r1], 0, 0);
-}
+// The row blocks' descriptors, in row order, and their counts (all, and those
+// below n_inst).
+struct RowBlockScan {
+    static constexpr int K = 1;
+    static constexpr bool kTotal = false, kHeavy = false;
+    using Raw = Pack<1>;
+    __device__ Pack<1> pack(const Pack<1>& p) const { return p; }
+    int32_t n, n_inst;
+    const int32_t* net_rp;
+    const int32_t* hint_rp;
+    int4* rb;
+    int32_t* counts;
+    __device__ Pack<1> first(int64_t i) const {
+        const int32_t r = static_cast<int32_t>(i);
+        if (is_long_row(r, net_rp, hint_rp)) return {{0}};
+        const bool st = r == 0 || is_long_row(r - 1, net_rp, hint_rp) || rb_break(r, n_inst, net_rp, hint_rp);
+        const bool en = r == n - 1 || is_long_row(r + 1, net_rp, hint_rp) || rb_break(r + 1, n_inst, net_rp, hint_rp);
+        return {{pack2(st ? 1 : 0, en ? 1 : 0)}};
+    }
+    __device__ Pack<1> again(int64_t i) const { return first(i); }
+    __device__ void item(int64_t r, const Pack<1>& own, const Pack<1>& before, const Pack<1>&) const {
+        if (r == n_inst) counts[1] = pack_lo(before.v[0]);
+        if (pack_lo(own.v[0])) {        // block k starts here
+            const int64_t k = pack_lo(before.v[0]);
+            rb[2 * k].x = static_cast<int32_t>(r);
+            rb[2 * k].z = net_rp[r];
+            rb[2 * k + 1].x = hint_rp[r];
+        }
+        if (pack_hi(own.v[0])) {        // block k ends with this row
+            const int64_t k = pack_hi(before.v[0]);
+            rb[2 * k].y = static_cast<int32_t>(r + 1);
+            rb[2 * k].w = net_rp[r + 1];
+            rb[2 * k + 1].y = hint_rp[r + 1];
+        }
+    }
+    __device__ void done(const Pack<1>& total) const { counts[0] = pack_lo(total.v[0]); }
+};
 
 __global__ void k_coef(int32_t n, const float* __restrict__ scale, const double* __restrict__ lam, double sigma,
                        float2* __restrict__ coef) {
@@ -1603,106 +1628,65 @@ void expand_batch_c(const ExpandArgs* d, const int32_t* blk0, int32_t n_blocks, 
 }  // namespace
 
 // Row classes in two halves around the read of their counts: the first
-// launches the flags, scans and the read; whatever the caller queues before
-// the second runs while the host waits for the counts.  `extra`, when given,
-// is one more device word read with them (to *extra_out).
-struct RowClassScratch {
-    DevBuf<int32_t> is_long, rank, nch, cscan;
-};
-
+// launches the scan and the read; whatever the caller queues before the
+// second runs while the host waits for the counts.  `extra`, when given, is
+// one more device word read with them (to *extra_out).  The lists are sized by
+// the bound on the entries: a long row has more than kLongRow of them.
 static void row_classes_begin(const int32_t* net_rp, const int32_t* hint_rp, int32_t N, int32_t n_inst,
-                              RowClassScratch& t, DevBuf<int64_t>& scan_tmp, hipStream_t s,
+                              int64_t max_entries, RowClasses& rc, DevBuf<int64_t>& scan_tmp, hipStream_t s,
                               const int32_t* extra = nullptr) {
-    const size_t n1 = static_cast<size_t>(N) + 1;
-    t.is_long.ensure(n1, s);
-    t.nch.ensure(n1, s);
-    hipLaunchKernelGGL(k_row_chunks, dim3(grid_for(N, kBT)), dim3(kBT), 0, s, N, net_rp, hint_rp, t.is_long.p,
-                       t.nch.p);
-    AHR_LAUNCHED("k_row_chunks");
-    t.rank.ensure(n1, s);
-    t.cscan.ensure(n1, s);
-    scan_tmp.ensure(scan_tmp_elems(N), s);
-    scan_i32_to_i32(t.is_long.p, t.rank.p, N, scan_tmp.p, s);
-    scan_i32_to_i32(t.nch.p, t.cscan.p, N, scan_tmp.p, s);
-    std::vector<const int32_t*> words{t.rank.p + N,  t.rank.p + n_inst, t.cscan.p + N, t.cscan.p + n_inst,
-                                      net_rp + n_inst, hint_rp + n_inst, net_rp + N, hint_rp + N};
+    const int64_t max_long = std::min<int64_t>(N, max_entries / kLongRow);
+    rc.long_rows.ensure(static_cast<size_t>(max_long) + 1, s);
+    rc.long_chunk0.ensure(static_cast<size_t>(max_long) + 1, s);
+    rc.chunk_row.ensure(static_cast<size_t>(max_long + max_entries / kChunk) + 1, s);
+    rc.counts.ensure(4, s);
+    run_scans(scan_job(LongRowScan{net_rp, hint_rp, n_inst, rc.long_rows.p, rc.long_chunk0.p, rc.chunk_row.p,
+                                   rc.counts.p},
+                       N),
+              scan_tmp, s);
+    std::vector<const int32_t*> words{rc.counts.p,     rc.counts.p + 1,  rc.counts.p + 2, rc.counts.p + 3,
+                                      net_rp + n_inst, hint_rp + n_inst, net_rp + N,      hint_rp + N};
     if (extra) words.push_back(extra);
     read_scalars_begin(words, s);
 }
 
-static void row_classes_end(int32_t N, RowClasses& rc, RowClassScratch& t, hipStream_t s,
-                            int32_t* extra_out = nullptr) {
+static void row_classes_end(int32_t N, int32_t n_inst, RowClasses& rc, hipStream_t s, int32_t* extra_out = nullptr) {
     int32_t v[9];
     read_scalars_end(v, extra_out ? 9 : 8);
     if (extra_out) *extra_out = v[8];
     rc.nnz_net_all = v[6];
     rc.nnz_hint_all = v[7];
     rc.n_long = v[0];
-    rc.n_long_inst = v[1];
     rc.n_chunks = v[2];
-    rc.n_chunks_inst = v[3];
+    // (no row n_inst: every row is an instance's)
+    rc.n_long_inst = n_inst < N ? v[1] : v[0];
+    rc.n_chunks_inst = n_inst < N ? v[3] : v[2];
     rc.nnz_inst = static_cast<int64_t>(v[4]) + v[5];
     rc.has_rb = 0;
-    rc.long_rows.ensure(static_cast<size_t>(rc.n_long) + 1, s);
-    list_rows(t.is_long.p, t.rank.p, N, rc.long_rows.p, s);
-    rc.long_chunk0.ensure(static_cast<size_t>(rc.n_long) + 1, s);
-    hipLaunchKernelGGL(k_long_chunk0, dim3(grid_for(static_cast<int64_t>(rc.n_long) + 1, kBT)), dim3(kBT), 0, s,
-                       rc.n_long, rc.long_rows.p, t.cscan.p, rc.n_chunks, rc.long_chunk0.p);
-    AHR_LAUNCHED("k_long_chunk0");
-    rc.chunk_row.ensure(static_cast<size_t>(rc.n_chunks) + 1, s);
-    if (rc.n_long) {
-        hipLaunchKernelGGL(k_chunk_rows, dim3(rc.n_long), dim3(kBT), 0, s, rc.n_long, rc.long_chunk0.p,
-                           rc.chunk_row.p);
-        AHR_LAUNCHED("k_chunk_rows");
-    }
     rc.partial.ensure(static_cast<size_t>(rc.n_chunks) * 8 + 8, s);
-    t.is_long.release(s);
-    t.rank.release(s);
-    t.nch.release(s);
-    t.cscan.release(s);
 }
 
-void row_classes(const int32_t* net_rp, const int32_t* hint_rp, int32_t N, int32_t n_inst, RowClasses& rc,
-                 DevBuf<int64_t>& scan_tmp, hipStream_t s) {
-    RowClassScratch t;
-    row_classes_begin(net_rp, hint_rp, N, n_inst, t, scan_tmp, s);
-    row_classes_end(N, rc, t, s);
+void row_classes(const int32_t* net_rp, const int32_t* hint_rp, int32_t N, int32_t n_inst, int64_t max_entries,
+                 RowClasses& rc, DevBuf<int64_t>& scan_tmp, hipStream_t s) {
+    row_classes_begin(net_rp, hint_rp, N, n_inst, max_entries, rc, scan_tmp, s);
+    row_classes_end(N, n_inst, rc, s);
 }
 
 void row_blocks(const int32_t* net_rp, const int32_t* hint_rp, int32_t N, int32_t n_inst, RowClasses& rc,
                 DevBuf<int64_t>& scan_tmp, hipStream_t s) {
     if (rc.has_rb) return;
-    DevBuf<int32_t> is_long, st, en, srank, erank, starts, ends;
-    const size_t n1 = static_cast<size_t>(N) + 1;
-    is_long.ensure(n1, s);
-    hipLaunchKernelGGL(k_row_len, dim3(grid_for(N, kBT)), dim3(kBT), 0, s, N, net_rp, hint_rp, is_long.p);
-    AHR_LAUNCHED("k_row_len");
-    st.ensure(n1, s);
-    en.ensure(n1, s);
-    hipLaunchKernelGGL(k_rb_marks, dim3(grid_for(N, kBT)), dim3(kBT), 0, s, N, n_inst, net_rp, hint_rp, is_long.p, st.p,
-                       en.p);
-    AHR_LAUNCHED("k_rb_marks");
-    srank.ensure(n1, s);
-    erank.ensure(n1, s);
-    scan_tmp.ensure(scan_tmp_elems(N), s);
-    scan_i32_to_i32(st.p, srank.p, N, scan_tmp.p, s);
-    scan_i32_to_i32(en.p, erank.p, N, scan_tmp.p, s);
+    // a block starts at row 0 or n_inst, after a long row, or in a new window
+    // of kRbRows rows or kRbEntries entries
+    const int64_t bound = 2 + rc.n_long + static_cast<int64_t>(N) / kRbRows +
+                          (rc.nnz_net_all + rc.nnz_hint_all) / kRbEntries;
+    rc.rb.ensure(2 * static_cast<size_t>(bound) + 2, s);
+    rc.counts.ensure(4, s);
+    run_scans(scan_job(RowBlockScan{N, n_inst, net_rp, hint_rp, rc.rb.p, rc.counts.p}, N), scan_tmp, s);
     int32_t t[2];
-    read_scalars({srank.p + N, srank.p + n_inst}, t, s);
+    read_scalars({rc.counts.p, rc.counts.p + 1}, t, s);
     rc.n_rb = t[0];
-    rc.n_rb_inst = t[1];
-    starts.ensure(static_cast<size_t>(rc.n_rb) + 1, s);
-    ends.ensure(static_cast<size_t>(rc.n_rb) + 1, s);
-    list_rows(st.p, srank.p, N, starts.p, s);
-    list_rows(en.p, erank.p, N, ends.p, s);
-    rc.rb.ensure(2 * static_cast<size_t>(rc.n_rb) + 2, s);
-    if (rc.n_rb) {
-        hipLaunchKernelGGL(k_rb_desc, dim3(grid_for(rc.n_rb, kBT)), dim3(kBT), 0, s, rc.n_rb, starts.p, ends.p, net_rp,
-                           hint_rp, rc.rb.p);
-        AHR_LAUNCHED("k_rb_desc");
-    }
+    rc.n_rb_inst = n_inst < N ? t[1] : t[0];
     rc.has_rb = 1;
-    for (auto* b : {&is_long, &st, &en, &srank, &erank, &starts, &ends}) b->release(s);
 }
 
 void hop_coefs(int32_t n, const float* scale, const double* lam, double sigma, float2* coef, hipStream_t s) {
@@ -1806,12 +1790,12 @@ void normalise_degrees(Graph& g, const ahr_filter_spec& spec, hipStream_t s) {
     RowRef m{g.xnet_rp.p, nullptr, g.xhint_rp.p, g.xhint_ent.p};
 
     // the row classes' counts are read while the short rows' degrees run
-    RowClassScratch rct;
     const bool new_rows = g.rows_version != g.hint_version;
     // the layout's locality verdict rides along with the first counts
     const bool want_loc = new_rows && g.hop_local < 0 && g.loc_flag.p;
     if (new_rows)
-        row_classes_begin(g.xnet_rp.p, g.xhint_rp.p, N, g.n_inst, rct, g.scan_tmp, s,
+        row_classes_begin(g.xnet_rp.p, g.xhint_rp.p, N, g.n_inst,
+                          static_cast<int64_t>(g.nnz_cap) + static_cast<int64_t>(g.xhint_ent.n), g.rc, g.scan_tmp, s,
                           want_loc ? g.loc_flag.p : nullptr);
 
     const double sigma = spec.sigma;
@@ -1834,7 +1818,7 @@ void normalise_degrees(Graph& g, const ahr_filter_spec& spec, hipStream_t s) {
     }
     if (new_rows) {
         int32_t loc = 1;
-        row_classes_end(N, g.rc, rct, s, want_loc ? &loc : nullptr);
+        row_classes_end(N, g.n_inst, g.rc, s, want_loc ? &loc : nullptr);
         if (want_loc) g.hop_local = loc ? 1 : 0;
         g.rows_version = g.hint_version;
         g.nnz_net = static_cast<int32_t>(g.rc.nnz_net_all);

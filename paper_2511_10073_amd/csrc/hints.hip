@@ -10,13 +10,13 @@
 
 #include "ahr_internal.hpp"
 #include "device_util.hpp"
+#include "scan.hpp"
 
 namespace ahr {
 
 namespace {
 
 constexpr int kBT = 256;
-constexpr double kAreaQ = 268435456.0;         // bin areas in units of 2^-28 (exact integer sums)
 
 struct Grid {
     int nbx, nby;
@@ -31,8 +31,6 @@ __device__ __forceinline__ int bin_coord(float v, float lo, float w, int nb) {
     if (f >= static_cast<float>(nb - 1)) return nb - 1;
     return static_cast<int>(f);
 }
-
-__device__ __forceinline__ bool is_std_movable(uint8_t f) { return (f & (AHR_NODE_FIXED | AHR_NODE_MACRO)) == 0; }
 
 // The bin-hint weight of a cell at (x, y) towards bin (bx, by) is
 // -exp(-max(rx, ry)) phi_b baseWeight_i, with rx and ry its distances from
@@ -64,31 +62,6 @@ __device__ __forceinline__ float w_macro(float x, float y, float4 m, double bw_i
     double ry = fabs(static_cast<double>(y) - static_cast<double>(m.y)) / static_cast<double>(m.w);
     double r = rx > ry ? rx : ry;
     return static_cast<float>(-exp(-r) * bw_i);
-}
-
-// Per execution row, once per graph: the cell's fixed-point area times 4
-// plus its class (0: not a movable standard cell, 1: movable standard cell
-// without nets, 2: movable standard cell with nets, a hint cell), and its
-// baseWeight; the per-round kernels then read them in row order.
-constexpr int64_t kCellOther = 0, kCellStd = 1, kCellHint = 2;
-
-// One thread per instance, in instance order (coalesced reads), storing to
-// its execution row (two scattered stores instead of four scattered loads).
-__global__ void k_exec_cells(int32_t n_inst, const int32_t* __restrict__ iperm, const uint8_t* __restrict__ flags,
-                             const float* __restrict__ size, const int64_t* __restrict__ qdeg,
-                             const double* __restrict__ base_w, int64_t* __restrict__ xcell,
-                             double* __restrict__ xbase_w) {
-    int64_t i = static_cast<int64_t>(blockIdx.x) * blockDim.x + threadIdx.x;
-    if (i >= n_inst) return;
-    const int r = iperm[i];
-    int64_t c = kCellOther;
-    if (is_std_movable(flags[i])) {
-        double a = static_cast<double>(size[2 * i]) * static_cast<double>(size[2 * i + 1]);
-        int64_t q = static_cast<int64_t>(__builtin_rint(a * kAreaQ));
-        c = q * 4 + (qdeg[i] > 0 ? kCellHint : kCellStd);
-    }
-    xcell[r] = c;
-    xbase_w[r] = base_w[i];
 }
 
 // Bin of every hint cell (-1 otherwise), indexed by execution row, the
@@ -210,11 +183,12 @@ __global__ void k_macros(Grid gr, const float* __restrict__ pos, int ncols, cons
     }
 }
 
-__global__ void k_phi(int nbins, double bin_area, double cap, double mu, const unsigned long long* __restrict__ area_q,
-                      double* __restrict__ phi) {
+// From a bin's cell area and macro area.
+__global__ void k_phi(int nbins, double bin_area, double cap, double mu, const int64_t* __restrict__ cell_q,
+                      const int64_t* __restrict__ macro_q, double* __restrict__ phi) {
     int b = blockIdx.x * blockDim.x + threadIdx.x;
     if (b >= nbins) return;
-    double D = (static_cast<double>(static_cast<int64_t>(area_q[b])) / kAreaQ) / bin_area;
+    double D = (static_cast<double>(cell_q[b] + macro_q[b]) / kAreaQ) / bin_area;
     phi[b] = 2.0 / (1.0 + exp(-mu * (D - cap))) - 1.0;
 }
 
@@ -257,7 +231,6 @@ struct HintArgs {
     const float4* rect;
     const int4* span;
     const double* phi;
-    const double* base_w;         // by instance
     const float2* xpos;           // by execution row
     const double* xbase_w;        // by execution row
     double* habs;                 // by execution row: sum of |weight| of the cell's hint entries
@@ -398,39 +371,57 @@ __global__ void k_tile_carry(const int32_t* __restrict__ tile_start, int nbins, 
     kept[i] = acc;
 }
 
-// The three row-count passes in one launch (they write disjoint rows of
-// cnt): cell rows, then macro rows (when mb > 0 workgroups), then bin rows.
-__global__ void k_hint_row_counts(HintArgs a, int32_t n_inst, const int32_t* __restrict__ nmac,
-                                  const int32_t* __restrict__ nwin, int32_t n_macro, int32_t first_mvirt,
-                                  const int32_t* __restrict__ mstart, int32_t cb, int32_t mb,
-                                  int32_t* __restrict__ cnt) {
-    const int32_t b = static_cast<int32_t>(blockIdx.x);
-    const int64_t t = static_cast<int64_t>(threadIdx.x);
-    if (b < cb) {
-        const int64_t r = static_cast<int64_t>(b) * kBT + t;
-        if (r < n_inst) cnt[r] = nmac[r] + nwin[r];
-    } else if (b < cb + mb) {
-        const int64_t k = static_cast<int64_t>(b - cb) * kBT + t;
-        if (k < n_macro) cnt[first_mvirt + k] = mstart[k + 1] - mstart[k];
-    } else {
-        const int64_t bin = static_cast<int64_t>(b - cb - mb) * kBT + t;
-        if (bin >= a.nbins) return;
-        int x0, x1, y0, y1;
-        window(a.gr, static_cast<int>(bin), x0, x1, y0, y1);
-        int n = 0;
+// The hint rows' entry counts, scanned into their offsets: cell rows hold
+// their macros and window bins, macro rows their pairs, bin rows the cells of
+// the bins of their window (with pruning, those that kept the edge).  A bin
+// row's window is walked slot by slot (row-major, out-of-grid slots empty);
+// wpre[b][slot] gets the entries of bin row b before that slot.
+struct HintRowScan {
+    static constexpr int K = 1;
+    static constexpr bool kTotal = false, kHeavy = true;
+    using Raw = Pack<1>;
+    __device__ Pack<1> pack(const Pack<1>& p) const { return p; }
+    HintArgs a;
+    int32_t n_tot;
+    const int32_t* nmac;
+    const int32_t* nwin;
+    const int32_t* mstart;
+    int32_t* wpre;
+    int32_t* rp;                // [n_tot + 1]; the counts until the rows are placed
+    int64_t* total;             // the exact count, also where it does not fit int32
+    __device__ int32_t count(int64_t r) const {
+        if (r < a.n_inst) return nmac[r] + nwin[r];
+        if (r < a.first_mvirt) return 0;
+        if (r < a.first_bvirt) return a.macro_hints ? mstart[r - a.first_mvirt + 1] - mstart[r - a.first_mvirt] : 0;
+        if (!a.bin_hints) return 0;
+        const int b = static_cast<int>(r - a.first_bvirt);
         const int ww = 2 * a.gr.hx + 1, wslots = ww * (2 * a.gr.hy + 1);
-        const int tbx = static_cast<int>(bin % a.gr.nbx), tby = static_cast<int>(bin / a.gr.nbx);
-        for (int by = y0; by <= y1; ++by)
-            for (int bx = x0; bx <= x1; ++bx) {
-                const int bb = by * a.gr.nbx + bx;
-                if (a.kept)     // the cells of bb keeping their edge to this bin
-                    n += a.kept[static_cast<int64_t>(bb) * wslots + (tby - by + a.gr.hy) * ww + (tbx - bx + a.gr.hx)];
-                else
-                    n += a.bin_start[bb + 1] - a.bin_start[bb];
-            }
-        cnt[a.first_bvirt + bin] = n;
+        const int bx = b % a.gr.nbx, by = b / a.gr.nbx;
+        int acc = 0;
+        for (int w = 0; w < wslots; ++w) {
+            wpre[static_cast<int64_t>(b) * wslots + w] = acc;
+            const int tx = bx + w % ww - a.gr.hx, ty = by + w / ww - a.gr.hy;
+            if (tx < 0 || tx >= a.gr.nbx || ty < 0 || ty >= a.gr.nby) continue;
+            const int bb = ty * a.gr.nbx + tx;
+            acc += a.kept ? a.kept[static_cast<int64_t>(bb) * wslots + (wslots - 1 - w)]
+                          : a.bin_start[bb + 1] - a.bin_start[bb];
+        }
+        return acc;
     }
-}
+    __device__ Pack<1> first(int64_t r) const {
+        const int32_t c = count(r);
+        rp[r] = c;
+        return {{c}};
+    }
+    __device__ Pack<1> again(int64_t r) const { return {{rp[r]}}; }
+    __device__ void item(int64_t r, const Pack<1>&, const Pack<1>& before, const Pack<1>&) const {
+        rp[r] = static_cast<int32_t>(before.v[0]);
+    }
+    __device__ void done(const Pack<1>& t) const {
+        rp[n_tot] = static_cast<int32_t>(t.v[0]);
+        *total = t.v[0];
+    }
+};
 
 // Cell rows: macro entries (ascending macro) then window bins (row-major).
 // Each bin entry is also written, with the same float, into the bin's own
@@ -596,24 +587,6 @@ __global__ void __launch_bounds__(kBT) k_bin_side_fill(HintArgs a, const int32_t
     }
 }
 
-// wpre[b][slot]: entries of bin row b before window slot `slot` (row-major,
-// out-of-grid slots empty).
-__global__ void k_window_prefix(HintArgs a, int32_t* __restrict__ wpre) {
-    int b = blockIdx.x * blockDim.x + threadIdx.x;
-    if (b >= a.nbins) return;
-    const int ww = 2 * a.gr.hx + 1, wh = 2 * a.gr.hy + 1;
-    const int bx = b % a.gr.nbx, by = b / a.gr.nbx;
-    int acc = 0;
-    for (int w = 0; w < ww * wh; ++w) {
-        wpre[static_cast<int64_t>(b) * ww * wh + w] = acc;
-        int tx = bx + w % ww - a.gr.hx, ty = by + w / ww - a.gr.hy;
-        if (tx < 0 || tx >= a.gr.nbx || ty < 0 || ty >= a.gr.nby) continue;
-        int bb = ty * a.gr.nbx + tx;
-        acc += a.kept ? a.kept[static_cast<int64_t>(bb) * ww * wh + (ww * wh - 1 - w)]
-                      : a.bin_start[bb + 1] - a.bin_start[bb];
-    }
-}
-
 // Macro virtual rows: the transpose of the cell->macro pairs (pairs grouped
 // by macro, ascending row); each weight is the cell-side entry's value.
 __global__ void k_macro_fill(int32_t n_pairs, int32_t first_mvirt, const int32_t* __restrict__ mlist,
@@ -629,21 +602,12 @@ __global__ void k_macro_fill(int32_t n_pairs, int32_t first_mvirt, const int32_t
     ent[rp[first_mvirt + k] + (t - mstart[k])] = make_int2(row, w);
 }
 
-__global__ void k_copy_u64(const unsigned long long* __restrict__ src, unsigned long long* __restrict__ dst,
-                           int64_t n) {
+// Zeros in one or two arrays of n values.
+__global__ void k_clear_u64(unsigned long long* __restrict__ p, unsigned long long* __restrict__ q, int64_t n) {
     const int64_t i = static_cast<int64_t>(blockIdx.x) * blockDim.x + threadIdx.x;
-    if (i < n) dst[i] = src[i];
-}
-
-__global__ void k_add_u64(const unsigned long long* __restrict__ src, unsigned long long* __restrict__ dst,
-                          int64_t n) {
-    const int64_t i = static_cast<int64_t>(blockIdx.x) * blockDim.x + threadIdx.x;
-    if (i < n) dst[i] += src[i];
-}
-
-__global__ void k_fill_u64(unsigned long long* p, int64_t n) {
-    int64_t i = static_cast<int64_t>(blockIdx.x) * blockDim.x + threadIdx.x;
-    if (i < n) p[i] = 0ull;
+    if (i >= n) return;
+    p[i] = 0ull;
+    if (q) q[i] = 0ull;
 }
 
 }  // namespace
@@ -713,9 +677,7 @@ void build_hints(Graph& g, const float* pos, int32_t ncols, hipStream_t s, bool 
     const int bin_hints = (hp.flags & AHR_BIN_HINTS) ? 1 : 0;
     const int32_t N = g.n_tot, n_inst = g.n_inst;
     if (!g.has_layout) set_layout(g, pos, ncols, s);
-    g.hint_cnt.ensure(static_cast<size_t>(N) + 1, s);
     g.xhint_rp.ensure(static_cast<size_t>(N) + 1, s);
-    fill_i32(g.hint_cnt.p, N + 1, 0, s);
     g.hint_version++;
     g.has_hints = 1;
     if (!macro_hints && !bin_hints) {
@@ -723,7 +685,6 @@ void build_hints(Graph& g, const float* pos, int32_t ncols, hipStream_t s, bool 
         g.nnz_hint = 0;
         g.n_hint_cells = 0;
         g.xhint_ent.ensure(1, s);
-        AHR_HIP(hipStreamSynchronize(s));
         return;
     }
 
@@ -743,14 +704,6 @@ void build_hints(Graph& g, const float* pos, int32_t ncols, hipStream_t s, bool 
     const int nbins = hp.nbx * hp.nby;
 
     // 1. cell bins (execution rows), cell areas, positions in row order
-    if (!g.has_xcell) {
-        g.xcell.ensure(static_cast<size_t>(n_inst) + 1, s);
-        g.xbase_w.ensure(static_cast<size_t>(n_inst) + 1, s);
-        hipLaunchKernelGGL(k_exec_cells, dim3(grid_for(n_inst, kBT)), dim3(kBT), 0, s, n_inst, g.iperm.p,
-                           g.nl.node_flags, g.nl.node_size, g.qdeg.p, g.base_w.p, g.xcell.p, g.xbase_w.p);
-        AHR_LAUNCHED("k_exec_cells");
-        g.has_xcell = 1;
-    }
     g.xpos.ensure(static_cast<size_t>(n_inst) + 1, s);
     g.cell_bin.ensure(static_cast<size_t>(n_inst) + 1, s);
     g.bin_area_q.ensure(static_cast<size_t>(nbins) + 1, s);
@@ -758,16 +711,13 @@ void build_hints(Graph& g, const float* pos, int32_t ncols, hipStream_t s, bool 
     // footprints, spans, per-bin areas and bin lists are those of that call.
     const bool reuse = macros_unchanged && g.macro_cache && g.n_movable_macro == 0;
     g.macro_cache = 0;
-    if (reuse && bin_hints) {     // the density starts from the macros' areas
-        hipLaunchKernelGGL(k_copy_u64, dim3(grid_for(nbins, kBT)), dim3(kBT), 0, s,
-                           reinterpret_cast<const unsigned long long*>(g.macro_area_q.p),
-                           reinterpret_cast<unsigned long long*>(g.bin_area_q.p), static_cast<int64_t>(nbins));
-        AHR_LAUNCHED("k_copy_u64");
-    } else {
-        hipLaunchKernelGGL(k_fill_u64, dim3(grid_for(nbins, kBT)), dim3(kBT), 0, s,
-                           reinterpret_cast<unsigned long long*>(g.bin_area_q.p), static_cast<int64_t>(nbins));
-        AHR_LAUNCHED("k_fill_u64");
-    }
+    // (the cells' area per bin, and the macros' where it is formed again)
+    g.macro_area_q.ensure(static_cast<size_t>(nbins) + 1, s);
+    hipLaunchKernelGGL(k_clear_u64, dim3(grid_for(nbins, kBT)), dim3(kBT), 0, s,
+                       reinterpret_cast<unsigned long long*>(g.bin_area_q.p),
+                       reinterpret_cast<unsigned long long*>(reuse ? nullptr : g.macro_area_q.p),
+                       static_cast<int64_t>(nbins));
+    AHR_LAUNCHED("k_clear_u64");
     const size_t bins_lds = nbins <= kLdsBins ? static_cast<size_t>(nbins) * sizeof(unsigned long long) : 0;
     hipLaunchKernelGGL(k_cell_bins, dim3(grid_for(n_inst, kBT * kCellBinRows)), dim3(kBT), bins_lds, s, gr, pos, ncols,
                        n_inst, g.perm.p, g.xcell.p, bin_hints, g.cell_bin.p, g.xpos.p,
@@ -786,27 +736,16 @@ void build_hints(Graph& g, const float* pos, int32_t ncols, hipStream_t s, bool 
     g.macro_rect.ensure(static_cast<size_t>(n_macro) + 1, s);
     g.macro_span.ensure(static_cast<size_t>(n_macro) + 1, s);
     if (n_macro && !reuse) {
-        // the macros' areas go to macro_area_q (kept), then into the density
-        g.macro_area_q.ensure(static_cast<size_t>(nbins) + 1, s);
-        hipLaunchKernelGGL(k_fill_u64, dim3(grid_for(nbins, kBT)), dim3(kBT), 0, s,
-                           reinterpret_cast<unsigned long long*>(g.macro_area_q.p), static_cast<int64_t>(nbins));
-        AHR_LAUNCHED("k_fill_u64");
         hipLaunchKernelGGL(k_macros, dim3(grid_for(n_macro, kBT)), dim3(kBT), 0, s, gr, pos, ncols, g.macro_ids.p,
                            n_macro, g.nl.node_size, bin_hints, g.macro_rect.p, g.macro_span.p,
                            reinterpret_cast<unsigned long long*>(g.macro_area_q.p));
         AHR_LAUNCHED("k_macros");
-        if (bin_hints) {
-            hipLaunchKernelGGL(k_add_u64, dim3(grid_for(nbins, kBT)), dim3(kBT), 0, s,
-                               reinterpret_cast<const unsigned long long*>(g.macro_area_q.p),
-                               reinterpret_cast<unsigned long long*>(g.bin_area_q.p), static_cast<int64_t>(nbins));
-            AHR_LAUNCHED("k_add_u64");
-        }
     }
     g.phi.ensure(static_cast<size_t>(nbins) + 1, s);
     if (bin_hints) {
         hipLaunchKernelGGL(k_phi, dim3(grid_for(nbins, kBT)), dim3(kBT), 0, s, nbins, gr.bw * gr.bh,
                            static_cast<double>(hp.bin_capacity), static_cast<double>(hp.mu),
-                           reinterpret_cast<const unsigned long long*>(g.bin_area_q.p), g.phi.p);
+                           g.bin_area_q.p, g.macro_area_q.p, g.phi.p);
         AHR_LAUNCHED("k_phi");
     }
 
@@ -856,7 +795,6 @@ void build_hints(Graph& g, const float* pos, int32_t ncols, hipStream_t s, bool 
     a.rect = g.macro_rect.p;
     a.span = g.macro_span.p;
     a.phi = g.phi.p;
-    a.base_w = g.base_w.p;
     a.xpos = g.xpos.p;
     a.xbase_w = g.xbase_w.p;
     g.xhabs.ensure(static_cast<size_t>(n_inst) + 1, s);
@@ -926,14 +864,10 @@ void build_hints(Graph& g, const float* pos, int32_t ncols, hipStream_t s, bool 
     if (use_macros) bucket_sort(g, {g.pair_mac.p}, n_pairs, n_macro, g.mlist, g.mstart, s);
 
     // 6. row counts and offsets (execution order)
-    {
-        const int32_t cb = static_cast<int32_t>(grid_for(n_inst, kBT));
-        const int32_t mb = use_macros ? static_cast<int32_t>(grid_for(n_macro, kBT)) : 0;
-        const int32_t bb = bin_hints ? static_cast<int32_t>(grid_for(nbins, kBT)) : 0;
-        hipLaunchKernelGGL(k_hint_row_counts, dim3(cb + mb + bb), dim3(kBT), 0, s, a, n_inst, g.nmac.p, g.nwin.p,
-                           n_macro, g.first_mvirt, g.mstart.p, cb, mb, g.hint_cnt.p);
-        AHR_LAUNCHED("k_hint_row_counts");
-    }
+    if (bin_hints) g.wpre.ensure(static_cast<size_t>(nbins) * wslots + 1, s);
+    g.i64a.ensure(1, s);
+    run_scans(scan_job(HintRowScan{a, N, g.nmac.p, g.nwin.p, g.mstart.p, g.wpre.p, g.xhint_rp.p, g.i64a.p}, N),
+              g.scan_tmp, s);
     // Every entry is one side of a (cell, macro) pair or of a (hint cell,
     // window bin) pair, so the entries number at most twice the pairs plus
     // twice the hint cells times the window slots: the entry array is sized
@@ -944,22 +878,15 @@ void build_hints(Graph& g, const float* pos, int32_t ncols, hipStream_t s, bool 
     int64_t cap = bound;
     g.nnz_hint = -1;
     if (bound + static_cast<int64_t>(g.nnz_net) >= INT32_MAX) {
-        const int64_t nnz = scan_i32_checked(g.hint_cnt.p, g.xhint_rp.p, N, g.scan_tmp.p, s);
+        const int64_t nnz = read_i64(g.i64a.p, s);
         if (nnz + static_cast<int64_t>(g.nnz_net) >= INT32_MAX)
             throw Error{AHR_EUNSUPPORTED, "graph with hints has 2^31 or more entries"};
         g.nnz_hint = static_cast<int32_t>(nnz);
         cap = nnz;
-    } else {
-        scan_i32_to_i32(g.hint_cnt.p, g.xhint_rp.p, N, g.scan_tmp.p, s);
     }
     g.xhint_ent.ensure(static_cast<size_t>(cap) + 1, s);
 
     // 7. entries: cell rows first (their weights are reused), then virtual rows
-    if (bin_hints) {
-        g.wpre.ensure(static_cast<size_t>(nbins) * wslots + 1, s);
-        hipLaunchKernelGGL(k_window_prefix, dim3(grid_for(nbins, kBT)), dim3(kBT), 0, s, a, g.wpre.p);
-        AHR_LAUNCHED("k_window_prefix");
-    }
     hipLaunchKernelGGL(k_cell_fill, dim3(grid_for(n_inst, kBT)), dim3(kBT), 0, s, a,
                        static_cast<const int32_t*>(g.xhint_rp.p), static_cast<const int32_t*>(g.pair_off.p),
                        static_cast<const int32_t*>(g.pair_mac.p), static_cast<const int32_t*>(g.bin_rank.p),

@@ -34,6 +34,7 @@
 // about 1/32 of them there), else the netlist order is taken.
 #include "ahr_internal.hpp"
 #include "device_util.hpp"
+#include "scan.hpp"
 
 namespace ahr {
 
@@ -115,20 +116,32 @@ __global__ void k_layout_keys(KeyArgs a, int32_t* __restrict__ key) {
     key[i] = (range << (2 * kGridBits)) | hilbert_index(gx, gy);
 }
 
-// Stable sort of each aligned window of kLenWindow positions of `in` by the
-// netlist row length of its instance (one wave per window): the rank of an
-// element is the number of elements of its window with a smaller length, or
-// the same length and an earlier position.
+// perm and iperm from the sorted order `in`.  The instances take a stable
+// sort of each aligned window of kLenWindow positions by netlist row length
+// (one wave per window): the rank of an element is the number of elements of
+// its window with a smaller length, or the same length and an earlier
+// position.  The macro pins and stars stay as sorted; the virtual rows (from
+// n_perm on) map to themselves.
 constexpr int kLenWindow = 64;
 
-__global__ void __launch_bounds__(kLenWindow) k_window_sort(int32_t n, const int32_t* __restrict__ in,
+__global__ void __launch_bounds__(kLenWindow) k_window_sort(int32_t n_inst, int32_t n_perm, int32_t n_tot,
+                                                            const int32_t* __restrict__ in,
                                                             const int32_t* __restrict__ net_len,
-                                                            int32_t* __restrict__ out) {
+                                                            int32_t* __restrict__ perm, int32_t* __restrict__ iperm) {
     __shared__ int32_t wlen[kLenWindow];
     const int t = threadIdx.x;
-    const int64_t j = static_cast<int64_t>(blockIdx.x) * kLenWindow + t;
-    int32_t id = 0, len = INT32_MAX;                 // positions past n sort last and are not written
-    if (j < n) {
+    const int32_t windows = (n_inst + kLenWindow - 1) / kLenWindow;
+    if (static_cast<int32_t>(blockIdx.x) >= windows) {
+        const int64_t r = n_inst + static_cast<int64_t>(blockIdx.x - windows) * kLenWindow + t;
+        if (r >= n_tot) return;
+        const int32_t v = r < n_perm ? in[r] : static_cast<int32_t>(r);
+        perm[r] = v;
+        iperm[v] = static_cast<int32_t>(r);
+        return;
+    }
+    const int32_t j = static_cast<int32_t>(blockIdx.x) * kLenWindow + t;
+    int32_t id = 0, len = INT32_MAX;                 // positions past n_inst sort last and are not written
+    if (j < n_inst) {
         id = in[j];
         len = net_len[id];
     }
@@ -139,26 +152,23 @@ __global__ void __launch_bounds__(kLenWindow) k_window_sort(int32_t n, const int
         const int32_t o = wlen[u];
         rank += (o < len || (o == len && u < t)) ? 1 : 0;
     }
-    if (j < n) out[static_cast<int64_t>(blockIdx.x) * kLenWindow + rank] = id;
-}
-
-// Both directions over all n_tot rows: the virtual rows (from n_perm on)
-// map to themselves.
-__global__ void k_iperm(int32_t* __restrict__ perm, int32_t n_perm, int32_t n_tot, int32_t* __restrict__ iperm) {
-    int64_t r = static_cast<int64_t>(blockIdx.x) * blockDim.x + threadIdx.x;
-    if (r < n_perm) {
-        iperm[perm[r]] = static_cast<int32_t>(r);
-    } else if (r < n_tot) {
-        perm[r] = static_cast<int32_t>(r);
-        iperm[r] = static_cast<int32_t>(r);
+    if (j < n_inst) {
+        const int32_t r = static_cast<int32_t>(blockIdx.x) * kLenWindow + rank;
+        perm[r] = id;
+        iperm[id] = r;
     }
 }
 
-
-// Per execution row, from its node: the netlist row length, the row weight
-// sum, and for the macro pin and star rows what the expansion reads (a
-// macro pin's owner instance and pin offset, a star's net).
-struct ExecRowArgs {
+// Per execution row, from its node: the netlist row length, scanned into the
+// row offsets, the row weight sum, for the macro pin and star rows what the
+// expansion reads (a macro pin's owner instance and pin offset, a star's
+// net), and for the instances what every hint round reads in row order (area
+// and class, baseWeight).
+struct ExecRowScan {
+    static constexpr int K = 1;
+    static constexpr bool kTotal = false, kHeavy = true;
+    using Raw = Pack<1>;
+    __device__ Pack<1> pack(const Pack<1>& p) const { return p; }
     int32_t n_tot, n_inst, first_star, first_mvirt;
     const int32_t* perm;
     const int32_t* net_len;
@@ -167,26 +177,44 @@ struct ExecRowArgs {
     const int32_t* pin_node;
     const float* pin_off;
     const int32_t* star_net;
-    int32_t* len;
+    const uint8_t* flags;
+    const float* size;
     int64_t* xqdeg;
     int4* xmpin;
     int32_t* xstar_net;
-};
-
-__global__ void k_exec_rows(ExecRowArgs a) {
-    const int64_t r = static_cast<int64_t>(blockIdx.x) * blockDim.x + threadIdx.x;
-    if (r >= a.n_tot) return;
-    const int v = a.perm[r];
-    a.len[r] = a.net_len[v];
-    a.xqdeg[r] = a.qdeg[v];
-    if (r >= a.n_inst && r < a.first_star) {
-        const int p = a.mpin_pin[v - a.n_inst];
-        a.xmpin[r - a.n_inst] =
-            make_int4(a.pin_node[p], __float_as_int(a.pin_off[2 * p]), __float_as_int(a.pin_off[2 * p + 1]), 0);
-    } else if (r >= a.first_star && r < a.first_mvirt) {
-        a.xstar_net[r - a.first_star] = a.star_net[v - a.first_star];
+    int64_t* xcell;             // or null: no hints will be built
+    double* xbase_w;
+    int32_t* rp;                // [n_tot + 1]; the lengths until the rows are placed
+    __device__ Pack<1> first(int64_t r) const {
+        const int v = perm[r], l = net_len[v];
+        const int64_t q = qdeg[v];
+        rp[r] = l;
+        xqdeg[r] = q;
+        if (r < n_inst) {
+            if (!xcell) return {{l}};
+            int64_t c = kCellOther;
+            if ((flags[v] & (AHR_NODE_FIXED | AHR_NODE_MACRO)) == 0) {
+                const double area = static_cast<double>(size[2 * v]) * static_cast<double>(size[2 * v + 1]);
+                c = static_cast<int64_t>(__builtin_rint(area * kAreaQ)) * 4 + (q > 0 ? kCellHint : kCellStd);
+            }
+            xcell[r] = c;
+            // Section V: baseWeight, the mean weight of the instance's netlist entries
+            xbase_w[r] = l > 0 && q != 0 ? (static_cast<double>(q) * 0x1p-32) / static_cast<double>(l) : 0.0;
+        } else if (r < first_star) {
+            const int p = mpin_pin[v - n_inst];
+            xmpin[r - n_inst] =
+                make_int4(pin_node[p], __float_as_int(pin_off[2 * p]), __float_as_int(pin_off[2 * p + 1]), 0);
+        } else if (r < first_mvirt) {
+            xstar_net[r - first_star] = star_net[v - first_star];
+        }
+        return {{l}};
     }
-}
+    __device__ Pack<1> again(int64_t r) const { return {{rp[r]}}; }
+    __device__ void item(int64_t r, const Pack<1>&, const Pack<1>& before, const Pack<1>&) const {
+        rp[r] = static_cast<int32_t>(before.v[0]);
+    }
+    __device__ void done(const Pack<1>& total) const { rp[n_tot] = static_cast<int32_t>(total.v[0]); }
+};
 
 // Execution-order netlist rows: each row copies its canonical row's
 // entries with columns renumbered and weights as float32.  Rows of at most
@@ -252,29 +280,18 @@ __global__ void __launch_bounds__(kBT) k_exec_net(int32_t n_tot, const int32_t* 
     }
 }
 
-// One workgroup per longer row; the workgroups stride over the list of
-// long rows, whose length they read from the device (*n_long).
-constexpr int kLongRowGrid = 512;
-
-__global__ void __launch_bounds__(kBT) k_exec_net_long(const int32_t* __restrict__ rows,
-                                                       const int32_t* __restrict__ n_long,
-                                                       const int32_t* __restrict__ perm,
+// The longer rows, one workgroup per node of the build's list (the nodes
+// whose rows may be that long).
+__global__ void __launch_bounds__(kBT) k_exec_net_long(const int32_t* __restrict__ nodes,
                                                        const int32_t* __restrict__ iperm,
                                                        const int64_t* __restrict__ off, const int32_t* __restrict__ col,
                                                        const int64_t* __restrict__ q, const int32_t* __restrict__ xrp,
                                                        int2* __restrict__ xent) {
-    const int nl = *n_long;
-    for (int li = blockIdx.x; li < nl; li += gridDim.x) {
-        const int r = rows[li];
-        const int d = xrp[r], len = xrp[r + 1] - d;
-        const int64_t a = off[perm[r]];
-        for (int k = threadIdx.x; k < len; k += kBT) xent[d + k] = exec_entry(col[a + k], q[a + k], iperm);
-    }
-}
-
-__global__ void k_long_flags(int32_t n_tot, const int32_t* __restrict__ xrp, int32_t* __restrict__ flag) {
-    int64_t r = static_cast<int64_t>(blockIdx.x) * blockDim.x + threadIdx.x;
-    if (r < n_tot) flag[r] = (xrp[r + 1] - xrp[r] > kShortRow) ? 1 : 0;
+    const int v = nodes[blockIdx.x], r = iperm[v];
+    const int d = xrp[r], len = xrp[r + 1] - d;
+    if (len <= kShortRow) return;
+    const int64_t a = off[v];
+    for (int k = threadIdx.x; k < len; k += kBT) xent[d + k] = exec_entry(col[a + k], q[a + k], iperm);
 }
 
 
@@ -550,15 +567,13 @@ static void sort_keys(Graph& g, const DevBuf<int32_t>& key, int32_t np, int lo_b
 static void finish_perm(Graph& g, const DevBuf<int32_t>& order, hipStream_t s) {
     const int32_t n = g.n_inst, N = g.n_tot, np = g.first_mvirt;
     g.perm.ensure(static_cast<size_t>(N) + 1, s);
-    hipLaunchKernelGGL(k_window_sort, dim3(grid_for(n, kLenWindow)), dim3(kLenWindow), 0, s, n, order.p, g.net_len.p,
-                       g.perm.p);
-    AHR_LAUNCHED("k_window_sort");
-    if (np > n)
-        AHR_HIP(hipMemcpyAsync(g.perm.p + n, order.p + n, static_cast<size_t>(np - n) * sizeof(int32_t),
-                               hipMemcpyDeviceToDevice, s));
     g.iperm.ensure(static_cast<size_t>(N) + 1, s);
-    hipLaunchKernelGGL(k_iperm, dim3(grid_for(N, kBT)), dim3(kBT), 0, s, g.perm.p, np, N, g.iperm.p);
-    AHR_LAUNCHED("k_iperm");
+    const unsigned windows = static_cast<unsigned>((n + kLenWindow - 1) / kLenWindow);
+    const unsigned others = static_cast<unsigned>((N - n + kLenWindow - 1) / kLenWindow);
+    if (windows + others)
+        hipLaunchKernelGGL(k_window_sort, dim3(windows + others), dim3(kLenWindow), 0, s, n, np, N, order.p,
+                           g.net_len.p, g.perm.p, g.iperm.p);
+    AHR_LAUNCHED("k_window_sort");
 }
 
 // The Hilbert order of the placement's positions.
@@ -708,19 +723,21 @@ void set_layout(Graph& g, const float* pos, int32_t ncols, hipStream_t s) {
     // verdict is read with the first row classes
     if (!tested) locality_begin(g, s);
 
-    DevBuf<int32_t> len;
-    len.ensure(static_cast<size_t>(N) + 1, s);
     g.xqdeg.ensure(static_cast<size_t>(N) + 1, s);
     g.xmpin.ensure(static_cast<size_t>(g.first_star - n) + 1, s);
     g.xstar_net.ensure(static_cast<size_t>(np - g.first_star) + 1, s);
-    ExecRowArgs ea{N, n, g.first_star, np, g.perm.p, g.net_len.p, g.qdeg.p, g.mpin_pin.p, g.nl.pin_node,
-                   g.nl.pin_off, g.star_net.p, len.p, g.xqdeg.p, g.xmpin.p, g.xstar_net.p};
-    hipLaunchKernelGGL(k_exec_rows, dim3(grid_for(N, kBT)), dim3(kBT), 0, s, ea);
-    AHR_LAUNCHED("k_exec_rows");
     g.xnet_rp.ensure(static_cast<size_t>(N) + 1, s);
-    g.scan_tmp.ensure(scan_tmp_elems(N), s);
-    scan_i32_to_i32(len.p, g.xnet_rp.p, N, g.scan_tmp.p, s);
-    len.release(s);
+    const bool hints = fl & (AHR_MACRO_HINTS | AHR_BIN_HINTS);
+    if (hints) {
+        g.xcell.ensure(static_cast<size_t>(n) + 1, s);
+        g.xbase_w.ensure(static_cast<size_t>(n) + 1, s);
+    }
+    run_scans(scan_job(ExecRowScan{N, n, g.first_star, np, g.perm.p, g.net_len.p, g.qdeg.p, g.mpin_pin.p,
+                                   g.nl.pin_node, g.nl.pin_off, g.star_net.p, g.nl.node_flags, g.nl.node_size,
+                                   g.xqdeg.p, g.xmpin.p, g.xstar_net.p, hints ? g.xcell.p : nullptr, g.xbase_w.p,
+                                   g.xnet_rp.p},
+                       N),
+              g.scan_tmp, s);
     g.xnet_ent.ensure(static_cast<size_t>(g.nnz_cap) + 1, s);      // the netlist arrays' bound
     if (g.nnz_cap) {
         // Nothing reads the execution-order entries before the first hop, so
@@ -747,28 +764,16 @@ void set_layout(Graph& g, const float* pos, int32_t ncols, hipStream_t s) {
 }
 
 // The execution-order netlist entries: short rows by k_exec_net, long rows
-// by k_exec_net_long from a device-built list, all on stream s2.
+// by k_exec_net_long, all on stream s2.
 static void exec_net_copy(Graph& g, int32_t N, hipStream_t s2) {
     hipLaunchKernelGGL(k_exec_net, dim3(grid_for(static_cast<int64_t>(N) * 8, kBT)), dim3(kBT), 0, s2, N,
                        g.perm.p, g.iperm.p, g.net_off.p, g.net_col.p, g.net_q.p, g.xnet_rp.p, g.xnet_ent.p);
     AHR_LAUNCHED("k_exec_net");
-    DevBuf<int32_t> flag, rank, rows;
-    DevBuf<int64_t> tmp;     // not g.scan_tmp: s uses that meanwhile
-    flag.ensure(static_cast<size_t>(N) + 1, s2);
-    rank.ensure(static_cast<size_t>(N) + 1, s2);
-    tmp.ensure(scan_tmp_elems(N), s2);
-    hipLaunchKernelGGL(k_long_flags, dim3(grid_for(N, kBT)), dim3(kBT), 0, s2, N, g.xnet_rp.p, flag.p);
-    AHR_LAUNCHED("k_long_flags");
-    scan_i32_to_i32(flag.p, rank.p, N, tmp.p, s2);
-    rows.ensure(static_cast<size_t>(N) + 1, s2);
-    list_rows(flag.p, rank.p, N, rows.p, s2);
-    hipLaunchKernelGGL(k_exec_net_long, dim3(kLongRowGrid), dim3(kBT), 0, s2, rows.p, rank.p + N, g.perm.p,
-                       g.iperm.p, g.net_off.p, g.net_col.p, g.net_q.p, g.xnet_rp.p, g.xnet_ent.p);
-    AHR_LAUNCHED("k_exec_net_long");
-    flag.release(s2);
-    rank.release(s2);
-    rows.release(s2);
-    tmp.release(s2);
+    if (g.n_long_nodes) {
+        hipLaunchKernelGGL(k_exec_net_long, dim3(g.n_long_nodes), dim3(kBT), 0, s2, g.long_nodes.p, g.iperm.p,
+                           g.net_off.p, g.net_col.p, g.net_q.p, g.xnet_rp.p, g.xnet_ent.p);
+        AHR_LAUNCHED("k_exec_net_long");
+    }
 }
 
 const int2* net_entries(const Graph& g, hipStream_t s) {

@@ -8,6 +8,7 @@
 
 #include "ahr_internal.hpp"
 #include "device_util.hpp"
+#include "scan.hpp"
 
 namespace ahr {
 
@@ -32,72 +33,130 @@ __global__ void k_validate(const int32_t* __restrict__ net_ptr, int32_t n_nets, 
     }
 }
 
-__global__ void k_mark_mpin(const int32_t* __restrict__ pin_node, const uint8_t* __restrict__ flags, int32_t n_pins,
-                            int32_t n_inst, int32_t expand, int32_t* __restrict__ is_mp) {
-    int64_t p = static_cast<int64_t>(blockIdx.x) * blockDim.x + threadIdx.x;
-    if (p >= n_pins) return;
-    const int v = pin_node[p];
-    const uint8_t f = flags[v >= 0 && v < n_inst ? v : 0];      // clamped: runs before the netlist is verified
-    is_mp[p] = (expand && (f & AHR_NODE_FIXED) && (f & AHR_NODE_MACRO)) ? 1 : 0;
-}
+// The ranks of the pins that become nodes of their own (pins of fixed macros).
+struct PinScan {
+    static constexpr int K = 1;
+    static constexpr bool kTotal = false, kHeavy = false;
+    using Raw = Pack<1>;
+    __device__ Pack<1> pack(const Pack<1>& p) const { return p; }
+    const int32_t* pin_node;
+    const uint8_t* flags;
+    int32_t n_pins, n_inst, expand;
+    uint8_t* is_mp;             // [n_pins] between the passes
+    int32_t* rank;              // [n_pins + 1]
+    int32_t* count;
+    __device__ Pack<1> first(int64_t p) const {
+        const int v = pin_node[p];
+        const uint8_t f = flags[v >= 0 && v < n_inst ? v : 0];      // clamped: runs before the netlist is verified
+        const bool mp = expand && (f & AHR_NODE_FIXED) && (f & AHR_NODE_MACRO);
+        is_mp[p] = mp ? 1 : 0;
+        return {{mp ? 1 : 0}};
+    }
+    __device__ Pack<1> again(int64_t p) const { return {{is_mp[p]}}; }
+    __device__ void item(int64_t p, const Pack<1>&, const Pack<1>& before, const Pack<1>&) const {
+        rank[p] = pack_lo(before.v[0]);
+    }
+    __device__ void done(const Pack<1>& total) const { rank[n_pins] = *count = pack_lo(total.v[0]); }
+};
 
-__global__ void k_pin_nodes(const int32_t* __restrict__ pin_node, const int32_t* __restrict__ is_mp,
-                            const int32_t* __restrict__ mp_rank, int32_t n_pins, int32_t n_inst,
-                            int32_t* __restrict__ pin_node_x, int32_t* __restrict__ mp_owner,
-                            int32_t* __restrict__ mp_pin) {
-    int64_t p = static_cast<int64_t>(blockIdx.x) * blockDim.x + threadIdx.x;
-    if (p >= n_pins) return;
-    int v = pin_node[p];
-    if (is_mp[p]) {
-        int r = mp_rank[p];
-        pin_node_x[p] = n_inst + r;
-        mp_owner[r] = v;
-        mp_pin[r] = static_cast<int32_t>(p);
-    } else {
-        pin_node_x[p] = v;
+// Per net: star (more than clique_max pins), big (more pins than a wave),
+// big star (a star whose spokes a whole workgroup averages); their ranks.
+struct NetScan {
+    static constexpr int K = 2;
+    static constexpr bool kTotal = false, kHeavy = false;
+    using Raw = Pack<2>;
+    __device__ Pack<2> pack(const Pack<2>& p) const { return p; }
+    const int32_t* net_ptr;
+    int32_t n_nets, clique_max;
+    int32_t *star, *big, *big_star;      // [n_nets + 1]
+    int32_t* counts;                     // the three totals
+    __device__ Pack<2> first(int64_t e) const {
+        const int deg = net_ptr[e + 1] - net_ptr[e];
+        return {{pack2(deg > clique_max ? 1 : 0, deg > kWave ? 1 : 0), deg > clique_max && deg > kStarMid ? 1 : 0}};
+    }
+    __device__ Pack<2> again(int64_t e) const { return first(e); }
+    __device__ void put(int64_t e, const Pack<2>& at) const {
+        star[e] = pack_lo(at.v[0]);
+        big[e] = pack_hi(at.v[0]);
+        big_star[e] = pack_lo(at.v[1]);
+    }
+    __device__ void item(int64_t e, const Pack<2>&, const Pack<2>& before, const Pack<2>&) const { put(e, before); }
+    __device__ void done(const Pack<2>& total) const {
+        put(n_nets, total);
+        counts[0] = pack_lo(total.v[0]);
+        counts[1] = pack_hi(total.v[0]);
+        counts[2] = pack_lo(total.v[1]);
+    }
+};
+
+// The macros' ranks, and the counts of all and of movable macros.
+struct MacroScan {
+    static constexpr int K = 1;
+    static constexpr bool kTotal = false, kHeavy = false;
+    using Raw = Pack<1>;
+    __device__ Pack<1> pack(const Pack<1>& p) const { return p; }
+    const uint8_t* flags;
+    int32_t n;
+    int32_t* rank;              // [n + 1]
+    int32_t* counts;
+    __device__ Pack<1> first(int64_t i) const {
+        const uint8_t f = flags[i];
+        const bool m = f & AHR_NODE_MACRO;
+        return {{pack2(m ? 1 : 0, m && !(f & AHR_NODE_FIXED) ? 1 : 0)}};
+    }
+    __device__ Pack<1> again(int64_t i) const { return first(i); }
+    __device__ void item(int64_t i, const Pack<1>&, const Pack<1>& before, const Pack<1>&) const {
+        rank[i] = pack_lo(before.v[0]);
+    }
+    __device__ void done(const Pack<1>& total) const {
+        rank[n] = counts[0] = pack_lo(total.v[0]);
+        counts[1] = pack_hi(total.v[0]);
+    }
+};
+
+// What the ranks place, in one launch: the pins' nodes, the lists of macro
+// pins, stars, big nets, big stars (by star index) and macros, the net of
+// every pin of the nets of at most a wave's worth of pins (k_pin_net_big
+// writes the others'), and zeros in the row counters.
+struct ListArgs {
+    const int32_t *net_ptr, *pin_node;
+    int32_t n_pins, n_nets, n_inst;
+    const int32_t *mp_rank, *star_rank, *big_rank, *bs_rank, *mac_rank;
+    int32_t *pin_node_x, *mp_owner, *mp_pin, *star_net, *big_nets, *big_stars, *macro_ids, *pin_net, *cnt;
+    int32_t n_cnt;
+};
+
+__global__ void k_build_lists(ListArgs a) {
+    const int64_t i = static_cast<int64_t>(blockIdx.x) * blockDim.x + threadIdx.x;
+    if (i < a.n_cnt) a.cnt[i] = 0;
+    if (i < a.n_pins) {
+        const int v = a.pin_node[i], r = a.mp_rank[i];
+        if (a.mp_rank[i + 1] > r) {
+            a.pin_node_x[i] = a.n_inst + r;
+            a.mp_owner[r] = v;
+            a.mp_pin[r] = static_cast<int32_t>(i);
+        } else {
+            a.pin_node_x[i] = v;
+        }
+    }
+    if (i < a.n_inst) {
+        const int r = a.mac_rank[i];
+        if (a.mac_rank[i + 1] > r) a.macro_ids[r] = static_cast<int32_t>(i);
+    }
+    if (i < a.n_nets) {
+        const int e = static_cast<int>(i), s = a.star_rank[i], b = a.big_rank[i], bs = a.bs_rank[i];
+        if (a.star_rank[i + 1] > s) a.star_net[s] = e;
+        if (a.bs_rank[i + 1] > bs) a.big_stars[bs] = s;
+        if (a.big_rank[i + 1] > b) {
+            a.big_nets[b] = e;
+        } else {
+            for (int p = a.net_ptr[i]; p < a.net_ptr[i + 1]; ++p) a.pin_net[p] = e;
+        }
     }
 }
 
-// Per net: star (more than clique_max pins), big (more pins than a wave),
-// big star (a star whose spokes a whole workgroup averages).
-__global__ void k_mark_star(const int32_t* __restrict__ net_ptr, int32_t n_nets, int32_t clique_max,
-                            int32_t* __restrict__ is_star, int32_t* __restrict__ is_big,
-                            int32_t* __restrict__ is_big_star) {
-    int64_t e = static_cast<int64_t>(blockIdx.x) * blockDim.x + threadIdx.x;
-    if (e >= n_nets) return;
-    int deg = net_ptr[e + 1] - net_ptr[e];
-    is_star[e] = deg > clique_max ? 1 : 0;
-    is_big[e] = deg > kWave ? 1 : 0;
-    is_big_star[e] = (deg > clique_max && deg > kStarMid) ? 1 : 0;
-}
-
-// Star index (rank among the stars) of every big-star net, ascending.
-__global__ void k_list_big_stars(const int32_t* __restrict__ flag, const int32_t* __restrict__ rank,
-                                 const int32_t* __restrict__ star_rank, int32_t n_nets, int32_t* __restrict__ out) {
-    int64_t e = static_cast<int64_t>(blockIdx.x) * blockDim.x + threadIdx.x;
-    if (e < n_nets && flag[e]) out[rank[e]] = star_rank[e];
-}
-
-// Macro flags, and the count of movable macros in *movable.
-__global__ void k_mark_macro(const uint8_t* __restrict__ flags, int32_t n, int32_t* __restrict__ out,
-                             int32_t* __restrict__ movable) {
-    int64_t i = static_cast<int64_t>(blockIdx.x) * blockDim.x + threadIdx.x;
-    if (i >= n) return;
-    const uint8_t f = flags[i];
-    out[i] = (f & AHR_NODE_MACRO) ? 1 : 0;
-    if ((f & AHR_NODE_MACRO) && !(f & AHR_NODE_FIXED)) atomicAdd(movable, 1);
-}
-
-// Net of every pin: one thread per net of at most a wave's worth of pins,
-// one workgroup per bigger net (k_pin_net_big over the big-net list).
-__global__ void k_pin_net(const int32_t* __restrict__ net_ptr, int32_t n_nets, int32_t* __restrict__ pin_net) {
-    int64_t e = static_cast<int64_t>(blockIdx.x) * blockDim.x + threadIdx.x;
-    if (e >= n_nets) return;
-    const int lo = net_ptr[e], hi = net_ptr[e + 1];
-    if (hi - lo > kWave) return;
-    for (int p = lo; p < hi; ++p) pin_net[p] = static_cast<int32_t>(e);
-}
-
+// Net of every pin of the nets with more than a wave's worth of pins, one
+// workgroup each.
 __global__ void k_pin_net_big(const int32_t* __restrict__ big, const int32_t* __restrict__ net_ptr,
                               int32_t* __restrict__ pin_net) {
     const int e = big[blockIdx.x];
@@ -227,59 +286,115 @@ __global__ void k_scatter(NetArgs a, const int64_t* __restrict__ rp, const int32
 }
 
 // Row classes by entry count: 0 (<= 1), 1 (<= 8), 2 (<= 16), 3 (<= 32),
-// 4 (<= 64), 5 (longer); classes 1-4 are sorted by 8, 16, 32 and 64 lanes
-// per row.
-constexpr int kSortClasses = 6;
-__device__ __forceinline__ int row_class(int c) {
-    return c <= 1 ? 0 : (c <= 8 ? 1 : (c <= 16 ? 2 : (c <= 32 ? 3 : (c <= 64 ? 4 : 5))));
+// 4 (<= 64), 5 (<= kMidRow), 6 (longer); classes 1-4 are sorted by 8, 16, 32
+// and 64 lanes per row, 5 and 6 by workgroups of kMidBT and kLongBT threads.
+constexpr int kSortClasses = 7;
+constexpr int kMidRow = 2048;
+__device__ __forceinline__ int row_class(int64_t c) {
+    return c <= 1 ? 0 : c <= 8 ? 1 : c <= 16 ? 2 : c <= 32 ? 3 : c <= 64 ? 4 : c <= kMidRow ? 5 : 6;
 }
 
-__global__ void k_class_keys(const int32_t* __restrict__ cnt, int32_t n, int32_t* __restrict__ key) {
-    int64_t r = static_cast<int64_t>(blockIdx.x) * blockDim.x + threadIdx.x;
-    if (r < n) key[r] = row_class(cnt[r]);
+// The rows' first slots, and the rows listed by class (ascending within one).
+struct RowScan {
+    static constexpr int K = 4;
+    static constexpr bool kTotal = true, kHeavy = false;
+    using Raw = int32_t;        // the row's count and one, 0 for no row
+    const int32_t* cnt;
+    int32_t n;
+    int64_t* rp;                // [n + 1]
+    int32_t* list;              // [n]
+    int32_t* start;             // [kSortClasses + 1]
+    __device__ int32_t first(int64_t r) const { return cnt[r] + 1; }
+    __device__ int32_t again(int64_t r) const { return first(r); }
+    __device__ Pack<4> pack(int32_t c1) const {
+        const int c = c1 > 0 ? c1 - 1 : 0, k = row_class(c);
+        Pack<4> p{{c, 0, 0, 0}};
+#pragma unroll
+        for (int q = 1; q < kSortClasses; ++q)
+            if (k == q) p.v[1 + (q - 1) / 2] = (q - 1) & 1 ? int64_t(1) << 32 : 1;
+        return p;
+    }
+    // of the rows counted in t (of which there are `rows`), those of class k
+    __device__ static int32_t of(const Pack<4>& t, int64_t rows, int k) {
+        int64_t others = 0;
+        int32_t own = 0;
+#pragma unroll
+        for (int q = 1; q < kSortClasses; ++q) {
+            const int32_t c = (q - 1) & 1 ? pack_hi(t.v[1 + (q - 1) / 2]) : pack_lo(t.v[1 + (q - 1) / 2]);
+            others += c;
+            own = q == k ? c : own;
+        }
+        return k ? own : static_cast<int32_t>(rows - others);
+    }
+    __device__ void item(int64_t r, int32_t c1, const Pack<4>& before, const Pack<4>& total) const {
+        rp[r] = before.v[0];
+        const int k = row_class(c1 - 1);
+        int32_t at = of(before, r, k);
+#pragma unroll
+        for (int q = 0; q < kSortClasses - 1; ++q) at += q < k ? of(total, n, q) : 0;
+        list[at] = static_cast<int32_t>(r);
+    }
+    __device__ void done(const Pack<4>& total) const {
+        rp[n] = total.v[0];
+        int32_t at = 0;
+        for (int q = 0; q <= kSortClasses; ++q) {
+            start[q] = at;
+            if (q < kSortClasses) at += of(total, n, q);
+        }
+    }
+};
+
+// The sorted rows' arrays: row r's raw entries are raw[rp[r]..+cnt[r]); its
+// merged entries go to the same slots of scol and sq, their number to len and
+// their weight sum to qdeg.
+struct SortArgs {
+    const int32_t* cnt;
+    const int64_t* rp;
+    const RawEnt* raw;
+    int32_t* scol;
+    int64_t* sq;
+    int32_t* len;
+    int64_t* qdeg;
+};
+
+__device__ __forceinline__ void row_done(const SortArgs& a, int r, int len, int64_t q) {
+    a.len[r] = len;
+    a.qdeg[r] = q;
 }
 
 // Rows with at most one entry: copy through.
-__global__ void k_sort_trivial(const int32_t* __restrict__ rows, int32_t nrows, const int32_t* __restrict__ cnt,
-                               const int64_t* __restrict__ rp, const RawEnt* __restrict__ raw,
-                               int32_t* __restrict__ scol, int64_t* __restrict__ sq,
-                               int32_t* __restrict__ ucnt, int64_t* __restrict__ qdeg) {
-    int64_t i = static_cast<int64_t>(blockIdx.x) * blockDim.x + threadIdx.x;
+__device__ __forceinline__ void sort_trivial(const SortArgs& a, const int32_t* rows, int32_t nrows, int32_t block) {
+    const int64_t i = static_cast<int64_t>(block) * kBT + threadIdx.x;
     if (i >= nrows) return;
-    int r = rows[i];
-    int c = cnt[r];
-    ucnt[r] = c;
+    const int r = rows[i], c = a.cnt[r];
     int64_t q = 0;
     if (c == 1) {
-        const RawEnt e = raw[rp[r]];
-        scol[rp[r]] = e.col;
-        sq[rp[r]] = e.q;
+        const int64_t base = a.rp[r];
+        const RawEnt e = a.raw[base];
+        a.scol[base] = e.col;
+        a.sq[base] = e.q;
         q = e.q;
     }
-    qdeg[r] = q;
+    row_done(a, r, c, q);
 }
 
 // G lanes per row (G = 8, 16, 32 or 64): bitonic sort by column across the lanes,
 // then merge equal columns by exact integer sums.  Narrow: the column ids
 // leave room for a lane index beside them in 31 bits.
 template <int G, bool Narrow>
-__global__ void __launch_bounds__(kBT) k_sort_group(const int32_t* __restrict__ rows, int32_t nrows,
-                                                    const int32_t* __restrict__ cnt, const int64_t* __restrict__ rp,
-                                                    const RawEnt* __restrict__ raw,
-                                                    int32_t* __restrict__ scol, int64_t* __restrict__ sq,
-                                                    int32_t* __restrict__ ucnt, int64_t* __restrict__ qdeg) {
-    int64_t gid = (static_cast<int64_t>(blockIdx.x) * kBT + threadIdx.x) / G;
+__device__ __forceinline__ void sort_group(const SortArgs& a, const int32_t* rows, int32_t nrows, int32_t block) {
+    int64_t gid = (static_cast<int64_t>(block) * kBT + threadIdx.x) / G;
     int l = threadIdx.x & (G - 1);
     int lane = lane_id();
     int gbase = lane - l;      // first lane of this group inside the wave
     bool valid_row = gid < nrows;
     int r = valid_row ? rows[gid] : 0;
-    int len = valid_row ? cnt[r] : 0;
-    int64_t base = valid_row ? rp[r] : 0;
+    int len = valid_row ? a.cnt[r] : 0;
+    int64_t base = valid_row ? a.rp[r] : 0;
     int key = 0x7fffffff;
     int64_t q = 0;
     if (l < len) {
-        const RawEnt e = raw[base + l];
+        const RawEnt e = a.raw[base + l];
         key = e.col;
         q = e.q;
     }
@@ -342,32 +457,51 @@ __global__ void __launch_bounds__(kBT) k_sort_group(const int32_t* __restrict__ 
     uint64_t below_start = (gbase + start) ? (~0ull >> (kWave - (gbase + start))) : 0ull;
     int idx = __popcll(hm & gm & below_start);
     if (tail) {
-        scol[base + idx] = key;
-        sq[base + idx] = sum;
+        a.scol[base + idx] = key;
+        a.sq[base + idx] = sum;
     }
-    if (valid_row && l == 0) ucnt[r] = __popcll(hm & gm);
-    if (valid_row && l == G - 1) qdeg[r] = pre;      // the inclusive scan's last lane: the row's weight sum
+    // (the inclusive scan's last lane holds the row's weight sum)
+    if (valid_row && l == G - 1) row_done(a, r, __popcll(hm & gm), pre);
 }
 
-// One workgroup of kLongBT threads per long row (star rows reach 10^4
-// entries, so the rows' sorts are spread over many lanes): bitonic sort of
-// (column, slot) keys --
-// in LDS when the padded row fits `lds_keys` (dynamic shared memory),
-// otherwise in the row's own segment of `tkey` (global memory) -- with
-// positions past the row end acting as +infinity, then an ordered merge of
-// equal columns.
+// The five classes of at most 64 entries in one launch: workgroups [b[k],
+// b[k+1]) take class k, the wide ones first.
+struct SortLists {
+    const int32_t* rows[5];
+    int32_t n[5];
+    int32_t b[6];
+};
+
+template <bool Narrow>
+__global__ void __launch_bounds__(kBT) k_sort_rows(SortArgs a, SortLists s) {
+    const int32_t b = static_cast<int32_t>(blockIdx.x);
+    if (b < s.b[1]) sort_group<64, Narrow>(a, s.rows[0], s.n[0], b);
+    else if (b < s.b[2]) sort_group<32, Narrow>(a, s.rows[1], s.n[1], b - s.b[1]);
+    else if (b < s.b[3]) sort_group<16, Narrow>(a, s.rows[2], s.n[2], b - s.b[2]);
+    else if (b < s.b[4]) sort_group<8, Narrow>(a, s.rows[3], s.n[3], b - s.b[3]);
+    else sort_trivial(a, s.rows[4], s.n[4], b - s.b[4]);
+}
+
+// One workgroup per longer row: sort of (column, slot) keys -- in LDS when
+// the row fits `lds_keys` (dynamic shared memory), otherwise a bitonic network
+// in the row's own segment of `tkey` (global memory), with positions past the
+// row end acting as +infinity -- then an ordered merge of equal columns.
+// Rows reach 10^4 entries, but most have a few hundred: with kLongBT threads
+// and the LDS of the longest row for each, one row a CU, the 1,700 of a
+// 600k-cell netlist took 441 us.  Up to kMidRow entries they take kMidBT
+// threads and 16 KB, eight rows a CU: 83 us, and 133 for the longer ones.
 constexpr int kLongBT = 1024;
+constexpr int kMidBT = 256;
 
 // Merge sort of a long row's keys (unique 64-bit) by one workgroup, for rows
-// of at most kLongBT * kRunMax keys: thread t sorts the E keys from t E on
-// in registers (odd-even transposition, fixed indices), then log2(kLongBT)
+// of at most BT * RunMax keys: thread t sorts the E keys from t E on
+// in registers (odd-even transposition, fixed indices), then log2(BT)
 // merge rounds double the sorted runs.  In a round each thread finds where
 // its E outputs start on the merge path of its pair of runs (binary
 // search), merges them into registers, and after a barrier writes them back
 // in place.  Slots past n hold ~0 and sort last.  O(n log n) LDS traffic,
 // against O(n log^2 n) for the bitonic network used for longer rows.
-constexpr int kRunMax = 16;
-
+template <int BT, int kRunMax>
 __device__ void block_merge_sort(const RawEnt* __restrict__ raw, int64_t base, int n, int E, uint64_t* key) {
     const int t = threadIdx.x;
     uint64_t v[kRunMax];
@@ -391,7 +525,7 @@ __device__ void block_merge_sort(const RawEnt* __restrict__ raw, int64_t base, i
     for (int u = 0; u < kRunMax; ++u)
         if (u < E) key[t * E + u] = v[u];
     __syncthreads();
-    const int total = kLongBT * E;
+    const int total = BT * E;
     for (int w = E; w < total; w <<= 1) {
         const int d0 = t * E;
         const int s = d0 / (2 * w) * (2 * w);
@@ -423,29 +557,27 @@ __device__ void block_merge_sort(const RawEnt* __restrict__ raw, int64_t base, i
     }
 }
 
-__global__ void __launch_bounds__(kLongBT) k_sort_long(const int32_t* __restrict__ rows, const int32_t* __restrict__ cnt,
-                                                   const int64_t* __restrict__ rp, const RawEnt* __restrict__ raw,
-                                                   uint64_t* __restrict__ tkey,
-                                                   int32_t* __restrict__ scol, int64_t* __restrict__ sq,
-                                                   int32_t* __restrict__ ucnt, int64_t* __restrict__ qdeg,
-                                                   int lds_keys) {
+template <int BT, int RunMax>
+__global__ void __launch_bounds__(BT) k_sort_long(SortArgs a, const int32_t* __restrict__ rows,
+                                                  uint64_t* __restrict__ tkey, int lds_keys) {
     extern __shared__ uint64_t lkey[];
-    __shared__ int red[kLongBT / kWave];
+    __shared__ int red[BT / kWave];
     __shared__ int carry;
     __shared__ unsigned long long qtot;      // the row's weight sum (exact: integer adds)
+    const RawEnt* raw = a.raw;
     int r = rows[blockIdx.x];
-    int n = cnt[r];
-    int64_t base = rp[r];
-    const int E = (n + kLongBT - 1) / kLongBT;
-    const bool merge = E <= kRunMax && kLongBT * E <= lds_keys;      // block-uniform
+    int n = a.cnt[r];
+    int64_t base = a.rp[r];
+    const int E = (n + BT - 1) / BT;
+    const bool merge = E <= RunMax && BT * E <= lds_keys;      // block-uniform
     int P = 1;
     while (P < n) P <<= 1;
     uint64_t* key = merge || P <= lds_keys ? lkey : tkey + base;
     if (merge) {
-        block_merge_sort(raw, base, n, E, key);
+        block_merge_sort<BT, RunMax>(raw, base, n, E, key);
         P = 0;                                                     // skips the network below
     } else {
-        for (int k = threadIdx.x; k < n; k += kLongBT)
+        for (int k = threadIdx.x; k < n; k += BT)
             key[k] = (static_cast<uint64_t>(static_cast<uint32_t>(raw[base + k].col)) << 32) | static_cast<uint32_t>(k);
         __threadfence_block();
         __syncthreads();
@@ -453,7 +585,7 @@ __global__ void __launch_bounds__(kLongBT) k_sort_long(const int32_t* __restrict
     for (int size = 2; size <= P; size <<= 1) {
         int half = size >> 1;
         // first comparator layer of a merge: mirror pairs
-        for (int i = threadIdx.x; i < P / 2; i += kLongBT) {
+        for (int i = threadIdx.x; i < P / 2; i += BT) {
             int blk = i / half, off = i % half;
             int a = blk * size + off;
             int b = blk * size + size - 1 - off;
@@ -465,7 +597,7 @@ __global__ void __launch_bounds__(kLongBT) k_sort_long(const int32_t* __restrict
         __threadfence_block();
         __syncthreads();
         for (int h = half >> 1; h > 0; h >>= 1) {
-            for (int i = threadIdx.x; i < P / 2; i += kLongBT) {
+            for (int i = threadIdx.x; i < P / 2; i += BT) {
                 int a = (i / h) * 2 * h + (i % h);
                 int b = a + h;
                 if (b < n) {
@@ -482,7 +614,7 @@ __global__ void __launch_bounds__(kLongBT) k_sort_long(const int32_t* __restrict
         qtot = 0;
     }
     __syncthreads();
-    for (int t0 = 0; t0 < n; t0 += kLongBT) {
+    for (int t0 = 0; t0 < n; t0 += BT) {
         int k = t0 + threadIdx.x;
         uint32_t col = 0;
         bool head = false;
@@ -491,32 +623,20 @@ __global__ void __launch_bounds__(kLongBT) k_sort_long(const int32_t* __restrict
             head = (k == 0) || (static_cast<uint32_t>(key[k - 1] >> 32) != col);
         }
         int tot;
-        int idx = block_rank<kLongBT>(head, red, &tot);
+        int idx = block_rank<BT>(head, red, &tot);
         if (head) {
             int64_t s = 0;
             for (int m = k; m < n && static_cast<uint32_t>(key[m] >> 32) == col; ++m)
                 s += raw[base + static_cast<uint32_t>(key[m] & 0xffffffffu)].q;
-            scol[base + carry + idx] = static_cast<int32_t>(col);
-            sq[base + carry + idx] = s;
+            a.scol[base + carry + idx] = static_cast<int32_t>(col);
+            a.sq[base + carry + idx] = s;
             atomicAdd(&qtot, static_cast<unsigned long long>(s));
         }
         __syncthreads();
         if (threadIdx.x == 0) carry += tot;
         __syncthreads();
     }
-    if (threadIdx.x == 0) {
-        ucnt[r] = carry;
-        qdeg[r] = static_cast<int64_t>(qtot);
-    }
-}
-
-__global__ void k_base_weight(int32_t n_inst, const int32_t* __restrict__ net_len, const int64_t* __restrict__ qdeg,
-                              double* __restrict__ bw) {
-    int64_t i = static_cast<int64_t>(blockIdx.x) * blockDim.x + threadIdx.x;
-    if (i >= n_inst) return;
-    int nnz = net_len[i];
-    int64_t q = qdeg[i];
-    bw[i] = (nnz > 0 && q != 0) ? (static_cast<double>(q) * 0x1p-32) / static_cast<double>(nnz) : 0.0;
+    if (threadIdx.x == 0) row_done(a, r, carry, static_cast<int64_t>(qtot));
 }
 
 // Keys of a long row that one workgroup sorts in LDS: the largest power of
@@ -552,79 +672,38 @@ void build_netlist(Graph& g, hipStream_t s) {
     // between index only with clamped pin nodes, so an invalid netlist reads
     // nothing out of bounds before it is rejected.
 
-    // flags of macro pins, star nets, big nets, macros; their ranks; one read of the four counts
-    DevBuf<int32_t> is_mp, mp_rank, is_star, star_rank, is_big, big_rank, is_mac, mac_rank, is_bs, bs_rank;
+    // ranks of macro pins, star nets, big nets, macros; one read of their counts
+    DevBuf<uint8_t> is_mp;
+    DevBuf<int32_t> mp_rank, star_rank, big_rank, mac_rank, bs_rank;
     is_mp.ensure(static_cast<size_t>(n_pins) + 1, s);
-    is_star.ensure(static_cast<size_t>(n_nets) + 1, s);
-    is_big.ensure(static_cast<size_t>(n_nets) + 1, s);
-    is_bs.ensure(static_cast<size_t>(n_nets) + 1, s);
-    is_mac.ensure(static_cast<size_t>(n_inst) + 1, s);
-    if (n_pins)
-        hipLaunchKernelGGL(k_mark_mpin, dim3(grid_for(n_pins, kBT)), dim3(kBT), 0, s, nl.pin_node, nl.node_flags,
-                           n_pins, n_inst, (hp.flags & AHR_EXPAND_MACRO_PINS) ? 1 : 0, is_mp.p);
-    AHR_LAUNCHED("k_mark_mpin");
-    if (n_nets)
-        hipLaunchKernelGGL(k_mark_star, dim3(grid_for(n_nets, kBT)), dim3(kBT), 0, s, nl.net_ptr, n_nets,
-                           hp.clique_max, is_star.p, is_big.p, is_bs.p);
-    AHR_LAUNCHED("k_mark_star");
-    hipLaunchKernelGGL(k_mark_macro, dim3(grid_for(n_inst, kBT)), dim3(kBT), 0, s, nl.node_flags, n_inst, is_mac.p,
-                       g.counter.p + 1);
-    AHR_LAUNCHED("k_mark_macro");
     mp_rank.ensure(static_cast<size_t>(n_pins) + 1, s);
     star_rank.ensure(static_cast<size_t>(n_nets) + 1, s);
     big_rank.ensure(static_cast<size_t>(n_nets) + 1, s);
     bs_rank.ensure(static_cast<size_t>(n_nets) + 1, s);
     mac_rank.ensure(static_cast<size_t>(n_inst) + 1, s);
-    g.scan_tmp.ensure(scan_tmp_elems(std::max<int64_t>(std::max<int64_t>(n_pins, n_nets), n_inst)), s);
-    scan_i32_to_i32(is_mp.p, mp_rank.p, n_pins, g.scan_tmp.p, s);
-    scan_i32_to_i32(is_star.p, star_rank.p, n_nets, g.scan_tmp.p, s);
-    scan_i32_to_i32(is_big.p, big_rank.p, n_nets, g.scan_tmp.p, s);
-    scan_i32_to_i32(is_mac.p, mac_rank.p, n_inst, g.scan_tmp.p, s);
-    scan_i32_to_i32(is_bs.p, bs_rank.p, n_nets, g.scan_tmp.p, s);
-    int32_t cnt5[7];
-    read_scalars({mp_rank.p + n_pins, star_rank.p + n_nets, big_rank.p + n_nets, mac_rank.p + n_inst,
-                  bs_rank.p + n_nets, g.counter.p, g.counter.p + 1},
-                 cnt5, s);
-    if (const int32_t bad = cnt5[5]) {
+    int32_t* c = g.counter.p;      // [0] verdict, [1] macro pins, [2..4] nets, [5..6] macros
+    run_scans(scan_job(PinScan{nl.pin_node, nl.node_flags, n_pins, n_inst, (hp.flags & AHR_EXPAND_MACRO_PINS) ? 1 : 0,
+                               is_mp.p, mp_rank.p, c + 1},
+                       n_pins),
+              g.scan_tmp, s,
+              scan_job(NetScan{nl.net_ptr, n_nets, hp.clique_max, star_rank.p, big_rank.p, bs_rank.p, c + 2}, n_nets),
+              scan_job(MacroScan{nl.node_flags, n_inst, mac_rank.p, c + 5}, n_inst));
+    int32_t cnt7[7];
+    read_scalars({c, c + 1, c + 2, c + 3, c + 4, c + 5, c + 6}, cnt7, s);
+    if (const int32_t bad = cnt7[0]) {
         static const char* why[] = {"", "pin_node out of [0, n_inst)", "net_ptr[0] != 0",
                                     "net_ptr[n_nets] != n_pins", "net_ptr decreasing"};
         throw Error{AHR_EINVAL, std::string("invalid netlist: ") + why[bad]};
     }
-    g.n_mpin = cnt5[0];
-    g.n_star = cnt5[1];
-    g.n_big_nets = cnt5[2];
-    g.n_macro = cnt5[3];
-    g.n_big_stars = cnt5[4];
-    g.n_movable_macro = cnt5[6];
+    is_mp.release(s);
+    g.n_mpin = cnt7[1];
+    g.n_star = cnt7[2];
+    g.n_big_nets = cnt7[3];
+    g.n_big_stars = cnt7[4];
+    g.n_macro = cnt7[5];
+    g.n_movable_macro = cnt7[6];
     if ((hp.flags & AHR_MACRO_HINTS) && g.n_macro > 16384)
         throw Error{AHR_EUNSUPPORTED, "macro hints support at most 16384 macros"};
-    g.star_net.ensure(static_cast<size_t>(g.n_star) + 1, s);
-    g.big_nets.ensure(static_cast<size_t>(g.n_big_nets) + 1, s);
-    g.macro_ids.ensure(static_cast<size_t>(g.n_macro) + 1, s);
-    list_rows(is_star.p, star_rank.p, n_nets, g.star_net.p, s);
-    list_rows(is_big.p, big_rank.p, n_nets, g.big_nets.p, s);
-    list_rows(is_mac.p, mac_rank.p, n_inst, g.macro_ids.p, s);
-    // stars averaged by a whole workgroup
-    g.big_stars.ensure(static_cast<size_t>(g.n_big_stars) + 1, s);
-    if (n_nets)
-        hipLaunchKernelGGL(k_list_big_stars, dim3(grid_for(n_nets, kBT)), dim3(kBT), 0, s, is_bs.p, bs_rank.p,
-                           star_rank.p, n_nets, g.big_stars.p);
-    AHR_LAUNCHED("k_list_big_stars");
-    is_bs.release(s);
-    bs_rank.release(s);
-    g.pin_node_x.ensure(static_cast<size_t>(n_pins) + 1, s);
-    g.mpin_owner.ensure(static_cast<size_t>(g.n_mpin) + 1, s);
-    g.mpin_pin.ensure(static_cast<size_t>(g.n_mpin) + 1, s);
-    if (n_pins)
-        hipLaunchKernelGGL(k_pin_nodes, dim3(grid_for(n_pins, kBT)), dim3(kBT), 0, s, nl.pin_node, is_mp.p, mp_rank.p,
-                           n_pins, n_inst, g.pin_node_x.p, g.mpin_owner.p, g.mpin_pin.p);
-    AHR_LAUNCHED("k_pin_nodes");
-    is_mp.release(s);
-    mp_rank.release(s);
-    is_big.release(s);
-    big_rank.release(s);
-    is_mac.release(s);
-    mac_rank.release(s);
 
     // node ranges
     int64_t first_mpin = n_inst;
@@ -644,22 +723,36 @@ void build_netlist(Graph& g, hipStream_t s) {
     g.n_inst = n_inst;
     const int32_t N = g.n_tot;
 
-    // net of every pin, then entry counts per row (parallel edges counted)
-    DevBuf<int32_t> pin_net;
+    // the lists, the net of every pin, then entry counts per row (parallel
+    // edges counted)
+    DevBuf<int32_t> pin_net, cnt, slot;
     pin_net.ensure(static_cast<size_t>(n_pins) + 1, s);
-    if (n_nets)
-        hipLaunchKernelGGL(k_pin_net, dim3(grid_for(n_nets, kBT)), dim3(kBT), 0, s, nl.net_ptr, n_nets, pin_net.p);
-    AHR_LAUNCHED("k_pin_net");
+    cnt.ensure(static_cast<size_t>(N) + 1, s);
+    slot.ensure(static_cast<size_t>(n_pins) + 1, s);
+    g.star_net.ensure(static_cast<size_t>(g.n_star) + 1, s);
+    g.big_nets.ensure(static_cast<size_t>(g.n_big_nets) + 1, s);
+    g.big_stars.ensure(static_cast<size_t>(g.n_big_stars) + 1, s);
+    g.macro_ids.ensure(static_cast<size_t>(g.n_macro) + 1, s);
+    g.pin_node_x.ensure(static_cast<size_t>(n_pins) + 1, s);
+    g.mpin_owner.ensure(static_cast<size_t>(g.n_mpin) + 1, s);
+    g.mpin_pin.ensure(static_cast<size_t>(g.n_mpin) + 1, s);
+    const ListArgs la{nl.net_ptr,     nl.pin_node,    n_pins,       n_nets,         n_inst,
+                      mp_rank.p,      star_rank.p,    big_rank.p,   bs_rank.p,      mac_rank.p,
+                      g.pin_node_x.p, g.mpin_owner.p, g.mpin_pin.p, g.star_net.p,   g.big_nets.p,
+                      g.big_stars.p,  g.macro_ids.p,  pin_net.p,    cnt.p,          N + 1};
+    const int64_t nlist = std::max<int64_t>(std::max<int64_t>(n_pins, n_nets), static_cast<int64_t>(N) + 1);
+    hipLaunchKernelGGL(k_build_lists, dim3(grid_for(nlist, kBT)), dim3(kBT), 0, s, la);
+    AHR_LAUNCHED("k_build_lists");
+    mp_rank.release(s);
+    big_rank.release(s);
+    bs_rank.release(s);
+    mac_rank.release(s);
     if (g.n_big_nets) {
         hipLaunchKernelGGL(k_pin_net_big, dim3(g.n_big_nets), dim3(kBT), 0, s, g.big_nets.p, nl.net_ptr, pin_net.p);
         AHR_LAUNCHED("k_pin_net_big");
     }
     NetArgs a{nl.net_ptr, pin_net.p, g.pin_node_x.p, nl.net_w, star_rank.p, n_nets, n_pins, hp.clique_max,
               g.first_star};
-    DevBuf<int32_t> cnt, slot;
-    cnt.ensure(static_cast<size_t>(N) + 1, s);
-    fill_i32(cnt.p, N + 1, 0, s);
-    slot.ensure(static_cast<size_t>(n_pins) + 1, s);
     if (n_pins)
         hipLaunchKernelGGL(k_row_counts, dim3(grid_for(n_pins, kBT)), dim3(kBT), 0, s, a, cnt.p, slot.p);
     AHR_LAUNCHED("k_row_counts");
@@ -667,29 +760,25 @@ void build_netlist(Graph& g, hipStream_t s) {
     // first slot, net_len[r] its merged entry count (set by the sorts)
     DevBuf<int64_t>& rp = g.net_off;
     rp.ensure(static_cast<size_t>(N) + 1, s);
-    g.scan_tmp.ensure(scan_tmp_elems(N), s);
-    scan_i32_to_i64(cnt.p, rp.p, N, g.scan_tmp.p, s);
-    // rows grouped by length class (ascending rows within a class), read
-    // with the raw entry total
+    // (rows grouped by length class, ascending within a class)
     constexpr int K = kSortClasses;
-    DevBuf<int32_t> ckey, lists, cstart;
-    ckey.ensure(static_cast<size_t>(N) + 1, s);
-    hipLaunchKernelGGL(k_class_keys, dim3(grid_for(N, kBT)), dim3(kBT), 0, s, cnt.p, N, ckey.p);
-    AHR_LAUNCHED("k_class_keys");
-    bucket_sort(g, {ckey.p}, N, K, lists, cstart, s);
-    ckey.release(s);
-    int64_t w[K + 2];
-    read_words({{rp.p + N, 1}, {cstart.p, 0}, {cstart.p + 1, 0}, {cstart.p + 2, 0}, {cstart.p + 3, 0},
-                {cstart.p + 4, 0}, {cstart.p + 5, 0}, {cstart.p + 6, 0}},
+    DevBuf<int32_t> lists, cstart;
+    lists.ensure(static_cast<size_t>(N) + 1, s);
+    cstart.ensure(K + 1, s);
+    run_scans(scan_job(RowScan{cnt.p, N, rp.p, lists.p, cstart.p}, N), g.scan_tmp, s);
+    int64_t w[K + 1];
+    read_words({{rp.p + N, 1}, {cstart.p + 1, 0}, {cstart.p + 2, 0}, {cstart.p + 3, 0}, {cstart.p + 4, 0},
+                {cstart.p + 5, 0}, {cstart.p + 6, 0}, {cstart.p + 7, 0}},
                w, s);
-    static_assert(K == 6, "class starts read above");
+    static_assert(K == 7, "class starts read above (the first is 0)");
     const int64_t nnz_dup = w[0];
     if (nnz_dup >= INT32_MAX) throw Error{AHR_EUNSUPPORTED, "netlist expands to 2^31 or more graph entries"};
     int32_t ncls[K];
     const int32_t* cls[K];
     for (int k = 0; k < K; ++k) {
-        ncls[k] = static_cast<int32_t>(w[2 + k] - w[1 + k]);
-        cls[k] = lists.p + w[1 + k];
+        const int64_t first = k ? w[k] : 0;
+        ncls[k] = static_cast<int32_t>(w[1 + k] - first);
+        cls[k] = lists.p + first;
     }
 
     DevBuf<int32_t>& scol = g.net_col;
@@ -702,51 +791,50 @@ void build_netlist(Graph& g, hipStream_t s) {
     AHR_LAUNCHED("k_scatter");
     slot.release(s);
     pin_net.release(s);
-    is_star.release(s);
     star_rank.release(s);
 
     // per-row sort + merge by length class
     scol.ensure(static_cast<size_t>(nnz_dup) + 1, s);
     sq.ensure(static_cast<size_t>(nnz_dup) + 1, s);
     ucnt.ensure(static_cast<size_t>(N) + 1, s);
-    fill_i32(ucnt.p, N + 1, 0, s);
     g.qdeg.ensure(static_cast<size_t>(N) + 1, s);
-    if (ncls[0])
-        hipLaunchKernelGGL(k_sort_trivial, dim3(grid_for(ncls[0], kBT)), dim3(kBT), 0, s, cls[0], ncls[0], cnt.p,
-                           rp.p, raw.p, scol.p, sq.p, ucnt.p, g.qdeg.p);
-    AHR_LAUNCHED("k_sort_trivial");
+    const SortArgs sa{cnt.p, rp.p, raw.p, scol.p, sq.p, ucnt.p, g.qdeg.p};
     // rows of up to 64 entries sort (column, lane) pairs packed in 32 bits
     const bool narrow = N < (1 << 25);
-    if (ncls[1])
-        hipLaunchKernelGGL((narrow ? k_sort_group<8, true> : k_sort_group<8, false>),
-                           dim3(grid_for(static_cast<int64_t>(ncls[1]) * 8, kBT)), dim3(kBT), 0, s,
-                           cls[1], ncls[1], cnt.p, rp.p, raw.p, scol.p, sq.p, ucnt.p, g.qdeg.p);
-    AHR_LAUNCHED("k_sort_group8");
-    if (ncls[2])
-        hipLaunchKernelGGL((narrow ? k_sort_group<16, true> : k_sort_group<16, false>),
-                           dim3(grid_for(static_cast<int64_t>(ncls[2]) * 16, kBT)), dim3(kBT), 0, s,
-                           cls[2], ncls[2], cnt.p, rp.p, raw.p, scol.p, sq.p, ucnt.p, g.qdeg.p);
-    AHR_LAUNCHED("k_sort_group16");
-    if (ncls[3])
-        hipLaunchKernelGGL((narrow ? k_sort_group<32, true> : k_sort_group<32, false>),
-                           dim3(grid_for(static_cast<int64_t>(ncls[3]) * 32, kBT)), dim3(kBT), 0, s,
-                           cls[3], ncls[3], cnt.p, rp.p, raw.p, scol.p, sq.p, ucnt.p, g.qdeg.p);
-    AHR_LAUNCHED("k_sort_group32");
-    if (ncls[4])
-        hipLaunchKernelGGL((narrow ? k_sort_group<64, true> : k_sort_group<64, false>),
-                           dim3(grid_for(static_cast<int64_t>(ncls[4]) * 64, kBT)), dim3(kBT), 0, s,
-                           cls[4], ncls[4], cnt.p, rp.p, raw.p, scol.p, sq.p, ucnt.p, g.qdeg.p);
-    AHR_LAUNCHED("k_sort_group64");
+    SortLists sl{};
+    const int lanes[5] = {64, 32, 16, 8, 1};
+    for (int k = 0; k < 5; ++k) {
+        sl.rows[k] = cls[4 - k];
+        sl.n[k] = ncls[4 - k];
+        const int64_t t = static_cast<int64_t>(ncls[4 - k]) * lanes[k];
+        sl.b[k + 1] = sl.b[k] + static_cast<int32_t>((t + kBT - 1) / kBT);
+    }
+    if (sl.b[5]) {
+        hipLaunchKernelGGL((narrow ? k_sort_rows<true> : k_sort_rows<false>), dim3(sl.b[5]), dim3(kBT), 0, s, sa, sl);
+        AHR_LAUNCHED("k_sort_rows");
+    }
     if (ncls[5]) {
+        hipLaunchKernelGGL((k_sort_long<kMidBT, kMidRow / kMidBT>), dim3(ncls[5]), dim3(kMidBT),
+                           kMidRow * sizeof(uint64_t), s, sa, cls[5], static_cast<uint64_t*>(nullptr), kMidRow);
+        AHR_LAUNCHED("k_sort_long mid");
+    }
+    if (ncls[6]) {
         DevBuf<uint64_t> tkey;
         tkey.ensure(static_cast<size_t>(nnz_dup) + 1, s);
         const int lds_keys = sort_lds_keys(g.device);
-        hipLaunchKernelGGL(k_sort_long, dim3(ncls[5]), dim3(kLongBT), static_cast<size_t>(lds_keys) * sizeof(uint64_t), s,
-                           cls[5], cnt.p, rp.p, raw.p, tkey.p, scol.p, sq.p, ucnt.p, g.qdeg.p, lds_keys);
+        hipLaunchKernelGGL((k_sort_long<kLongBT, 16>), dim3(ncls[6]), dim3(kLongBT),
+                           static_cast<size_t>(lds_keys) * sizeof(uint64_t), s, sa, cls[6], tkey.p, lds_keys);
         AHR_LAUNCHED("k_sort_long");
         tkey.release(s);
     }
     raw.release(s);
+    // the rows the execution-order copy gives a workgroup each (it takes
+    // those still above kShortRow entries)
+    g.n_long_nodes = ncls[5] + ncls[6];
+    g.long_nodes.ensure(static_cast<size_t>(g.n_long_nodes) + 1, s);
+    if (g.n_long_nodes)
+        AHR_HIP(hipMemcpyAsync(g.long_nodes.p, cls[5], static_cast<size_t>(g.n_long_nodes) * sizeof(int32_t),
+                               hipMemcpyDeviceToDevice, s));
 
     // The merged rows stay in place (no compaction): slots past a row's
     // merged count are unused.  The arrays hold the raw count; the exact
@@ -755,10 +843,6 @@ void build_netlist(Graph& g, hipStream_t s) {
     g.nnz_cap = static_cast<int32_t>(nnz_dup);
     lists.release(s);
     cstart.release(s);
-    g.base_w.ensure(static_cast<size_t>(n_inst) + 1, s);
-    hipLaunchKernelGGL(k_base_weight, dim3(grid_for(n_inst, kBT)), dim3(kBT), 0, s, n_inst, g.net_len.p, g.qdeg.p,
-                       g.base_w.p);
-    AHR_LAUNCHED("k_base_weight");
     cnt.release(s);
 }
 
