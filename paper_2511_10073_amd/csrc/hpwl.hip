@@ -2,12 +2,22 @@
 // (x, y) column pair, (max - min) of the pin x plus that of the pin y, pin
 // position = instance position + pin offset, in float64.
 //
-// Each workgroup owns one contiguous range of nets.  Nets with at most a
-// wave's worth of pins take kLanes lanes each; the rest of the range's nets
-// are then summed one after another by the whole workgroup.  Workgroup
-// totals go to a partial-sum buffer, which one workgroup adds in a fixed
-// order, so the result is deterministic and no list of the big nets is
-// needed: the pass reads the netlist arrays alone.
+// A workgroup takes kBT nets at a time.  Their pins are consecutive, so they
+// are read in windows of kWindow pins with one lane a pin (coalesced node and
+// offset loads, every lane's position gathers in flight together) and left in
+// LDS; then one thread a net runs over its pins there.  Nets with more than
+// a wave's worth of pins are left out of the windows and summed by the whole
+// workgroup, in net order.  Workgroup totals go to a partial-sum buffer,
+// which one workgroup adds in a fixed order, so the result is deterministic
+// and no list of the big nets is needed: the pass reads the netlist arrays
+// alone.
+//
+// What bounds it: the position gathers, a line each from a table that only
+// the Infinity Cache holds (about 18 ps a pin; 26 of the 84 us of a 1.1M-cell
+// netlist without big nets).  8 lanes a net, which ran a chain of three
+// dependent loads with most lanes idle (60 % of the nets have 2 pins), and
+// one workgroup after another over the big nets took 61 us at 210k cells and
+// 4 columns (35 now), 158 at 1.1M (134), 390 at 2.2M and 8 columns (286).
 //
 // ahr_hpwl draws the partial-sum buffer from the library's stream-ordered
 // pool for each call, so calls on different streams share no memory.
@@ -19,122 +29,182 @@ namespace ahr {
 namespace {
 
 constexpr int kBT = 256;
-constexpr int kLanes = 8;           // lanes per small net
-constexpr int kGroups = kBT / kLanes;
-constexpr int kMaxGrid = 8192;      // workgroups (enough nets in flight to hide the two dependent loads of each)
-constexpr int kNetsPerWg = 256;     // fewer nets per workgroup only below kMaxGrid workgroups
+constexpr int kMaxGrid = 8192;      // workgroups, each of a multiple of kBT nets
 constexpr int kMaxPairs = 4;        // ncols <= 8
 constexpr size_t kPartialElems = static_cast<size_t>(kMaxGrid) * kMaxPairs;
 
+// Pins a window holds: 16 P bytes of LDS each, four workgroups a CU or more.
 template <int P>
-__device__ __forceinline__ void pin_bounds(const float* pos, int ncols, const int32_t* pin_node, const float* pin_off,
-                                           int p, double* lo, double* hi) {
-    int v = pin_node[p];
-    double ox = pin_off[2 * p], oy = pin_off[2 * p + 1];
-    const float* g = pos + static_cast<int64_t>(v) * ncols;
+constexpr int kWindow = P <= 2 ? 1024 : 512;
+
+// Big nets up to this many pins take one wave, longer ones the workgroup, as
+// does a batch's only big net: all of them by the workgroup, one after
+// another, took 42 us at 210k cells (33 with both rules).
+constexpr int kWaveNet = 2048;
+constexpr int kFewBig = 1;
+
+template <int P>
+__device__ __forceinline__ void bounds_init(double* lo, double* hi) {
 #pragma unroll
     for (int c = 0; c < 2 * P; ++c) {
-        double x = static_cast<double>(g[c]) + ((c & 1) ? oy : ox);
-        lo[c] = x < lo[c] ? x : lo[c];
-        hi[c] = x > hi[c] ? x : hi[c];
+        lo[c] = 1e300;
+        hi[c] = -1e300;
     }
 }
 
+// (a NaN coordinate moves no bound)
+__device__ __forceinline__ void bound(double x, double& lo, double& hi) {
+    lo = __builtin_fmin(lo, x);
+    hi = __builtin_fmax(hi, x);
+}
+
+// Bounds over pins [p0, p1) of one net by W waves (t: the lane among them).
+template <int P, int W>
+__device__ __forceinline__ void net_bounds(const float* __restrict__ pos, const int32_t* __restrict__ pin_node,
+                                           const float* __restrict__ pin_off, int p0, int p1, int t, double* lo,
+                                           double* hi) {
+    constexpr int U = P <= 2 ? 4 : 2;        // pins in flight a lane (a repeated last pin changes no bound)
+    bounds_init<P>(lo, hi);
+    for (int q = p0 + t; q < p1; q += U * W * kWave) {
+        int v[U];
+        float off[U][2], g[U][2 * P];
+#pragma unroll
+        for (int u = 0; u < U; ++u) {
+            const int p = q + u * W * kWave < p1 ? q + u * W * kWave : p1 - 1;
+            v[u] = pin_node[p];
+            off[u][0] = pin_off[2 * p];
+            off[u][1] = pin_off[2 * p + 1];
+        }
+#pragma unroll
+        for (int u = 0; u < U; ++u)
+#pragma unroll
+            for (int c = 0; c < 2 * P; ++c) g[u][c] = pos[static_cast<int64_t>(v[u]) * (2 * P) + c];
+#pragma unroll
+        for (int u = 0; u < U; ++u)
+#pragma unroll
+            for (int c = 0; c < 2 * P; ++c)
+                bound(static_cast<double>(g[u][c]) + static_cast<double>(off[u][c & 1]), lo[c], hi[c]);
+    }
+#pragma unroll
+    for (int o = kWave / 2; o > 0; o >>= 1)
+#pragma unroll
+        for (int c = 0; c < 2 * P; ++c) {
+            lo[c] = __builtin_fmin(lo[c], __shfl_xor(lo[c], o));
+            hi[c] = __builtin_fmax(hi[c], __shfl_xor(hi[c], o));
+        }
+}
+
 template <int P>
-__global__ void __launch_bounds__(kBT) k_hpwl(const float* __restrict__ pos, int ncols,
-                                              const int32_t* __restrict__ net_ptr, int32_t n_nets, int32_t per,
-                                              const int32_t* __restrict__ pin_node, const float* __restrict__ pin_off,
-                                              double* __restrict__ partial) {
+__global__ void __launch_bounds__(kBT, 4) k_hpwl(const float* __restrict__ pos, const int32_t* __restrict__ net_ptr,
+                                              int32_t n_nets, int32_t per, const int32_t* __restrict__ pin_node,
+                                              const float* __restrict__ pin_off, double* __restrict__ partial) {
+    constexpr int T = kWindow<P>, U = T / kBT;
+    __shared__ double win[2 * P][T];
+    __shared__ double ext[2 * P][2][kBT / kWave];
     __shared__ double red[kBT / kWave];
-    __shared__ double ext[2 * 2 * P][kBT / kWave];
-    __shared__ unsigned long long big_mask[kBT / kWave];
+    __shared__ int cnt[kBT / kWave];
+    __shared__ int bstart[kBT], blen[kBT];      // the batch's big nets, in net order
     const int64_t lo_net = static_cast<int64_t>(blockIdx.x) * per;
     const int64_t hi_net = lo_net + per < n_nets ? lo_net + per : n_nets;
-    const int l = threadIdx.x & (kLanes - 1);
     double tot[P];
 #pragma unroll
     for (int c = 0; c < P; ++c) tot[c] = 0;
+    double lo[2 * P], hi[2 * P];
+    auto add = [&]() {
+#pragma unroll
+        for (int c = 0; c < P; ++c) tot[c] += (hi[2 * c] - lo[2 * c]) + (hi[2 * c + 1] - lo[2 * c + 1]);
+    };
 
-    // nets of at most kWave pins: kLanes lanes each
-    for (int64_t e = lo_net + threadIdx.x / kLanes; e < hi_net; e += kGroups) {
-        int p0 = net_ptr[e], p1 = net_ptr[e + 1];
-        if (p1 - p0 > kWave || p1 - p0 < 1) continue;   // group-uniform
-        double lo[2 * P], hi[2 * P];
-#pragma unroll
-        for (int c = 0; c < 2 * P; ++c) {
-            lo[c] = 1e300;
-            hi[c] = -1e300;
-        }
-        for (int p = p0 + l; p < p1; p += kLanes) pin_bounds<P>(pos, ncols, pin_node, pin_off, p, lo, hi);
-#pragma unroll
-        for (int o = kLanes / 2; o > 0; o >>= 1) {
-#pragma unroll
-            for (int c = 0; c < 2 * P; ++c) {
-                double a = __shfl_xor(lo[c], o), b = __shfl_xor(hi[c], o);
-                lo[c] = a < lo[c] ? a : lo[c];
-                hi[c] = b > hi[c] ? b : hi[c];
-            }
-        }
-        if (l == 0) {
-#pragma unroll
-            for (int c = 0; c < P; ++c) tot[c] += (hi[2 * c] - lo[2 * c]) + (hi[2 * c + 1] - lo[2 * c + 1]);
-        }
-    }
-
-    // the range's bigger nets, in net order, by the whole workgroup
     for (int64_t c0 = lo_net; c0 < hi_net; c0 += kBT) {
         const int64_t e = c0 + threadIdx.x;
-        const bool big = e < hi_net && net_ptr[e + 1] - net_ptr[e] > kWave;
-        const unsigned long long m = __ballot(big);
+        const int64_t last = c0 + kBT < hi_net ? c0 + kBT : hi_net;
+        const int first = net_ptr[c0];
+        const int p0 = net_ptr[e < last ? e : last], p1 = net_ptr[e < last ? e + 1 : last];
+        const bool big = p1 - p0 > kWave;
+        int nb;
+        const int k = block_rank<kBT>(big, cnt, &nb);
+        if (big) {
+            bstart[k] = p0;
+            blen[k] = p1 - p0;
+        }
         __syncthreads();
-        if (lane_id() == 0) big_mask[wave_id()] = m;
-        __syncthreads();
-        for (int w = 0; w < kBT / kWave; ++w) {
-            unsigned long long mm = big_mask[w];          // uniform over the workgroup
-            while (mm) {
-                const int b = __ffsll(static_cast<long long>(mm)) - 1;
-                mm &= mm - 1;
-                const int64_t net = c0 + w * kWave + b;
-                const int p0 = net_ptr[net], p1 = net_ptr[net + 1];
-                double lo[2 * P], hi[2 * P];
+        // the batch's pins without the big nets' are counted from 0; pins
+        // of big nets before place q of that count: shift(q)
+        auto shift = [&](int q) {
+            int sh = 0;
+            for (int b = 0; b < nb && bstart[b] - first - sh <= q; ++b) sh += blen[b];
+            return sh;
+        };
+        int skipped = 0, all = 0;
+        for (int b = 0; b < nb; ++b) {
+            skipped += bstart[b] < p0 ? blen[b] : 0;
+            all += blen[b];
+        }
+        const int n = net_ptr[last] - first - all;
+        const int q0 = p0 - first - skipped, q1 = big ? q0 : q0 + (p1 - p0);
+        bounds_init<P>(lo, hi);
+        for (int at = 0; at < n; at += T) {
+            int v[U];
+            float ox[U], oy[U];
+#pragma unroll
+            for (int u = 0; u < U; ++u) {
+                const int q = at + static_cast<int>(threadIdx.x) + u * kBT, qc = q < n ? q : n - 1;
+                const int p = first + qc + shift(qc);
+                v[u] = pin_node[p];
+                ox[u] = pin_off[2 * p];
+                oy[u] = pin_off[2 * p + 1];
+            }
+            float g[U][2 * P];
+#pragma unroll
+            for (int u = 0; u < U; ++u)
+#pragma unroll
+                for (int c = 0; c < 2 * P; ++c) g[u][c] = pos[static_cast<int64_t>(v[u]) * (2 * P) + c];
+#pragma unroll
+            for (int u = 0; u < U; ++u)
+#pragma unroll
+                for (int c = 0; c < 2 * P; ++c)
+                    win[c][threadIdx.x + u * kBT] =
+                        static_cast<double>(g[u][c]) + static_cast<double>((c & 1) ? oy[u] : ox[u]);
+            __syncthreads();
+            const int a = q0 > at ? q0 - at : 0, b = q1 < at + T ? q1 - at : T;
+            for (int i = a; i < b; i += 4)           // four pins' reads at once (the last one repeats)
+#pragma unroll
+                for (int u = 0; u < 4; ++u)
+#pragma unroll
+                    for (int c = 0; c < 2 * P; ++c) bound(win[c][i + u < b ? i + u : b - 1], lo[c], hi[c]);
+            __syncthreads();
+        }
+        if (q1 > q0) add();
+        // the big nets: a wave each, the longest by the workgroup
+        const int wave_net = nb > kFewBig ? kWaveNet : 0;
+        for (int b = wave_id(); b < nb; b += kBT / kWave) {
+            if (blen[b] > wave_net) continue;
+            net_bounds<P, 1>(pos, pin_node, pin_off, bstart[b], bstart[b] + blen[b], lane_id(), lo, hi);
+            if (lane_id() == 0) add();
+        }
+        for (int b = 0; b < nb; ++b) {
+            if (blen[b] <= wave_net) continue;       // (the same in every thread)
+            net_bounds<P, kBT / kWave>(pos, pin_node, pin_off, bstart[b], bstart[b] + blen[b], threadIdx.x, lo, hi);
+            __syncthreads();
+            if (lane_id() == 0) {
 #pragma unroll
                 for (int c = 0; c < 2 * P; ++c) {
-                    lo[c] = 1e300;
-                    hi[c] = -1e300;
-                }
-                for (int p = p0 + threadIdx.x; p < p1; p += kBT) pin_bounds<P>(pos, ncols, pin_node, pin_off, p, lo, hi);
-#pragma unroll
-                for (int c = 0; c < 2 * P; ++c) {
-                    lo[c] = -wave_max(-lo[c]);
-                    hi[c] = wave_max(hi[c]);
-                }
-                __syncthreads();
-                if (lane_id() == 0) {
-#pragma unroll
-                    for (int c = 0; c < 2 * P; ++c) {
-                        ext[2 * c][wave_id()] = lo[c];
-                        ext[2 * c + 1][wave_id()] = hi[c];
-                    }
-                }
-                __syncthreads();
-                if (threadIdx.x == 0) {
-#pragma unroll
-                    for (int c = 0; c < P; ++c) {
-                        double h = 0;
-#pragma unroll
-                        for (int d = 0; d < 2; ++d) {
-                            double a = ext[2 * (2 * c + d)][0], bb = ext[2 * (2 * c + d) + 1][0];
-                            for (int u = 1; u < kBT / kWave; ++u) {
-                                a = ext[2 * (2 * c + d)][u] < a ? ext[2 * (2 * c + d)][u] : a;
-                                bb = ext[2 * (2 * c + d) + 1][u] > bb ? ext[2 * (2 * c + d) + 1][u] : bb;
-                            }
-                            h += bb - a;
-                        }
-                        tot[c] += h;
-                    }
+                    ext[c][0][wave_id()] = lo[c];
+                    ext[c][1][wave_id()] = hi[c];
                 }
             }
+            __syncthreads();
+            if (threadIdx.x == 0) {
+                for (int w = 1; w < kBT / kWave; ++w)
+#pragma unroll
+                    for (int c = 0; c < 2 * P; ++c) {
+                        lo[c] = ext[c][0][w] < lo[c] ? ext[c][0][w] : lo[c];
+                        hi[c] = ext[c][1][w] > hi[c] ? ext[c][1][w] : hi[c];
+                    }
+                add();
+            }
         }
+        __syncthreads();
     }
 #pragma unroll
     for (int c = 0; c < P; ++c) {
@@ -166,17 +236,21 @@ __global__ void __launch_bounds__(kFinalBT) k_hpwl_final(const double* __restric
     }
 }
 
+// Nets per workgroup: kBT, or the multiple that stays within kMaxGrid.
+int32_t hpwl_per(int32_t n_nets) {
+    const int64_t batches = (static_cast<int64_t>(n_nets) + kBT - 1) / kBT;
+    return static_cast<int32_t>((batches + kMaxGrid - 1) / kMaxGrid) * kBT;
+}
+
 int hpwl_grid(int32_t n_nets) {
-    int64_t g = (static_cast<int64_t>(n_nets) + kNetsPerWg - 1) / kNetsPerWg;
-    return static_cast<int>(g < 1 ? 1 : (g > kMaxGrid ? kMaxGrid : g));
+    return n_nets < 1 ? 1 : static_cast<int>(grid_for(n_nets, hpwl_per(n_nets)));
 }
 
 template <int P>
-void hpwl_p(const ahr_netlist& nl, const float* pos, int32_t ncols, double* out, double* partial, hipStream_t s) {
+void hpwl_p(const ahr_netlist& nl, const float* pos, double* out, double* partial, hipStream_t s) {
     const int grid = hpwl_grid(nl.n_nets);
-    const int32_t per = static_cast<int32_t>((static_cast<int64_t>(nl.n_nets) + grid - 1) / grid);
-    hipLaunchKernelGGL(k_hpwl<P>, dim3(grid), dim3(kBT), 0, s, pos, ncols, nl.net_ptr, nl.n_nets, per, nl.pin_node,
-                       nl.pin_off, partial);
+    hipLaunchKernelGGL(k_hpwl<P>, dim3(grid), dim3(kBT), 0, s, pos, nl.net_ptr, nl.n_nets, hpwl_per(nl.n_nets),
+                       nl.pin_node, nl.pin_off, partial);
     AHR_LAUNCHED("k_hpwl");
     hipLaunchKernelGGL(k_hpwl_final, dim3(1), dim3(kFinalBT), 0, s, partial, grid, P, out);
     AHR_LAUNCHED("k_hpwl_final");
@@ -187,9 +261,9 @@ void hpwl_p(const ahr_netlist& nl, const float* pos, int32_t ncols, double* out,
 void hpwl_launch(const ahr_netlist& nl, const float* pos, int32_t ncols, double* out, double* partial,
                  hipStream_t s) {
     switch (ncols) {
-        case 2: hpwl_p<1>(nl, pos, ncols, out, partial, s); break;
-        case 4: hpwl_p<2>(nl, pos, ncols, out, partial, s); break;
-        case 8: hpwl_p<4>(nl, pos, ncols, out, partial, s); break;
+        case 2: hpwl_p<1>(nl, pos, out, partial, s); break;
+        case 4: hpwl_p<2>(nl, pos, out, partial, s); break;
+        case 8: hpwl_p<4>(nl, pos, out, partial, s); break;
         default: throw Error{AHR_EUNSUPPORTED, "hpwl needs ncols of 2, 4 or 8"};
     }
 }
