@@ -108,9 +108,10 @@ const int64_t* scan_i32_total(const int32_t* in, int32_t* out, int64_t n, int64_
 void list_rows(const int32_t* flags, const int32_t* rank, int32_t n, int32_t* list, hipStream_t s);
 // p[0..n) = v
 void fill_i32(int32_t* p, int64_t n, int32_t v, hipStream_t s);
-// host[k] = *src[k] for up to 8 device int32 scalars, with one synchronisation
+// host[k] = *src[k] for up to 8 device int32 scalars: one read, which waits
+// for the stream's work so far
 void read_scalars(const std::vector<const int32_t*>& src, int32_t* host, hipStream_t s);
-// Device scalars of 4 (wide = 0) or 8 (wide = 1) bytes, read in one synchronisation.
+// The same for device scalars of 4 (wide = 0) or 8 (wide = 1) bytes.
 struct DevWord {
     const void* p;
     int wide;
@@ -118,13 +119,12 @@ struct DevWord {
 void read_words(std::initializer_list<DevWord> src, int64_t* out, hipStream_t s);
 // The same read split in two, so that work queued between the halves runs
 // while the host waits: read_scalars_begin gathers up to 8 int32 values on
-// stream s into the device's pinned words (a second set, kept apart from
-// the synchronous reads) and records an event; read_scalars_end waits for
-// that event alone and copies the values out.  One read in flight per
-// device and host thread.
+// stream s into pinned words of the host; read_scalars_end waits for those
+// words alone and copies the values out.  One split read in flight per host
+// thread.
 void read_scalars_begin(const std::vector<const int32_t*>& src, hipStream_t s);
 void read_scalars_end(int32_t* host, int n);
-// One device scalar (synchronises the stream).
+// One device scalar (waits for the stream's work so far).
 int32_t read_i32(const int32_t* src, hipStream_t s);
 int64_t read_i64(const int64_t* src, hipStream_t s);
 double read_f64(const double* src, hipStream_t s);
