@@ -104,8 +104,6 @@ int64_t scan_i32_checked(const int32_t* in, int32_t* out, int64_t n, int64_t* tm
 // int64 total (valid until tmp is reused), for a later combined read.
 const int64_t* scan_i32_total(const int32_t* in, int32_t* out, int64_t n, int64_t* tmp, hipStream_t s);
 
-// list[rank[i]] = i for every i with flags[i] != 0 (rank = exclusive scan of flags).
-void list_rows(const int32_t* flags, const int32_t* rank, int32_t n, int32_t* list, hipStream_t s);
 // p[0..n) = v
 void fill_i32(int32_t* p, int64_t n, int32_t v, hipStream_t s);
 // host[k] = *src[k] for up to 8 device int32 scalars: one read, which waits

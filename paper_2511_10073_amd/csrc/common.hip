@@ -590,19 +590,7 @@ void scan_i32_to_i32(const int32_t* in, int32_t* out, int64_t n, int64_t* tmp, h
     scan_impl<int32_t, int32_t>(in, out, n, tmp, s);
 }
 
-// ---------------------------------------------------------------- lists, fills
-
-__global__ void k_list_rows(const int32_t* __restrict__ flag, const int32_t* __restrict__ rank, int32_t n,
-                            int32_t* __restrict__ list) {
-    int64_t i = static_cast<int64_t>(blockIdx.x) * blockDim.x + threadIdx.x;
-    if (i < n && flag[i]) list[rank[i]] = static_cast<int32_t>(i);
-}
-
-void list_rows(const int32_t* flags, const int32_t* rank, int32_t n, int32_t* list, hipStream_t s) {
-    if (n <= 0) return;
-    hipLaunchKernelGGL(k_list_rows, dim3(grid_for(n, 256)), dim3(256), 0, s, flags, rank, n, list);
-    AHR_LAUNCHED("k_list_rows");
-}
+// ---------------------------------------------------------------- reads, fills
 
 // Small reads of device counts.  A gather kernel writes the values into
 // pinned, coherent host memory, each 32-bit half in a 64-bit word beside the

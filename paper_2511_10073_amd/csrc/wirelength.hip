@@ -17,27 +17,23 @@
 // the node pass meets the pins does not change the result.
 //
 // Layout: an index built once per netlist (ahr_wl_create) lists every
-// instance's pins (node_ptr / node_pins), the nets of at most 64 pins in
-// ascending degree (a stable bucket sort, so the lanes of a wave mostly
-// meet nets of one degree and run the same trip counts) and the larger nets.
-// One call is four kernels: the small-net pass (one thread per net: no lane
-// idles on a short net and no cross-lane reduction; nets of at most 8 pins
-// keep their pins in registers), the big-net pass (one workgroup per net),
-// both writing net totals into workgroup partials and per-pin gradients into
-// a [pins][ncols] float64 buffer in pin order; the node pass (one thread per
-// instance gathers its pins' rows); and the fixed-order reduction of the
-// partials.
+// instance's pins (node_ptr / node_pins) and the nets of more than 64 pins.
+// One call is three kernels: the net pass (256 nets a workgroup, and one
+// workgroup for each net of more than 64 pins), writing net totals into
+// workgroup partials and per-pin gradients into a [pins][ncols] float64
+// buffer in pin order; the node pass (one thread per instance gathers its
+// pins' rows); and the fixed-order reduction of the partials.
 #include <cmath>
 
 #include "ahr_internal.hpp"
 #include "device_util.hpp"
+#include "scan.hpp"
 
 namespace ahr {
 
 namespace {
 
 constexpr int kBT = 256;
-constexpr int kReg = 8;             // nets of up to kReg pins keep their pins in registers
 constexpr int kMaxPairs = 4;
 constexpr double kFix = 1099511627776.0;          // 2^40
 constexpr double kUnfix = 1.0 / 1099511627776.0;
@@ -46,8 +42,6 @@ struct WlIndex {
     ahr_netlist nl;
     DevBuf<int32_t> node_ptr;     // [n_inst + 1]
     DevBuf<int32_t> node_pins;    // [n_pins] pins of each instance (order within an instance unspecified)
-    DevBuf<int32_t> small;        // nets of 1..kWave pins, by ascending degree, ascending within a degree
-    int32_t n_small = 0;
     DevBuf<int32_t> big;          // nets of more than kWave pins, ascending
     int32_t n_big = 0;
     int device = 0;
@@ -66,22 +60,26 @@ struct WlIndex {
         if (stream_uses > 1) (void)hipDeviceSynchronize();
         node_ptr.release(s);
         node_pins.release(s);
-        small.release(s);
         big.release(s);
     }
 };
 
-// flag[e] = 1 for a net of more than kWave pins; key[e] = its degree for
-// one of 1..kWave pins, -1 otherwise (the bucket sort's key).
-__global__ void k_net_classes(const int32_t* __restrict__ net_ptr, int32_t n_nets, int32_t* __restrict__ flag,
-                              int32_t* __restrict__ key) {
-    const int64_t e = static_cast<int64_t>(blockIdx.x) * blockDim.x + threadIdx.x;
-    if (e < n_nets) {
-        const int32_t d = net_ptr[e + 1] - net_ptr[e];
-        flag[e] = d > kWave ? 1 : 0;
-        key[e] = d >= 1 && d <= kWave ? d : -1;
+// The nets of more than kWave pins, ascending.
+struct BigNetScan {
+    static constexpr int K = 1;
+    static constexpr bool kTotal = false, kHeavy = false;
+    using Raw = Pack<1>;
+    __device__ Pack<1> pack(const Pack<1>& p) const { return p; }
+    const int32_t* net_ptr;
+    int32_t* list;              // or null: count only
+    int32_t* count;
+    __device__ Pack<1> first(int64_t e) const { return {{net_ptr[e + 1] - net_ptr[e] > kWave ? 1 : 0}}; }
+    __device__ Pack<1> again(int64_t e) const { return first(e); }
+    __device__ void item(int64_t e, const Pack<1>& own, const Pack<1>& before, const Pack<1>&) const {
+        if (list && own.v[0]) list[before.v[0]] = static_cast<int32_t>(e);
     }
-}
+    __device__ void done(const Pack<1>& total) const { *count = static_cast<int32_t>(total.v[0]); }
+};
 
 __global__ void k_pin_slots(const int32_t* __restrict__ pin_node, int32_t n_pins, int32_t* __restrict__ cnt,
                             int32_t* __restrict__ slot) {
@@ -99,15 +97,7 @@ __global__ void k_pin_scatter(const int32_t* __restrict__ pin_node, int32_t n_pi
 // exp(a) for a <= 0, in float32.
 __device__ __forceinline__ double wexp(double a) { return static_cast<double>(expf(static_cast<float>(a))); }
 
-// Coordinate of pin p in column c: instance position + pin offset (x or y).
-__device__ __forceinline__ double pin_coord(const float* pos, int ncols, const int32_t* pin_node, const float* pin_off,
-                                            int p, int c) {
-    return static_cast<double>(pos[static_cast<int64_t>(pin_node[p]) * ncols + c]) +
-           static_cast<double>(pin_off[2 * p + (c & 1)]);
-}
-
-// One net and one column at a time (only that column's sums are live, so the
-// kernel keeps its registers few and its occupancy high).
+// One net's sums in one column.
 struct ColAcc {
     double hi, lo;      // extremes
     double sp, tp;      // sum exp((x-hi)/g), sum x exp((x-hi)/g)
@@ -139,191 +129,175 @@ __device__ __forceinline__ void load_row(const float* p, float* v) {
     }
 }
 
-// The D pins from p0 (indexes past the net's last pin p1 - 1 are clamped to
-// it) of a net: node rows and offsets, every load issued before any is used.
-template <int C, int D>
-__device__ __forceinline__ void gather_pins(const float* __restrict__ pos, const int32_t* __restrict__ pin_node,
-                                            const float* __restrict__ pin_off, int p0, int p1, float (&v)[D][C],
-                                            float2 (&off)[D]) {
-    int node[D];
-#pragma unroll
-    for (int k = 0; k < D; ++k) {
-        const int p = p0 + k < p1 ? p0 + k : p1 - 1;
-        node[k] = pin_node[p];
-        off[k] = reinterpret_cast<const float2*>(pin_off)[p];
-    }
-#pragma unroll
-    for (int k = 0; k < D; ++k) load_row<C>(pos + static_cast<int64_t>(node[k]) * C, v[k]);
-}
-
+// Coordinate in column c of a pin: its instance's position + its offset (x or y).
 __device__ __forceinline__ double coord(const float (&v), float2 off, int c) {
     return static_cast<double>(v) + static_cast<double>((c & 1) ? off.y : off.x);
 }
 
-// A net of d <= D pins (D the wave's bound), its pins in registers: per
-// column pair the extremes (clamped repeats of the last pin change no
-// extreme), the shifted sums over its d pins, the pair's WA term, and each
-// pin's gradient from the weights already taken (1/sp and 1/sm once per net
-// and column).
-template <int P, int D>
-__device__ __forceinline__ void wa_net_regs(const float* __restrict__ pos, const int32_t* __restrict__ pin_node,
-                                            const float* __restrict__ pin_off, int p0, int d, double inv_g,
-                                            double* tot, double* __restrict__ pin_g) {
-    constexpr int C = 2 * P;
-    float v[D][C];
-    float2 off[D];
-    gather_pins<C, D>(pos, pin_node, pin_off, p0, p0 + d, v, off);
+// The nets of up to kWave pins, kBT of them a workgroup.  Their pins are
+// consecutive, so they are read with one lane a pin (coalesced node and offset
+// loads, every gather in flight) in runs of whole nets of at most kRun pins;
+// each column pair's coordinates go to LDS, and the work alternates between
+// one thread a net (extremes, then the shifted sums in pin order) and one lane
+// a pin (the two weights, then the gradient), so the exponentials and the
+// stores idle no lane and every weight is taken once.  Pins of larger nets
+// are left out.
+//
+// What bounds it: the position gathers (HPWL, which makes the same ones, takes
+// 165 us at 2.2M cells and 2 columns) beside the gradient's stores.  Against
+// one thread a net, over nets sorted by size, with the pins in registers:
+// 786 -> 516 us a call at 2.2M cells and 2 columns, 948 -> 722 at 4 columns,
+// 276 -> 194 at 200k cells and 4 columns, 64 -> 45 at 2k cells.
+constexpr int kRun = 1024;
+
+template <int P>
+__device__ __forceinline__ void wa_batch(const float* __restrict__ pos, const int32_t* __restrict__ net_ptr,
+                                         int32_t n_nets, int32_t batch, const int32_t* __restrict__ pin_node,
+                                         const float* __restrict__ pin_off, double inv_g, double* tot,
+                                         double* __restrict__ pin_g) {
+    constexpr int C = 2 * P, U = kRun / kBT;
+    __shared__ double xs[2][kRun];
+    __shared__ float es[2][2][kRun];            // [axis][maximum side, minimum side]
+    __shared__ double st[2][4][kBT];            // per net and axis: extremes, then means and reciprocal sums
+    __shared__ uint8_t owner[kRun];
+    __shared__ int bstart[kBT], blen[kBT], cnt[kBT / kWave], stop_q[2];
+    const int t = threadIdx.x;
+    const int64_t c0 = static_cast<int64_t>(batch) * kBT, e = c0 + t;
+    const int64_t last = c0 + kBT < n_nets ? c0 + kBT : n_nets;
+    const int first = net_ptr[c0];
+    const int p0 = net_ptr[e < last ? e : last], p1 = net_ptr[e < last ? e + 1 : last];
+    const bool big = p1 - p0 > kWave;
+    int nb;
+    const int k = block_rank<kBT>(big, cnt, &nb);
+    if (big) {
+        bstart[k] = p0;
+        blen[k] = p1 - p0;
+    }
+    __syncthreads();
+    // the pins without the big nets' are counted from 0; pins of big nets
+    // before place q of that count
+    auto shift = [&](int q) {
+        int sh = 0;
+        for (int b = 0; b < nb && bstart[b] - first - sh <= q; ++b) sh += blen[b];
+        return sh;
+    };
+    int skipped = 0, all = 0;
+    for (int b = 0; b < nb; ++b) {
+        skipped += bstart[b] < p0 ? blen[b] : 0;
+        all += blen[b];
+    }
+    const int n = net_ptr[last] - first - all;
+    const int q0 = p0 - first - skipped, q1 = big ? q0 : q0 + (p1 - p0);
+    for (int at = 0, run = 0; at < n; ++run) {
+        // the run: the nets from place `at` on that end within kRun pins
+        const bool in_run = q0 >= at && q1 > q0 && q1 <= at + kRun;
+        if (t == 0) stop_q[run & 1] = at;
+        __syncthreads();
+        if (in_run) atomicMax(&stop_q[run & 1], q1);
+        __syncthreads();
+        const int m = stop_q[run & 1] - at;        // at least one net's pins
+        int v[U], pin[U];
+        float2 off[U];
 #pragma unroll
-    for (int q = 0; q < P; ++q) {
-        double hi[2], lo[2], sp[2], tp[2], sm[2], tm[2];
-        float ep[D][2], em[D][2];
-#pragma unroll
-        for (int c = 0; c < 2; ++c) {
-            hi[c] = -1e300;
-            lo[c] = 1e300;
-#pragma unroll
-            for (int k = 0; k < D; ++k) {
-                const double x = coord(v[k][2 * q + c], off[k], c);
-                hi[c] = x > hi[c] ? x : hi[c];
-                lo[c] = x < lo[c] ? x : lo[c];
-            }
-            sp[c] = tp[c] = sm[c] = tm[c] = 0;
-#pragma unroll
-            for (int k = 0; k < D; ++k) {
-                const double x = coord(v[k][2 * q + c], off[k], c);
-                ep[k][c] = expf(static_cast<float>((x - hi[c]) * inv_g));
-                em[k][c] = expf(static_cast<float>((lo[c] - x) * inv_g));
-                if (k < d) {
-                    sp[c] += ep[k][c];
-                    tp[c] += x * ep[k][c];
-                    sm[c] += em[k][c];
-                    tm[c] += x * em[k][c];
-                }
-            }
+        for (int u = 0; u < U; ++u) {
+            const int q = at + (t + u * kBT < m ? t + u * kBT : m - 1);
+            pin[u] = first + q + shift(q);
+            v[u] = pin_node[pin[u]];
+            off[u] = reinterpret_cast<const float2*>(pin_off)[pin[u]];
         }
-        tot[q] += (tp[0] / sp[0] - tm[0] / sm[0]) + (tp[1] / sp[1] - tm[1] / sm[1]);
-        if (!pin_g) continue;
-        double rsp[2], rsm[2], xp[2], xm[2];
+        float g[U][C];
 #pragma unroll
-        for (int c = 0; c < 2; ++c) {
-            rsp[c] = 1.0 / sp[c];
-            rsm[c] = 1.0 / sm[c];
-            xp[c] = tp[c] * rsp[c];
-            xm[c] = tm[c] * rsm[c];
-        }
+        for (int u = 0; u < U; ++u) load_row<C>(pos + static_cast<int64_t>(v[u]) * C, g[u]);
+        const int a = q0 - at, b = q1 - at;        // this thread's net inside the run
+        for (int pr = 0; pr < P; ++pr) {
+            double x[U][2];
 #pragma unroll
-        for (int k = 0; k < D; ++k)
-            if (k < d) {
-                double g[2];
+            for (int u = 0; u < U; ++u)
 #pragma unroll
                 for (int c = 0; c < 2; ++c) {
-                    const double x = coord(v[k][2 * q + c], off[k], c);
-                    const double pp = static_cast<double>(ep[k][c]) * rsp[c], pm = static_cast<double>(em[k][c]) * rsm[c];
-                    g[c] = pp * (1.0 + (x - xp[c]) * inv_g) - pm * (1.0 - (x - xm[c]) * inv_g);
+                    float gc = g[u][c];
+#pragma unroll
+                    for (int q = 1; q < P; ++q) gc = pr == q ? g[u][2 * q + c] : gc;
+                    x[u][c] = coord(gc, off[u], c);
+                    xs[c][t + u * kBT] = x[u][c];
                 }
-                *reinterpret_cast<double2*>(pin_g + static_cast<int64_t>(p0 + k) * C + 2 * q) = make_double2(g[0], g[1]);
-            }
-    }
-}
-
-// A net of more than kReg pins (up to a wave's worth): kReg pins at a time
-// (loads clamped and all in flight), three passes per column pair --
-// extremes, shifted sums, gradients.
-template <int P>
-__device__ __forceinline__ void wa_net_loop(const float* __restrict__ pos, const int32_t* __restrict__ pin_node,
-                                            const float* __restrict__ pin_off, int p0, int d, double inv_g,
-                                            double* tot, double* __restrict__ pin_g) {
-    constexpr int C = 2 * P, D = kReg;
-    const int p1 = p0 + d;
-    double hi[C], lo[C], sp[C], tp[C], sm[C], tm[C];
+            __syncthreads();
+            if (in_run) {
+                double hi[2] = {-1e300, -1e300}, lo[2] = {1e300, 1e300};
+                for (int i = a; i < b; ++i) {
+                    if (pr == 0) owner[i] = static_cast<uint8_t>(t);
 #pragma unroll
-    for (int c = 0; c < C; ++c) {
-        hi[c] = -1e300;
-        lo[c] = 1e300;
-        sp[c] = tp[c] = sm[c] = tm[c] = 0;
-    }
-    float v[D][C];
-    float2 off[D];
-    for (int b = p0; b < p1; b += D) {
-        gather_pins<C, D>(pos, pin_node, pin_off, b, p1, v, off);
-#pragma unroll
-        for (int k = 0; k < D; ++k)
-#pragma unroll
-            for (int c = 0; c < C; ++c) {
-                const double x = coord(v[k][c], off[k], c);
-                hi[c] = x > hi[c] ? x : hi[c];
-                lo[c] = x < lo[c] ? x : lo[c];
-            }
-    }
-    for (int b = p0; b < p1; b += D) {
-        gather_pins<C, D>(pos, pin_node, pin_off, b, p1, v, off);
-#pragma unroll
-        for (int k = 0; k < D; ++k)
-            if (b + k < p1)
-#pragma unroll
-                for (int c = 0; c < C; ++c) {
-                    const double x = coord(v[k][c], off[k], c);
-                    const double ep = wexp((x - hi[c]) * inv_g), em = wexp((lo[c] - x) * inv_g);
-                    sp[c] += ep;
-                    tp[c] += x * ep;
-                    sm[c] += em;
-                    tm[c] += x * em;
+                    for (int c = 0; c < 2; ++c) {
+                        const double y = xs[c][i];
+                        hi[c] = __builtin_fmax(hi[c], y);
+                        lo[c] = __builtin_fmin(lo[c], y);
+                    }
                 }
-    }
 #pragma unroll
-    for (int q = 0; q < P; ++q)
-        tot[q] += (tp[2 * q] / sp[2 * q] - tm[2 * q] / sm[2 * q]) + (tp[2 * q + 1] / sp[2 * q + 1] - tm[2 * q + 1] / sm[2 * q + 1]);
-    if (!pin_g) return;
-    ColAcc a[C];
+                for (int c = 0; c < 2; ++c) {
+                    st[c][0][t] = hi[c];
+                    st[c][1][t] = lo[c];
+                }
+            }
+            __syncthreads();
+            float ep[U][2], em[U][2];
+            int own[U];
 #pragma unroll
-    for (int c = 0; c < C; ++c) a[c] = ColAcc{hi[c], lo[c], sp[c], tp[c], sm[c], tm[c]};
-    for (int b = p0; b < p1; b += D) {
-        gather_pins<C, D>(pos, pin_node, pin_off, b, p1, v, off);
+            for (int u = 0; u < U; ++u) {
+                own[u] = owner[t + u * kBT < m ? t + u * kBT : m - 1];
 #pragma unroll
-        for (int k = 0; k < D; ++k)
-            if (b + k < p1)
+                for (int c = 0; c < 2; ++c) {
+                    ep[u][c] = expf(static_cast<float>((x[u][c] - st[c][0][own[u]]) * inv_g));
+                    em[u][c] = expf(static_cast<float>((st[c][1][own[u]] - x[u][c]) * inv_g));
+                    es[c][0][t + u * kBT] = ep[u][c];
+                    es[c][1][t + u * kBT] = em[u][c];
+                }
+            }
+            __syncthreads();
+            if (in_run) {
+                double sp[2] = {0, 0}, tp[2] = {0, 0}, sm[2] = {0, 0}, tm[2] = {0, 0};
+                for (int i = a; i < b; ++i)
 #pragma unroll
-                for (int q = 0; q < P; ++q)
-                    *reinterpret_cast<double2*>(pin_g + static_cast<int64_t>(b + k) * C + 2 * q) =
-                        make_double2(gpin(coord(v[k][2 * q], off[k], 0), a[2 * q], inv_g),
-                                     gpin(coord(v[k][2 * q + 1], off[k], 1), a[2 * q + 1], inv_g));
-    }
-}
-
-// One net per thread.  The list is sorted by degree, so the lanes of a wave
-// hold nets of about one degree: the wave's largest degree picks how many
-// pins each lane gathers at once (2, 3, 4 or kReg in registers; more than
-// kReg in passes).  Workgroup totals to partial[blockIdx.x].
-template <int P>
-__global__ void __launch_bounds__(kBT) k_wa_small(const float* __restrict__ pos, int ncols,
-                                                  const int32_t* __restrict__ net_ptr,
-                                                  const int32_t* __restrict__ list, int32_t n_list,
-                                                  const int32_t* __restrict__ pin_node,
-                                                  const float* __restrict__ pin_off, double inv_g,
-                                                  double* __restrict__ partial, double* __restrict__ pin_g) {
-    __shared__ double red[kBT / kWave];
-    const int64_t i = static_cast<int64_t>(blockIdx.x) * kBT + threadIdx.x;
-    double tot[P];
+                    for (int c = 0; c < 2; ++c) {
+                        const double y = xs[c][i], f = es[c][0][i], h = es[c][1][i];
+                        sp[c] += f;
+                        tp[c] += y * f;
+                        sm[c] += h;
+                        tm[c] += y * h;
+                    }
+                double w = 0;
 #pragma unroll
-    for (int q = 0; q < P; ++q) tot[q] = 0;
-    int p0 = 0, d = 0;
-    if (i < n_list) {
-        const int e = list[i];
-        p0 = net_ptr[e];
-        d = net_ptr[e + 1] - p0;
-    }
-    const int dmax = wave_max(d);
-    if (d > 0) {
-        if (dmax <= 2) wa_net_regs<P, 2>(pos, pin_node, pin_off, p0, d, inv_g, tot, pin_g);
-        else if (dmax <= 3) wa_net_regs<P, 3>(pos, pin_node, pin_off, p0, d, inv_g, tot, pin_g);
-        else if (dmax <= 4) wa_net_regs<P, 4>(pos, pin_node, pin_off, p0, d, inv_g, tot, pin_g);
-        else if (dmax <= kReg) wa_net_regs<P, kReg>(pos, pin_node, pin_off, p0, d, inv_g, tot, pin_g);
-        else wa_net_loop<P>(pos, pin_node, pin_off, p0, d, inv_g, tot, pin_g);
-    }
+                for (int c = 0; c < 2; ++c) {
+                    const double rp = 1.0 / sp[c], rm = 1.0 / sm[c];
+                    w += tp[c] / sp[c] - tm[c] / sm[c];
+                    st[c][0][t] = rp;
+                    st[c][1][t] = rm;
+                    st[c][2][t] = tp[c] * rp;
+                    st[c][3][t] = tm[c] * rm;
+                }
 #pragma unroll
-    for (int q = 0; q < P; ++q) {
-        const double s2 = block_sum_f64<kBT>(tot[q], red);
-        if (threadIdx.x == 0) partial[static_cast<int64_t>(blockIdx.x) * kMaxPairs + q] = s2;
+                for (int q = 0; q < P; ++q) tot[q] += pr == q ? w : 0.0;
+            }
+            __syncthreads();
+            if (pin_g) {
+#pragma unroll
+                for (int u = 0; u < U; ++u) {
+                    double d[2];
+#pragma unroll
+                    for (int c = 0; c < 2; ++c) {
+                        const double pp = static_cast<double>(ep[u][c]) * st[c][0][own[u]];
+                        const double pm = static_cast<double>(em[u][c]) * st[c][1][own[u]];
+                        d[c] = pp * (1.0 + (x[u][c] - st[c][2][own[u]]) * inv_g) -
+                               pm * (1.0 - (x[u][c] - st[c][3][own[u]]) * inv_g);
+                    }
+                    if (t + u * kBT < m)
+                        *reinterpret_cast<double2*>(pin_g + static_cast<int64_t>(pin[u]) * C + 2 * pr) =
+                            make_double2(d[0], d[1]);
+                }
+            }
+            __syncthreads();
+        }
+        at += m;
     }
 }
 
@@ -364,37 +338,61 @@ __device__ __forceinline__ Run run_merge(Run a, Run b, double sgn_inv_g) {
 
 // The nets above kWave pins, one workgroup each (listed once per index):
 // one pass for the shifted sums of every column, one for the gradients.
-template <int P>
-__global__ void __launch_bounds__(kBT) k_wa_big(const float* __restrict__ pos, int ncols,
-                                                const int32_t* __restrict__ net_ptr, const int32_t* __restrict__ big,
-                                                const int32_t* __restrict__ pin_node,
-                                                const float* __restrict__ pin_off, double inv_g,
-                                                double* __restrict__ partial, double* __restrict__ pin_g) {
-    __shared__ Run red[2 * P][2][kBT / kWave];
-    const int e = big[blockIdx.x];
-    const int p0 = net_ptr[e], p1 = net_ptr[e + 1];
-    Run rp[2 * P], rm[2 * P];
+// A net above kWave pins by one workgroup: one pass for the shifted sums of
+// every column, one for the gradients, kBigU pins a lane in flight.
+constexpr int kBigU = 4;
+
+// The lane's pins p, p + kBT, ... (clamped to the net's last): rows and offsets.
+template <int C>
+__device__ __forceinline__ void big_pins(const float* __restrict__ pos, const int32_t* __restrict__ pin_node,
+                                         const float* __restrict__ pin_off, int p, int p1, float (&v)[kBigU][C],
+                                         float2 (&off)[kBigU]) {
+    int node[kBigU];
 #pragma unroll
-    for (int c = 0; c < 2 * P; ++c) {
+    for (int u = 0; u < kBigU; ++u) {
+        const int q = p + u * kBT < p1 ? p + u * kBT : p1 - 1;
+        node[u] = pin_node[q];
+        off[u] = reinterpret_cast<const float2*>(pin_off)[q];
+    }
+#pragma unroll
+    for (int u = 0; u < kBigU; ++u) load_row<C>(pos + static_cast<int64_t>(node[u]) * C, v[u]);
+}
+
+template <int P>
+__device__ __forceinline__ void wa_big(const float* __restrict__ pos, const int32_t* __restrict__ pin_node,
+                                       const float* __restrict__ pin_off, int p0, int p1, double inv_g, double* tot,
+                                       double* __restrict__ pin_g) {
+    constexpr int C = 2 * P;
+    __shared__ Run red[C][2][kBT / kWave];
+    Run rp[C], rm[C];
+    float v[kBigU][C];
+    float2 off[kBigU];
+#pragma unroll
+    for (int c = 0; c < C; ++c) {
         rp[c] = Run{-1e300, 0, 0};
         rm[c] = Run{1e300, 0, 0};
     }
-    for (int p = p0 + threadIdx.x; p < p1; p += kBT) {
+    for (int p = p0 + threadIdx.x; p < p1; p += kBigU * kBT) {
+        big_pins<C>(pos, pin_node, pin_off, p, p1, v, off);
 #pragma unroll
-        for (int c = 0; c < 2 * P; ++c) {
-            const double x = pin_coord(pos, ncols, pin_node, pin_off, p, c);
-            if (rp[c].s == 0) {
-                rp[c] = Run{x, 1.0, x};
-                rm[c] = Run{x, 1.0, x};
-            } else {
-                run_add(rp[c], x, inv_g);
-                run_add(rm[c], x, -inv_g);
+        for (int u = 0; u < kBigU; ++u) {
+            if (p + u * kBT >= p1) break;
+#pragma unroll
+            for (int c = 0; c < C; ++c) {
+                const double x = coord(v[u][c], off[u], c);
+                if (rp[c].s == 0) {
+                    rp[c] = Run{x, 1.0, x};
+                    rm[c] = Run{x, 1.0, x};
+                } else {
+                    run_add(rp[c], x, inv_g);
+                    run_add(rm[c], x, -inv_g);
+                }
             }
         }
     }
     // wave then workgroup merges, in a fixed order
 #pragma unroll
-    for (int c = 0; c < 2 * P; ++c) {
+    for (int c = 0; c < C; ++c) {
 #pragma unroll
         for (int o = kWave / 2; o > 0; o >>= 1) {
             Run a{__shfl_xor(rp[c].m, o), __shfl_xor(rp[c].s, o), __shfl_xor(rp[c].t, o)};
@@ -410,7 +408,7 @@ __global__ void __launch_bounds__(kBT) k_wa_big(const float* __restrict__ pos, i
     }
     __syncthreads();
 #pragma unroll
-    for (int c = 0; c < 2 * P; ++c) {
+    for (int c = 0; c < C; ++c) {
         rp[c] = red[c][0][0];
         rm[c] = red[c][1][0];
         for (int w = 1; w < kBT / kWave; ++w) {
@@ -419,22 +417,52 @@ __global__ void __launch_bounds__(kBT) k_wa_big(const float* __restrict__ pos, i
         }
     }
     if (pin_g) {
-        for (int p = p0 + threadIdx.x; p < p1; p += kBT) {
-            const int64_t k = static_cast<int64_t>(p) * ncols;
+        for (int p = p0 + threadIdx.x; p < p1; p += kBigU * kBT) {
+            big_pins<C>(pos, pin_node, pin_off, p, p1, v, off);
 #pragma unroll
-            for (int c = 0; c < 2 * P; ++c) {
-                const double x = pin_coord(pos, ncols, pin_node, pin_off, p, c);
-                const ColAcc a{rp[c].m, rm[c].m, rp[c].s, rp[c].t, rm[c].s, rm[c].t};
-                pin_g[k + c] = gpin(x, a, inv_g);
+            for (int u = 0; u < kBigU; ++u) {
+                if (p + u * kBT >= p1) break;
+                const int64_t k = static_cast<int64_t>(p + u * kBT) * C;
+#pragma unroll
+                for (int c = 0; c < C; ++c) {
+                    const ColAcc a{rp[c].m, rm[c].m, rp[c].s, rp[c].t, rm[c].s, rm[c].t};
+                    pin_g[k + c] = gpin(coord(v[u][c], off[u], c), a, inv_g);
+                }
             }
         }
     }
     if (threadIdx.x == 0) {
 #pragma unroll
         for (int c = 0; c < P; ++c)
-            partial[static_cast<int64_t>(blockIdx.x) * kMaxPairs + c] =
-                (rp[2 * c].t / rp[2 * c].s - rm[2 * c].t / rm[2 * c].s) +
-                (rp[2 * c + 1].t / rp[2 * c + 1].s - rm[2 * c + 1].t / rm[2 * c + 1].s);
+            tot[c] = (rp[2 * c].t / rp[2 * c].s - rm[2 * c].t / rm[2 * c].s) +
+                     (rp[2 * c + 1].t / rp[2 * c + 1].s - rm[2 * c + 1].t / rm[2 * c + 1].s);
+    }
+}
+
+// The net pass: workgroups [0, n_big) take a large net each (first, as the
+// longest of them outlast a batch), the others a batch of kBT nets.
+// Workgroup totals to partial[blockIdx.x].
+template <int P>
+__global__ void __launch_bounds__(kBT) k_wa_nets(const float* __restrict__ pos, const int32_t* __restrict__ net_ptr,
+                                                 int32_t n_nets, const int32_t* __restrict__ big, int32_t n_big,
+                                                 const int32_t* __restrict__ pin_node,
+                                                 const float* __restrict__ pin_off, double inv_g,
+                                                 double* __restrict__ partial, double* __restrict__ pin_g) {
+    __shared__ double red[kBT / kWave];
+    double tot[P];
+#pragma unroll
+    for (int q = 0; q < P; ++q) tot[q] = 0;
+    const int32_t blk = static_cast<int32_t>(blockIdx.x);
+    if (blk < n_big) {
+        const int e = big[blk];
+        wa_big<P>(pos, pin_node, pin_off, net_ptr[e], net_ptr[e + 1], inv_g, tot, pin_g);
+    } else {
+        wa_batch<P>(pos, net_ptr, n_nets, blk - n_big, pin_node, pin_off, inv_g, tot, pin_g);
+    }
+#pragma unroll
+    for (int q = 0; q < P; ++q) {
+        const double s = block_sum_f64<kBT>(tot[q], red);
+        if (threadIdx.x == 0) partial[static_cast<int64_t>(blk) * kMaxPairs + q] = s;
     }
 }
 
@@ -498,9 +526,9 @@ template <int P>
 void wa_p(const WlIndex& w, const float* pos, double inv_g, double* wl, float* grad, hipStream_t s) {
     const ahr_netlist& nl = w.nl;
     constexpr int C = 2 * P;
-    const int grid = static_cast<int>((static_cast<int64_t>(w.n_small) + kBT - 1) / kBT);
+    const int grid = w.n_big + static_cast<int>((static_cast<int64_t>(nl.n_nets) + kBT - 1) / kBT);
     DevBuf<double> partial, pin_g;
-    partial.ensure(static_cast<size_t>(grid + w.n_big + 1) * kMaxPairs, s);
+    partial.ensure(static_cast<size_t>(grid + 1) * kMaxPairs, s);
     if (grad) pin_g.ensure(static_cast<size_t>(nl.n_pins > 0 ? nl.n_pins : 1) * C, s);
     const double bytes = static_cast<double>(nl.n_pins) * (4 + 8 + 4 * C + (grad ? 8 * C * 2 + 4 : 0)) +
                          static_cast<double>(nl.n_nets + 1) * 4 +
@@ -508,22 +536,16 @@ void wa_p(const WlIndex& w, const float* pos, double inv_g, double* wl, float* g
     {
         ProfScope ps(kStageWa, s, bytes);
         if (grid) {
-            hipLaunchKernelGGL(k_wa_small<P>, dim3(grid), dim3(kBT), 0, s, pos, C, nl.net_ptr, w.small.p, w.n_small,
+            hipLaunchKernelGGL(k_wa_nets<P>, dim3(grid), dim3(kBT), 0, s, pos, nl.net_ptr, nl.n_nets, w.big.p, w.n_big,
                                nl.pin_node, nl.pin_off, inv_g, partial.p, grad ? pin_g.p : nullptr);
-            AHR_LAUNCHED("k_wa_small");
-        }
-        if (w.n_big) {
-            hipLaunchKernelGGL(k_wa_big<P>, dim3(w.n_big), dim3(kBT), 0, s, pos, C, nl.net_ptr, w.big.p, nl.pin_node,
-                               nl.pin_off, inv_g, partial.p + static_cast<int64_t>(grid) * kMaxPairs,
-                               grad ? pin_g.p : nullptr);
-            AHR_LAUNCHED("k_wa_big");
+            AHR_LAUNCHED("k_wa_nets");
         }
         if (grad) {
             hipLaunchKernelGGL(k_wa_nodes<C>, dim3(grid_for(nl.n_inst, kBT)), dim3(kBT), 0, s, w.node_ptr.p,
                                w.node_pins.p, pin_g.p, nl.n_inst, grad);
             AHR_LAUNCHED("k_wa_nodes");
         }
-        hipLaunchKernelGGL(k_wa_final, dim3(1), dim3(kFinalBT), 0, s, partial.p, grid + w.n_big, P, wl);
+        hipLaunchKernelGGL(k_wa_final, dim3(1), dim3(kFinalBT), 0, s, partial.p, grid, P, wl);
         AHR_LAUNCHED("k_wa_final");
     }
     partial.release(s);
@@ -573,27 +595,16 @@ ahr_status ahr_wl_create(const ahr_netlist* nl, void* stream, ahr_wl** out) {
                 AHR_LAUNCHED("k_pin_scatter");
             }
             slot.release(s);
-            // nets above kWave pins, ascending (a flag scan); the others by degree
+            // nets above kWave pins, ascending: counted, then listed
             if (nl->n_nets > 0) {
-                ahr::DevBuf<int32_t> flag, rank, key, start, a, b;
-                flag.ensure(static_cast<size_t>(nl->n_nets) + 1, s);
-                rank.ensure(static_cast<size_t>(nl->n_nets) + 1, s);
-                key.ensure(static_cast<size_t>(nl->n_nets) + 1, s);
-                tmp.ensure(ahr::scan_tmp_elems(nl->n_nets), s);
-                hipLaunchKernelGGL(ahr::k_net_classes, dim3(ahr::grid_for(nl->n_nets, ahr::kBT)), dim3(ahr::kBT), 0,
-                                   s, nl->net_ptr, nl->n_nets, flag.p, key.p);
-                AHR_LAUNCHED("k_net_classes");
-                w->n_big = static_cast<int32_t>(ahr::scan_i32_checked(flag.p, rank.p, nl->n_nets, tmp.p, s));
+                ahr::DevBuf<int32_t> count;
+                count.ensure(1, s);
+                ahr::run_scans(ahr::scan_job(ahr::BigNetScan{nl->net_ptr, nullptr, count.p}, nl->n_nets), tmp, s);
+                w->n_big = ahr::read_i32(count.p, s);
                 w->big.ensure(static_cast<size_t>(w->n_big) + 1, s);
-                ahr::list_rows(flag.p, rank.p, nl->n_nets, w->big.p, s);
-                flag.release(s);
-                rank.release(s);
-                ahr::bucket_sort({key.p}, nl->n_nets, ahr::kWave + 1, w->small, start, a, b, tmp, s);
-                w->n_small = ahr::read_i32(start.p + ahr::kWave + 1, s);
-                key.release(s);
-                start.release(s);
-                a.release(s);
-                b.release(s);
+                if (w->n_big)
+                    ahr::run_scans(ahr::scan_job(ahr::BigNetScan{nl->net_ptr, w->big.p, count.p}, nl->n_nets), tmp, s);
+                count.release(s);
             }
             cnt.release(s);
             tmp.release(s);
