@@ -16,13 +16,17 @@
 // its pins, added in int64 fixed point (2^-40 units), so the order in which
 // the node pass meets the pins does not change the result.
 //
-// Layout: an index built once per netlist (ahr_wl_create) lists every
-// instance's pins (node_ptr / node_pins) and the nets of more than 64 pins.
-// One call is three kernels: the net pass (256 nets a workgroup, and one
-// workgroup for each net of more than 64 pins), writing net totals into
-// workgroup partials and per-pin gradients into a [pins][ncols] float64
-// buffer in pin order; the node pass (one thread per instance gathers its
-// pins' rows); and the fixed-order reduction of the partials.
+// Layout: an index built once per netlist (ahr_wl_create) gives every pin its
+// place among the pins ordered by instance (node_ptr / place) and lists the
+// nets of more than 64 pins.  One call is three kernels: the net pass (256
+// nets a workgroup, and one workgroup for each net of more than 64 pins),
+// writing net totals into workgroup partials and every pin's gradient to its
+// place in a [pins][ncols] float64 buffer; the node pass (one thread per
+// instance reads its pins' consecutive rows); and the fixed-order reduction
+// of the partials.  The net pass scatters and the node pass streams, as a
+// store in flight holds up no wave: with the buffer in pin order and the node
+// pass gathering, the two take 278 + 225 us at 2.2M cells and 2 columns,
+// against 410 + 69 us this way.
 #include <cmath>
 
 #include "ahr_internal.hpp"
@@ -41,7 +45,7 @@ constexpr double kUnfix = 1.0 / 1099511627776.0;
 struct WlIndex {
     ahr_netlist nl;
     DevBuf<int32_t> node_ptr;     // [n_inst + 1]
-    DevBuf<int32_t> node_pins;    // [n_pins] pins of each instance (order within an instance unspecified)
+    DevBuf<int32_t> place;        // [n_pins] where each pin's gradient goes: instances ascending (pins of one in no order)
     DevBuf<int32_t> big;          // nets of more than kWave pins, ascending
     int32_t n_big = 0;
     int device = 0;
@@ -59,7 +63,7 @@ struct WlIndex {
         hipStream_t s = stream_uses == 1 ? work_stream : nullptr;
         if (stream_uses > 1) (void)hipDeviceSynchronize();
         node_ptr.release(s);
-        node_pins.release(s);
+        place.release(s);
         big.release(s);
     }
 };
@@ -87,11 +91,10 @@ __global__ void k_pin_slots(const int32_t* __restrict__ pin_node, int32_t n_pins
     if (p < n_pins) slot[p] = atomicAdd(&cnt[pin_node[p]], 1);
 }
 
-__global__ void k_pin_scatter(const int32_t* __restrict__ pin_node, int32_t n_pins,
-                              const int32_t* __restrict__ slot, const int32_t* __restrict__ node_ptr,
-                              int32_t* __restrict__ node_pins) {
+__global__ void k_pin_places(const int32_t* __restrict__ pin_node, int32_t n_pins,
+                             const int32_t* __restrict__ node_ptr, int32_t* __restrict__ slot) {
     const int64_t p = static_cast<int64_t>(blockIdx.x) * blockDim.x + threadIdx.x;
-    if (p < n_pins) node_pins[node_ptr[pin_node[p]] + slot[p]] = static_cast<int32_t>(p);
+    if (p < n_pins) slot[p] += node_ptr[pin_node[p]];
 }
 
 // exp(a) for a <= 0, in float32.
@@ -144,21 +147,26 @@ __device__ __forceinline__ double coord(const float (&v), float2 off, int c) {
 // are left out.
 //
 // What bounds it: the position gathers (HPWL, which makes the same ones, takes
-// 165 us at 2.2M cells and 2 columns) beside the gradient's stores.  Against
-// one thread a net, over nets sorted by size, with the pins in registers:
-// 786 -> 516 us a call at 2.2M cells and 2 columns, 948 -> 722 at 4 columns,
-// 276 -> 194 at 200k cells and 4 columns, 64 -> 45 at 2k cells.
+// 134 us at 1.1M cells) and the scattered stores of the gradient, with the
+// waves in flight, which the LDS limits: the nets' extremes lie where the
+// weights then go, and the means where the coordinates were, so that four
+// workgroups fit a CU instead of three (wa at 2.2M cells and 2 columns: 480
+// -> 455 us, 751 -> 681 at 4).  Against one thread a net, over nets sorted by
+// size, with the pins in registers and the gradients in pin order, a call
+// takes 455 us for 786 (2.2M cells, 2 columns), 681 for 948 (4 columns), 163
+// for 276 (200k cells, 4 columns) and 41 for 64 (2k cells, 2 columns).
 constexpr int kRun = 1024;
 
 template <int P>
 __device__ __forceinline__ void wa_batch(const float* __restrict__ pos, const int32_t* __restrict__ net_ptr,
                                          int32_t n_nets, int32_t batch, const int32_t* __restrict__ pin_node,
                                          const float* __restrict__ pin_off, double inv_g, double* tot,
-                                         double* __restrict__ pin_g) {
+                                         const int32_t* __restrict__ place, double* __restrict__ pin_g) {
     constexpr int C = 2 * P, U = kRun / kBT;
-    __shared__ double xs[2][kRun];
-    __shared__ float es[2][2][kRun];            // [axis][maximum side, minimum side]
-    __shared__ double st[2][4][kBT];            // per net and axis: extremes, then means and reciprocal sums
+    static_assert(kRun >= 4 * kBT, "a run's coordinates leave room for the nets' means");
+    __shared__ double xs[2][kRun];              // the axes' coordinates; then [mean, reciprocal sum][side] of each net
+    __shared__ double ex[2][kRun];              // [axis][maximum, minimum] of each net; then the weights' float32 pairs
+    auto es = [&](int c, int side) { return reinterpret_cast<float*>(ex[c]) + side * kRun; };
     __shared__ uint8_t owner[kRun];
     __shared__ int bstart[kBT], blen[kBT], cnt[kBT / kWave], stop_q[2];
     const int t = threadIdx.x;
@@ -197,6 +205,7 @@ __device__ __forceinline__ void wa_batch(const float* __restrict__ pos, const in
         __syncthreads();
         const int m = stop_q[run & 1] - at;        // at least one net's pins
         int v[U], pin[U];
+        int at_g[U];
         float2 off[U];
 #pragma unroll
         for (int u = 0; u < U; ++u) {
@@ -204,6 +213,7 @@ __device__ __forceinline__ void wa_batch(const float* __restrict__ pos, const in
             pin[u] = first + q + shift(q);
             v[u] = pin_node[pin[u]];
             off[u] = reinterpret_cast<const float2*>(pin_off)[pin[u]];
+            at_g[u] = pin_g ? place[pin[u]] : 0;
         }
         float g[U][C];
 #pragma unroll
@@ -235,8 +245,8 @@ __device__ __forceinline__ void wa_batch(const float* __restrict__ pos, const in
                 }
 #pragma unroll
                 for (int c = 0; c < 2; ++c) {
-                    st[c][0][t] = hi[c];
-                    st[c][1][t] = lo[c];
+                    ex[c][t] = hi[c];
+                    ex[c][kBT + t] = lo[c];
                 }
             }
             __syncthreads();
@@ -247,19 +257,25 @@ __device__ __forceinline__ void wa_batch(const float* __restrict__ pos, const in
                 own[u] = owner[t + u * kBT < m ? t + u * kBT : m - 1];
 #pragma unroll
                 for (int c = 0; c < 2; ++c) {
-                    ep[u][c] = expf(static_cast<float>((x[u][c] - st[c][0][own[u]]) * inv_g));
-                    em[u][c] = expf(static_cast<float>((st[c][1][own[u]] - x[u][c]) * inv_g));
-                    es[c][0][t + u * kBT] = ep[u][c];
-                    es[c][1][t + u * kBT] = em[u][c];
+                    ep[u][c] = expf(static_cast<float>((x[u][c] - ex[c][own[u]]) * inv_g));
+                    em[u][c] = expf(static_cast<float>((ex[c][kBT + own[u]] - x[u][c]) * inv_g));
                 }
             }
             __syncthreads();
+#pragma unroll
+            for (int u = 0; u < U; ++u)
+#pragma unroll
+                for (int c = 0; c < 2; ++c) {
+                    es(c, 0)[t + u * kBT] = ep[u][c];
+                    es(c, 1)[t + u * kBT] = em[u][c];
+                }
+            __syncthreads();
+            double sp[2] = {0, 0}, tp[2] = {0, 0}, sm[2] = {0, 0}, tm[2] = {0, 0};
             if (in_run) {
-                double sp[2] = {0, 0}, tp[2] = {0, 0}, sm[2] = {0, 0}, tm[2] = {0, 0};
                 for (int i = a; i < b; ++i)
 #pragma unroll
                     for (int c = 0; c < 2; ++c) {
-                        const double y = xs[c][i], f = es[c][0][i], h = es[c][1][i];
+                        const double y = xs[c][i], f = es(c, 0)[i], h = es(c, 1)[i];
                         sp[c] += f;
                         tp[c] += y * f;
                         sm[c] += h;
@@ -267,16 +283,20 @@ __device__ __forceinline__ void wa_batch(const float* __restrict__ pos, const in
                     }
                 double w = 0;
 #pragma unroll
-                for (int c = 0; c < 2; ++c) {
-                    const double rp = 1.0 / sp[c], rm = 1.0 / sm[c];
-                    w += tp[c] / sp[c] - tm[c] / sm[c];
-                    st[c][0][t] = rp;
-                    st[c][1][t] = rm;
-                    st[c][2][t] = tp[c] * rp;
-                    st[c][3][t] = tm[c] * rm;
-                }
+                for (int c = 0; c < 2; ++c) w += tp[c] / sp[c] - tm[c] / sm[c];
 #pragma unroll
                 for (int q = 0; q < P; ++q) tot[q] += pr == q ? w : 0.0;
+            }
+            __syncthreads();
+            if (in_run && pin_g) {
+#pragma unroll
+                for (int c = 0; c < 2; ++c) {
+                    const double rp = 1.0 / sp[c], rm = 1.0 / sm[c];
+                    xs[c][t] = rp;
+                    xs[c][kBT + t] = rm;
+                    xs[c][2 * kBT + t] = tp[c] * rp;
+                    xs[c][3 * kBT + t] = tm[c] * rm;
+                }
             }
             __syncthreads();
             if (pin_g) {
@@ -285,13 +305,13 @@ __device__ __forceinline__ void wa_batch(const float* __restrict__ pos, const in
                     double d[2];
 #pragma unroll
                     for (int c = 0; c < 2; ++c) {
-                        const double pp = static_cast<double>(ep[u][c]) * st[c][0][own[u]];
-                        const double pm = static_cast<double>(em[u][c]) * st[c][1][own[u]];
-                        d[c] = pp * (1.0 + (x[u][c] - st[c][2][own[u]]) * inv_g) -
-                               pm * (1.0 - (x[u][c] - st[c][3][own[u]]) * inv_g);
+                        const double pp = static_cast<double>(ep[u][c]) * xs[c][own[u]];
+                        const double pm = static_cast<double>(em[u][c]) * xs[c][kBT + own[u]];
+                        d[c] = pp * (1.0 + (x[u][c] - xs[c][2 * kBT + own[u]]) * inv_g) -
+                               pm * (1.0 - (x[u][c] - xs[c][3 * kBT + own[u]]) * inv_g);
                     }
                     if (t + u * kBT < m)
-                        *reinterpret_cast<double2*>(pin_g + static_cast<int64_t>(pin[u]) * C + 2 * pr) =
+                        *reinterpret_cast<double2*>(pin_g + static_cast<int64_t>(at_g[u]) * C + 2 * pr) =
                             make_double2(d[0], d[1]);
                 }
             }
@@ -361,7 +381,7 @@ __device__ __forceinline__ void big_pins(const float* __restrict__ pos, const in
 template <int P>
 __device__ __forceinline__ void wa_big(const float* __restrict__ pos, const int32_t* __restrict__ pin_node,
                                        const float* __restrict__ pin_off, int p0, int p1, double inv_g, double* tot,
-                                       double* __restrict__ pin_g) {
+                                       const int32_t* __restrict__ place, double* __restrict__ pin_g) {
     constexpr int C = 2 * P;
     __shared__ Run red[C][2][kBT / kWave];
     Run rp[C], rm[C];
@@ -422,7 +442,7 @@ __device__ __forceinline__ void wa_big(const float* __restrict__ pos, const int3
 #pragma unroll
             for (int u = 0; u < kBigU; ++u) {
                 if (p + u * kBT >= p1) break;
-                const int64_t k = static_cast<int64_t>(p + u * kBT) * C;
+                const int64_t k = static_cast<int64_t>(place[p + u * kBT]) * C;
 #pragma unroll
                 for (int c = 0; c < C; ++c) {
                     const ColAcc a{rp[c].m, rm[c].m, rp[c].s, rp[c].t, rm[c].s, rm[c].t};
@@ -447,7 +467,8 @@ __global__ void __launch_bounds__(kBT) k_wa_nets(const float* __restrict__ pos, 
                                                  int32_t n_nets, const int32_t* __restrict__ big, int32_t n_big,
                                                  const int32_t* __restrict__ pin_node,
                                                  const float* __restrict__ pin_off, double inv_g,
-                                                 double* __restrict__ partial, double* __restrict__ pin_g) {
+                                                 double* __restrict__ partial,
+                                                 const int32_t* __restrict__ place, double* __restrict__ pin_g) {
     __shared__ double red[kBT / kWave];
     double tot[P];
 #pragma unroll
@@ -455,9 +476,9 @@ __global__ void __launch_bounds__(kBT) k_wa_nets(const float* __restrict__ pos, 
     const int32_t blk = static_cast<int32_t>(blockIdx.x);
     if (blk < n_big) {
         const int e = big[blk];
-        wa_big<P>(pos, pin_node, pin_off, net_ptr[e], net_ptr[e + 1], inv_g, tot, pin_g);
+        wa_big<P>(pos, pin_node, pin_off, net_ptr[e], net_ptr[e + 1], inv_g, tot, place, pin_g);
     } else {
-        wa_batch<P>(pos, net_ptr, n_nets, blk - n_big, pin_node, pin_off, inv_g, tot, pin_g);
+        wa_batch<P>(pos, net_ptr, n_nets, blk - n_big, pin_node, pin_off, inv_g, tot, place, pin_g);
     }
 #pragma unroll
     for (int q = 0; q < P; ++q) {
@@ -470,7 +491,6 @@ __global__ void __launch_bounds__(kBT) k_wa_nets(const float* __restrict__ pos, 
 // pins' gradients, rounded once to float32.
 template <int C>
 __global__ void __launch_bounds__(kBT) k_wa_nodes(const int32_t* __restrict__ node_ptr,
-                                                  const int32_t* __restrict__ node_pins,
                                                   const double* __restrict__ pin_g, int32_t n_inst,
                                                   float* __restrict__ grad) {
     const int64_t v = static_cast<int64_t>(blockIdx.x) * kBT + threadIdx.x;
@@ -483,13 +503,11 @@ __global__ void __launch_bounds__(kBT) k_wa_nodes(const int32_t* __restrict__ no
     // pin; the repeats are not added)
     constexpr int kB = 4;
     for (int b = k0; b < k1; b += kB) {
-        int pin[kB];
-#pragma unroll
-        for (int u = 0; u < kB; ++u) pin[u] = node_pins[b + u < k1 ? b + u : k1 - 1];
         double g[kB][C];
 #pragma unroll
         for (int u = 0; u < kB; ++u) {
-            const double2* r = reinterpret_cast<const double2*>(pin_g + static_cast<int64_t>(pin[u]) * C);
+            const double2* r =
+                reinterpret_cast<const double2*>(pin_g + static_cast<int64_t>(b + u < k1 ? b + u : k1 - 1) * C);
 #pragma unroll
             for (int h = 0; h < C / 2; ++h) {
                 const double2 t = r[h];
@@ -537,12 +555,12 @@ void wa_p(const WlIndex& w, const float* pos, double inv_g, double* wl, float* g
         ProfScope ps(kStageWa, s, bytes);
         if (grid) {
             hipLaunchKernelGGL(k_wa_nets<P>, dim3(grid), dim3(kBT), 0, s, pos, nl.net_ptr, nl.n_nets, w.big.p, w.n_big,
-                               nl.pin_node, nl.pin_off, inv_g, partial.p, grad ? pin_g.p : nullptr);
+                               nl.pin_node, nl.pin_off, inv_g, partial.p, w.place.p, grad ? pin_g.p : nullptr);
             AHR_LAUNCHED("k_wa_nets");
         }
         if (grad) {
             hipLaunchKernelGGL(k_wa_nodes<C>, dim3(grid_for(nl.n_inst, kBT)), dim3(kBT), 0, s, w.node_ptr.p,
-                               w.node_pins.p, pin_g.p, nl.n_inst, grad);
+                               pin_g.p, nl.n_inst, grad);
             AHR_LAUNCHED("k_wa_nodes");
         }
         hipLaunchKernelGGL(k_wa_final, dim3(1), dim3(kFinalBT), 0, s, partial.p, grid, P, wl);
@@ -575,26 +593,24 @@ ahr_status ahr_wl_create(const ahr_netlist* nl, void* stream, ahr_wl** out) {
         try {
             AHR_HIP(hipGetDevice(&w->device));
             const int32_t n = nl->n_inst, P = nl->n_pins;
-            ahr::DevBuf<int32_t> cnt, slot;
+            ahr::DevBuf<int32_t> cnt;
             ahr::DevBuf<int64_t> tmp;
             cnt.ensure(static_cast<size_t>(n) + 1, s);
-            slot.ensure(static_cast<size_t>(P > 0 ? P : 1), s);
             tmp.ensure(ahr::scan_tmp_elems(n), s);
             w->node_ptr.ensure(static_cast<size_t>(n) + 1, s);
-            w->node_pins.ensure(static_cast<size_t>(P > 0 ? P : 1), s);
+            w->place.ensure(static_cast<size_t>(P > 0 ? P : 1), s);
             ahr::fill_i32(cnt.p, n, 0, s);
             if (P > 0) {
                 hipLaunchKernelGGL(ahr::k_pin_slots, dim3(ahr::grid_for(P, ahr::kBT)), dim3(ahr::kBT), 0, s,
-                                   nl->pin_node, P, cnt.p, slot.p);
+                                   nl->pin_node, P, cnt.p, w->place.p);
                 AHR_LAUNCHED("k_pin_slots");
             }
             ahr::scan_i32_to_i32(cnt.p, w->node_ptr.p, n, tmp.p, s);
             if (P > 0) {
-                hipLaunchKernelGGL(ahr::k_pin_scatter, dim3(ahr::grid_for(P, ahr::kBT)), dim3(ahr::kBT), 0, s,
-                                   nl->pin_node, P, slot.p, w->node_ptr.p, w->node_pins.p);
-                AHR_LAUNCHED("k_pin_scatter");
+                hipLaunchKernelGGL(ahr::k_pin_places, dim3(ahr::grid_for(P, ahr::kBT)), dim3(ahr::kBT), 0, s,
+                                   nl->pin_node, P, w->node_ptr.p, w->place.p);
+                AHR_LAUNCHED("k_pin_places");
             }
-            slot.release(s);
             // nets above kWave pins, ascending: counted, then listed
             if (nl->n_nets > 0) {
                 ahr::DevBuf<int32_t> count;
