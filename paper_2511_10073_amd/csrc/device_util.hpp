@@ -125,4 +125,19 @@ __device__ __forceinline__ int block_rank(bool flag, int* red, int* total) {
 __device__ __forceinline__ float bits_f(int v) { return __int_as_float(v); }
 __device__ __forceinline__ int f_bits(float v) { return __float_as_int(v); }
 
+// Workgroups over rows in spatial order are renumbered so that each XCD (blocks
+// are dealt round-robin over the 8 XCDs) takes one contiguous range of rows:
+// their gathers then share that XCD's L2.
+constexpr int kXcds = 8;
+
+// b in [0, nb), nb a multiple of kXcds: a bijection onto [0, nb) that gives
+// XCD x (blocks b with b % kXcds == x) the tiles [x nb/8, (x+1) nb/8).
+__device__ __forceinline__ int64_t xcd_tile(int64_t b, int64_t nb) {
+    int64_t per = nb / kXcds;
+    return (b % kXcds) * per + b / kXcds;
+}
+
+// The least multiple of kXcds not below nb.
+inline unsigned xcd_grid(int64_t nb) { return static_cast<unsigned>((nb + kXcds - 1) / kXcds * kXcds); }
+
 }  // namespace ahr

@@ -873,18 +873,6 @@ __global__ void __launch_bounds__(kBT) k_hop_long(HopArgs a0, int32_t n_long_row
     epilogue<C>(a, r, ops, sum);
 }
 
-// Workgroups of the short-row part are renumbered so that each XCD (blocks
-// are dealt round-robin over the 8 XCDs) takes one contiguous range of rows:
-// rows are in spatial order, so their gathers then share that XCD's L2.
-constexpr int kXcds = 8;
-
-// b in [0, nb), nb a multiple of kXcds: a bijection onto [0, nb) that gives
-// XCD x (blocks b with b % kXcds == x) the tiles [x nb/8, (x+1) nb/8).
-__device__ __forceinline__ int64_t xcd_tile(int64_t b, int64_t nb) {
-    int64_t per = nb / kXcds;
-    return (b % kXcds) * per + b / kXcds;
-}
-
 template <int C, int G, int U, bool NT>
 __global__ void __launch_bounds__(kBT) k_hop(HopArgs a0) {
     const HopArgs a = tile_args<C>(a0);

@@ -220,62 +220,108 @@ struct ExecRowScan {
 // entries with columns renumbered and weights as float32.  Rows of at most
 // kShortRow entries are put in ascending order of the renumbered column, so
 // that the lanes of a row gather neighbouring nodes in turn (a row's columns
-// are distinct, so an entry's place is the count of smaller ones); G lanes
-// per such row.  Longer rows keep their canonical entry order and have one
-// workgroup each (k_exec_net_long).
+// are distinct, so an entry's place is the count of smaller ones).  Longer
+// rows keep their canonical entry order and have one workgroup each
+// (k_exec_net_long).
 constexpr int kShortRow = 64;
 
 __device__ __forceinline__ int2 exec_entry(int32_t c, int64_t q, const int32_t* iperm) {
     return make_int2(iperm[c], f_bits(static_cast<float>(static_cast<double>(q) * 0x1p-32)));
 }
 
+// kExecRows consecutive rows a workgroup, one lane an entry: their short rows'
+// entries are numbered through, so that no lane idles on a short row (with 8
+// lanes a row and 8 slots a lane, which covers the longest row, six of seven
+// loads were repeats).  What bounds it are the lines it fetches, 2.1 GB at 2.2M
+// cells: parts of 128-byte lines at each canonical row's ends and at each
+// renumbered column; neighbouring rows share columns, so each XCD takes a
+// contiguous range of them.  569 -> 406 us at 2.2M cells (456 with the rows
+// dealt over the XCDs), 149 -> 122 at 600k, 48 -> 35 at 210k, 24 -> 20 at 73k.
+constexpr int kExecRows = 64;
+constexpr int kExecUnroll = 4;
+
 __global__ void __launch_bounds__(kBT) k_exec_net(int32_t n_tot, const int32_t* __restrict__ perm,
                                                   const int32_t* __restrict__ iperm, const int64_t* __restrict__ off,
                                                   const int32_t* __restrict__ col, const int64_t* __restrict__ q,
                                                   const int32_t* __restrict__ xrp, int2* __restrict__ xent) {
-    constexpr int G = 8, U = kShortRow / G;
-    __shared__ int32_t cols[kBT / G][kShortRow];
-    const int64_t r = (static_cast<int64_t>(blockIdx.x) * kBT + threadIdx.x) / G;
-    const int l = threadIdx.x & (G - 1);
-    int32_t* mine = cols[threadIdx.x / G];
-    int d = 0, len = 0;
-    if (r < n_tot) {
-        d = xrp[r];
-        len = xrp[r + 1] - d;
-        if (len > kShortRow) len = 0;                      // group-uniform: k_exec_net_long
-    }
-    // No branch around any global load, so that all of a lane's loads are in
-    // flight together: indexes are clamped to the row's last entry.
-    int32_t m[U];
-    int2 e[U];
-    if (len > 0) {
+    constexpr int L = 4;                                        // a row's slots are a multiple of L
+    static_assert(kExecRows == kWave && kShortRow % L == 0 && kBT == L * kExecRows, "layout of the slots");
+    __shared__ int4 cols[kExecRows * kShortRow / L];
+    __shared__ uint32_t owner[kExecRows * kShortRow / L];       // the row of L slots
+    __shared__ int32_t at[kExecRows + 1], end[kExecRows];       // a row's first slot and the end of its entries
+    __shared__ int32_t dst[kExecRows];
+    __shared__ int64_t src[kExecRows];                          // where slot 0 would be in col and q
+    const int t = threadIdx.x;
+    const int64_t r0 = xcd_tile(blockIdx.x, gridDim.x) * kExecRows;
+    if (t < kExecRows) {
+        const int64_t r = r0 + t < n_tot ? r0 + t : n_tot - 1;
+        const int d = xrp[r];
+        int len = xrp[r + 1] - d;
+        if (r0 + t >= n_tot || len > kShortRow) len = 0;
         const int64_t a = off[perm[r]];
-        int32_t c[U];
-        int64_t w[U];
+        const int slots = (len + L - 1) / L * L;
+        int sum = slots;
 #pragma unroll
-        for (int u = 0; u < U; ++u) {
-            const int k = l + u * G < len ? l + u * G : len - 1;
-            c[u] = col[a + k];
-            w[u] = q[a + k];
+        for (int o = 1; o < kWave; o <<= 1) {
+            const int x = __shfl_up(sum, o);
+            sum += t >= o ? x : 0;
         }
+        at[t] = sum - slots;
+        if (t == kExecRows - 1) at[kExecRows] = sum;
+        end[t] = sum - slots + len;
+        dst[t] = d;
+        src[t] = a - (sum - slots);
+    }
+    __syncthreads();
+    for (int k = at[t / L] / L + t % L; k < at[t / L + 1] / L; k += L) owner[k] = t / L;
+    __syncthreads();
+    const int n = at[kExecRows];
+    if (n == 0) return;
+    constexpr int U = kExecUnroll, kPasses = kExecRows * kShortRow / (kBT * U);
+    static_assert(kExecRows * kShortRow % (kBT * U) == 0, "whole passes");
+    int32_t* mine = reinterpret_cast<int32_t*>(cols);
+    int w[kPasses][U];
 #pragma unroll
-        for (int u = 0; u < U; ++u) m[u] = iperm[c[u]];
-        // slots past the row's end hold repeats; the counts read below len only
+    for (int h = 0; h < kPasses; ++h) {
+        const int k0 = h * kBT * U + t;
+        if (h * kBT * U < n) {                                  // workgroup-uniform
+            int32_t c[U];
+            int64_t v[U];
+            bool live[U];
 #pragma unroll
-        for (int u = 0; u < U; ++u) {
-            mine[l + u * G] = m[u];
-            e[u] = make_int2(m[u], f_bits(static_cast<float>(static_cast<double>(w[u]) * 0x1p-32)));
+            for (int u = 0; u < U; ++u) {
+                const int k = k0 + u * kBT < n ? k0 + u * kBT : n - 1;
+                const int o = owner[k / L];
+                live[u] = k < end[o];
+                const int64_t e = src[o] + (live[u] ? k : end[o] - 1);
+                c[u] = col[e];
+                v[u] = q[e];
+            }
+            int32_t m[U];
+#pragma unroll
+            for (int u = 0; u < U; ++u) m[u] = iperm[c[u]];
+#pragma unroll
+            for (int u = 0; u < U; ++u) {
+                w[h][u] = f_bits(static_cast<float>(static_cast<double>(v[u]) * 0x1p-32));
+                if (k0 + u * kBT < n) mine[k0 + u * kBT] = live[u] ? m[u] : INT32_MAX;
+            }
         }
     }
     __syncthreads();
-    if (len == 0) return;
-    // (every load is consumed by now, so a guarded store waits for nothing)
 #pragma unroll
-    for (int u = 0; u < U; ++u) {
-        if (l + u * G < len) {
-            int rank = 0;
-            for (int j = 0; j < len; ++j) rank += mine[j] < m[u] ? 1 : 0;
-            xent[static_cast<int64_t>(d) + rank] = e[u];
+    for (int h = 0; h < kPasses; ++h) {
+#pragma unroll
+        for (int u = 0; u < U; ++u) {
+            const int k = h * kBT * U + t + u * kBT;
+            if (k < n) {
+                const int o = owner[k / L], m = mine[k];
+                int rank = 0;
+                for (int j = at[o] / L; j < at[o + 1] / L; ++j) {
+                    const int4 y = cols[j];
+                    rank += (y.x < m ? 1 : 0) + (y.y < m ? 1 : 0) + (y.z < m ? 1 : 0) + (y.w < m ? 1 : 0);
+                }
+                if (k < end[o]) xent[static_cast<int64_t>(dst[o]) + rank] = make_int2(m, w[h][u]);
+            }
         }
     }
 }
@@ -766,7 +812,7 @@ void set_layout(Graph& g, const float* pos, int32_t ncols, hipStream_t s) {
 // The execution-order netlist entries: short rows by k_exec_net, long rows
 // by k_exec_net_long, all on stream s2.
 static void exec_net_copy(Graph& g, int32_t N, hipStream_t s2) {
-    hipLaunchKernelGGL(k_exec_net, dim3(grid_for(static_cast<int64_t>(N) * 8, kBT)), dim3(kBT), 0, s2, N,
+    hipLaunchKernelGGL(k_exec_net, dim3(xcd_grid(grid_for(N, kExecRows))), dim3(kBT), 0, s2, N,
                        g.perm.p, g.iperm.p, g.net_off.p, g.net_col.p, g.net_q.p, g.xnet_rp.p, g.xnet_ent.p);
     AHR_LAUNCHED("k_exec_net");
     if (g.n_long_nodes) {
