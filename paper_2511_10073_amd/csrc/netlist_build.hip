@@ -489,7 +489,11 @@ __global__ void __launch_bounds__(kBT) k_sort_rows(SortArgs a, SortLists s) {
 // Rows reach 10^4 entries, but most have a few hundred: with kLongBT threads
 // and the LDS of the longest row for each, one row a CU, the 1,700 of a
 // 600k-cell netlist took 441 us.  Up to kMidRow entries they take kMidBT
-// threads and 16 KB, eight rows a CU: 83 us, and 133 for the longer ones.
+// threads and 16 KB, eight rows a CU.  What bounds a row is its chain of LDS
+// steps and barriers, so its tail is one pass of block scans (merge_row): 45
+// us for the rows up to kMidRow and 82 for the longer ones, against 83 and 133
+// with a merge that ranked BT entries at a time and added each column's
+// weights one load after another (210k cells: 32 us for 60; 73k: 20 for 37).
 constexpr int kLongBT = 1024;
 constexpr int kMidBT = 256;
 
@@ -499,15 +503,15 @@ constexpr int kMidBT = 256;
 // merge rounds double the sorted runs.  In a round each thread finds where
 // its E outputs start on the merge path of its pair of runs (binary
 // search), merges them into registers, and after a barrier writes them back
-// in place.  Slots past n hold ~0 and sort last.  O(n log n) LDS traffic,
+// in place (the thread's keys stay in v as well).  Slots past n hold ~0 and sort last.  O(n log n) LDS traffic,
 // against O(n log^2 n) for the bitonic network used for longer rows.
 template <int BT, int kRunMax>
-__device__ void block_merge_sort(const RawEnt* __restrict__ raw, int64_t base, int n, int E, uint64_t* key) {
+__device__ __forceinline__ void block_merge_sort(const RawEnt* __restrict__ raw, int64_t base, int n, int E,
+                                                 uint64_t* key, uint64_t (&v)[kRunMax]) {
     const int t = threadIdx.x;
-    uint64_t v[kRunMax];
 #pragma unroll
     for (int u = 0; u < kRunMax; ++u) {
-        const int k = t * E + u;
+        const int k = t + u * BT;
         const bool ok = u < E && k < n;
         const int32_t c = raw[base + (ok ? k : 0)].col;          // every load in flight at once
         v[u] = ok ? (static_cast<uint64_t>(static_cast<uint32_t>(c)) << 32) | static_cast<uint32_t>(k) : ~0ull;
@@ -557,6 +561,56 @@ __device__ void block_merge_sort(const RawEnt* __restrict__ raw, int64_t base, i
     }
 }
 
+// A row sorted that way, and its equal columns merged: each thread counts the
+// columns that start among its E keys and adds their weights (every gather in
+// flight), and the weight of a column is the difference of the exact prefix
+// sums where it and the next one start.
+template <int BT, int RunMax>
+__device__ __forceinline__ void merge_row(const SortArgs& a, int r, int64_t base, int n, int E, uint64_t* key) {
+    __shared__ int64_t red[BT / kWave];
+    const int t = threadIdx.x;
+    uint64_t v[RunMax];
+    block_merge_sort<BT, RunMax>(a.raw, base, n, E, key, v);
+    uint32_t col = t > 0 ? static_cast<uint32_t>(key[t * E - 1] >> 32) : 0;
+    uint32_t heads = 0;
+#pragma unroll
+    for (int u = 0; u < RunMax; ++u) {
+        const uint32_t c = static_cast<uint32_t>(v[u] >> 32);
+        if (u < E && t * E + u < n && (c != col || (t == 0 && u == 0))) heads |= 1u << u;
+        col = c;
+    }
+    asm("" : "+v"(heads));                 // one register here and below, not what is made of it
+    int64_t cols, weight, sum = 0;
+    const int at = static_cast<int>(block_exclusive_scan_i64<BT>(__popc(heads), red, &cols));
+    int32_t* scol = a.scol + base;
+#pragma unroll
+    for (int u = 0; u < RunMax; ++u)
+        if (heads >> u & 1) scol[at + __popc(heads & ((1u << u) - 1))] = static_cast<int32_t>(v[u] >> 32);
+    static_assert(BT * RunMax <= 1 << 16, "slots of a row");
+    const RawEnt* raw = a.raw + base;
+    int64_t q[RunMax];
+#pragma unroll
+    for (int u = 0; u < RunMax; ++u) {
+        const bool ok = u < E && t * E + u < n;
+        q[u] = raw[ok ? static_cast<uint32_t>(v[u]) & 0xffffu : 0].q;      // (a 32-bit offset: slots stay below 2^16)
+        if (!ok) q[u] = 0;
+    }
+#pragma unroll
+    for (int u = 0; u < RunMax; ++u) sum += q[u];
+    sum = block_exclusive_scan_i64<BT>(sum, red, &weight);
+    asm("" : "+v"(heads));
+    // (every key has been read: the scans' barriers lie between)
+    int64_t* first = reinterpret_cast<int64_t*>(key);
+#pragma unroll
+    for (int u = 0; u < RunMax; ++u) {
+        if (heads >> u & 1) first[at + __popc(heads & ((1u << u) - 1))] = sum;
+        sum += q[u];
+    }
+    __syncthreads();
+    for (int k = t; k < cols; k += BT) a.sq[base + k] = (k + 1 < cols ? first[k + 1] : weight) - first[k];
+    if (t == 0) row_done(a, r, static_cast<int>(cols), weight);
+}
+
 template <int BT, int RunMax>
 __global__ void __launch_bounds__(BT) k_sort_long(SortArgs a, const int32_t* __restrict__ rows,
                                                   uint64_t* __restrict__ tkey, int lds_keys) {
@@ -568,20 +622,21 @@ __global__ void __launch_bounds__(BT) k_sort_long(SortArgs a, const int32_t* __r
     int r = rows[blockIdx.x];
     int n = a.cnt[r];
     int64_t base = a.rp[r];
-    const int E = (n + BT - 1) / BT;
-    const bool merge = E <= RunMax && BT * E <= lds_keys;      // block-uniform
+    // an odd number of keys a thread, where it fits, keeps the threads' runs
+    // off one another's LDS banks
+    int E = (n + BT - 1) / BT;
+    E = (E | 1) <= RunMax && BT * (E | 1) <= lds_keys ? E | 1 : E;
+    if (E <= RunMax && BT * E <= lds_keys) {                       // block-uniform
+        merge_row<BT, RunMax>(a, r, base, n, E, lkey);
+        return;
+    }
     int P = 1;
     while (P < n) P <<= 1;
-    uint64_t* key = merge || P <= lds_keys ? lkey : tkey + base;
-    if (merge) {
-        block_merge_sort<BT, RunMax>(raw, base, n, E, key);
-        P = 0;                                                     // skips the network below
-    } else {
-        for (int k = threadIdx.x; k < n; k += BT)
-            key[k] = (static_cast<uint64_t>(static_cast<uint32_t>(raw[base + k].col)) << 32) | static_cast<uint32_t>(k);
-        __threadfence_block();
-        __syncthreads();
-    }
+    uint64_t* key = P <= lds_keys ? lkey : tkey + base;
+    for (int k = threadIdx.x; k < n; k += BT)
+        key[k] = (static_cast<uint64_t>(static_cast<uint32_t>(raw[base + k].col)) << 32) | static_cast<uint32_t>(k);
+    __threadfence_block();
+    __syncthreads();
     for (int size = 2; size <= P; size <<= 1) {
         int half = size >> 1;
         // first comparator layer of a merge: mirror pairs
