@@ -81,9 +81,9 @@ __device__ __forceinline__ v4s relu_bf16x4(v4f acc) {
 }
 
 struct MlpRegs {
-    v4s w1[4];        // A tiles of W1 (hidden 16m.., features 0..15)
+    v8s w1[4];        // A tiles of W1 (hidden 16m..), features 0..7 in the K slots of every lane group
     v8s w2[8];        // A tiles of W2 (out 16n.., in chunk p of 32, K permuted), index 2n + p
-    v8s w3[2];        // A tiles with w3 in row 0 (chunk p, K permuted)
+    v8s w3[2];        // A tiles with w3 in every row (chunk p, K permuted)
     float b1[16], b2[16];
     float b3;
 };
@@ -95,34 +95,46 @@ __device__ __forceinline__ void load_mlp(const float* __restrict__ P, MlpRegs& R
 #pragma unroll
         for (int j = 0; j < 4; ++j) {
             int k = 4 * g + j;
-            R.w1[m][j] = k < kFP ? bf16_bits(P[oW1 + (16 * m + i) * kFP + k]) : static_cast<short>(0);
             R.b1[4 * m + j] = P[oB1 + 16 * m + k];
             R.b2[4 * m + j] = P[oB2 + 16 * m + k];
         }
+#pragma unroll
+    for (int m = 0; m < 4; ++m)
+#pragma unroll
+        for (int k = 0; k < kFP; ++k) R.w1[m][k] = bf16_bits(P[oW1 + (16 * m + i) * kFP + k]);
 #pragma unroll
     for (int p = 0; p < 2; ++p)
 #pragma unroll
         for (int j = 0; j < 8; ++j) {
             const int h = hid(p, 8 * g + j);
-            R.w3[p][j] = i == 0 ? bf16_bits(P[oW3 + h]) : static_cast<short>(0);
+            R.w3[p][j] = bf16_bits(P[oW3 + h]);
 #pragma unroll
             for (int n = 0; n < 4; ++n) R.w2[2 * n + p][j] = bf16_bits(P[oW2 + (16 * n + i) * kH + h]);
         }
     R.b3 = P[oB3];
 }
 
-// One tile of 16 samples.  f holds features 4(l/16)..4(l/16)+3 of sample
-// l%16; the result is valid in lanes 0..15 (sample = lane).
-__device__ __forceinline__ float mlp_tile(const MlpRegs& R, const float f[4]) {
-    const v2bf x01 = __builtin_convertvector((v2f{f[0], f[1]}), v2bf);
-    const v2bf x23 = __builtin_convertvector((v2f{f[2], f[3]}), v2bf);
-    const v4s x = __builtin_shufflevector(__builtin_bit_cast(v2s, x01), __builtin_bit_cast(v2s, x23), 0, 1, 2, 3);
+// A sample's eight features as one lane's B operand.
+__device__ __forceinline__ v4i pack_features(const float F[kFP]) {
+    v4i x;
+#pragma unroll
+    for (int k = 0; k < 4; ++k) {
+        const v2bf t = __builtin_convertvector((v2f{F[2 * k], F[2 * k + 1]}), v2bf);
+        x[k] = __builtin_bit_cast(int, t);
+    }
+    return x;
+}
+
+// One tile of 16 samples: x holds the features of sample l%16 in one group of
+// 16 lanes (whichever) and zeros in the other three, whose K slots so add
+// nothing; the result of sample l%16 is in every lane.
+__device__ __forceinline__ float mlp_tile(const MlpRegs& R, v4i x) {
     v4s a1[4], a2[4];
     // each layer's accumulator starts at its bias (float32)
 #pragma unroll
     for (int m = 0; m < 4; ++m) {
         v4f acc = {R.b1[4 * m], R.b1[4 * m + 1], R.b1[4 * m + 2], R.b1[4 * m + 3]};
-        acc = __builtin_amdgcn_mfma_f32_16x16x16bf16_1k(R.w1[m], x, acc, 0, 0, 0);
+        acc = mfma32(R.w1[m], __builtin_bit_cast(v8s, x), acc);
         a1[m] = relu_bf16x4(acc);
     }
     // the lane's rows of output tiles 2p and 2p+1: the B operand of chunk p
@@ -148,7 +160,7 @@ __device__ __forceinline__ float mlp_tile(const MlpRegs& R, const float f[4]) {
             b2[p][j] = a2[2 * p][j];
             b2[p][4 + j] = a2[2 * p + 1][j];
         }
-    v4f acc = {R.b3, 0.f, 0.f, 0.f};
+    v4f acc = {R.b3, R.b3, R.b3, R.b3};
 #pragma unroll
     for (int p = 0; p < 2; ++p) acc = mfma32(R.w3[p], b2[p], acc);
     return acc[0];
@@ -164,12 +176,14 @@ __global__ void __launch_bounds__(kBT) k_mlp_forward(const float* __restrict__ P
     const int64_t ntiles = (n + 15) / 16;
     for (int64_t t = static_cast<int64_t>(blockIdx.x) * (kBT / kWave) + wave_id(); t < ntiles; t += waves) {
         const int64_t smp = t * 16 + (l & 15);
-        float f[4] = {0.f, 0.f, 0.f, 0.f};
-        if (smp < n && g < 2) {
-            float4 v = reinterpret_cast<const float4*>(feats + smp * kFP)[g];
-            f[0] = v.x, f[1] = v.y, f[2] = v.z, f[3] = v.w;
+        float F[kFP] = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
+        if (smp < n && g == 0) {
+            const float4 u = reinterpret_cast<const float4*>(feats + smp * kFP)[0];
+            const float4 v = reinterpret_cast<const float4*>(feats + smp * kFP)[1];
+            F[0] = u.x, F[1] = u.y, F[2] = u.z, F[3] = u.w;
+            F[4] = v.x, F[5] = v.y, F[6] = v.z, F[7] = v.w;
         }
-        float r = mlp_tile(R, f);
+        float r = mlp_tile(R, pack_features(F));
         if (l < 16 && smp < n) o[smp] = r;
     }
 }
@@ -268,15 +282,19 @@ __device__ __forceinline__ void sample_unscale(const LearnArgs& a, SampleIn& t, 
 // columns) per wavefront and step: each lane loads and featurises its own
 // sample (its column is the same at every step, as 64 % C == 0, so its
 // column statistics are loaded once), then the network runs the four
-// 16-sample matrix-core tiles in turn, each fed by shuffles (features 0..3
-// to lanes 0..15, features 4..7 to lanes 16..31), and every lane takes its
-// sample's result back and writes it.  The next step's loads are in flight
-// meanwhile.  A sample's result does not depend on its tile's other samples.
+// 16-sample matrix-core tiles in turn, each fed by the lanes that own its
+// samples (the other lanes' K slots hold zeros), which find their results in
+// place and write them.  The next step's loads are in flight meanwhile.  A
+// sample's result does not depend on its tile's other samples.
+// What bounds it: the matrix and conversion steps of a tile follow one another
+// (14 products, 32 conversions), with three waves a SIMD to fill in.  880k
+// cells x 4 columns: 60 us, against 84 with the features and results moved by
+// nine shuffles a tile.
 template <int C>
 __global__ void __launch_bounds__(kBT) k_mlp_learned(LearnArgs a) {
     MlpRegs R;
     load_mlp(a.params, R);
-    const int l = lane_id(), g = l >> 4, i = l & 15;
+    const int l = lane_id(), g = l >> 4;
     const int c = l % C;
     const float mc = a.stats[c], sc = a.stats[C + c], rc = a.stats[2 * C + c];
     const float inv_sc = 1.f / sc, inv_rc = 1.f / rc;
@@ -298,17 +316,14 @@ __global__ void __launch_bounds__(kBT) k_mlp_learned(LearnArgs a) {
         F[5] = cur.rf.z;
         F[6] = lsr;
         F[7] = 0.f;
+        const v4i x = pack_features(F);
         float mine = 0.f;
-#pragma unroll
+#pragma unroll 2
         for (int j = 0; j < kWave / 16; ++j) {
-            const int src = 16 * j + i;
-            float f[4];
+            v4i own;
 #pragma unroll
-            for (int k = 0; k < 4; ++k) {
-                const float lo = __shfl(F[k], src), hi = __shfl(F[4 + k], src);
-                f[k] = g == 0 ? lo : (g == 1 ? hi : 0.f);
-            }
-            const float o = __shfl(mlp_tile(R, f), i);     // tile j's result for sample 16 j + i
+            for (int k = 0; k < 4; ++k) own[k] = g == j ? x[k] : 0;
+            const float o = mlp_tile(R, own);              // of sample 16 j + i
             if (g == j) mine = o;
         }
         const int64_t r = smp / C;
