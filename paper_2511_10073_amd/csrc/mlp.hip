@@ -204,7 +204,7 @@ struct LearnArgs {
     const double* deg;
     const float* hsum;
     const float* stats;     // [3][C]: mean and std of h3, rms of h0 - h3
-    const float4* rowf;     // [n_inst] per execution row: 1/s, log1p(d), hsum/d, row code (bits)
+    float4* rowf;           // [n_inst] per execution row: 1/s, log1p(d), hsum/d, row code (bits)
     const float* in;
     float* out;
     float* feats;           // optional [n_inst * C][8], instance order
@@ -224,17 +224,10 @@ struct LearnArgs {
 __device__ __forceinline__ int row_inst(int code) { return code & 0x7fffffff; }
 __device__ __forceinline__ bool row_fixed(int code) { return code < 0; }
 
-__global__ void k_row_feat(int32_t n, const float* __restrict__ scale, const double* __restrict__ deg,
-                           const float* __restrict__ hsum, const int32_t* __restrict__ perm,
-                           const uint8_t* __restrict__ flags, float4* __restrict__ rowf) {
-    int64_t r = static_cast<int64_t>(blockIdx.x) * blockDim.x + threadIdx.x;
-    if (r >= n) return;
-    const float s = scale[r];
-    const double d = deg[r];
-    const int inst = perm[r];
-    const int code = inst | ((flags[inst] & AHR_NODE_FIXED) ? static_cast<int>(0x80000000u) : 0);
-    rowf[r] = make_float4(s > 0.f ? 1.f / s : 0.f, static_cast<float>(log1p(d)),
-                          d > 0 ? static_cast<float>(static_cast<double>(hsum[r]) / d) : 0.f, __int_as_float(code));
+__device__ __forceinline__ float4 row_feat(float s, double d, float hs, int inst, uint8_t flags) {
+    const int code = inst | ((flags & AHR_NODE_FIXED) ? static_cast<int>(0x80000000u) : 0);
+    return make_float4(s > 0.f ? 1.f / s : 0.f, static_cast<float>(log1p(d)),
+                       d > 0 ? static_cast<float>(static_cast<double>(hs) / d) : 0.f, __int_as_float(code));
 }
 
 // One sample's inputs: the scaled hops z_j (h = z_j / s once the row's 1/s
@@ -392,9 +385,10 @@ __device__ __forceinline__ void block_sums(double (&v)[W], double (*red)[kBT / k
     }
 }
 
-// The loads of kStatRows rows a thread are in flight together (the rows are
-// read from memory once, 48 bytes each at 4 columns; with a row's loads one
-// after another 880k cells took 23 us).
+// The same pass forms the rows' inputs of the features (rowf).  The loads of
+// kStatRows rows a thread are in flight together: 880k cells x 4 columns take
+// 22 us, against 13 us for a kernel of rowf alone and 23 us for the sums with
+// a row's loads one after another.
 constexpr int kStatRows = 4;
 
 template <int C>
@@ -405,7 +399,7 @@ __global__ void __launch_bounds__(kBT) k_colstat(LearnArgs a, double* __restrict
 #pragma unroll
     for (int c = 0; c < C; ++c) shift[c] = 0;
     if (a.n_inst > 0) {
-        const float inv_s0 = a.rowf[0].x;
+        const float inv_s0 = a.scale[0] > 0.f ? 1.f / a.scale[0] : 0.f;
 #pragma unroll
         for (int c = 0; c < C; ++c) shift[c] = unscale(a.z3, C, 0, c, inv_s0, a.in, a.perm);
     }
@@ -414,21 +408,32 @@ __global__ void __launch_bounds__(kBT) k_colstat(LearnArgs a, double* __restrict
     for (int c = 0; c < W; ++c) acc[c] = 0;
     constexpr int64_t kStep = static_cast<int64_t>(kStatGrid) * kBT;
     for (int64_t r0 = static_cast<int64_t>(blockIdx.x) * kBT + threadIdx.x; r0 < a.n_inst; r0 += kStatRows * kStep) {
-        float4 rf[kStatRows];
+        float s[kStatRows], hs[kStatRows];
+        double deg[kStatRows];
+        int inst[kStatRows];
+        uint8_t fl[kStatRows];
         ZRow<C> z3[kStatRows], z0[kStatRows];
 #pragma unroll
         for (int u = 0; u < kStatRows; ++u) {
             const int64_t r = r0 + u * kStep < a.n_inst ? r0 + u * kStep : r0;
-            rf[u] = a.rowf[r];
+            inst[u] = a.perm[r];
+            s[u] = a.scale[r];
+            hs[u] = a.hsum[r];
+            deg[u] = a.deg[r];
             z3[u] = reinterpret_cast<const ZRow<C>*>(a.z3)[r];
             z0[u] = reinterpret_cast<const ZRow<C>*>(a.z0)[r];
         }
 #pragma unroll
+        for (int u = 0; u < kStatRows; ++u) fl[u] = a.flags[inst[u]];
+#pragma unroll
         for (int u = 0; u < kStatRows; ++u) {
             const int64_t r = r0 + u * kStep;
-            const int code = __float_as_int(rf[u].w);
-            if (r >= a.n_inst || row_fixed(code)) continue;
-            const float inv_s = rf[u].x;
+            if (r >= a.n_inst) break;
+            const float4 rf = row_feat(s[u], deg[u], hs[u], inst[u], fl[u]);
+            a.rowf[r] = rf;
+            const int code = __float_as_int(rf.w);
+            if (row_fixed(code)) continue;
+            const float inv_s = rf.x;
 #pragma unroll
             for (int c = 0; c < C; ++c) {
                 float h3 = z3[u].v[c] * inv_s, h0 = z0[u].v[c] * inv_s;
@@ -967,9 +972,6 @@ void learned_c(Graph& g, const ahr_filter_spec& spec, const float* params, const
     rowf.ensure(static_cast<size_t>(g.n_inst) + 1, s);
     a.stats = stats.p;
     a.rowf = rowf.p;
-    hipLaunchKernelGGL(k_row_feat, dim3(grid_for(g.n_inst, kBT)), dim3(kBT), 0, s, g.n_inst, g.scale.p, g.deg.p,
-                       g.hsum.p, g.perm.p, g.nl.node_flags, rowf.p);
-    AHR_LAUNCHED("k_row_feat");
     hipLaunchKernelGGL((k_colstat<C>), dim3(kStatGrid), dim3(kBT), 0, s, a, part.p);
     AHR_LAUNCHED("k_colstat");
     hipLaunchKernelGGL((k_colstat_final<C>), dim3(1), dim3(kBT), 0, s, a, part.p, stats.p);
