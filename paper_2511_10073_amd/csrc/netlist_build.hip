@@ -378,9 +378,80 @@ __device__ __forceinline__ void sort_trivial(const SortArgs& a, const int32_t* r
     row_done(a, r, c, q);
 }
 
-// G lanes per row (G = 8, 16, 32 or 64): bitonic sort by column across the lanes,
-// then merge equal columns by exact integer sums.  Narrow: the column ids
-// leave room for a lane index beside them in 31 bits.
+// Lane exchanges without the LDS crossbar (every lane of the wave active).
+template <int Ctrl>
+__device__ __forceinline__ int dpp(int x) {
+    return __builtin_amdgcn_mov_dpp(x, Ctrl, 0xf, 0xf, true);
+}
+constexpr int kDppPrev = 0x138, kDppNext = 0x130;       // the lane below / above, across the wave (zeros at its ends)
+
+// The values of lanes l and l ^ J as a pair of which one is the caller's own
+// (which one is unspecified: for operations that commute).
+template <int J>
+__device__ __forceinline__ void lane_pair(int x, int& a, int& b) {
+    a = x;
+    if constexpr (J == 1) {
+        b = dpp<0xb1>(x);                               // quad [1, 0, 3, 2]
+    } else if constexpr (J == 2) {
+        b = dpp<0x4e>(x);                               // quad [2, 3, 0, 1]
+    } else if constexpr (J == 4) {
+        b = dpp<0x1b>(dpp<0x141>(x));                   // mirrored in 8, then in 4
+    } else if constexpr (J == 8) {
+        b = dpp<0x128>(x);                              // rotated by 8 in 16
+    } else {
+        static_assert(J == 16 || J == 32, "lane distance");
+        const auto r = J == 16 ? __builtin_amdgcn_permlane16_swap(x, x, false, false)
+                               : __builtin_amdgcn_permlane32_swap(x, x, false, false);
+        a = static_cast<int>(r[0]);
+        b = static_cast<int>(r[1]);
+    }
+}
+
+// The lanes that keep the smaller key in step (K, J) of the bitonic network
+// over groups of G lanes.
+template <int G>
+constexpr uint64_t bitonic_low(int K, int J) {
+    uint64_t m = 0;
+    for (int i = 0; i < kWave; ++i) {
+        const int l = i & (G - 1);
+        if (((l & J) == 0) == ((l & K) == 0)) m |= 1ull << i;
+    }
+    return m;
+}
+
+template <int G, int K, int J>
+__device__ __forceinline__ int bitonic_steps(int x) {
+    int a, b;
+    lane_pair<J>(x, a, b);
+    constexpr uint64_t low = bitonic_low<G>(K, J);
+    x = __builtin_amdgcn_inverse_ballot_w64(low) ? (a < b ? a : b) : (a < b ? b : a);
+    if constexpr (J > 1) return bitonic_steps<G, K, J / 2>(x);
+    else if constexpr (K < G) return bitonic_steps<G, 2 * K, K>(x);
+    else return x;
+}
+
+// Sum over the lane's group of G (the lanes of a group end with the same).
+template <int J>
+__device__ __forceinline__ int64_t pair_sum(int64_t v) {
+    int a0, b0, a1, b1;
+    lane_pair<J>(static_cast<int>(v), a0, b0);
+    lane_pair<J>(static_cast<int>(v >> 32), a1, b1);
+    const auto join = [](int lo, int hi) {
+        return static_cast<int64_t>(static_cast<uint64_t>(static_cast<uint32_t>(hi)) << 32 | static_cast<uint32_t>(lo));
+    };
+    return join(a0, a1) + join(b0, b1);
+}
+
+// G lanes per row (G = 8, 16, 32 or 64): bitonic sort by column across the
+// lanes, then equal columns merged by exact integer sums.  Narrow: the column
+// ids leave room for a lane index beside them in 31 bits.
+// What bounds it: the vector instructions of a wave (a row of few entries
+// takes the whole of its lanes through the network) beside 28 bytes of memory
+// an entry, so the exchanges are part of the comparisons (no shuffles), the
+// network's directions are constants, and the run sums take as many steps as
+// the wave's longest run of equal columns needs.
+// 108 us at 600k cells (gift), against 135 with shuffles and full-length sums;
+// 32 for 44 at 210k, 12.6 for 17.8 at 73k, 415 for 445 at 2.2M.
 template <int G, bool Narrow>
 __device__ __forceinline__ void sort_group(const SortArgs& a, const int32_t* rows, int32_t nrows, int32_t block) {
     int64_t gid = (static_cast<int64_t>(block) * kBT + threadIdx.x) / G;
@@ -403,18 +474,7 @@ __device__ __forceinline__ void sort_group(const SortArgs& a, const int32_t* row
         // network moves the key alone and each lane then fetches the weight
         // of the entry it ended up with
         constexpr int LB = G == 8 ? 3 : G == 16 ? 4 : G == 32 ? 5 : 6;
-        int ck = l < len ? ((key << LB) | l) : 0x7fffffff;
-#pragma unroll
-        for (int k = 2; k <= G; k <<= 1) {
-#pragma unroll
-            for (int j = k >> 1; j > 0; j >>= 1) {
-                const int pk = __shfl_xor(ck, j);
-                const bool up = (l & k) == 0;
-                const bool lower = (l & j) == 0;
-                const bool take = lower ? (up ? (pk < ck) : (pk > ck)) : (up ? (pk > ck) : (pk < ck));
-                ck = take ? pk : ck;
-            }
-        }
+        const int ck = bitonic_steps<G, 2, 1>(l < len ? ((key << LB) | l) : 0x7fffffff);
         q = __shfl(q, gbase + (ck & (G - 1)));
         key = l < len ? (ck >> LB) : 0x7fffffff;
     } else {
@@ -434,34 +494,40 @@ __device__ __forceinline__ void sort_group(const SortArgs& a, const int32_t* row
             }
         }
     }
-    int prev = __shfl(key, gbase + (l > 0 ? l - 1 : 0));
-    int next = __shfl(key, gbase + (l + 1 < G ? l + 1 : l));
-    bool head = (l < len) && (l == 0 || prev != key);
-    bool tail = (l < len) && (l + 1 == len || next != key);
-    // run sums from exact int64 prefix sums: sum = pre[l] - pre[start - 1]
-    int64_t pre = q;
-    int start = head ? l : 0;
-#pragma unroll
+    const bool live = l < len;
+    if (!live) q = 0;
+    const int prev = dpp<kDppPrev>(key), next = dpp<kDppNext>(key);
+    const bool head = live && (l == 0 || prev != key);
+    const bool tail = live && (l + 1 == len || next != key);
+    // the row's weight sum
+    int64_t total = q;
+    total = pair_sum<1>(total);
+    total = pair_sum<2>(total);
+    total = pair_sum<4>(total);
+    if constexpr (G > 8) total = pair_sum<8>(total);
+    if constexpr (G > 16) total = pair_sum<16>(total);
+    if constexpr (G > 32) total = pair_sum<32>(total);
+    // sums of the runs of equal columns, complete at their last lanes; done
+    // with the first distance that no lane has an equal column at
+    int64_t sum = q;
     for (int d = 1; d < G; d <<= 1) {
-        int64_t pu = __shfl(pre, gbase + (l >= d ? l - d : l));
-        int su = __shfl(start, gbase + (l >= d ? l - d : l));
-        if (l >= d) {
-            pre += pu;
-            start = su > start ? su : start;
-        }
+        const int from = l >= d ? lane - d : lane;
+        const int there = __shfl(key, from);
+        const bool same = live && l >= d && there == key;
+        if (!__any(same)) break;
+        const int64_t add = __shfl(sum, from);
+        sum += same ? add : 0;
     }
-    int64_t before = __shfl(pre, gbase + (start > 0 ? start - 1 : 0));
-    int64_t sum = pre - (start > 0 ? before : 0);
-    uint64_t hm = __ballot(head);
-    uint64_t gm = (G == 64) ? ~0ull : (((1ull << G) - 1ull) << gbase);
-    uint64_t below_start = (gbase + start) ? (~0ull >> (kWave - (gbase + start))) : 0ull;
-    int idx = __popcll(hm & gm & below_start);
+    const uint64_t hm = __ballot(head);
+    // the runs that start at or before the lane, of which those of the groups below
+    const int upto = __builtin_amdgcn_mbcnt_hi(static_cast<uint32_t>(hm >> 32),
+                                               __builtin_amdgcn_mbcnt_lo(static_cast<uint32_t>(hm), head ? 1 : 0));
+    const int idx = upto - __popcll(hm & ((1ull << gbase) - 1ull)) - 1;
     if (tail) {
         a.scol[base + idx] = key;
         a.sq[base + idx] = sum;
     }
-    // (the inclusive scan's last lane holds the row's weight sum)
-    if (valid_row && l == G - 1) row_done(a, r, __popcll(hm & gm), pre);
+    if (valid_row && l == G - 1) row_done(a, r, idx + 1, total);
 }
 
 // The five classes of at most 64 entries in one launch: workgroups [b[k],
