@@ -182,11 +182,13 @@ struct RowClasses {
     DevBuf<int32_t> long_rows;    // rows split over chunks, ascending
     DevBuf<int32_t> long_chunk0;  // [n_long+1] first chunk of each long row
     DevBuf<int32_t> chunk_row;    // [n_chunks] long-row index of each chunk
+    DevBuf<int4> chunks;          // [n_chunks] first netlist entry, netlist entries, first hint entry, entries
     DevBuf<double> partial;       // [n_chunks * 8]
     DevBuf<int4> rb;              // [2 n_rb] row blocks: (r0, r1, net_lo, net_hi), (hint_lo, hint_hi, -, -)
     DevBuf<int32_t> counts;       // counts of the scans that make them
     int32_t n_long = 0, n_long_inst = 0;      // long rows, those below n_inst
     int32_t n_chunks = 0, n_chunks_inst = 0;  // chunks, those of long rows below n_inst
+    int32_t n_chunks_net = 0;                 // those of long rows below the hint nodes
     int32_t n_rb = 0, n_rb_inst = 0;          // row blocks, those below n_inst
     int32_t has_rb = 0;                       // row blocks built (on first use of the row-block hop)
     int64_t nnz_inst = 0;                     // entries of rows below n_inst (netlist + hints)
@@ -195,6 +197,7 @@ struct RowClasses {
         long_rows.release(s);
         long_chunk0.release(s);
         chunk_row.release(s);
+        chunks.release(s);
         partial.release(s);
         rb.release(s);
         counts.release(s);
@@ -479,11 +482,11 @@ struct ChainView {
     const uint8_t* flags;     // instance flags, instance order
     const int32_t* perm;      // execution row -> instance
     const int32_t* long_rows;
-    const int32_t* chunk_row;
+    const int4* chunks;
     const int32_t* chunk0;
     double* partial;
     const int4* rb;
-    int32_t n_tot, n_inst, n_long, n_long_inst, n_chunks, n_chunks_inst, n_rb, n_rb_inst;
+    int32_t n_tot, n_inst, n_long, n_long_inst, n_chunks, n_chunks_inst, n_chunks_net, n_rb, n_rb_inst;
     int64_t nnz_inst, nnz_all;
     float* z0;
     float* z1;
@@ -492,9 +495,11 @@ struct ChainView {
 
 // Row classes of an operator with rows [0, N), instance rows first: the
 // long rows (more than kLongRow entries) with their chunks and a
-// partial-sum buffer for C <= 8 columns.  Resets the row blocks.
+// partial-sum buffer for C <= 8 columns.  Resets the row blocks.  Rows from
+// first_hint on (N: none) are hint nodes.
 // max_entries: a bound on the operator's entries (it sizes the lists).
-void row_classes(const int32_t* net_rp, const int32_t* hint_rp, int32_t N, int32_t n_inst, int64_t max_entries,
+void row_classes(const int32_t* net_rp, const int32_t* hint_rp, int32_t N, int32_t n_inst, int32_t first_hint,
+                 int64_t max_entries,
                  RowClasses& rc, DevBuf<int64_t>& scan_tmp, hipStream_t s);
 // The row blocks of the short rows (for the row-block hop), if not built.
 void row_blocks(const int32_t* net_rp, const int32_t* hint_rp, int32_t N, int32_t n_inst, RowClasses& rc,

@@ -176,7 +176,7 @@ ChainView batch_view(Batch& b, const ahr_filter_spec& spec) {
     v.flags = b.flags.p;
     v.perm = b.perm.p;
     v.long_rows = b.rc.long_rows.p;
-    v.chunk_row = b.rc.chunk_row.p;
+    v.chunks = b.rc.chunks.p;
     v.chunk0 = b.rc.long_chunk0.p;
     v.partial = b.rc.partial.p;
     v.rb = b.rc.rb.p;
@@ -186,6 +186,7 @@ ChainView batch_view(Batch& b, const ahr_filter_spec& spec) {
     v.n_long_inst = b.rc.n_long_inst;
     v.n_chunks = b.rc.n_chunks;
     v.n_chunks_inst = b.rc.n_chunks_inst;
+    v.n_chunks_net = b.rc.n_chunks_net;
     v.n_rb = b.rc.n_rb;
     v.n_rb_inst = b.rc.n_rb_inst;
     v.nnz_inst = b.rc.nnz_inst;
@@ -427,7 +428,7 @@ void batch_assemble(Batch& b, hipStream_t s) {
     b.scale.ensure(static_cast<size_t>(b.n_tot) + 1, s);
     b.coef.ensure(static_cast<size_t>(b.n_tot) + 1, s);
     b.op_version.assign(n, -1);
-    row_classes(b.net_rp.p, b.hint_rp.p, b.n_tot, b.n_inst, b.nnz_net + b.nnz_hint, b.rc, b.scan_tmp, s);
+    row_classes(b.net_rp.p, b.hint_rp.p, b.n_tot, b.n_inst, b.n_tot, b.nnz_net + b.nnz_hint, b.rc, b.scan_tmp, s);
     std::vector<int32_t> blk(n + 1, 0), sblk(n + 1, 0);
     for (size_t i = 0; i < n; ++i) {
         blk[i + 1] = blk[i] + static_cast<int32_t>(grid_for(b.g[i]->n_tot, kBT));

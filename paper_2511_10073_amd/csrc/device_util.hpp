@@ -18,11 +18,58 @@ using GlobalPtr = const __attribute__((address_space(1))) T*;
 __device__ __forceinline__ int lane_id() { return threadIdx.x & (kWave - 1); }
 __device__ __forceinline__ int wave_id() { return threadIdx.x / kWave; }
 
+// Lane exchanges without the LDS crossbar (every lane of the wave active).
+template <int Ctrl>
+__device__ __forceinline__ int dpp(int x) {
+    return __builtin_amdgcn_mov_dpp(x, Ctrl, 0xf, 0xf, true);
+}
+constexpr int kDppPrev = 0x138, kDppNext = 0x130;       // the lane below / above, across the wave (zeros at its ends)
+
+// The values of lanes l and l ^ J as a pair of which one is the caller's own
+// (which one is unspecified: for operations that commute).
+template <int J>
+__device__ __forceinline__ void lane_pair(int x, int& a, int& b) {
+    a = x;
+    if constexpr (J == 1) {
+        b = dpp<0xb1>(x);                               // quad [1, 0, 3, 2]
+    } else if constexpr (J == 2) {
+        b = dpp<0x4e>(x);                               // quad [2, 3, 0, 1]
+    } else if constexpr (J == 4) {
+        b = dpp<0x1b>(dpp<0x141>(x));                   // mirrored in 8, then in 4
+    } else if constexpr (J == 8) {
+        b = dpp<0x128>(x);                              // rotated by 8 in 16
+    } else {
+        static_assert(J == 16 || J == 32, "lane distance");
+        const auto r = J == 16 ? __builtin_amdgcn_permlane16_swap(x, x, false, false)
+                               : __builtin_amdgcn_permlane32_swap(x, x, false, false);
+        a = static_cast<int>(r[0]);
+        b = static_cast<int>(r[1]);
+    }
+}
+
+// v of lane l plus v of lane l ^ J, for a 64-bit integer or a double.
+template <int J, class T>
+__device__ __forceinline__ T pair_sum(T v) {
+    static_assert(sizeof(T) == 8, "two words");
+    struct Words {
+        int w[2];
+    };
+    const Words x = __builtin_bit_cast(Words, v);
+    Words a, b;
+    lane_pair<J>(x.w[0], a.w[0], b.w[0]);
+    lane_pair<J>(x.w[1], a.w[1], b.w[1]);
+    return __builtin_bit_cast(T, a) + __builtin_bit_cast(T, b);
+}
+
+// Sum over the wave, in every lane (halves first, then quarters, ...).
 template <class T>
 __device__ __forceinline__ T wave_sum(T v) {
-#pragma unroll
-    for (int o = kWave / 2; o > 0; o >>= 1) v += __shfl_xor(v, o);
-    return v;
+    v = pair_sum<32>(v);
+    v = pair_sum<16>(v);
+    v = pair_sum<8>(v);
+    v = pair_sum<4>(v);
+    v = pair_sum<2>(v);
+    return pair_sum<1>(v);
 }
 
 template <class T>
@@ -80,6 +127,24 @@ __device__ __forceinline__ double block_sum_f64(double v, double* red) {
 #pragma unroll
     for (int w = 0; w < BT / kWave; ++w) t += red[w];
     return t;
+}
+
+// The same for W doubles a thread with one pass of the barriers.  red is free
+// before the call (a caller that uses it again puts a barrier between).
+template <int BT, int W>
+__device__ __forceinline__ void block_sums_f64(double (&v)[W], double (*red)[BT / kWave]) {
+#pragma unroll
+    for (int c = 0; c < W; ++c) {
+        const double t = wave_sum(v[c]);
+        if (lane_id() == 0) red[c][wave_id()] = t;
+    }
+    __syncthreads();
+#pragma unroll
+    for (int c = 0; c < W; ++c) {
+        v[c] = 0;
+#pragma unroll
+        for (int w = 0; w < BT / kWave; ++w) v[c] += red[c][w];
+    }
 }
 
 // Block exclusive scan of int64; *total gets the block sum. red: BT/64 slots.

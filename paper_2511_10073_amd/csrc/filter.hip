@@ -20,6 +20,7 @@
 #include <hip/hip_ext.h>
 
 #include <algorithm>
+#include <type_traits>
 
 #include "ahr_internal.hpp"
 #include "device_util.hpp"
@@ -110,11 +111,11 @@ struct LongRowScan {
     __device__ Pack<1> pack(const Pack<1>& p) const { return p; }
     const int32_t* net_rp;
     const int32_t* hint_rp;
-    int32_t n_inst;
+    int32_t n_inst, first_hint;
     int32_t* long_rows;
     int32_t* chunk0;
     int32_t* chunk_row;
-    int32_t* counts;       // long rows, those below n_inst, chunks, those below n_inst
+    int32_t* counts;       // long rows, those below n_inst, chunks, those below n_inst and below first_hint
     __device__ Pack<1> first(int64_t r) const {
         const int len = (net_rp[r + 1] - net_rp[r]) + (hint_rp[r + 1] - hint_rp[r]);
         return {{len > kLongRow ? pack2(1, (len + kChunk - 1) / kChunk) : 0}};
@@ -126,6 +127,7 @@ struct LongRowScan {
             counts[1] = k;
             counts[3] = c0;
         }
+        if (r == first_hint) counts[4] = c0;
         if (!nc) return;
         long_rows[k] = static_cast<int32_t>(r);
         chunk0[k] = c0;
@@ -276,66 +278,98 @@ __global__ void __launch_bounds__(kBT) k_deg_rows(int32_t r0, int32_t n, int32_t
                          scale, hsum);
 }
 
-__device__ __forceinline__ void chunk_range(int c, const int32_t* long_rows, const int32_t* chunk_row,
-                                            const int32_t* chunk0, const RowRef& m, int& r, int& li, int& k0, int& k1,
-                                            int& n0, int& ln, int& h0) {
-    li = chunk_row[c];
-    r = long_rows[li];
-    n0 = m.net_rp[r];
-    ln = m.net_rp[r + 1] - n0;
-    h0 = m.hint_rp[r];
-    int len = ln + (m.hint_rp[r + 1] - h0);
-    k0 = (c - chunk0[li]) * kChunk;
-    k1 = k0 + kChunk < len ? k0 + kChunk : len;
+// f(U) with U the entries a lane takes in a chunk of n: 1, 2, 4 or all 8 (most
+// long rows have a few hundred entries, and a slot past the end costs the
+// loads and gathers of an entry).
+template <class F>
+__device__ __forceinline__ void in_chunk(int n, const F& f) {
+    static_assert(kChunk == 8 * kBT, "entries a lane");
+    if (n <= kBT) f(std::integral_constant<int, 1>());
+    else if (n <= 2 * kBT) f(std::integral_constant<int, 2>());
+    else if (n <= 4 * kBT) f(std::integral_constant<int, 4>());
+    else f(std::integral_constant<int, 8>());
 }
 
+// The entries of chunk c (RowClasses::chunks).
+__device__ __forceinline__ int4 chunk_range(int c, const int32_t* long_rows, const int32_t* chunk_row,
+                                            const int32_t* chunk0, const RowRef& m) {
+    const int li = chunk_row[c], r = long_rows[li];
+    const int n0 = m.net_rp[r], ln = m.net_rp[r + 1] - n0, h0 = m.hint_rp[r], len = ln + (m.hint_rp[r + 1] - h0);
+    const int at = (c - chunk0[li]) * kChunk, n = at + kChunk < len ? kChunk : len - at;
+    const int net = at >= ln ? 0 : at + n < ln ? n : ln - at;
+    return make_int4(n0 + (at < ln ? at : ln), net, h0 + (at > ln ? at - ln : 0), n);
+}
+
+// The chunks' entries where no degrees are formed (k_chunk_absdeg).
+__global__ void k_chunk_ranges(RowRef m, int32_t n_chunks, const int32_t* __restrict__ long_rows,
+                               const int32_t* __restrict__ chunk_row, const int32_t* __restrict__ chunk0,
+                               int4* __restrict__ chunks) {
+    const int64_t c = static_cast<int64_t>(blockIdx.x) * blockDim.x + threadIdx.x;
+    if (c < n_chunks) chunks[c] = chunk_range(static_cast<int>(c), long_rows, chunk_row, chunk0, m);
+}
+
+// One workgroup a chunk: its entries' range, which every later kernel takes
+// with one load (following the row lists costs a hop's chunk four loads one
+// after another), and the sums of its hint entries.
 __global__ void __launch_bounds__(kBT) k_chunk_absdeg(RowRef m, const int32_t* __restrict__ long_rows,
                                                       const int32_t* __restrict__ chunk_row,
-                                                      const int32_t* __restrict__ chunk0, double* __restrict__ partial) {
-    __shared__ double red[kBT / kWave];
-    int r, li, k0, k1, n0, ln, h0;
-    chunk_range(blockIdx.x, long_rows, chunk_row, chunk0, m, r, li, k0, k1, n0, ln, h0);
-    // the lane's entries k0 + t + u kBT (ascending), all loaded at once: a
-    // net entry or a slot past the chunk reads the row's first hint slot (the
-    // hint array holds one more than its count) and adds nothing
-    constexpr int U = kChunk / kBT;
-    float wv[U];
+                                                      const int32_t* __restrict__ chunk0, int4* __restrict__ chunks,
+                                                      double* __restrict__ partial) {
+    __shared__ double red[2][kBT / kWave];
+    const int4 d = chunk_range(blockIdx.x, long_rows, chunk_row, chunk0, m);
+    if (threadIdx.x == 0) chunks[blockIdx.x] = d;
+    // the lane's hint entries t + u kBT (ascending), all loaded at once: a
+    // net entry or a slot past the chunk reads the chunk's first hint slot
+    // (the hint array holds one more than its count) and adds nothing
+    double sums[2] = {0, 0};
+    in_chunk(d.w, [&](auto n) {
+        constexpr int U = decltype(n)::value;
+        float wv[U];
 #pragma unroll
-    for (int u = 0; u < U; ++u) {
-        const int k = k0 + static_cast<int>(threadIdx.x) + u * kBT;
-        const int kh = k < k1 && k >= ln ? k - ln : 0;
-        wv[u] = bits_f(m.hint_ent[h0 + kh].y);
-    }
-    double a = 0, sg = 0;
-#pragma unroll
-    for (int u = 0; u < U; ++u) {
-        const int k = k0 + static_cast<int>(threadIdx.x) + u * kBT;
-        if (k < k1 && k >= ln) {
-            const double w = static_cast<double>(wv[u]);
-            a += fabs(w);
-            sg += w;
+        for (int u = 0; u < U; ++u) {
+            const int k = static_cast<int>(threadIdx.x) + u * kBT;
+            wv[u] = bits_f(m.hint_ent[d.z + (k < d.w && k >= d.y ? k - d.y : 0)].y);
         }
-    }
-    a = block_sum_f64<kBT>(a, red);
-    sg = block_sum_f64<kBT>(sg, red);
+#pragma unroll
+        for (int u = 0; u < U; ++u) {
+            const int k = static_cast<int>(threadIdx.x) + u * kBT;
+            if (k < d.w && k >= d.y) {
+                const double w = static_cast<double>(wv[u]);
+                sums[0] += fabs(w);
+                sums[1] += w;
+            }
+        }
+    });
+    block_sums_f64<kBT>(sums, red);
     if (threadIdx.x == 0) {
-        partial[static_cast<int64_t>(blockIdx.x) * 8] = a;
-        partial[static_cast<int64_t>(blockIdx.x) * 8 + 1] = sg;
+        partial[static_cast<int64_t>(blockIdx.x) * 8] = sums[0];
+        partial[static_cast<int64_t>(blockIdx.x) * 8 + 1] = sums[1];
     }
 }
 
-__global__ void k_long_deg_final(int32_t n_long, const int32_t* __restrict__ long_rows,
-                                 const int32_t* __restrict__ chunk0, const double* __restrict__ partial,
-                                 const int64_t* __restrict__ qdeg, double sigma, double* __restrict__ deg,
-                                 float* __restrict__ scale, float* __restrict__ hsum) {
-    int i = blockIdx.x * blockDim.x + threadIdx.x;
-    if (i >= n_long) return;
-    int r = long_rows[i];
+// One wave a long row: its chunks' sums are loaded side by side and added in
+// order.
+__global__ void __launch_bounds__(kBT) k_long_deg_final(int32_t n_long, const int32_t* __restrict__ long_rows,
+                                                        const int32_t* __restrict__ chunk0,
+                                                        const double* __restrict__ partial,
+                                                        const int64_t* __restrict__ qdeg, double sigma,
+                                                        double* __restrict__ deg, float* __restrict__ scale,
+                                                        float* __restrict__ hsum) {
+    const int64_t i = (static_cast<int64_t>(blockIdx.x) * kBT + threadIdx.x) / kWave;
+    if (i >= n_long) return;                                   // wave-uniform
+    const int l = lane_id();
     double a = 0, sg = 0;
-    for (int c = chunk0[i]; c < chunk0[i + 1]; ++c) {
-        a += partial[static_cast<int64_t>(c) * 8];
-        sg += partial[static_cast<int64_t>(c) * 8 + 1];
+    const int c1 = chunk0[i + 1];
+    for (int c = chunk0[i]; c < c1; c += kWave) {
+        const int n = c1 - c < kWave ? c1 - c : kWave;
+        const double2 v = *reinterpret_cast<const double2*>(partial + static_cast<int64_t>(c + (l < n ? l : n - 1)) * 8);
+        for (int u = 0; u < n; ++u) {
+            a += __shfl(v.x, u);
+            sg += __shfl(v.y, u);
+        }
     }
+    if (l != 0) return;
+    const int r = long_rows[i];
     double d = static_cast<double>(qdeg[r]) * 0x1p-32 + a + sigma;
     deg[r] = d;
     scale[r] = d > 0 ? static_cast<float>(1.0 / sqrt(d)) : 0.f;
@@ -407,16 +441,13 @@ __global__ void __launch_bounds__(kBT) k_gersh_short(int32_t n, RowRef m, const 
     }
 }
 
-__global__ void __launch_bounds__(kBT) k_chunk_gersh(RowRef m, const int32_t* __restrict__ long_rows,
-                                                     const int32_t* __restrict__ chunk_row,
-                                                     const int32_t* __restrict__ chunk0, const float* __restrict__ scale,
-                                                     double* __restrict__ partial) {
+__global__ void __launch_bounds__(kBT) k_chunk_gersh(RowRef m, const int4* __restrict__ chunks,
+                                                     const float* __restrict__ scale, double* __restrict__ partial) {
     __shared__ double red[kBT / kWave];
-    int r, li, k0, k1, n0, ln, h0;
-    chunk_range(blockIdx.x, long_rows, chunk_row, chunk0, m, r, li, k0, k1, n0, ln, h0);
+    const int4 d = chunks[blockIdx.x];
     double a = 0;
-    for (int k = k0 + threadIdx.x; k < k1; k += kBT) {
-        int2 e = k < ln ? m.net_ent[n0 + k] : m.hint_ent[h0 + k - ln];
+    for (int k = threadIdx.x; k < d.w; k += kBT) {
+        int2 e = k < d.y ? m.net_ent[d.x + k] : m.hint_ent[d.z + k - d.y];
         a += fabs(static_cast<double>(bits_f(e.y))) * static_cast<double>(scale[e.x]);
     }
     a = block_sum_f64<kBT>(a, red);
@@ -686,9 +717,10 @@ struct HopArgs {
     const uint8_t* flags;
     const int32_t* perm;      // execution row -> instance
     int32_t n_rows;           // rows of the short path
-    int32_t n_chunk_blocks;   // chunk workgroups of this hop (placed first)
+    int32_t n_chunks;         // chunks of this hop (their workgroups are placed first)
+    int32_t n_chunks_net;     // of which the first are netlist nodes' rows
     const int32_t* long_rows;
-    const int32_t* chunk_row;
+    const int4* chunks;
     const int32_t* chunk0;
     double* partial;
     const int4* rb;           // row blocks (two int4 each)
@@ -822,23 +854,47 @@ __device__ __forceinline__ void gather_batch(const HopArgs& a, int n0, int ln, i
     }
 }
 
+// The chunks are dealt over the XCDs as the short rows are (xcd_tile): each
+// takes a contiguous eighth of the netlist nodes' chunks, which are in spatial
+// order like the rows whose values they gather, and of the hint nodes', whose
+// windows overlap their neighbours'.
+// At 517k cells and 8 columns a hop reads 3.1M lines of 128 bytes instead of
+// 4.1M.  With this, a chunk's entries found by one load (chunks), as many
+// slots as it has entries (in_chunk) and one pass of sums, a hop takes 92 us
+// for 108 there, 249 for 259 at 2.2M cells and 4 columns, 26 for 28 at 210k.
+__host__ __device__ inline int chunk_blocks(const HopArgs& a) {
+    const int net = a.n_chunks_net < a.n_chunks ? a.n_chunks_net : a.n_chunks;
+    return ((net + kXcds - 1) / kXcds + (a.n_chunks - net + kXcds - 1) / kXcds) * kXcds;
+}
+
+// The chunk of workgroup b, -1 for none.
+__device__ __forceinline__ int dealt_chunk(const HopArgs& a, int b) {
+    const int net = a.n_chunks_net < a.n_chunks ? a.n_chunks_net : a.n_chunks, hint = a.n_chunks - net;
+    const int pn = (net + kXcds - 1) / kXcds, ph = (hint + kXcds - 1) / kXcds;
+    const int x = b % kXcds, i = b / kXcds;
+    if (i < pn) return x * pn + i < net ? x * pn + i : -1;
+    const int c = x * ph + i - pn;
+    return c < hint ? net + c : -1;
+}
+
 // One chunk of a long row: the workgroup's float64 partial sum goes to
 // partial[chunk]; k_hop_long adds a row's partials after the launch ends (no
 // device-scope fence inside the hop: on this chip that is an L2 write-back).
 template <int C, bool NT>
 __device__ __forceinline__ void hop_chunk(const HopArgs& a) {   // a: tile-adjusted
-    __shared__ double red[kBT / kWave];
-    int r, li, k0, k1, n0, ln, h0;
-    chunk_range(blockIdx.x, a.long_rows, a.chunk_row, a.chunk0, a.m, r, li, k0, k1, n0, ln, h0);
-    constexpr int U = kChunk / kBT;
+    __shared__ double red[C][kBT / kWave];
+    const int chunk = dealt_chunk(a, blockIdx.x);
+    if (chunk < 0) return;
+    const int4 d = a.chunks[chunk];
     double acc[C];
 #pragma unroll
     for (int c = 0; c < C; ++c) acc[c] = 0;
-    gather_batch<C, U, double, NT>(a, n0, ln, h0, k1, k0 + threadIdx.x, kBT, acc);
-#pragma unroll
-    for (int c = 0; c < C; ++c) acc[c] = block_sum_f64<kBT>(acc[c], red);
+    in_chunk(d.w, [&](auto u) {
+        gather_batch<C, decltype(u)::value, double, NT>(a, d.x, d.y, d.z, d.w, threadIdx.x, kBT, acc);
+    });
+    block_sums_f64<kBT>(acc, red);
     if (threadIdx.x == 0) {
-        double* part = a.partial + static_cast<int64_t>(blockIdx.x) * 8;
+        double* part = a.partial + static_cast<int64_t>(chunk) * 8;
 #pragma unroll
         for (int c = 0; c < C; ++c) part[c] = acc[c];
     }
@@ -876,12 +932,13 @@ __global__ void __launch_bounds__(kBT) k_hop_long(HopArgs a0, int32_t n_long_row
 template <int C, int G, int U, bool NT>
 __global__ void __launch_bounds__(kBT) k_hop(HopArgs a0) {
     const HopArgs a = tile_args<C>(a0);
-    if (static_cast<int>(blockIdx.x) < a.n_chunk_blocks) {
+    const int ncb = chunk_blocks(a);
+    if (static_cast<int>(blockIdx.x) < ncb) {
         hop_chunk<C, NT>(a);
         return;
     }
-    const int64_t nb = static_cast<int64_t>(gridDim.x) - a.n_chunk_blocks;     // a multiple of kXcds
-    const int64_t tile = xcd_tile(static_cast<int64_t>(blockIdx.x) - a.n_chunk_blocks, nb);
+    const int64_t nb = static_cast<int64_t>(gridDim.x) - ncb;     // a multiple of kXcds
+    const int64_t tile = xcd_tile(static_cast<int64_t>(blockIdx.x) - ncb, nb);
     const int64_t r64 = (tile * kBT + threadIdx.x) / G;
     const int l = static_cast<int>(threadIdx.x & (G - 1));
     if (r64 >= a.n_rows) return;
@@ -995,12 +1052,13 @@ __device__ __forceinline__ void hop_row_block(const HopArgs& a, int blk) {
 template <int C, bool NT>
 __global__ void __launch_bounds__(kBT) k_hop_rb(HopArgs a0) {
     const HopArgs a = tile_args<C>(a0);
-    if (static_cast<int>(blockIdx.x) < a.n_chunk_blocks) {
+    const int ncb = chunk_blocks(a);
+    if (static_cast<int>(blockIdx.x) < ncb) {
         hop_chunk<C, NT>(a);
         return;
     }
-    const int64_t nb = static_cast<int64_t>(gridDim.x) - a.n_chunk_blocks;     // a multiple of kXcds
-    const int64_t blk = xcd_tile(static_cast<int64_t>(blockIdx.x) - a.n_chunk_blocks, nb);
+    const int64_t nb = static_cast<int64_t>(gridDim.x) - ncb;     // a multiple of kXcds
+    const int64_t blk = xcd_tile(static_cast<int64_t>(blockIdx.x) - ncb, nb);
     if (blk >= a.n_rb) return;
     hop_row_block<C, NT>(a, static_cast<int>(blk));
 }
@@ -1054,22 +1112,23 @@ __device__ __forceinline__ void gather_batch_gersh(const HopArgs& a, const float
 // partial[chunk * 8 + c] and of the Gershgorin sum at partial[chunk * 8 + C].
 template <int C>
 __device__ __forceinline__ void hop1_chunk(const HopArgs& a, const float* zpk) {
-    __shared__ double red[kBT / kWave];
-    int r, li, k0, k1, n0, ln, h0;
-    chunk_range(blockIdx.x, a.long_rows, a.chunk_row, a.chunk0, a.m, r, li, k0, k1, n0, ln, h0);
-    constexpr int U = kChunk / kBT;
-    double acc[C];
+    __shared__ double red[C + 1][kBT / kWave];
+    const int chunk = dealt_chunk(a, blockIdx.x);
+    if (chunk < 0) return;
+    const int4 d = a.chunks[chunk];
+    double acc[C + 1];
 #pragma unroll
     for (int c = 0; c < C; ++c) acc[c] = 0;
     double ag = 0;
-    {
+    in_chunk(d.w, [&](auto n) {
+        constexpr int U = decltype(n)::value;
         int2 e[U];
 #pragma unroll
         for (int u = 0; u < U; ++u) {
-            int k = k0 + static_cast<int>(threadIdx.x) + u * kBT;
-            int kc = k < k1 ? k : k1 - 1;
-            e[u] = row_entry<false>(a.m, n0, ln, h0, kc);
-            if (k >= k1) e[u].y = 0;
+            int k = static_cast<int>(threadIdx.x) + u * kBT;
+            int kc = k < d.w ? k : d.w - 1;
+            e[u] = row_entry<false>(a.m, d.x, d.y, d.z, kc);
+            if (k >= d.w) e[u].y = 0;
         }
         Vec<C> v[U];
         float sc[U];
@@ -1082,15 +1141,14 @@ __device__ __forceinline__ void hop1_chunk(const HopArgs& a, const float* zpk) {
             for (int c = 0; c < C; ++c) acc[c] += w * static_cast<double>(v[u].v[c]);
             ag += fabs(w) * static_cast<double>(sc[u]);
         }
-    }
-#pragma unroll
-    for (int c = 0; c < C; ++c) acc[c] = block_sum_f64<kBT>(acc[c], red);
-    ag = block_sum_f64<kBT>(ag, red);
+    });
+    acc[C] = ag;
+    block_sums_f64<kBT>(acc, red);
     if (threadIdx.x == 0) {
-        double* part = a.partial + static_cast<int64_t>(blockIdx.x) * 8;
+        double* part = a.partial + static_cast<int64_t>(chunk) * 8;
 #pragma unroll
         for (int c = 0; c < C; ++c) part[c] = acc[c];
-        part[C] = ag;
+        part[C] = acc[C];
     }
 }
 
@@ -1101,12 +1159,13 @@ template <int C, int G, int U>
 __global__ void __launch_bounds__(kBT) k_hop1_gersh(HopArgs a, const float* __restrict__ zpk,
                                                     const double* __restrict__ deg, double* __restrict__ wgmax) {
     __shared__ double red[kBT / kWave];
-    if (static_cast<int>(blockIdx.x) < a.n_chunk_blocks) {
+    const int ncb = chunk_blocks(a);
+    if (static_cast<int>(blockIdx.x) < ncb) {
         hop1_chunk<C>(a, zpk);
         return;
     }
-    const int64_t nb = static_cast<int64_t>(gridDim.x) - a.n_chunk_blocks;     // a multiple of kXcds
-    const int64_t tile = xcd_tile(static_cast<int64_t>(blockIdx.x) - a.n_chunk_blocks, nb);
+    const int64_t nb = static_cast<int64_t>(gridDim.x) - ncb;     // a multiple of kXcds
+    const int64_t tile = xcd_tile(static_cast<int64_t>(blockIdx.x) - ncb, nb);
     const int64_t r64 = (tile * kBT + threadIdx.x) / G;
     const int l = static_cast<int>(threadIdx.x & (G - 1));
     bool valid = r64 < a.n_rows;
@@ -1270,7 +1329,7 @@ void launch_hop(const HopArgs& a, int32_t n_long_rows, double bytes, int ntiles,
     constexpr int U = 16 / G > 8 ? 8 : (16 / G < 1 ? 1 : 16 / G);   // entries per lane per batch (16 per row, at most 8)
     int64_t tiles = grid_for(static_cast<int64_t>(a.n_rows) * G, kBT);
     tiles = (tiles + kXcds - 1) / kXcds * kXcds;                    // see xcd_tile
-    int64_t blocks = a.n_chunk_blocks + tiles;
+    int64_t blocks = chunk_blocks(a) + tiles;
     const dim3 grid(static_cast<unsigned>(blocks), static_cast<unsigned>(ntiles));
     hipEvent_t e0, e1;
     if (prof_kernel_events(kStageHop, &e0, &e1)) {
@@ -1299,7 +1358,7 @@ template <int C>
 void launch_hop_rb(const HopArgs& a, int32_t n_long_rows, double bytes, int ntiles, hipStream_t s) {
     int64_t tiles = (static_cast<int64_t>(a.n_rb) + kXcds - 1) / kXcds * kXcds;   // see xcd_tile
     if (tiles < kXcds) tiles = kXcds;
-    const dim3 grid(static_cast<unsigned>(a.n_chunk_blocks + tiles), static_cast<unsigned>(ntiles));
+    const dim3 grid(static_cast<unsigned>(chunk_blocks(a) + tiles), static_cast<unsigned>(ntiles));
     hipEvent_t e0, e1;
     if (prof_kernel_events(kStageHop, &e0, &e1)) {
         if (g_hop_nt)
@@ -1371,7 +1430,7 @@ ChainView chain_view(Graph& g, const ahr_filter_spec& spec, hipStream_t s) {
     v.flags = g.nl.node_flags;
     v.perm = g.perm.p;
     v.long_rows = g.rc.long_rows.p;
-    v.chunk_row = g.rc.chunk_row.p;
+    v.chunks = g.rc.chunks.p;
     v.chunk0 = g.rc.long_chunk0.p;
     v.partial = g.rc.partial.p;
     v.rb = g.rc.rb.p;
@@ -1381,6 +1440,7 @@ ChainView chain_view(Graph& g, const ahr_filter_spec& spec, hipStream_t s) {
     v.n_long_inst = g.rc.n_long_inst;
     v.n_chunks = g.rc.n_chunks;
     v.n_chunks_inst = g.rc.n_chunks_inst;
+    v.n_chunks_net = g.rc.n_chunks_net;
     v.n_rb = g.rc.n_rb;
     v.n_rb_inst = g.rc.n_rb_inst;
     v.nnz_inst = g.rc.nnz_inst;
@@ -1404,7 +1464,7 @@ HopArgs hop_args(const ChainView& v, const float* in, float* out, int ncols) {
     h.out = out;
     h.flags = v.flags;
     h.long_rows = v.long_rows;
-    h.chunk_row = v.chunk_row;
+    h.chunks = v.chunks;
     h.chunk0 = v.chunk0;
     h.partial = v.partial;
     h.rb = v.rb;
@@ -1416,7 +1476,8 @@ HopArgs hop_args(const ChainView& v, const float* in, float* out, int ncols) {
     h.zin = nullptr;
     h.zout = nullptr;
     h.n_rows = 0;
-    h.n_chunk_blocks = 0;
+    h.n_chunks = 0;
+    h.n_chunks_net = v.n_chunks_net;
     h.tile_stride = 0;
     h.ldo = ncols;
     h.col0 = 0;
@@ -1452,7 +1513,7 @@ void hops_c(Graph& g, const ahr_filter_spec& spec, const float* in, int lanes, h
         h.zout = g.zh[j].p;
         const bool inst_only = j == 2;
         h.n_rows = inst_only ? v.n_inst : v.n_tot;
-        h.n_chunk_blocks = inst_only ? v.n_chunks_inst : v.n_chunks;
+        h.n_chunks = inst_only ? v.n_chunks_inst : v.n_chunks;
         h.n_rb = inst_only ? v.n_rb_inst : v.n_rb;
         hop_dispatch<C>(h, lanes, inst_only ? v.n_long_inst : v.n_long, hop_bytes(v, h, C), 1, s);
         zin = g.zh[j].p;
@@ -1486,7 +1547,7 @@ void hop1_gersh(const ChainView& v, HopArgs h, const Hop1Gersh& f, hipStream_t s
     constexpr int G = 4, U = 4;
     int64_t tiles = grid_for(static_cast<int64_t>(h.n_rows) * G, kBT);
     tiles = (tiles + kXcds - 1) / kXcds * kXcds;                    // see xcd_tile
-    hipLaunchKernelGGL((k_hop1_gersh<C, G, U>), dim3(static_cast<unsigned>(h.n_chunk_blocks + tiles)), dim3(kBT), 0,
+    hipLaunchKernelGGL((k_hop1_gersh<C, G, U>), dim3(static_cast<unsigned>(chunk_blocks(h) + tiles)), dim3(kBT), 0,
                        s, h, f.zpk, f.deg, f.gmax);
     AHR_LAUNCHED("k_hop1_gersh");
     if (v.n_long > 0) {
@@ -1528,7 +1589,7 @@ void chain_c(const ChainView& v, const ahr_filter_spec& spec, const float* in, f
         h.band = isb ? (has_acc ? 2 : 1) : 0;
         h.alpha = aj;
         h.n_rows = h.last ? v.n_inst : v.n_tot;
-        h.n_chunk_blocks = h.last ? v.n_chunks_inst : v.n_chunks;
+        h.n_chunks = h.last ? v.n_chunks_inst : v.n_chunks;
         h.n_rb = h.last ? v.n_rb_inst : v.n_rb;
         if (f && j == 1) {
             if constexpr (CT == C && C <= 4) {
@@ -1621,27 +1682,29 @@ void expand_batch_c(const ExpandArgs* d, const int32_t* blk0, int32_t n_blocks, 
 // one more device word read with them (to *extra_out).  The lists are sized by
 // the bound on the entries: a long row has more than kLongRow of them.
 static void row_classes_begin(const int32_t* net_rp, const int32_t* hint_rp, int32_t N, int32_t n_inst,
-                              int64_t max_entries, RowClasses& rc, DevBuf<int64_t>& scan_tmp, hipStream_t s,
+                              int32_t first_hint, int64_t max_entries, RowClasses& rc, DevBuf<int64_t>& scan_tmp, hipStream_t s,
                               const int32_t* extra = nullptr) {
     const int64_t max_long = std::min<int64_t>(N, max_entries / kLongRow);
     rc.long_rows.ensure(static_cast<size_t>(max_long) + 1, s);
     rc.long_chunk0.ensure(static_cast<size_t>(max_long) + 1, s);
     rc.chunk_row.ensure(static_cast<size_t>(max_long + max_entries / kChunk) + 1, s);
-    rc.counts.ensure(4, s);
-    run_scans(scan_job(LongRowScan{net_rp, hint_rp, n_inst, rc.long_rows.p, rc.long_chunk0.p, rc.chunk_row.p,
+    rc.counts.ensure(5, s);
+    run_scans(scan_job(LongRowScan{net_rp, hint_rp, n_inst, first_hint, rc.long_rows.p, rc.long_chunk0.p, rc.chunk_row.p,
                                    rc.counts.p},
                        N),
               scan_tmp, s);
     std::vector<const int32_t*> words{rc.counts.p,     rc.counts.p + 1,  rc.counts.p + 2, rc.counts.p + 3,
-                                      net_rp + n_inst, hint_rp + n_inst, net_rp + N,      hint_rp + N};
+                                      net_rp + n_inst, hint_rp + n_inst, net_rp + N,      hint_rp + N,
+                                      rc.counts.p + 4};
     if (extra) words.push_back(extra);
     read_scalars_begin(words, s);
 }
 
-static void row_classes_end(int32_t N, int32_t n_inst, RowClasses& rc, hipStream_t s, int32_t* extra_out = nullptr) {
-    int32_t v[9];
-    read_scalars_end(v, extra_out ? 9 : 8);
-    if (extra_out) *extra_out = v[8];
+static void row_classes_end(int32_t N, int32_t n_inst, int32_t first_hint, RowClasses& rc, hipStream_t s,
+                            int32_t* extra_out = nullptr) {
+    int32_t v[10];
+    read_scalars_end(v, extra_out ? 10 : 9);
+    if (extra_out) *extra_out = v[9];
     rc.nnz_net_all = v[6];
     rc.nnz_hint_all = v[7];
     rc.n_long = v[0];
@@ -1649,15 +1712,22 @@ static void row_classes_end(int32_t N, int32_t n_inst, RowClasses& rc, hipStream
     // (no row n_inst: every row is an instance's)
     rc.n_long_inst = n_inst < N ? v[1] : v[0];
     rc.n_chunks_inst = n_inst < N ? v[3] : v[2];
+    rc.n_chunks_net = first_hint < N ? v[8] : v[2];
     rc.nnz_inst = static_cast<int64_t>(v[4]) + v[5];
     rc.has_rb = 0;
     rc.partial.ensure(static_cast<size_t>(rc.n_chunks) * 8 + 8, s);
+    rc.chunks.ensure(static_cast<size_t>(rc.n_chunks) + 1, s);
 }
 
-void row_classes(const int32_t* net_rp, const int32_t* hint_rp, int32_t N, int32_t n_inst, int64_t max_entries,
-                 RowClasses& rc, DevBuf<int64_t>& scan_tmp, hipStream_t s) {
-    row_classes_begin(net_rp, hint_rp, N, n_inst, max_entries, rc, scan_tmp, s);
-    row_classes_end(N, n_inst, rc, s);
+void row_classes(const int32_t* net_rp, const int32_t* hint_rp, int32_t N, int32_t n_inst, int32_t first_hint,
+                 int64_t max_entries, RowClasses& rc, DevBuf<int64_t>& scan_tmp, hipStream_t s) {
+    row_classes_begin(net_rp, hint_rp, N, n_inst, first_hint, max_entries, rc, scan_tmp, s);
+    row_classes_end(N, n_inst, first_hint, rc, s);
+    if (!rc.n_chunks) return;
+    hipLaunchKernelGGL(k_chunk_ranges, dim3(grid_for(rc.n_chunks, kBT)), dim3(kBT), 0, s,
+                       RowRef{net_rp, nullptr, hint_rp, nullptr}, rc.n_chunks, rc.long_rows.p, rc.chunk_row.p,
+                       rc.long_chunk0.p, rc.chunks.p);
+    AHR_LAUNCHED("k_chunk_ranges");
 }
 
 void row_blocks(const int32_t* net_rp, const int32_t* hint_rp, int32_t N, int32_t n_inst, RowClasses& rc,
@@ -1668,7 +1738,7 @@ void row_blocks(const int32_t* net_rp, const int32_t* hint_rp, int32_t N, int32_
     const int64_t bound = 2 + rc.n_long + static_cast<int64_t>(N) / kRbRows +
                           (rc.nnz_net_all + rc.nnz_hint_all) / kRbEntries;
     rc.rb.ensure(2 * static_cast<size_t>(bound) + 2, s);
-    rc.counts.ensure(4, s);
+    rc.counts.ensure(5, s);
     run_scans(scan_job(RowBlockScan{N, n_inst, net_rp, hint_rp, rc.rb.p, rc.counts.p}, N), scan_tmp, s);
     int32_t t[2];
     read_scalars({rc.counts.p, rc.counts.p + 1}, t, s);
@@ -1782,7 +1852,7 @@ void normalise_degrees(Graph& g, const ahr_filter_spec& spec, hipStream_t s) {
     // the layout's locality verdict rides along with the first counts
     const bool want_loc = new_rows && g.hop_local < 0 && g.loc_flag.p;
     if (new_rows)
-        row_classes_begin(g.xnet_rp.p, g.xhint_rp.p, N, g.n_inst,
+        row_classes_begin(g.xnet_rp.p, g.xhint_rp.p, N, g.n_inst, g.first_mvirt,
                           static_cast<int64_t>(g.nnz_cap) + static_cast<int64_t>(g.xhint_ent.n), g.rc, g.scan_tmp, s,
                           want_loc ? g.loc_flag.p : nullptr);
 
@@ -1806,7 +1876,7 @@ void normalise_degrees(Graph& g, const ahr_filter_spec& spec, hipStream_t s) {
     }
     if (new_rows) {
         int32_t loc = 1;
-        row_classes_end(N, g.n_inst, g.rc, s, want_loc ? &loc : nullptr);
+        row_classes_end(N, g.n_inst, g.first_mvirt, g.rc, s, want_loc ? &loc : nullptr);
         if (want_loc) g.hop_local = loc ? 1 : 0;
         g.rows_version = g.hint_version;
         g.nnz_net = static_cast<int32_t>(g.rc.nnz_net_all);
@@ -1814,9 +1884,9 @@ void normalise_degrees(Graph& g, const ahr_filter_spec& spec, hipStream_t s) {
     }
     if (g.rc.n_long) {
         hipLaunchKernelGGL(k_chunk_absdeg, dim3(g.rc.n_chunks), dim3(kBT), 0, s, m, g.rc.long_rows.p, g.rc.chunk_row.p,
-                           g.rc.long_chunk0.p, g.rc.partial.p);
+                           g.rc.long_chunk0.p, g.rc.chunks.p, g.rc.partial.p);
         AHR_LAUNCHED("k_chunk_absdeg");
-        hipLaunchKernelGGL(k_long_deg_final, dim3(grid_for(g.rc.n_long, kBT)), dim3(kBT), 0, s, g.rc.n_long, g.rc.long_rows.p,
+        hipLaunchKernelGGL(k_long_deg_final, dim3(grid_for(static_cast<int64_t>(g.rc.n_long) * kWave, kBT)), dim3(kBT), 0, s, g.rc.n_long, g.rc.long_rows.p,
                            g.rc.long_chunk0.p, g.rc.partial.p, g.xqdeg.p, sigma, g.deg.p, g.scale.p, g.hsum.p);
         AHR_LAUNCHED("k_long_deg_final");
     }
@@ -1842,8 +1912,8 @@ void normalise(Graph& g, const ahr_filter_spec& spec, hipStream_t s) {
                            g.deg.p, g.scale.p, sigma, g.lam.p);
         AHR_LAUNCHED("k_gersh_short");
         if (g.rc.n_long) {
-            hipLaunchKernelGGL(k_chunk_gersh, dim3(g.rc.n_chunks), dim3(kBT), 0, s, m, g.rc.long_rows.p, g.rc.chunk_row.p,
-                               g.rc.long_chunk0.p, g.scale.p, g.rc.partial.p);
+            hipLaunchKernelGGL(k_chunk_gersh, dim3(g.rc.n_chunks), dim3(kBT), 0, s, m, g.rc.chunks.p, g.scale.p,
+                               g.rc.partial.p);
             AHR_LAUNCHED("k_chunk_gersh");
             hipLaunchKernelGGL(k_long_gersh_final, dim3(grid_for(g.rc.n_long, kBT)), dim3(kBT), 0, s, g.rc.n_long,
                                g.rc.long_rows.p, g.rc.long_chunk0.p, g.rc.partial.p, g.deg.p, g.scale.p, sigma, g.lam.p);

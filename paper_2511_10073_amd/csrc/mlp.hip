@@ -368,23 +368,6 @@ struct alignas(C * sizeof(float) < 16 ? C * sizeof(float) : 16) ZRow {
     float v[C];
 };
 
-// Fixed-order block sums of W doubles a thread, in one pass of the barriers.
-template <int W>
-__device__ __forceinline__ void block_sums(double (&v)[W], double (*red)[kBT / kWave]) {
-#pragma unroll
-    for (int c = 0; c < W; ++c) {
-        const double t = wave_sum(v[c]);
-        if (lane_id() == 0) red[c][wave_id()] = t;
-    }
-    __syncthreads();
-#pragma unroll
-    for (int c = 0; c < W; ++c) {
-        v[c] = 0;
-#pragma unroll
-        for (int w = 0; w < kBT / kWave; ++w) v[c] += red[c][w];
-    }
-}
-
 // The same pass forms the rows' inputs of the features (rowf).  The loads of
 // kStatRows rows a thread are in flight together: 880k cells x 4 columns take
 // 22 us, against 13 us for a kernel of rowf alone and 23 us for the sums with
@@ -446,7 +429,7 @@ __global__ void __launch_bounds__(kBT) k_colstat(LearnArgs a, double* __restrict
             acc[3 * C] += 1.0;
         }
     }
-    block_sums<W>(acc, red);
+    block_sums_f64<kBT>(acc, red);
     if (threadIdx.x == 0) {
 #pragma unroll
         for (int c = 0; c < W; ++c) part[static_cast<int64_t>(blockIdx.x) * W + c] = acc[c];
@@ -467,7 +450,7 @@ __global__ void __launch_bounds__(kBT) k_colstat_final(LearnArgs a, const double
     for (int b = threadIdx.x; b < kStatGrid; b += kBT)
 #pragma unroll
         for (int c = 0; c < W; ++c) tot[c] += part[static_cast<int64_t>(b) * W + c];
-    block_sums<W>(tot, red);
+    block_sums_f64<kBT>(tot, red);
     if (threadIdx.x != 0) return;
     const double n = tot[3 * C];
     const float inv_s0 = a.n_inst > 0 ? a.rowf[0].x : 0.f;

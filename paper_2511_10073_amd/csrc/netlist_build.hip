@@ -378,35 +378,6 @@ __device__ __forceinline__ void sort_trivial(const SortArgs& a, const int32_t* r
     row_done(a, r, c, q);
 }
 
-// Lane exchanges without the LDS crossbar (every lane of the wave active).
-template <int Ctrl>
-__device__ __forceinline__ int dpp(int x) {
-    return __builtin_amdgcn_mov_dpp(x, Ctrl, 0xf, 0xf, true);
-}
-constexpr int kDppPrev = 0x138, kDppNext = 0x130;       // the lane below / above, across the wave (zeros at its ends)
-
-// The values of lanes l and l ^ J as a pair of which one is the caller's own
-// (which one is unspecified: for operations that commute).
-template <int J>
-__device__ __forceinline__ void lane_pair(int x, int& a, int& b) {
-    a = x;
-    if constexpr (J == 1) {
-        b = dpp<0xb1>(x);                               // quad [1, 0, 3, 2]
-    } else if constexpr (J == 2) {
-        b = dpp<0x4e>(x);                               // quad [2, 3, 0, 1]
-    } else if constexpr (J == 4) {
-        b = dpp<0x1b>(dpp<0x141>(x));                   // mirrored in 8, then in 4
-    } else if constexpr (J == 8) {
-        b = dpp<0x128>(x);                              // rotated by 8 in 16
-    } else {
-        static_assert(J == 16 || J == 32, "lane distance");
-        const auto r = J == 16 ? __builtin_amdgcn_permlane16_swap(x, x, false, false)
-                               : __builtin_amdgcn_permlane32_swap(x, x, false, false);
-        a = static_cast<int>(r[0]);
-        b = static_cast<int>(r[1]);
-    }
-}
-
 // The lanes that keep the smaller key in step (K, J) of the bitonic network
 // over groups of G lanes.
 template <int G>
@@ -428,18 +399,6 @@ __device__ __forceinline__ int bitonic_steps(int x) {
     if constexpr (J > 1) return bitonic_steps<G, K, J / 2>(x);
     else if constexpr (K < G) return bitonic_steps<G, 2 * K, K>(x);
     else return x;
-}
-
-// Sum over the lane's group of G (the lanes of a group end with the same).
-template <int J>
-__device__ __forceinline__ int64_t pair_sum(int64_t v) {
-    int a0, b0, a1, b1;
-    lane_pair<J>(static_cast<int>(v), a0, b0);
-    lane_pair<J>(static_cast<int>(v >> 32), a1, b1);
-    const auto join = [](int lo, int hi) {
-        return static_cast<int64_t>(static_cast<uint64_t>(static_cast<uint32_t>(hi)) << 32 | static_cast<uint32_t>(lo));
-    };
-    return join(a0, a1) + join(b0, b1);
 }
 
 // G lanes per row (G = 8, 16, 32 or 64): bitonic sort by column across the
