@@ -169,6 +169,7 @@ class ProfScope {
 // LDS-staged hop.
 constexpr int kLongRow = 128;
 constexpr int kChunk = 2048;
+constexpr int kWholeChunks = 8;      // the most chunks of a row that one workgroup finishes
 constexpr int kRbRows = 256;
 constexpr int kRbEntries = 1024;
 // Star nodes are averaged over their pins by their row's thread up to
@@ -182,13 +183,14 @@ struct RowClasses {
     DevBuf<int32_t> long_rows;    // rows split over chunks, ascending
     DevBuf<int32_t> long_chunk0;  // [n_long+1] first chunk of each long row
     DevBuf<int32_t> chunk_row;    // [n_chunks] long-row index of each chunk
-    DevBuf<int4> chunks;          // [n_chunks] first netlist entry, netlist entries, first hint entry, entries
+    DevBuf<int4> chunks;          // [n_chunks] the entries of each chunk (Chunk in filter.hip)
     DevBuf<double> partial;       // [n_chunks * 8]
     DevBuf<int4> rb;              // [2 n_rb] row blocks: (r0, r1, net_lo, net_hi), (hint_lo, hint_hi, -, -)
     DevBuf<int32_t> counts;       // counts of the scans that make them
     int32_t n_long = 0, n_long_inst = 0;      // long rows, those below n_inst
     int32_t n_chunks = 0, n_chunks_inst = 0;  // chunks, those of long rows below n_inst
     int32_t n_chunks_net = 0;                 // those of long rows below the hint nodes
+    int32_t in_parts = 0;                     // chunks summed apart: a row has more than kWholeChunks
     int32_t n_rb = 0, n_rb_inst = 0;          // row blocks, those below n_inst
     int32_t has_rb = 0;                       // row blocks built (on first use of the row-block hop)
     int64_t nnz_inst = 0;                     // entries of rows below n_inst (netlist + hints)
@@ -486,7 +488,7 @@ struct ChainView {
     const int32_t* chunk0;
     double* partial;
     const int4* rb;
-    int32_t n_tot, n_inst, n_long, n_long_inst, n_chunks, n_chunks_inst, n_chunks_net, n_rb, n_rb_inst;
+    int32_t n_tot, n_inst, n_long, n_long_inst, in_parts, n_chunks, n_chunks_inst, n_chunks_net, n_rb, n_rb_inst;
     int64_t nnz_inst, nnz_all;
     float* z0;
     float* z1;

@@ -184,6 +184,7 @@ ChainView batch_view(Batch& b, const ahr_filter_spec& spec) {
     v.n_inst = b.n_inst;
     v.n_long = b.rc.n_long;
     v.n_long_inst = b.rc.n_long_inst;
+    v.in_parts = b.rc.in_parts;
     v.n_chunks = b.rc.n_chunks;
     v.n_chunks_inst = b.rc.n_chunks_inst;
     v.n_chunks_net = b.rc.n_chunks_net;

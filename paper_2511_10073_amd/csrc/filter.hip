@@ -115,12 +115,16 @@ struct LongRowScan {
     int32_t* long_rows;
     int32_t* chunk0;
     int32_t* chunk_row;
-    int32_t* counts;       // long rows, those below n_inst, chunks, those below n_inst and below first_hint
+    int32_t* counts;       // long rows, those below n_inst, chunks, those below n_inst and below first_hint; and
+                           // whether a row has more than kWholeChunks
     __device__ Pack<1> first(int64_t r) const {
+        if (r == 0) counts[5] = 0;                  // before any item()
+        return again(r);
+    }
+    __device__ Pack<1> again(int64_t r) const {
         const int len = (net_rp[r + 1] - net_rp[r]) + (hint_rp[r + 1] - hint_rp[r]);
         return {{len > kLongRow ? pack2(1, (len + kChunk - 1) / kChunk) : 0}};
     }
-    __device__ Pack<1> again(int64_t r) const { return first(r); }
     __device__ void item(int64_t r, const Pack<1>& own, const Pack<1>& before, const Pack<1>&) const {
         const int32_t k = pack_lo(before.v[0]), c0 = pack_hi(before.v[0]), nc = pack_hi(own.v[0]);
         if (r == n_inst) {
@@ -129,6 +133,7 @@ struct LongRowScan {
         }
         if (r == first_hint) counts[4] = c0;
         if (!nc) return;
+        if (nc > kWholeChunks) counts[5] = 1;
         long_rows[k] = static_cast<int32_t>(r);
         chunk0[k] = c0;
         for (int c = 0; c < nc; ++c) chunk_row[c0 + c] = k;
@@ -290,22 +295,45 @@ __device__ __forceinline__ void in_chunk(int n, const F& f) {
     else f(std::integral_constant<int, 8>());
 }
 
-// The entries of chunk c (RowClasses::chunks).
-__device__ __forceinline__ int4 chunk_range(int c, const int32_t* long_rows, const int32_t* chunk_row,
-                                            const int32_t* chunk0, const RowRef& m) {
+// A chunk: `net` netlist entries from nb, then hint entries from hb, n in all,
+// of long row li.  take: the chunks that its workgroup sums, this and the
+// following ones: all of a row for its first, 0 for its others (whose
+// workgroups have nothing to do); or kApart, where every chunk is summed by a
+// workgroup of its own and the rows are added up by a launch of their own.
+// Whole rows save that launch (5 us a hop) where no row has more than
+// kWholeChunks chunks, 27.8 us for 26.1 + 4.8 a hop at 210k cells; taken
+// together with longer rows in parts they only lengthened the hop (2.2M cells:
+// 258 us for 249, 880k: 114 for 106).
+struct Chunk {
+    int nb, net, hb, n, li, take;
+};
+constexpr int kApart = kWholeChunks + 1;
+static_assert(kChunk < 1 << 12 && kApart < 1 << 7, "packing of a chunk");
+
+__device__ __forceinline__ int4 pack_chunk(const Chunk& c) {
+    return make_int4(c.nb, c.net | c.n << 12 | c.take << 24, c.hb, c.li);
+}
+
+__device__ __forceinline__ Chunk unpack_chunk(int4 w) {
+    return {w.x, w.y & 0xfff, w.z, w.y >> 12 & 0xfff, w.w, w.y >> 24};
+}
+
+__device__ __forceinline__ Chunk chunk_range(int c, const int32_t* long_rows, const int32_t* chunk_row,
+                                             const int32_t* chunk0, const int32_t* counts, const RowRef& m) {
     const int li = chunk_row[c], r = long_rows[li];
     const int n0 = m.net_rp[r], ln = m.net_rp[r + 1] - n0, h0 = m.hint_rp[r], len = ln + (m.hint_rp[r + 1] - h0);
     const int at = (c - chunk0[li]) * kChunk, n = at + kChunk < len ? kChunk : len - at;
     const int net = at >= ln ? 0 : at + n < ln ? n : ln - at;
-    return make_int4(n0 + (at < ln ? at : ln), net, h0 + (at > ln ? at - ln : 0), n);
+    const int take = counts[5] ? kApart : at ? 0 : (len + kChunk - 1) / kChunk;
+    return {n0 + (at < ln ? at : ln), net, h0 + (at > ln ? at - ln : 0), n, li, take};
 }
 
 // The chunks' entries where no degrees are formed (k_chunk_absdeg).
 __global__ void k_chunk_ranges(RowRef m, int32_t n_chunks, const int32_t* __restrict__ long_rows,
                                const int32_t* __restrict__ chunk_row, const int32_t* __restrict__ chunk0,
-                               int4* __restrict__ chunks) {
+                               const int32_t* __restrict__ counts, int4* __restrict__ chunks) {
     const int64_t c = static_cast<int64_t>(blockIdx.x) * blockDim.x + threadIdx.x;
-    if (c < n_chunks) chunks[c] = chunk_range(static_cast<int>(c), long_rows, chunk_row, chunk0, m);
+    if (c < n_chunks) chunks[c] = pack_chunk(chunk_range(static_cast<int>(c), long_rows, chunk_row, chunk0, counts, m));
 }
 
 // One workgroup a chunk: its entries' range, which every later kernel takes
@@ -313,27 +341,28 @@ __global__ void k_chunk_ranges(RowRef m, int32_t n_chunks, const int32_t* __rest
 // after another), and the sums of its hint entries.
 __global__ void __launch_bounds__(kBT) k_chunk_absdeg(RowRef m, const int32_t* __restrict__ long_rows,
                                                       const int32_t* __restrict__ chunk_row,
-                                                      const int32_t* __restrict__ chunk0, int4* __restrict__ chunks,
+                                                      const int32_t* __restrict__ chunk0,
+                                                      const int32_t* __restrict__ counts, int4* __restrict__ chunks,
                                                       double* __restrict__ partial) {
     __shared__ double red[2][kBT / kWave];
-    const int4 d = chunk_range(blockIdx.x, long_rows, chunk_row, chunk0, m);
-    if (threadIdx.x == 0) chunks[blockIdx.x] = d;
+    const Chunk d = chunk_range(blockIdx.x, long_rows, chunk_row, chunk0, counts, m);
+    if (threadIdx.x == 0) chunks[blockIdx.x] = pack_chunk(d);
     // the lane's hint entries t + u kBT (ascending), all loaded at once: a
     // net entry or a slot past the chunk reads the chunk's first hint slot
     // (the hint array holds one more than its count) and adds nothing
     double sums[2] = {0, 0};
-    in_chunk(d.w, [&](auto n) {
+    in_chunk(d.n, [&](auto n) {
         constexpr int U = decltype(n)::value;
         float wv[U];
 #pragma unroll
         for (int u = 0; u < U; ++u) {
             const int k = static_cast<int>(threadIdx.x) + u * kBT;
-            wv[u] = bits_f(m.hint_ent[d.z + (k < d.w && k >= d.y ? k - d.y : 0)].y);
+            wv[u] = bits_f(m.hint_ent[d.hb + (k < d.n && k >= d.net ? k - d.net : 0)].y);
         }
 #pragma unroll
         for (int u = 0; u < U; ++u) {
             const int k = static_cast<int>(threadIdx.x) + u * kBT;
-            if (k < d.w && k >= d.y) {
+            if (k < d.n && k >= d.net) {
                 const double w = static_cast<double>(wv[u]);
                 sums[0] += fabs(w);
                 sums[1] += w;
@@ -444,10 +473,10 @@ __global__ void __launch_bounds__(kBT) k_gersh_short(int32_t n, RowRef m, const 
 __global__ void __launch_bounds__(kBT) k_chunk_gersh(RowRef m, const int4* __restrict__ chunks,
                                                      const float* __restrict__ scale, double* __restrict__ partial) {
     __shared__ double red[kBT / kWave];
-    const int4 d = chunks[blockIdx.x];
+    const Chunk d = unpack_chunk(chunks[blockIdx.x]);
     double a = 0;
-    for (int k = threadIdx.x; k < d.w; k += kBT) {
-        int2 e = k < d.y ? m.net_ent[d.x + k] : m.hint_ent[d.z + k - d.y];
+    for (int k = threadIdx.x; k < d.n; k += kBT) {
+        int2 e = k < d.net ? m.net_ent[d.nb + k] : m.hint_ent[d.hb + k - d.net];
         a += fabs(static_cast<double>(bits_f(e.y))) * static_cast<double>(scale[e.x]);
     }
     a = block_sum_f64<kBT>(a, red);
@@ -877,30 +906,99 @@ __device__ __forceinline__ int dealt_chunk(const HopArgs& a, int b) {
     return c < hint ? net + c : -1;
 }
 
-// One chunk of a long row: the workgroup's float64 partial sum goes to
-// partial[chunk]; k_hop_long adds a row's partials after the launch ends (no
-// device-scope fence inside the hop: on this chip that is an L2 write-back).
-template <int C, bool NT>
+// A workgroup's chunks of a long row, one after another: value(chunk, acc)
+// adds the chunk's entries to the lane's W sums.  Each wave leaves its sums of
+// every chunk in LDS, and the waves meet once.  Lane c of the first wave then
+// holds sum c of the row in tot, added in the order of k_hop_long (a wave with
+// a chunk a lane, in halves) and, with Last, the last of the W sums in chunk
+// order (k_hop1_long).  d is the first chunk; false where the workgroup has
+// none to take.
+template <int W, bool Last, class F>
+__device__ __forceinline__ bool chunk_sums(const HopArgs& a, int chunk, Chunk& d, double& tot, const F& value) {
+    __shared__ double red[kWholeChunks][W][kBT / kWave];
+    d = unpack_chunk(a.chunks[chunk]);
+    if (d.take == 0) return false;
+    const int take = d.take;
+    Chunk at = d;
+    for (int q = 0; q < take; ++q) {
+        const Chunk next = unpack_chunk(a.chunks[q + 1 < take ? chunk + q + 1 : chunk]);
+        double acc[W];
+#pragma unroll
+        for (int c = 0; c < W; ++c) acc[c] = 0;
+        value(at, acc);
+#pragma unroll
+        for (int c = 0; c < W; ++c) {
+            const double t = wave_sum(acc[c]);
+            if (lane_id() == 0) red[q][c][wave_id()] = t;
+        }
+        at = next;
+    }
+    __syncthreads();
+    if (wave_id() != 0) return true;
+    const int c = lane_id() < W ? lane_id() : 0;
+    double s[kWholeChunks];
+#pragma unroll
+    for (int q = 0; q < kWholeChunks; ++q) {
+        s[q] = 0;
+        if (q < take) {
+#pragma unroll
+            for (int w = 0; w < kBT / kWave; ++w) s[q] += red[q][c][w];
+        }
+    }
+    if (Last && c == W - 1) {
+        tot = 0;
+#pragma unroll
+        for (int q = 0; q < kWholeChunks; ++q)
+            if (q < take) tot += s[q];
+        return true;
+    }
+#pragma unroll
+    for (int o = kWholeChunks / 2; o > 0; o >>= 1)
+#pragma unroll
+        for (int q = 0; q < o; ++q) s[q] += s[q + o];
+    tot = s[0];
+    return true;
+}
+
+// Chunks of a long row.  Whole: the row is finished here.  Otherwise the
+// chunk's float64 sums go to partial[chunk], and k_hop_long adds a row's
+// partials after the launch ends (no device-scope fence inside the hop: on
+// this chip that is an L2 write-back).
+template <int C, bool NT, bool Whole>
 __device__ __forceinline__ void hop_chunk(const HopArgs& a) {   // a: tile-adjusted
-    __shared__ double red[C][kBT / kWave];
     const int chunk = dealt_chunk(a, blockIdx.x);
     if (chunk < 0) return;
-    const int4 d = a.chunks[chunk];
-    double acc[C];
+    const auto add = [&](const Chunk& k, double (&acc)[C]) {
+        in_chunk(k.n, [&](auto u) {
+            gather_batch<C, decltype(u)::value, double, NT>(a, k.nb, k.net, k.hb, k.n, threadIdx.x, kBT, acc);
+        });
+    };
+    if constexpr (Whole) {
+        Chunk d;
+        double tot;
+        if (!chunk_sums<C, false>(a, chunk, d, tot, add) || wave_id() != 0) return;
+        Vec<C> sum;
 #pragma unroll
-    for (int c = 0; c < C; ++c) acc[c] = 0;
-    in_chunk(d.w, [&](auto u) {
-        gather_batch<C, decltype(u)::value, double, NT>(a, d.x, d.y, d.z, d.w, threadIdx.x, kBT, acc);
-    });
-    block_sums_f64<kBT>(acc, red);
-    if (threadIdx.x == 0) {
-        double* part = a.partial + static_cast<int64_t>(chunk) * 8;
+        for (int c = 0; c < C; ++c) sum.v[c] = static_cast<float>(__shfl(tot, c));
+        if (lane_id() != 0) return;
+        const int r = a.long_rows[d.li];
+        epilogue<C>(a, r, row_ops<C>(a, r), sum);
+    } else {
+        __shared__ double red[C][kBT / kWave];
+        double acc[C];
 #pragma unroll
-        for (int c = 0; c < C; ++c) part[c] = acc[c];
+        for (int c = 0; c < C; ++c) acc[c] = 0;
+        add(unpack_chunk(a.chunks[chunk]), acc);
+        block_sums_f64<kBT>(acc, red);
+        if (threadIdx.x == 0) {
+            double* part = a.partial + static_cast<int64_t>(chunk) * 8;
+#pragma unroll
+            for (int c = 0; c < C; ++c) part[c] = acc[c];
+        }
     }
 }
 
-// Long rows after a hop: one wave per row adds its chunk partials (fixed
+// Long rows in parts, after a hop: one wave per row adds its chunk partials (fixed
 // order: lanes stride the chunks, then a fixed butterfly) and applies the
 // row epilogue.
 template <int C>
@@ -929,12 +1027,12 @@ __global__ void __launch_bounds__(kBT) k_hop_long(HopArgs a0, int32_t n_long_row
     epilogue<C>(a, r, ops, sum);
 }
 
-template <int C, int G, int U, bool NT>
-__global__ void __launch_bounds__(kBT) k_hop(HopArgs a0) {
+template <int C, int G, int U, bool NT, bool Whole>
+__global__ void __launch_bounds__(kBT, Whole && C <= 4 && U <= 4 ? 7 : 1) k_hop(HopArgs a0) {
     const HopArgs a = tile_args<C>(a0);
     const int ncb = chunk_blocks(a);
     if (static_cast<int>(blockIdx.x) < ncb) {
-        hop_chunk<C, NT>(a);
+        hop_chunk<C, NT, Whole>(a);
         return;
     }
     const int64_t nb = static_cast<int64_t>(gridDim.x) - ncb;     // a multiple of kXcds
@@ -1049,12 +1147,12 @@ __device__ __forceinline__ void hop_row_block(const HopArgs& a, int blk) {
     epilogue<C>(a, r0 + t, ops, sum);
 }
 
-template <int C, bool NT>
-__global__ void __launch_bounds__(kBT) k_hop_rb(HopArgs a0) {
+template <int C, bool NT, bool Whole>
+__global__ void __launch_bounds__(kBT, Whole && C == 4 ? 6 : 1) k_hop_rb(HopArgs a0) {
     const HopArgs a = tile_args<C>(a0);
     const int ncb = chunk_blocks(a);
     if (static_cast<int>(blockIdx.x) < ncb) {
-        hop_chunk<C, NT>(a);
+        hop_chunk<C, NT, Whole>(a);
         return;
     }
     const int64_t nb = static_cast<int64_t>(gridDim.x) - ncb;     // a multiple of kXcds
@@ -1110,58 +1208,73 @@ __device__ __forceinline__ void gather_batch_gersh(const HopArgs& a, const float
 
 // One chunk of a long row: float64 partials of the C neighbour sums at
 // partial[chunk * 8 + c] and of the Gershgorin sum at partial[chunk * 8 + C].
-template <int C>
-__device__ __forceinline__ void hop1_chunk(const HopArgs& a, const float* zpk) {
-    __shared__ double red[C + 1][kBT / kWave];
+template <int C, bool Whole>
+__device__ __forceinline__ void hop1_chunk(const HopArgs& a, const float* zpk, const double* __restrict__ deg,
+                                           double* __restrict__ lmax) {
     const int chunk = dealt_chunk(a, blockIdx.x);
     if (chunk < 0) return;
-    const int4 d = a.chunks[chunk];
-    double acc[C + 1];
+    const auto add = [&](const Chunk& ch, double (&acc)[C + 1]) {
+        in_chunk(ch.n, [&](auto n) {
+            constexpr int U = decltype(n)::value;
+            int2 e[U];
 #pragma unroll
-    for (int c = 0; c < C; ++c) acc[c] = 0;
-    double ag = 0;
-    in_chunk(d.w, [&](auto n) {
-        constexpr int U = decltype(n)::value;
-        int2 e[U];
+            for (int u = 0; u < U; ++u) {
+                int k = static_cast<int>(threadIdx.x) + u * kBT;
+                int kc = k < ch.n ? k : ch.n - 1;
+                e[u] = row_entry<false>(a.m, ch.nb, ch.net, ch.hb, kc);
+                if (k >= ch.n) e[u].y = 0;
+            }
+            Vec<C> v[U];
+            float sc[U];
 #pragma unroll
-        for (int u = 0; u < U; ++u) {
-            int k = static_cast<int>(threadIdx.x) + u * kBT;
-            int kc = k < d.w ? k : d.w - 1;
-            e[u] = row_entry<false>(a.m, d.x, d.y, d.z, kc);
-            if (k >= d.w) e[u].y = 0;
+            for (int u = 0; u < U; ++u) load_record<C>(zpk, e[u].x, v[u], sc[u]);
+#pragma unroll
+            for (int u = 0; u < U; ++u) {
+                double w = static_cast<double>(bits_f(e[u].y));
+#pragma unroll
+                for (int c = 0; c < C; ++c) acc[c] += w * static_cast<double>(v[u].v[c]);
+                acc[C] += fabs(w) * static_cast<double>(sc[u]);
+            }
+        });
+    };
+    if constexpr (Whole) {
+        Chunk d;
+        double tot;
+        if (!chunk_sums<C + 1, true>(a, chunk, d, tot, add) || wave_id() != 0) return;
+        Vec<C> sum;
+#pragma unroll
+        for (int c = 0; c < C; ++c) sum.v[c] = static_cast<float>(__shfl(tot, c));
+        const double g = __shfl(tot, C);
+        if (lane_id() != 0) return;
+        const int r = a.long_rows[d.li];
+        vstore<C>(a.zout + static_cast<int64_t>(r) * C, sum);
+        const float sr = a.scale[r];
+        lmax[d.li] = diag_abs(sr, deg[r], a.sigma) + static_cast<double>(sr) * g;
+    } else {
+        __shared__ double red[C + 1][kBT / kWave];
+        double acc[C + 1];
+#pragma unroll
+        for (int c = 0; c <= C; ++c) acc[c] = 0;
+        add(unpack_chunk(a.chunks[chunk]), acc);
+        block_sums_f64<kBT>(acc, red);
+        if (threadIdx.x == 0) {
+            double* part = a.partial + static_cast<int64_t>(chunk) * 8;
+#pragma unroll
+            for (int c = 0; c <= C; ++c) part[c] = acc[c];
         }
-        Vec<C> v[U];
-        float sc[U];
-#pragma unroll
-        for (int u = 0; u < U; ++u) load_record<C>(zpk, e[u].x, v[u], sc[u]);
-#pragma unroll
-        for (int u = 0; u < U; ++u) {
-            double w = static_cast<double>(bits_f(e[u].y));
-#pragma unroll
-            for (int c = 0; c < C; ++c) acc[c] += w * static_cast<double>(v[u].v[c]);
-            ag += fabs(w) * static_cast<double>(sc[u]);
-        }
-    });
-    acc[C] = ag;
-    block_sums_f64<kBT>(acc, red);
-    if (threadIdx.x == 0) {
-        double* part = a.partial + static_cast<int64_t>(chunk) * 8;
-#pragma unroll
-        for (int c = 0; c < C; ++c) part[c] = acc[c];
-        part[C] = acc[C];
     }
 }
 
 // Chunk workgroups first, then short-row tiles (G lanes per row, XCD-dealt
 // as in k_hop); every thread reaches the workgroup's maximum, which goes to
 // wgmax[tile].
-template <int C, int G, int U>
+template <int C, int G, int U, bool Whole>
 __global__ void __launch_bounds__(kBT) k_hop1_gersh(HopArgs a, const float* __restrict__ zpk,
                                                     const double* __restrict__ deg, double* __restrict__ wgmax) {
     __shared__ double red[kBT / kWave];
     const int ncb = chunk_blocks(a);
     if (static_cast<int>(blockIdx.x) < ncb) {
-        hop1_chunk<C>(a, zpk);
+        hop1_chunk<C, Whole>(a, zpk, deg, wgmax + (gridDim.x - ncb));
         return;
     }
     const int64_t nb = static_cast<int64_t>(gridDim.x) - ncb;     // a multiple of kXcds
@@ -1325,74 +1438,66 @@ __global__ void k_relax(int32_t n_inst, const uint8_t* __restrict__ flags, const
 // matches a kernel trace of k_hop; `bytes` are the algorithmic bytes of the whole hop.  ntiles
 // column tiles of C columns each run as blockIdx.y.
 template <int C, int G>
-void launch_hop(const HopArgs& a, int32_t n_long_rows, double bytes, int ntiles, hipStream_t s) {
+void launch_hop(const HopArgs& a, int32_t n_parts_rows, double bytes, int ntiles, hipStream_t s) {
     constexpr int U = 16 / G > 8 ? 8 : (16 / G < 1 ? 1 : 16 / G);   // entries per lane per batch (16 per row, at most 8)
     int64_t tiles = grid_for(static_cast<int64_t>(a.n_rows) * G, kBT);
     tiles = (tiles + kXcds - 1) / kXcds * kXcds;                    // see xcd_tile
     int64_t blocks = chunk_blocks(a) + tiles;
     const dim3 grid(static_cast<unsigned>(blocks), static_cast<unsigned>(ntiles));
+    const auto kernel = n_parts_rows ? (g_hop_nt ? k_hop<C, G, U, true, false> : k_hop<C, G, U, false, false>)
+                                     : (g_hop_nt ? k_hop<C, G, U, true, true> : k_hop<C, G, U, false, true>);
     hipEvent_t e0, e1;
     if (prof_kernel_events(kStageHop, &e0, &e1)) {
-        if (g_hop_nt)
-            hipExtLaunchKernelGGL((k_hop<C, G, U, true>), grid, dim3(kBT), 0, s, e0, e1, 0, a);
-        else
-            hipExtLaunchKernelGGL((k_hop<C, G, U, false>), grid, dim3(kBT), 0, s, e0, e1, 0, a);
+        hipExtLaunchKernelGGL(kernel, grid, dim3(kBT), 0, s, e0, e1, 0, a);
         AHR_LAUNCHED("k_hop");
         prof_kernel_done(kStageHop, e0, e1, bytes);
     } else {
-        if (g_hop_nt)
-            hipLaunchKernelGGL((k_hop<C, G, U, true>), grid, dim3(kBT), 0, s, a);
-        else
-            hipLaunchKernelGGL((k_hop<C, G, U, false>), grid, dim3(kBT), 0, s, a);
+        hipLaunchKernelGGL(kernel, grid, dim3(kBT), 0, s, a);
         AHR_LAUNCHED("k_hop");
     }
-    if (n_long_rows > 0) {
+    if (n_parts_rows > 0) {
         hipLaunchKernelGGL(k_hop_long<C>,
-                           dim3(grid_for(static_cast<int64_t>(n_long_rows) * kWave, kBT), static_cast<unsigned>(ntiles)),
-                           dim3(kBT), 0, s, a, n_long_rows);
+                           dim3(grid_for(static_cast<int64_t>(n_parts_rows) * kWave, kBT), static_cast<unsigned>(ntiles)),
+                           dim3(kBT), 0, s, a, n_parts_rows);
         AHR_LAUNCHED("k_hop_long");
     }
 }
 
 template <int C>
-void launch_hop_rb(const HopArgs& a, int32_t n_long_rows, double bytes, int ntiles, hipStream_t s) {
+void launch_hop_rb(const HopArgs& a, int32_t n_parts_rows, double bytes, int ntiles, hipStream_t s) {
     int64_t tiles = (static_cast<int64_t>(a.n_rb) + kXcds - 1) / kXcds * kXcds;   // see xcd_tile
     if (tiles < kXcds) tiles = kXcds;
     const dim3 grid(static_cast<unsigned>(chunk_blocks(a) + tiles), static_cast<unsigned>(ntiles));
+    const auto kernel = n_parts_rows ? (g_hop_nt ? k_hop_rb<C, true, false> : k_hop_rb<C, false, false>)
+                                     : (g_hop_nt ? k_hop_rb<C, true, true> : k_hop_rb<C, false, true>);
     hipEvent_t e0, e1;
     if (prof_kernel_events(kStageHop, &e0, &e1)) {
-        if (g_hop_nt)
-            hipExtLaunchKernelGGL((k_hop_rb<C, true>), grid, dim3(kBT), 0, s, e0, e1, 0, a);
-        else
-            hipExtLaunchKernelGGL((k_hop_rb<C, false>), grid, dim3(kBT), 0, s, e0, e1, 0, a);
+        hipExtLaunchKernelGGL(kernel, grid, dim3(kBT), 0, s, e0, e1, 0, a);
         AHR_LAUNCHED("k_hop_rb");
         prof_kernel_done(kStageHop, e0, e1, bytes);
     } else {
-        if (g_hop_nt)
-            hipLaunchKernelGGL((k_hop_rb<C, true>), grid, dim3(kBT), 0, s, a);
-        else
-            hipLaunchKernelGGL((k_hop_rb<C, false>), grid, dim3(kBT), 0, s, a);
+        hipLaunchKernelGGL(kernel, grid, dim3(kBT), 0, s, a);
         AHR_LAUNCHED("k_hop_rb");
     }
-    if (n_long_rows > 0) {
+    if (n_parts_rows > 0) {
         hipLaunchKernelGGL(k_hop_long<C>,
-                           dim3(grid_for(static_cast<int64_t>(n_long_rows) * kWave, kBT), static_cast<unsigned>(ntiles)),
-                           dim3(kBT), 0, s, a, n_long_rows);
+                           dim3(grid_for(static_cast<int64_t>(n_parts_rows) * kWave, kBT), static_cast<unsigned>(ntiles)),
+                           dim3(kBT), 0, s, a, n_parts_rows);
         AHR_LAUNCHED("k_hop_long");
     }
 }
 
 template <int C>
-void hop_dispatch(const HopArgs& a, int lanes, int32_t n_long_rows, double bytes, int ntiles, hipStream_t s) {
+void hop_dispatch(const HopArgs& a, int lanes, int32_t n_parts_rows, double bytes, int ntiles, hipStream_t s) {
     switch (lanes) {
-        case AHR_HOP_ROW_BLOCK: launch_hop_rb<C>(a, n_long_rows, bytes, ntiles, s); break;
-        case 1: launch_hop<C, 1>(a, n_long_rows, bytes, ntiles, s); break;
-        case 2: launch_hop<C, 2>(a, n_long_rows, bytes, ntiles, s); break;
-        case 4: launch_hop<C, 4>(a, n_long_rows, bytes, ntiles, s); break;
-        case 8: launch_hop<C, 8>(a, n_long_rows, bytes, ntiles, s); break;
-        case 16: launch_hop<C, 16>(a, n_long_rows, bytes, ntiles, s); break;
-        case 32: launch_hop<C, 32>(a, n_long_rows, bytes, ntiles, s); break;
-        default: launch_hop<C, 64>(a, n_long_rows, bytes, ntiles, s); break;
+        case AHR_HOP_ROW_BLOCK: launch_hop_rb<C>(a, n_parts_rows, bytes, ntiles, s); break;
+        case 1: launch_hop<C, 1>(a, n_parts_rows, bytes, ntiles, s); break;
+        case 2: launch_hop<C, 2>(a, n_parts_rows, bytes, ntiles, s); break;
+        case 4: launch_hop<C, 4>(a, n_parts_rows, bytes, ntiles, s); break;
+        case 8: launch_hop<C, 8>(a, n_parts_rows, bytes, ntiles, s); break;
+        case 16: launch_hop<C, 16>(a, n_parts_rows, bytes, ntiles, s); break;
+        case 32: launch_hop<C, 32>(a, n_parts_rows, bytes, ntiles, s); break;
+        default: launch_hop<C, 64>(a, n_parts_rows, bytes, ntiles, s); break;
     }
 }
 
@@ -1438,6 +1543,7 @@ ChainView chain_view(Graph& g, const ahr_filter_spec& spec, hipStream_t s) {
     v.n_inst = g.n_inst;
     v.n_long = g.rc.n_long;
     v.n_long_inst = g.rc.n_long_inst;
+    v.in_parts = g.rc.in_parts;
     v.n_chunks = g.rc.n_chunks;
     v.n_chunks_inst = g.rc.n_chunks_inst;
     v.n_chunks_net = g.rc.n_chunks_net;
@@ -1484,6 +1590,11 @@ HopArgs hop_args(const ChainView& v, const float* in, float* out, int ncols) {
     return h;
 }
 
+// Long rows that a launch after the hop adds up (of the instances' only, or all).
+int32_t parts_rows(const ChainView& v, bool inst_only) {
+    return !v.in_parts ? 0 : inst_only ? v.n_long_inst : v.n_long;
+}
+
 // Algorithmic bytes of one hop launch over C columns: row pointers,
 // (column, weight) entries, one read of the gathered signal, the row
 // writes, the band accumulator.
@@ -1515,7 +1626,7 @@ void hops_c(Graph& g, const ahr_filter_spec& spec, const float* in, int lanes, h
         h.n_rows = inst_only ? v.n_inst : v.n_tot;
         h.n_chunks = inst_only ? v.n_chunks_inst : v.n_chunks;
         h.n_rb = inst_only ? v.n_rb_inst : v.n_rb;
-        hop_dispatch<C>(h, lanes, inst_only ? v.n_long_inst : v.n_long, hop_bytes(v, h, C), 1, s);
+        hop_dispatch<C>(h, lanes, parts_rows(v, inst_only), hop_bytes(v, h, C), 1, s);
         zin = g.zh[j].p;
     }
 }
@@ -1547,12 +1658,13 @@ void hop1_gersh(const ChainView& v, HopArgs h, const Hop1Gersh& f, hipStream_t s
     constexpr int G = 4, U = 4;
     int64_t tiles = grid_for(static_cast<int64_t>(h.n_rows) * G, kBT);
     tiles = (tiles + kXcds - 1) / kXcds * kXcds;                    // see xcd_tile
-    hipLaunchKernelGGL((k_hop1_gersh<C, G, U>), dim3(static_cast<unsigned>(chunk_blocks(h) + tiles)), dim3(kBT), 0,
+    const int32_t rows = parts_rows(v, false);
+    hipLaunchKernelGGL((rows ? k_hop1_gersh<C, G, U, false> : k_hop1_gersh<C, G, U, true>), dim3(static_cast<unsigned>(chunk_blocks(h) + tiles)), dim3(kBT), 0,
                        s, h, f.zpk, f.deg, f.gmax);
     AHR_LAUNCHED("k_hop1_gersh");
-    if (v.n_long > 0) {
-        hipLaunchKernelGGL(k_hop1_long<C>, dim3(grid_for(static_cast<int64_t>(v.n_long) * kWave, kBT)), dim3(kBT), 0, s,
-                           h, v.n_long, f.deg, f.gmax + tiles);
+    if (rows) {
+        hipLaunchKernelGGL(k_hop1_long<C>, dim3(grid_for(static_cast<int64_t>(rows) * kWave, kBT)), dim3(kBT), 0, s,
+                           h, rows, f.deg, f.gmax + tiles);
         AHR_LAUNCHED("k_hop1_long");
     }
     hipLaunchKernelGGL(k_lam_reduce, dim3(1), dim3(1024), 0, s, f.gmax, tiles, f.gmax + tiles, v.n_long, f.lam);
@@ -1599,7 +1711,7 @@ void chain_c(const ChainView& v, const ahr_filter_spec& spec, const float* in, f
                 throw Error{AHR_EINVAL, "first-hop bound needs one column tile of at most 4 columns"};
             }
         } else {
-            hop_dispatch<CT>(h, lanes, h.last ? v.n_long_inst : v.n_long, hop_bytes(v, h, C), C / CT, s);
+            hop_dispatch<CT>(h, lanes, parts_rows(v, h.last), hop_bytes(v, h, C), C / CT, s);
         }
         has_acc = has_acc || isb;
         float* t = zin;
@@ -1688,23 +1800,23 @@ static void row_classes_begin(const int32_t* net_rp, const int32_t* hint_rp, int
     rc.long_rows.ensure(static_cast<size_t>(max_long) + 1, s);
     rc.long_chunk0.ensure(static_cast<size_t>(max_long) + 1, s);
     rc.chunk_row.ensure(static_cast<size_t>(max_long + max_entries / kChunk) + 1, s);
-    rc.counts.ensure(5, s);
+    rc.counts.ensure(6, s);
     run_scans(scan_job(LongRowScan{net_rp, hint_rp, n_inst, first_hint, rc.long_rows.p, rc.long_chunk0.p, rc.chunk_row.p,
                                    rc.counts.p},
                        N),
               scan_tmp, s);
     std::vector<const int32_t*> words{rc.counts.p,     rc.counts.p + 1,  rc.counts.p + 2, rc.counts.p + 3,
                                       net_rp + n_inst, hint_rp + n_inst, net_rp + N,      hint_rp + N,
-                                      rc.counts.p + 4};
+                                      rc.counts.p + 4, rc.counts.p + 5};
     if (extra) words.push_back(extra);
     read_scalars_begin(words, s);
 }
 
 static void row_classes_end(int32_t N, int32_t n_inst, int32_t first_hint, RowClasses& rc, hipStream_t s,
                             int32_t* extra_out = nullptr) {
-    int32_t v[10];
-    read_scalars_end(v, extra_out ? 10 : 9);
-    if (extra_out) *extra_out = v[9];
+    int32_t v[11];
+    read_scalars_end(v, extra_out ? 11 : 10);
+    if (extra_out) *extra_out = v[10];
     rc.nnz_net_all = v[6];
     rc.nnz_hint_all = v[7];
     rc.n_long = v[0];
@@ -1713,6 +1825,7 @@ static void row_classes_end(int32_t N, int32_t n_inst, int32_t first_hint, RowCl
     rc.n_long_inst = n_inst < N ? v[1] : v[0];
     rc.n_chunks_inst = n_inst < N ? v[3] : v[2];
     rc.n_chunks_net = first_hint < N ? v[8] : v[2];
+    rc.in_parts = v[9];
     rc.nnz_inst = static_cast<int64_t>(v[4]) + v[5];
     rc.has_rb = 0;
     rc.partial.ensure(static_cast<size_t>(rc.n_chunks) * 8 + 8, s);
@@ -1726,7 +1839,7 @@ void row_classes(const int32_t* net_rp, const int32_t* hint_rp, int32_t N, int32
     if (!rc.n_chunks) return;
     hipLaunchKernelGGL(k_chunk_ranges, dim3(grid_for(rc.n_chunks, kBT)), dim3(kBT), 0, s,
                        RowRef{net_rp, nullptr, hint_rp, nullptr}, rc.n_chunks, rc.long_rows.p, rc.chunk_row.p,
-                       rc.long_chunk0.p, rc.chunks.p);
+                       rc.long_chunk0.p, rc.counts.p, rc.chunks.p);
     AHR_LAUNCHED("k_chunk_ranges");
 }
 
@@ -1738,7 +1851,7 @@ void row_blocks(const int32_t* net_rp, const int32_t* hint_rp, int32_t N, int32_
     const int64_t bound = 2 + rc.n_long + static_cast<int64_t>(N) / kRbRows +
                           (rc.nnz_net_all + rc.nnz_hint_all) / kRbEntries;
     rc.rb.ensure(2 * static_cast<size_t>(bound) + 2, s);
-    rc.counts.ensure(5, s);
+    rc.counts.ensure(6, s);
     run_scans(scan_job(RowBlockScan{N, n_inst, net_rp, hint_rp, rc.rb.p, rc.counts.p}, N), scan_tmp, s);
     int32_t t[2];
     read_scalars({rc.counts.p, rc.counts.p + 1}, t, s);
@@ -1884,7 +1997,7 @@ void normalise_degrees(Graph& g, const ahr_filter_spec& spec, hipStream_t s) {
     }
     if (g.rc.n_long) {
         hipLaunchKernelGGL(k_chunk_absdeg, dim3(g.rc.n_chunks), dim3(kBT), 0, s, m, g.rc.long_rows.p, g.rc.chunk_row.p,
-                           g.rc.long_chunk0.p, g.rc.chunks.p, g.rc.partial.p);
+                           g.rc.long_chunk0.p, g.rc.counts.p, g.rc.chunks.p, g.rc.partial.p);
         AHR_LAUNCHED("k_chunk_absdeg");
         hipLaunchKernelGGL(k_long_deg_final, dim3(grid_for(static_cast<int64_t>(g.rc.n_long) * kWave, kBT)), dim3(kBT), 0, s, g.rc.n_long, g.rc.long_rows.p,
                            g.rc.long_chunk0.p, g.rc.partial.p, g.xqdeg.p, sigma, g.deg.p, g.scale.p, g.hsum.p);
