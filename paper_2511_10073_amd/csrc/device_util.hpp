@@ -92,15 +92,43 @@ __device__ __forceinline__ T wave_min(T v) {
     return v;
 }
 
-// Inclusive scan over the wave.
+// v plus the value of the lane that the exchange Ctrl takes it from, in the
+// rows of 16 lanes in Rows, where there is one.
+template <int Ctrl, int Rows = 0xf>
+__device__ __forceinline__ int64_t dpp_add(int64_t v) {
+    const int lo = __builtin_amdgcn_update_dpp(0, static_cast<int>(v), Ctrl, Rows, 0xf, false);
+    const int hi = __builtin_amdgcn_update_dpp(0, static_cast<int>(v >> 32), Ctrl, Rows, 0xf, false);
+    return v + static_cast<int64_t>(static_cast<uint64_t>(static_cast<uint32_t>(hi)) << 32 | static_cast<uint32_t>(lo));
+}
+
+// Inclusive scan over each row of 16 lanes: the lanes 1, 2, 4 and 8 below.
+__device__ __forceinline__ int64_t row_incl_scan_i64(int64_t v) {
+    return dpp_add<0x118>(dpp_add<0x114>(dpp_add<0x112>(dpp_add<0x111>(v))));
+}
+
+// Inclusive scan over the wave: the rows, then lane 15 of the row below into
+// the odd rows, then lane 31 into the upper two.
 __device__ __forceinline__ int64_t wave_incl_scan_i64(int64_t v) {
-    int l = lane_id();
-#pragma unroll
-    for (int o = 1; o < kWave; o <<= 1) {
-        int64_t u = __shfl_up(v, o);
-        if (l >= o) v += u;
-    }
-    return v;
+    return dpp_add<0x143, 0xc>(dpp_add<0x142, 0xa>(row_incl_scan_i64(v)));
+}
+
+__device__ __forceinline__ int64_t readlane_i64(int64_t v, int l) {
+    const int lo = __builtin_amdgcn_readlane(static_cast<int>(v), l);
+    const int hi = __builtin_amdgcn_readlane(static_cast<int>(v >> 32), l);
+    return static_cast<int64_t>(static_cast<uint64_t>(static_cast<uint32_t>(hi)) << 32 | static_cast<uint32_t>(lo));
+}
+
+// From the waves' sums red[w * stride]: the sum of those before the caller's
+// wave, and of all (a loop over the 16 waves of a workgroup of 1024 in every
+// lane cost the small scans more than all the rest).
+template <int BT>
+__device__ __forceinline__ void across_waves(const int64_t* red, int stride, int64_t* before, int64_t* total) {
+    constexpr int W = BT / kWave;
+    static_assert(W <= 16, "waves of a workgroup");
+    const int l = lane_id(), w = __builtin_amdgcn_readfirstlane(wave_id());
+    const int64_t r = row_incl_scan_i64(l < W ? red[l * stride] : 0);
+    *total = readlane_i64(r, W - 1);
+    *before = w ? readlane_i64(r, w - 1) : 0;
 }
 
 // Block-wide sum; every thread gets the result. red: BT/64 slots.
@@ -154,14 +182,8 @@ __device__ __forceinline__ int64_t block_exclusive_scan_i64(int64_t v, int64_t* 
     __syncthreads();
     if (lane_id() == kWave - 1) red[wave_id()] = inc;
     __syncthreads();
-    int64_t before = 0, tot = 0;
-#pragma unroll
-    for (int w = 0; w < BT / kWave; ++w) {
-        int64_t r = red[w];
-        if (w < wave_id()) before += r;
-        tot += r;
-    }
-    *total = tot;
+    int64_t before;
+    across_waves<BT>(red, 1, &before, total);
     return before + inc - v;
 }
 

@@ -47,11 +47,16 @@ __host__ __device__ __forceinline__ int32_t pack_lo(int64_t v) { return static_c
 __host__ __device__ __forceinline__ int32_t pack_hi(int64_t v) { return static_cast<int32_t>(v >> 32); }
 
 constexpr int kScanBT = 256;
-// Consecutive items of a thread: fewer where an item carries many sums
-// (8 of four each need 128 registers more than there are).
+// Consecutive items of a thread in a tile: fewer where an item carries many
+// sums (8 of four each need 128 registers more than there are).
 template <class F>
 constexpr int kScanPer = F::K >= 3 ? 2 : 8;
 constexpr int kScanSmallBT = 1024;
+// Items of a thread at a time in the small form: its cost at a few thousand
+// items is fetching its code, which grows with them (2,211 rows: 8.3 us for the
+// execution rows with 4, 13.6 with 8; 5.6 and 9.5 for the hint rows), while
+// the largest inputs take more rounds of it.
+constexpr int kSmallPer = 4;
 constexpr int64_t kScanSmall = 16384;
 constexpr int64_t kScanTiles = 4096;
 
@@ -69,43 +74,36 @@ __device__ __forceinline__ Pack<K> block_scan_pack(Pack<K> v, int64_t (*red)[K],
     Pack<K> ex;
 #pragma unroll
     for (int k = 0; k < K; ++k) {
-        int64_t before = 0, tot = 0;
-#pragma unroll 4
-        for (int w = 0; w < BT / kWave; ++w) {
-            const int64_t r = red[w][k];
-            if (w < wave_id()) before += r;
-            tot += r;
-        }
-        total->v[k] = tot;
+        int64_t before;
+        across_waves<BT>(&red[0][k], K, &before, &total->v[k]);
         ex.v[k] = before + inc.v[k] - v.v[k];
     }
     return ex;
 }
 
-// Items base..base+kScanPer<F>-1 of a job (none past n): their values and sums.
-template <bool First, class F>
-__device__ __forceinline__ Pack<F::K> scan_load(const F& f, int64_t n, int64_t base,
-                                                typename F::Raw (&p)[kScanPer<F>]) {
+// Items base..base+Per-1 of a job (none past n): their values and sums.
+template <bool First, int Per, class F>
+__device__ __forceinline__ Pack<F::K> scan_load(const F& f, int64_t n, int64_t base, typename F::Raw (&p)[Per]) {
     Pack<F::K> sum{};
 #pragma unroll
-    for (int k = 0; k < kScanPer<F>; ++k) {
+    for (int k = 0; k < Per; ++k) {
         const int64_t i = base + k < n ? base + k : n - 1;     // clamped: no branch around a load
         if constexpr (First) p[k] = f.first(i);
         else p[k] = f.again(i);
     }
 #pragma unroll
-    for (int k = 0; k < kScanPer<F>; ++k) {
+    for (int k = 0; k < Per; ++k) {
         if (base + k >= n) p[k] = typename F::Raw{};
         pack_add(sum, f.pack(p[k]));
     }
     return sum;
 }
 
-template <class F>
+template <int Per, class F>
 __device__ __forceinline__ void scan_emit(const F& f, int64_t n, int64_t base, Pack<F::K> run,
-                                          const typename F::Raw (&p)[kScanPer<F>], const Pack<F::K>& total) {
+                                          const typename F::Raw (&p)[Per], const Pack<F::K>& total) {
 #pragma unroll
-    for (int k = 0; k < kScanPer<F>; ++k) {
+    for (int k = 0; k < Per; ++k) {
         if (base + k < n) f.item(base + k, p[k], run, total);
         pack_add(run, f.pack(p[k]));
     }
@@ -123,20 +121,20 @@ struct ScanJob {
 template <class F>
 __device__ __forceinline__ void scan_small(const ScanJob<F>& j, int64_t (*red)[F::K]) {
     constexpr int K = F::K;
-    constexpr int64_t kStep = static_cast<int64_t>(kScanSmallBT) * kScanPer<F>;
-    typename F::Raw p[kScanPer<F>];
+    constexpr int64_t kStep = static_cast<int64_t>(kScanSmallBT) * kSmallPer;
+    typename F::Raw p[kSmallPer];
     Pack<K> carry{}, total{}, tot;
     if constexpr (F::kTotal) {
         for (int64_t b = 0; b < j.n; b += kStep) {
-            block_scan_pack<kScanSmallBT, K>(scan_load<true>(j.f, j.n, b + threadIdx.x * kScanPer<F>, p), red, &tot);
+            block_scan_pack<kScanSmallBT, K>(scan_load<true, kSmallPer>(j.f, j.n, b + threadIdx.x * kSmallPer, p), red, &tot);
             pack_add(total, tot);
         }
     }
     for (int64_t b = 0; b < j.n; b += kStep) {
-        const int64_t base = b + threadIdx.x * kScanPer<F>;
-        Pack<K> run = block_scan_pack<kScanSmallBT, K>(scan_load<!F::kTotal>(j.f, j.n, base, p), red, &tot);
+        const int64_t base = b + threadIdx.x * kSmallPer;
+        Pack<K> run = block_scan_pack<kScanSmallBT, K>(scan_load<!F::kTotal, kSmallPer>(j.f, j.n, base, p), red, &tot);
         pack_add(run, carry);
-        scan_emit(j.f, j.n, base, run, p, total);
+        scan_emit<kSmallPer>(j.f, j.n, base, run, p, total);
         pack_add(carry, tot);
     }
     if (threadIdx.x == 0) j.f.done(carry);
@@ -150,7 +148,7 @@ __device__ __forceinline__ void scan_sums(const ScanJob<F>& j, int64_t tile, int
     Pack<K> sum{}, tot;
     for (int r = 0; r < j.rounds; ++r) {
         const int64_t base = ((tile * j.rounds + r) * kScanBT + threadIdx.x) * kScanPer<F>;
-        pack_add(sum, scan_load<!F::kHeavy>(j.f, j.n, base, p));
+        pack_add(sum, scan_load<!F::kHeavy, kScanPer<F>>(j.f, j.n, base, p));
     }
     block_scan_pack<kScanBT, K>(sum, red, &tot);
     if (threadIdx.x == 0)
@@ -185,9 +183,9 @@ __device__ __forceinline__ void scan_tile(const ScanJob<F>& j, int64_t tile, int
     typename F::Raw p[kScanPer<F>];
     for (int r = 0; r < j.rounds; ++r) {
         const int64_t base = ((tile * j.rounds + r) * kScanBT + threadIdx.x) * kScanPer<F>;
-        Pack<K> ex = block_scan_pack<kScanBT, K>(scan_load<false>(j.f, j.n, base, p), red, &tot);
+        Pack<K> ex = block_scan_pack<kScanBT, K>(scan_load<false, kScanPer<F>>(j.f, j.n, base, p), red, &tot);
         pack_add(ex, run);
-        scan_emit(j.f, j.n, base, ex, p, total);
+        scan_emit<kScanPer<F>>(j.f, j.n, base, ex, p, total);
         pack_add(run, tot);
     }
     if (tile == 0 && threadIdx.x == 0) j.f.done(total);

@@ -34,6 +34,7 @@ constexpr int kLdsWords = 32768;
 // Up to kSmallIters x 64 elements a wave one workgroup of up to 16 waves does
 // the whole sort, in one launch instead of four.
 constexpr int kSmallIters = 16;
+constexpr int kSmallStep = 2;
 constexpr int kSmallWaves = 16;
 
 __device__ __forceinline__ int sort_key(const SortKeys& k, int64_t i) {
@@ -157,16 +158,23 @@ __global__ void __launch_bounds__(kSmallWaves * kWave) k_bucket_small(SortKeys k
     int32_t* mine = run + wave_id() * nkeys;
     const int per = (n + static_cast<int>(blockDim.x) - 1) / static_cast<int>(blockDim.x);      // <= kSmallIters
     const int64_t base = static_cast<int64_t>(wave_id()) * per * kWave + lane_id();
-    int key[kSmallIters];
+    // kSmallStep keys a lane at a time, read again where they are placed: code
+    // for all of a lane's keys costs more to fetch than a small input to sort
+    int key[kSmallStep];
+    const auto load = [&](int t0) {
 #pragma unroll
-    for (int t = 0; t < kSmallIters; ++t) {
-        const int64_t i = base + t * kWave;
-        key[t] = sort_key(k, i < n ? i : n - 1);
-        if (i >= n || t >= per) key[t] = -1;
+        for (int u = 0; u < kSmallStep; ++u) {
+            const int64_t i = base + (t0 + u) * kWave;
+            key[u] = sort_key(k, i < n ? i : n - 1);
+            if (i >= n || t0 + u >= per) key[u] = -1;
+        }
+    };
+    for (int t0 = 0; t0 < per; t0 += kSmallStep) {
+        load(t0);
+#pragma unroll
+        for (int u = 0; u < kSmallStep; ++u)
+            if (key[u] >= 0) atomicAdd(&mine[key[u]], 1);
     }
-#pragma unroll
-    for (int t = 0; t < kSmallIters; ++t)
-        if (key[t] >= 0) atomicAdd(&mine[key[t]], 1);
     __syncthreads();
     for (int b0 = 0; b0 < nkeys; b0 += static_cast<int>(blockDim.x)) {
         const int b = b0 + static_cast<int>(threadIdx.x);
@@ -187,9 +195,12 @@ __global__ void __launch_bounds__(kSmallWaves * kWave) k_bucket_small(SortKeys k
         __syncthreads();
     }
     if (threadIdx.x == 0) start[nkeys] = static_cast<int32_t>(carry);
+    for (int t0 = 0; t0 < per; t0 += kSmallStep) {
+        load(t0);
 #pragma unroll
-    for (int t = 0; t < kSmallIters; ++t)
-        if (t < per) put(k, base + t * kWave, place_keys(key[t], bits, mine), list);
+        for (int u = 0; u < kSmallStep; ++u)
+            if (t0 + u < per) put(k, base + (t0 + u) * kWave, place_keys(key[u], bits, mine), list);
+    }
 }
 
 template <int I>
