@@ -35,8 +35,8 @@ HOP_SRCS = [os.path.join(ROOT, "paper_2511_10073_amd", "csrc", f) for f in ("fil
 # (FETCH_SIZE, WRITE_SIZE) scaled by the same counters for a 1 GiB device
 # copy; valid only for the hop and layout sources they were taken with.
 HOP_TRAFFIC = {"workload": "large-2.2M",
-               "sources_sha256": "987462926ef64ed24c05d786a7f7b76961cceff49a418d359935575d049beb3b",
-               "bytes_per_launch": 1419557188,
+               "sources_sha256": "2d0b0610c2cb073eb0e12c3346cf9560310b76322722a956326387d931fc7bd6",
+               "bytes_per_launch": 1270500054,
                "source": "profiles/k_hop_large-2.2M_l2_fabric_traffic.md"}
 
 
