@@ -35,8 +35,8 @@ HOP_SRCS = [os.path.join(ROOT, "paper_2511_10073_amd", "csrc", f) for f in ("fil
 # (FETCH_SIZE, WRITE_SIZE) scaled by the same counters for a 1 GiB device
 # copy; valid only for the hop and layout sources they were taken with.
 HOP_TRAFFIC = {"workload": "large-2.2M",
-               "sources_sha256": "2d0b0610c2cb073eb0e12c3346cf9560310b76322722a956326387d931fc7bd6",
-               "bytes_per_launch": 1270500054,
+               "sources_sha256": "6aa91018704c471c7880e70a219bee365ec7705d9e9065845790d61969d7a861",
+               "bytes_per_launch": 1270191009,
                "source": "profiles/k_hop_large-2.2M_l2_fabric_traffic.md"}
 
 

@@ -15,8 +15,9 @@
 //
 // Rows with up to kLongRow entries are handled by G lanes each; longer rows
 // (bin and macro virtual nodes, big-net stars) are split into kChunk-entry
-// chunks, one workgroup each, whose float64 partial sums a small kernel adds
-// after the hop in a fixed order -- deterministic for any schedule.
+// chunks, whose float64 sums are added in a fixed order -- deterministic for
+// any schedule -- by the workgroup that takes a row's chunks or, where a row
+// has too many for one, by a small kernel after the hop.
 #include <hip/hip_ext.h>
 
 #include <algorithm>
@@ -1444,8 +1445,8 @@ void launch_hop(const HopArgs& a, int32_t n_parts_rows, double bytes, int ntiles
     tiles = (tiles + kXcds - 1) / kXcds * kXcds;                    // see xcd_tile
     int64_t blocks = chunk_blocks(a) + tiles;
     const dim3 grid(static_cast<unsigned>(blocks), static_cast<unsigned>(ntiles));
-    const auto kernel = n_parts_rows ? (g_hop_nt ? k_hop<C, G, U, true, false> : k_hop<C, G, U, false, false>)
-                                     : (g_hop_nt ? k_hop<C, G, U, true, true> : k_hop<C, G, U, false, true>);
+    const auto kernel = n_parts_rows >= 0 ? (g_hop_nt ? k_hop<C, G, U, true, false> : k_hop<C, G, U, false, false>)
+                                          : (g_hop_nt ? k_hop<C, G, U, true, true> : k_hop<C, G, U, false, true>);
     hipEvent_t e0, e1;
     if (prof_kernel_events(kStageHop, &e0, &e1)) {
         hipExtLaunchKernelGGL(kernel, grid, dim3(kBT), 0, s, e0, e1, 0, a);
@@ -1468,8 +1469,8 @@ void launch_hop_rb(const HopArgs& a, int32_t n_parts_rows, double bytes, int nti
     int64_t tiles = (static_cast<int64_t>(a.n_rb) + kXcds - 1) / kXcds * kXcds;   // see xcd_tile
     if (tiles < kXcds) tiles = kXcds;
     const dim3 grid(static_cast<unsigned>(chunk_blocks(a) + tiles), static_cast<unsigned>(ntiles));
-    const auto kernel = n_parts_rows ? (g_hop_nt ? k_hop_rb<C, true, false> : k_hop_rb<C, false, false>)
-                                     : (g_hop_nt ? k_hop_rb<C, true, true> : k_hop_rb<C, false, true>);
+    const auto kernel = n_parts_rows >= 0 ? (g_hop_nt ? k_hop_rb<C, true, false> : k_hop_rb<C, false, false>)
+                                          : (g_hop_nt ? k_hop_rb<C, true, true> : k_hop_rb<C, false, true>);
     hipEvent_t e0, e1;
     if (prof_kernel_events(kStageHop, &e0, &e1)) {
         hipExtLaunchKernelGGL(kernel, grid, dim3(kBT), 0, s, e0, e1, 0, a);
@@ -1590,9 +1591,10 @@ HopArgs hop_args(const ChainView& v, const float* in, float* out, int ncols) {
     return h;
 }
 
-// Long rows that a launch after the hop adds up (of the instances' only, or all).
+// Long rows that a launch after the hop adds up (of the instances' only, or
+// all); -1 where the hop finishes them itself.
 int32_t parts_rows(const ChainView& v, bool inst_only) {
-    return !v.in_parts ? 0 : inst_only ? v.n_long_inst : v.n_long;
+    return !v.in_parts ? -1 : inst_only ? v.n_long_inst : v.n_long;
 }
 
 // Algorithmic bytes of one hop launch over C columns: row pointers,
@@ -1659,10 +1661,10 @@ void hop1_gersh(const ChainView& v, HopArgs h, const Hop1Gersh& f, hipStream_t s
     int64_t tiles = grid_for(static_cast<int64_t>(h.n_rows) * G, kBT);
     tiles = (tiles + kXcds - 1) / kXcds * kXcds;                    // see xcd_tile
     const int32_t rows = parts_rows(v, false);
-    hipLaunchKernelGGL((rows ? k_hop1_gersh<C, G, U, false> : k_hop1_gersh<C, G, U, true>), dim3(static_cast<unsigned>(chunk_blocks(h) + tiles)), dim3(kBT), 0,
+    hipLaunchKernelGGL((rows >= 0 ? k_hop1_gersh<C, G, U, false> : k_hop1_gersh<C, G, U, true>), dim3(static_cast<unsigned>(chunk_blocks(h) + tiles)), dim3(kBT), 0,
                        s, h, f.zpk, f.deg, f.gmax);
     AHR_LAUNCHED("k_hop1_gersh");
-    if (rows) {
+    if (rows > 0) {
         hipLaunchKernelGGL(k_hop1_long<C>, dim3(grid_for(static_cast<int64_t>(rows) * kWave, kBT)), dim3(kBT), 0, s,
                            h, rows, f.deg, f.gmax + tiles);
         AHR_LAUNCHED("k_hop1_long");
