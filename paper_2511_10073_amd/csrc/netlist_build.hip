@@ -150,7 +150,8 @@ __global__ void k_build_lists(ListArgs a) {
         if (a.big_rank[i + 1] > b) {
             a.big_nets[b] = e;
         } else {
-            for (int p = a.net_ptr[i]; p < a.net_ptr[i + 1]; ++p) a.pin_net[p] = e;
+            const int p0 = a.net_ptr[i], p1 = a.net_ptr[i + 1];      // (read once: the stores may alias)
+            for (int p = p0; p < p1; ++p) a.pin_net[p] = e;
         }
     }
 }
