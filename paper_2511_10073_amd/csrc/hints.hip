@@ -262,6 +262,10 @@ __device__ __forceinline__ void window(const Grid& gr, int b, int& x0, int& x1, 
 // Per hint cell (execution row): the macros whose footprint holds it and the
 // size of its bin window.  With `pairs`, also lists its (row, macro) pairs
 // at pair_off[r] in ascending macro order.
+// Macros of a bin that a cell tests at a time: one after another, each test
+// waits for two loads (2.2M cells, about ten macros a bin: 31 us against 36).
+constexpr int kBinMacros = 4;
+
 __global__ void __launch_bounds__(kBT) k_cell_count(HintArgs a, int32_t* __restrict__ nmac,
                                                     int32_t* __restrict__ nwin, const int32_t* __restrict__ pair_off,
                                                     int32_t* __restrict__ pair_row, int32_t* __restrict__ pair_mac) {
@@ -277,14 +281,24 @@ __global__ void __launch_bounds__(kBT) k_cell_count(HintArgs a, int32_t* __restr
         const float2 xy = a.xpos[r];
         const float x = xy.x, y = xy.y;
         int o = pair_row ? pair_off[r] : 0;
-        for (int t = a.bm_start[b]; t < a.bm_start[b + 1]; ++t) {
-            int k = a.bm_list[t];
-            if (inside(x, y, a.rect[k])) {
-                if (pair_row) {
-                    pair_row[o + n] = static_cast<int32_t>(r);
-                    pair_mac[o + n] = k;
+        // kBinMacros of the bin's macros in flight (indexes clamped to its last)
+        const int t0 = a.bm_start[b], t1 = a.bm_start[b + 1];
+        for (int t = t0; t < t1; t += kBinMacros) {
+            int k[kBinMacros];
+            float4 rect[kBinMacros];
+#pragma unroll
+            for (int u = 0; u < kBinMacros; ++u) k[u] = a.bm_list[t + u < t1 ? t + u : t1 - 1];
+#pragma unroll
+            for (int u = 0; u < kBinMacros; ++u) rect[u] = a.rect[k[u]];
+#pragma unroll
+            for (int u = 0; u < kBinMacros; ++u) {
+                if (t + u < t1 && inside(x, y, rect[u])) {
+                    if (pair_row) {
+                        pair_row[o + n] = static_cast<int32_t>(r);
+                        pair_mac[o + n] = k[u];
+                    }
+                    ++n;
                 }
-                ++n;
             }
         }
     }
