@@ -86,8 +86,11 @@ struct MlpRegs {
     v8s w3[2];        // A tiles with w3 in every row (chunk p, K permuted)
     float b1[16], b2[16];
     float b3;
+    bool wild;        // W1 has a bfloat16 infinity or NaN (the same in every lane)
 };
 
+// OneGroup: the samples' features always lie in lanes 0..15 (see mlp_tile).
+template <bool OneGroup>
 __device__ __forceinline__ void load_mlp(const float* __restrict__ P, MlpRegs& R) {
     const int l = lane_id(), i = l & 15, g = l >> 4;
 #pragma unroll
@@ -102,6 +105,15 @@ __device__ __forceinline__ void load_mlp(const float* __restrict__ P, MlpRegs& R
     for (int m = 0; m < 4; ++m)
 #pragma unroll
         for (int k = 0; k < kFP; ++k) R.w1[m][k] = bf16_bits(P[oW1 + (16 * m + i) * kFP + k]);
+    bool wild = false;
+#pragma unroll
+    for (int m = 0; m < 4; ++m)
+#pragma unroll
+        for (int k = 0; k < kFP; ++k) wild |= (R.w1[m][k] & 0x7f80) == 0x7f80;
+    R.wild = __any(wild);
+    if (OneGroup && g != 0)
+#pragma unroll
+        for (int m = 0; m < 4; ++m) R.w1[m] = v8s{0, 0, 0, 0, 0, 0, 0, 0};
 #pragma unroll
     for (int p = 0; p < 2; ++p)
 #pragma unroll
@@ -126,15 +138,20 @@ __device__ __forceinline__ v4i pack_features(const float F[kFP]) {
 }
 
 // One tile of 16 samples: x holds the features of sample l%16 in one group of
-// 16 lanes (whichever) and zeros in the other three, whose K slots so add
-// nothing; the result of sample l%16 is in every lane.
-__device__ __forceinline__ float mlp_tile(const MlpRegs& R, v4i x) {
+// 16 lanes and zeros in the other three, whose K slots so add nothing; the
+// result of sample l%16 is in every lane.  Wild: with weights that are not
+// finite, where 0 x inf would be NaN, which the relu may turn into 0; the
+// weights beside the zeros are zeroed as well (own: the features' group).
+template <bool Wild>
+__device__ __forceinline__ float mlp_tile(const MlpRegs& R, v4i x, int own) {
     v4s a1[4], a2[4];
     // each layer's accumulator starts at its bias (float32)
 #pragma unroll
     for (int m = 0; m < 4; ++m) {
         v4f acc = {R.b1[4 * m], R.b1[4 * m + 1], R.b1[4 * m + 2], R.b1[4 * m + 3]};
-        acc = mfma32(R.w1[m], __builtin_bit_cast(v8s, x), acc);
+        v8s w = R.w1[m];
+        if (Wild && lane_id() >> 4 != own) w = v8s{0, 0, 0, 0, 0, 0, 0, 0};
+        acc = mfma32(w, __builtin_bit_cast(v8s, x), acc);
         a1[m] = relu_bf16x4(acc);
     }
     // the lane's rows of output tiles 2p and 2p+1: the B operand of chunk p
@@ -170,7 +187,7 @@ __device__ __forceinline__ float mlp_tile(const MlpRegs& R, v4i x) {
 __global__ void __launch_bounds__(kBT) k_mlp_forward(const float* __restrict__ P, const float* __restrict__ feats,
                                                      int64_t n, float* __restrict__ o) {
     MlpRegs R;
-    load_mlp(P, R);
+    load_mlp<true>(P, R);
     const int l = lane_id(), g = l >> 4;
     const int64_t waves = static_cast<int64_t>(gridDim.x) * (kBT / kWave);
     const int64_t ntiles = (n + 15) / 16;
@@ -183,7 +200,7 @@ __global__ void __launch_bounds__(kBT) k_mlp_forward(const float* __restrict__ P
             F[0] = u.x, F[1] = u.y, F[2] = u.z, F[3] = u.w;
             F[4] = v.x, F[5] = v.y, F[6] = v.z, F[7] = v.w;
         }
-        float r = mlp_tile(R, pack_features(F));
+        float r = mlp_tile<false>(R, pack_features(F), 0);
         if (l < 16 && smp < n) o[smp] = r;
     }
 }
@@ -286,7 +303,7 @@ __device__ __forceinline__ void sample_unscale(const LearnArgs& a, SampleIn& t, 
 template <int C>
 __global__ void __launch_bounds__(kBT) k_mlp_learned(LearnArgs a) {
     MlpRegs R;
-    load_mlp(a.params, R);
+    load_mlp<false>(a.params, R);
     const int l = lane_id(), g = l >> 4;
     const int c = l % C;
     const float mc = a.stats[c], sc = a.stats[C + c], rc = a.stats[2 * C + c];
@@ -316,7 +333,7 @@ __global__ void __launch_bounds__(kBT) k_mlp_learned(LearnArgs a) {
             v4i own;
 #pragma unroll
             for (int k = 0; k < 4; ++k) own[k] = g == j ? x[k] : 0;
-            const float o = mlp_tile(R, own);              // of sample 16 j + i
+            const float o = R.wild ? mlp_tile<true>(R, own, j) : mlp_tile<false>(R, own, j);     // of sample 16 j + i
             if (g == j) mine = o;
         }
         const int64_t r = smp / C;
