@@ -61,6 +61,7 @@ __device__ __forceinline__ v4f mfma32(v8s a, v8s b, v4f c) {
 
 // float32 -> bfloat16, round to nearest even (v_cvt_pk_bf16_f32 on gfx950)
 __device__ __forceinline__ short bf16_bits(float x) { return __builtin_bit_cast(short, static_cast<__bf16>(x)); }
+__device__ __forceinline__ float bf16_value(short b) { return static_cast<float>(__builtin_bit_cast(__bf16, b)); }
 __device__ __forceinline__ float bf16_round(float x) { return static_cast<float>(static_cast<__bf16>(x)); }
 
 // ---------------------------------------------------------------- inference
@@ -547,13 +548,30 @@ __device__ __forceinline__ v8s masked(v4i m, v8s a) {
     return __builtin_bit_cast(v8s, w);
 }
 
+// From here on a float32 rounds to an infinite bfloat16.
+constexpr float kBf16Over = 0x1.ffp127f;
+
 // x = hi + mid + lo, each bfloat16 (exact for finite x whose parts are normal).
+// Below kBf16Over, or with Far for any x: a finite one past it has the largest
+// bfloat16 as its first part, an infinity is its first part alone (the rest
+// would be inf - inf).
+template <bool Far>
 __device__ __forceinline__ void split3(v2f x, v2s (&p)[3]) {
 #pragma unroll
     for (int c = 0; c < 3; ++c) {
-        const v2bf h = __builtin_convertvector(x, v2bf);
+        v2f top = x;
+        if constexpr (Far)
+#pragma unroll
+            for (int k = 0; k < 2; ++k)
+                if (fabsf(x[k]) >= kBf16Over && fabsf(x[k]) < INFINITY) top[k] = copysignf(0x1.fep127f, x[k]);
+        const v2bf h = __builtin_convertvector(top, v2bf);
         p[c] = __builtin_bit_cast(v2s, h);
-        x -= __builtin_convertvector(h, v2f);
+        v2f rest = x - __builtin_convertvector(h, v2f);
+        if constexpr (Far)
+#pragma unroll
+            for (int k = 0; k < 2; ++k)
+                if (fabsf(x[k]) == INFINITY) rest[k] = 0.f;
+        x = rest;
     }
 }
 
@@ -588,8 +606,11 @@ __global__ void __launch_bounds__(kBT, 2) k_mlp_grad_mfma(const float* __restric
     constexpr int kXS = 20;
     __shared__ __attribute__((aligned(16))) float xs[kBT / kWave][kTS][kXS], ts[kBT / kWave][kTS];
     __shared__ float sum[kNP];
+    __shared__ float gb2[kBT / kWave][kH];       // of the samples whose do may not be finite
     __shared__ double lsum[kBT / kWave];
     const int t = threadIdx.x, l = lane_id(), i = l & 15, g = l >> 4;
+    (&gb2[0][0])[t] = 0.f;
+    static_assert(kBT == kBT / kWave * kH, "one value a thread");
     for (int e = t; e < 8 * kWave; e += kBT) {
         const int q = e / kWave, el = e % kWave, ei = el & 15, eg = el >> 4, row = 16 * (q >> 1) + ei;
         v8s a, b;
@@ -616,7 +637,7 @@ __global__ void __launch_bounds__(kBT, 2) k_mlp_grad_mfma(const float* __restric
 #pragma unroll
     for (int m = 0; m < 4; ++m) {
         v2s bp[3];
-        split3(v2f{P[oB1 + 16 * m + i], 0.f}, bp);
+        split3<true>(v2f{P[oB1 + 16 * m + i], 0.f}, bp);
 #pragma unroll
         for (int j = 0; j < 4; ++j) {
             const short wv = bf16_bits(P[oW1 + (16 * m + i) * kFP + 4 * (g & 1) + j]);
@@ -640,6 +661,10 @@ __global__ void __launch_bounds__(kBT, 2) k_mlp_grad_mfma(const float* __restric
     }
     float gb3 = 0.f;
     double loss = 0;
+    // The loss of any one sample whose do may round to an infinite bfloat16 (an
+    // infinity or NaN keeps it there for good): asked once a pair, where a test
+    // of the eight do's took 4 % of the kernel.
+    const double far_e = 0.99 * kBf16Over / (2.0 * inv_n), far_loss = far_e * far_e;
     __syncthreads();
     const int64_t npairs = (n + kTS - 1) / kTS;
     const int64_t waves = static_cast<int64_t>(gridDim.x) * (kBT / kWave);
@@ -699,8 +724,9 @@ __global__ void __launch_bounds__(kBT, 2) k_mlp_grad_mfma(const float* __restric
                 gb3 += dO[j];
             }
             v2s p01[3], p23[3];
-            split3(v2f{dO[0], dO[1]}, p01);
-            split3(v2f{dO[2], dO[3]}, p23);
+            *reinterpret_cast<v4f*>(&T[16 * u + 4 * g]) = dO;       // (for the far case below)
+            split3<false>(v2f{dO[0], dO[1]}, p01);
+            split3<false>(v2f{dO[2], dO[3]}, p23);
 #pragma unroll
             for (int c = 0; c < 3; ++c) dp[u][c] = __builtin_shufflevector(p01[c], p23[c], 0, 1, 2, 3);
             // dz1 = [z1 > 0] do u, then gW1 and gb1
@@ -724,12 +750,39 @@ __global__ void __launch_bounds__(kBT, 2) k_mlp_grad_mfma(const float* __restric
         __builtin_amdgcn_sched_barrier(0);
         // contractions over the 32 samples: slots 8g..8g+3 hold tile 0's
         // samples 4g..4g+3, slots 8g+4..8g+7 tile 1's
+        const bool far = __any(!(loss < far_loss));
+        if (far) {      // split again, for any do; and gb2 here: 0 x inf in its product would be NaN for the dead units
+            __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+#pragma unroll
+            for (int u = 0; u < 2; ++u) {
+                const v4f x = *reinterpret_cast<const v4f*>(&T[16 * u + 4 * g]);
+                v2s p01[3], p23[3];
+                split3<true>(v2f{x[0], x[1]}, p01);
+                split3<true>(v2f{x[2], x[3]}, p23);
+#pragma unroll
+                for (int c = 0; c < 3; ++c) dp[u][c] = __builtin_shufflevector(p01[c], p23[c], 0, 1, 2, 3);
+            }
+#pragma unroll
+            for (int m = 0; m < 4; ++m) {
+                float v = 0.f;
+#pragma unroll
+                for (int u = 0; u < 2; ++u)
+#pragma unroll
+                    for (int j = 0; j < 4; ++j) {
+                        const float x = (bf16_value(dp[u][0][j]) + bf16_value(dp[u][1][j])) + bf16_value(dp[u][2][j]);
+                        v += a2n[u][m][j] ? x : 0.f;
+                    }
+                v += __shfl_xor(v, 16);
+                v += __shfl_xor(v, 32);
+                if (g == 0) gb2[wave_id()][16 * m + i] += v;
+            }
+        }
         v8s d[3];
 #pragma unroll
         for (int c = 0; c < 3; ++c) d[c] = join(dp[0][c], dp[1][c]);
         const v8s dsel = (i & 3) == 0 ? d[0] : (i & 3) == 1 ? d[1] : d[2];
         const v8s none = {0, 0, 0, 0, 0, 0, 0, 0};
-        const v8s d3 = i < 3 ? dsel : none, d2 = i >= 4 && i < 7 ? dsel : none;
+        const v8s d3 = i < 3 ? dsel : none, d2 = !far && i >= 4 && i < 7 ? dsel : none;
         v8s a1[4];
 #pragma unroll
         for (int k = 0; k < 4; ++k) a1[k] = join(a1n[0][k], a1n[1][k]);
@@ -767,7 +820,7 @@ __global__ void __launch_bounds__(kBT, 2) k_mlp_grad_mfma(const float* __restric
                     if (i == kFP) sum[oB1 + h] += gw1[m][j];
                     const float v = gv[m][j] + __shfl_down(gv[m][j], 1) + __shfl_down(gv[m][j], 2);
                     if (i == 0) sum[oW3 + h] += v;
-                    if (i == 4) sum[oB2 + h] += v;
+                    if (i == 4) sum[oB2 + h] += v + gb2[w][h];
                 }
             if (l == 0) {        // (every lane of a group holds the group's samples' values)
                 sum[oB3] += gb3;
