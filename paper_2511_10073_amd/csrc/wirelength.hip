@@ -137,6 +137,42 @@ __device__ __forceinline__ double coord(const float (&v), float2 off, int c) {
     return static_cast<double>(v) + static_cast<double>((c & 1) ? off.y : off.x);
 }
 
+// One net by one thread, a column at a time.
+template <int P>
+__device__ __forceinline__ void wa_alone(const float* __restrict__ pos, const int32_t* __restrict__ pin_node,
+                                         const float* __restrict__ pin_off, int p0, int p1, double inv_g, double* tot,
+                                         const int32_t* __restrict__ place, double* __restrict__ pin_g) {
+    constexpr int C = 2 * P;
+#pragma unroll 1
+    for (int c = 0; c < C; ++c) {
+        const auto at = [&](int p) {
+            return static_cast<double>(pos[static_cast<int64_t>(pin_node[p]) * C + c]) +
+                   static_cast<double>(pin_off[2 * p + (c & 1)]);
+        };
+        ColAcc a{-1e300, 1e300, 0, 0, 0, 0};
+#pragma unroll 1
+        for (int p = p0; p < p1; ++p) {
+            const double x = at(p);
+            a.hi = __builtin_fmax(a.hi, x);
+            a.lo = __builtin_fmin(a.lo, x);
+        }
+#pragma unroll 1
+        for (int p = p0; p < p1; ++p) {
+            const double x = at(p), f = wexp((x - a.hi) * inv_g), h = wexp((a.lo - x) * inv_g);
+            a.sp += f;
+            a.tp += x * f;
+            a.sm += h;
+            a.tm += x * h;
+        }
+        const double w = a.tp / a.sp - a.tm / a.sm;
+#pragma unroll
+        for (int q = 0; q < P; ++q) tot[q] += q == c / 2 ? w : 0.0;
+        if (!pin_g) continue;
+#pragma unroll 1
+        for (int p = p0; p < p1; ++p) pin_g[static_cast<int64_t>(place[p]) * C + c] = gpin(at(p), a, inv_g);
+    }
+}
+
 // The nets of up to kWave pins, kBT of them a workgroup.  Their pins are
 // consecutive, so they are read with one lane a pin (coalesced node and offset
 // loads, every gather in flight) in runs of whole nets of at most kRun pins;
@@ -168,20 +204,28 @@ __device__ __forceinline__ void wa_batch(const float* __restrict__ pos, const in
     __shared__ double ex[2][kRun];              // [axis][maximum, minimum] of each net; then the weights' float32 pairs
     auto es = [&](int c, int side) { return reinterpret_cast<float*>(ex[c]) + side * kRun; };
     __shared__ uint8_t owner[kRun];
-    __shared__ int bstart[kBT], blen[kBT], cnt[kBT / kWave], stop_q[2];
+    __shared__ int bstart[kBT], blen[kBT], cnt[kBT / kWave], stop_q[2], down;
     const int t = threadIdx.x;
+    if (t == 0) down = 0;
     const int64_t c0 = static_cast<int64_t>(batch) * kBT, e = c0 + t;
     const int64_t last = c0 + kBT < n_nets ? c0 + kBT : n_nets;
     const int first = net_ptr[c0];
     const int p0 = net_ptr[e < last ? e : last], p1 = net_ptr[e < last ? e + 1 : last];
     const bool big = p1 - p0 > kWave;
     int nb;
-    const int k = block_rank<kBT>(big, cnt, &nb);
+    const int k = block_rank<kBT>(big, cnt, &nb);      // (its barriers follow down = 0)
     if (big) {
         bstart[k] = p0;
         blen[k] = p1 - p0;
     }
+    if (p1 < p0) down = 1;
     __syncthreads();
+    // A net_ptr that decreases is no netlist, but the host has not seen it: the
+    // count of the pins below might not end, or leave the nets' ranges.
+    if (down) {
+        if (p1 > p0 && !big) wa_alone<P>(pos, pin_node, pin_off, p0, p1, inv_g, tot, place, pin_g);
+        return;
+    }
     // the pins without the big nets' are counted from 0; pins of big nets
     // before place q of that count
     auto shift = [&](int q) {
