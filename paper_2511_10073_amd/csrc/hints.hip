@@ -390,6 +390,13 @@ __global__ void k_tile_carry(const int32_t* __restrict__ tile_start, int nbins, 
 // the bins of their window (with pruning, those that kept the edge).  A bin
 // row's window is walked slot by slot (row-major, out-of-grid slots empty);
 // wpre[b][slot] gets the entries of bin row b before that slot.
+// Walks of more than kWalkSlots slots get a launch of their own, a thread a
+// row, also where the scan has one launch (ScanJob::ahead): its one workgroup
+// takes four rows a thread, one after another.  A refinement of 3 rounds at
+// 2,000 cells, with the walks inside and ahead: 9 slots (32 x 32 bins) 404 and
+// 399 us, 25 slots (16 x 16) 455 and 422, 49 slots (64 x 64) 1046 and 580, 361
+// slots 5050 and 1610.
+constexpr int kWalkSlots = 9;
 struct HintRowScan {
     static constexpr int K = 1;
     static constexpr bool kTotal = false, kHeavy = true;
@@ -880,8 +887,9 @@ void build_hints(Graph& g, const float* pos, int32_t ncols, hipStream_t s, bool 
     // 6. row counts and offsets (execution order)
     if (bin_hints) g.wpre.ensure(static_cast<size_t>(nbins) * wslots + 1, s);
     g.i64a.ensure(1, s);
-    run_scans(scan_job(HintRowScan{a, N, g.nmac.p, g.nwin.p, g.mstart.p, g.wpre.p, g.xhint_rp.p, g.i64a.p}, N),
-              g.scan_tmp, s);
+    auto rows = scan_job(HintRowScan{a, N, g.nmac.p, g.nwin.p, g.mstart.p, g.wpre.p, g.xhint_rp.p, g.i64a.p}, N);
+    rows.ahead = bin_hints && wslots > kWalkSlots;
+    run_scans(rows, g.scan_tmp, s);
     // Every entry is one side of a (cell, macro) pair or of a (hint cell,
     // window bin) pair, so the entries number at most twice the pairs plus
     // twice the hint cells times the window slots: the entry array is sized

@@ -23,7 +23,8 @@
 // of its own before them, with consecutive items in consecutive lanes: the
 // 2.7M execution rows took 174 us inside the tile sums, eight items a thread,
 // and take 166 that way with the cells' areas and weights formed as well
-// (which had a kernel of 147 us).
+// (which had a kernel of 147 us).  Up to kScanSmall items it runs inside the one
+// launch, unless the job asks for that launch there as well (ahead).
 #pragma once
 
 #include "ahr_internal.hpp"
@@ -116,9 +117,11 @@ struct ScanJob {
     int64_t tiles = 0;       // 0: nothing to do
     int rounds = 0;          // kScanBT x kScanPer<F> items each, per tile
     int64_t* sums = nullptr; // [tiles][K]
+    int ahead = 0;           // a heavy job's first() gets a launch of its own in the small form too
 };
 
-template <class F>
+// Ahead: first() has run.
+template <bool Ahead, class F>
 __device__ __forceinline__ void scan_small(const ScanJob<F>& j, int64_t (*red)[F::K]) {
     constexpr int K = F::K;
     constexpr int64_t kStep = static_cast<int64_t>(kScanSmallBT) * kSmallPer;
@@ -126,13 +129,13 @@ __device__ __forceinline__ void scan_small(const ScanJob<F>& j, int64_t (*red)[F
     Pack<K> carry{}, total{}, tot;
     if constexpr (F::kTotal) {
         for (int64_t b = 0; b < j.n; b += kStep) {
-            block_scan_pack<kScanSmallBT, K>(scan_load<true, kSmallPer>(j.f, j.n, b + threadIdx.x * kSmallPer, p), red, &tot);
+            block_scan_pack<kScanSmallBT, K>(scan_load<!Ahead, kSmallPer>(j.f, j.n, b + threadIdx.x * kSmallPer, p), red, &tot);
             pack_add(total, tot);
         }
     }
     for (int64_t b = 0; b < j.n; b += kStep) {
         const int64_t base = b + threadIdx.x * kSmallPer;
-        Pack<K> run = block_scan_pack<kScanSmallBT, K>(scan_load<!F::kTotal, kSmallPer>(j.f, j.n, base, p), red, &tot);
+        Pack<K> run = block_scan_pack<kScanSmallBT, K>(scan_load<!F::kTotal && !Ahead, kSmallPer>(j.f, j.n, base, p), red, &tot);
         pack_add(run, carry);
         scan_emit<kSmallPer>(j.f, j.n, base, run, p, total);
         pack_add(carry, tot);
@@ -204,12 +207,12 @@ struct NoScan {
     __device__ void done(const Pack<1>&) const {}
 };
 
-template <class A, class B, class C>
+template <bool Ahead, class A, class B, class C>
 __global__ void __launch_bounds__(kScanSmallBT) k_scan_small(ScanJob<A> a, ScanJob<B> b, ScanJob<C> c) {
     __shared__ int64_t red[kScanSmallBT / kWave * (A::K > B::K ? (A::K > C::K ? A::K : C::K) : (B::K > C::K ? B::K : C::K))];
-    if (blockIdx.x == 0) scan_small(a, reinterpret_cast<int64_t(*)[A::K]>(red));
-    else if (blockIdx.x == 1) scan_small(b, reinterpret_cast<int64_t(*)[B::K]>(red));
-    else scan_small(c, reinterpret_cast<int64_t(*)[C::K]>(red));
+    if (blockIdx.x == 0) scan_small<Ahead>(a, reinterpret_cast<int64_t(*)[A::K]>(red));
+    else if (blockIdx.x == 1) scan_small<false>(b, reinterpret_cast<int64_t(*)[B::K]>(red));
+    else scan_small<false>(c, reinterpret_cast<int64_t(*)[C::K]>(red));
 }
 
 template <class A, class B, class C>
@@ -254,7 +257,16 @@ template <class A, class B = NoScan, class C = NoScan>
 void run_scans(ScanJob<A> a, DevBuf<int64_t>& tmp, hipStream_t s, ScanJob<B> b = {}, ScanJob<C> c = {}) {
     if (a.n <= kScanSmall && b.n <= kScanSmall && c.n <= kScanSmall) {
         const unsigned jobs = c.tiles ? 3 : b.tiles ? 2 : 1;
-        hipLaunchKernelGGL((k_scan_small<A, B, C>), dim3(jobs), dim3(kScanSmallBT), 0, s, a, b, c);
+        if constexpr (A::kHeavy) {
+            if (a.ahead && a.n > 0) {
+                hipLaunchKernelGGL(k_scan_first<A>, dim3(grid_for(a.n, kScanBT)), dim3(kScanBT), 0, s, a);
+                AHR_LAUNCHED("k_scan_first");
+                hipLaunchKernelGGL((k_scan_small<true, A, B, C>), dim3(jobs), dim3(kScanSmallBT), 0, s, a, b, c);
+                AHR_LAUNCHED("k_scan_small");
+                return;
+            }
+        }
+        hipLaunchKernelGGL((k_scan_small<false, A, B, C>), dim3(jobs), dim3(kScanSmallBT), 0, s, a, b, c);
         AHR_LAUNCHED("k_scan_small");
         return;
     }
