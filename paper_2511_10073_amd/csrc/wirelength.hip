@@ -184,25 +184,33 @@ __device__ __forceinline__ void wa_alone(const float* __restrict__ pos, const in
 //
 // What bounds it: the position gathers (HPWL, which makes the same ones, takes
 // 134 us at 1.1M cells) and the scattered stores of the gradient, with the
-// waves in flight, which the LDS limits: the nets' extremes lie where the
-// weights then go, and the means where the coordinates were, so that four
-// workgroups fit a CU instead of three (wa at 2.2M cells and 2 columns: 480
-// -> 455 us, 751 -> 681 at 4).  Against one thread a net, over nets sorted by
-// size, with the pins in registers and the gradients in pin order, a call
-// takes 455 us for 786 (2.2M cells, 2 columns), 681 for 948 (4 columns), 163
-// for 276 (200k cells, 4 columns) and 41 for 64 (2k cells, 2 columns).
+// waves in flight, which LDS and registers limit: the nets' extremes lie where
+// the weights then go, and the means where the coordinates were, so that four
+// workgroups fit a CU instead of three, and the large nets beside the batches
+// take a few column pairs at a time.  A net's thread reads a pin with two
+// 16-byte reads and several pins at once: in arrays an axis, a pin after
+// another, its loops were the longest part of a small netlist's call (7,000
+// cells, 8 columns: 133 us for 101, 105 for 72 without the gradient).
+// Against one thread a net, over nets sorted by size, with the pins in
+// registers and the gradients in pin order, a call takes, at 2.2M cells and 2,
+// 4 and 8 columns, 436, 626 and 1206 us for 792, 956 and 1348, without the
+// gradient 189, 310 and 604 for 368, 420 and 535; at 2,000 cells 48, 74 and 123
+// for 82, 119 and 194, without it 25, 38 and 71 for 28, 40 and 65.
 constexpr int kRun = 1024;
+constexpr int kMaxPins = 4;                             // pins whose coordinates a thread reads at a time for the extremes
+template <int P, bool Grad>
+constexpr int kSumPins = Grad && P > 1 ? 2 : 4;         // and for the sums: more take registers of the gradient's waves
 
-template <int P>
+template <int P, bool Grad>
 __device__ __forceinline__ void wa_batch(const float* __restrict__ pos, const int32_t* __restrict__ net_ptr,
                                          int32_t n_nets, int32_t batch, const int32_t* __restrict__ pin_node,
                                          const float* __restrict__ pin_off, double inv_g, double* tot,
                                          const int32_t* __restrict__ place, double* __restrict__ pin_g) {
-    constexpr int C = 2 * P, U = kRun / kBT;
+    constexpr int C = 2 * P, U = kRun / kBT, S = kSumPins<P, Grad>;
     static_assert(kRun >= 4 * kBT, "a run's coordinates leave room for the nets' means");
-    __shared__ double xs[2][kRun];              // the axes' coordinates; then [mean, reciprocal sum][side] of each net
-    __shared__ double ex[2][kRun];              // [axis][maximum, minimum] of each net; then the weights' float32 pairs
-    auto es = [&](int c, int side) { return reinterpret_cast<float*>(ex[c]) + side * kRun; };
+    __shared__ double2 xy[kRun];                // a pair's coordinates; then [mean, reciprocal sum] of each net
+    __shared__ float4 ew[kRun];                 // the weights (x max, x min, y max, y min); before, each net's extremes
+    double2* ex = reinterpret_cast<double2*>(ew);
     __shared__ uint8_t owner[kRun];
     __shared__ int bstart[kBT], blen[kBT], cnt[kBT / kWave], stop_q[2], down;
     const int t = threadIdx.x;
@@ -257,107 +265,114 @@ __device__ __forceinline__ void wa_batch(const float* __restrict__ pos, const in
             pin[u] = first + q + shift(q);
             v[u] = pin_node[pin[u]];
             off[u] = reinterpret_cast<const float2*>(pin_off)[pin[u]];
-            at_g[u] = pin_g ? place[pin[u]] : 0;
+            at_g[u] = Grad ? place[pin[u]] : 0;
         }
         float g[U][C];
 #pragma unroll
         for (int u = 0; u < U; ++u) load_row<C>(pos + static_cast<int64_t>(v[u]) * C, g[u]);
         const int a = q0 - at, b = q1 - at;        // this thread's net inside the run
         for (int pr = 0; pr < P; ++pr) {
-            double x[U][2];
+            double2 x[U];
 #pragma unroll
-            for (int u = 0; u < U; ++u)
+            for (int u = 0; u < U; ++u) {
+                float gx = g[u][0], gy = g[u][1];
 #pragma unroll
-                for (int c = 0; c < 2; ++c) {
-                    float gc = g[u][c];
-#pragma unroll
-                    for (int q = 1; q < P; ++q) gc = pr == q ? g[u][2 * q + c] : gc;
-                    x[u][c] = coord(gc, off[u], c);
-                    xs[c][t + u * kBT] = x[u][c];
+                for (int q = 1; q < P; ++q) {
+                    gx = pr == q ? g[u][2 * q] : gx;
+                    gy = pr == q ? g[u][2 * q + 1] : gy;
                 }
-            __syncthreads();
-            if (in_run) {
-                double hi[2] = {-1e300, -1e300}, lo[2] = {1e300, 1e300};
-                for (int i = a; i < b; ++i) {
-                    if (pr == 0) owner[i] = static_cast<uint8_t>(t);
-#pragma unroll
-                    for (int c = 0; c < 2; ++c) {
-                        const double y = xs[c][i];
-                        hi[c] = __builtin_fmax(hi[c], y);
-                        lo[c] = __builtin_fmin(lo[c], y);
-                    }
-                }
-#pragma unroll
-                for (int c = 0; c < 2; ++c) {
-                    ex[c][t] = hi[c];
-                    ex[c][kBT + t] = lo[c];
-                }
+                x[u] = make_double2(coord(gx, off[u], 0), coord(gy, off[u], 1));
+                xy[t + u * kBT] = x[u];
             }
             __syncthreads();
-            float ep[U][2], em[U][2];
+            if (in_run) {
+                double2 hi = {-1e300, -1e300}, lo = {1e300, 1e300};
+                for (int i = a; i < b; i += kMaxPins) {           // kMaxPins pins' reads at once (the last one repeats)
+                    double2 y[kMaxPins];
+#pragma unroll
+                    for (int u = 0; u < kMaxPins; ++u) {
+                        const int j = i + u < b ? i + u : b - 1;
+                        if (pr == 0) owner[j] = static_cast<uint8_t>(t);
+                        y[u] = xy[j];
+                    }
+#pragma unroll
+                    for (int u = 0; u < kMaxPins; ++u) {
+                        hi.x = __builtin_fmax(hi.x, y[u].x);
+                        lo.x = __builtin_fmin(lo.x, y[u].x);
+                        hi.y = __builtin_fmax(hi.y, y[u].y);
+                        lo.y = __builtin_fmin(lo.y, y[u].y);
+                    }
+                }
+                ex[2 * t] = make_double2(hi.x, lo.x);
+                ex[2 * t + 1] = make_double2(hi.y, lo.y);
+            }
+            __syncthreads();
+            float4 w[U];
             int own[U];
 #pragma unroll
             for (int u = 0; u < U; ++u) {
                 own[u] = owner[t + u * kBT < m ? t + u * kBT : m - 1];
-#pragma unroll
-                for (int c = 0; c < 2; ++c) {
-                    ep[u][c] = expf(static_cast<float>((x[u][c] - ex[c][own[u]]) * inv_g));
-                    em[u][c] = expf(static_cast<float>((ex[c][kBT + own[u]] - x[u][c]) * inv_g));
-                }
+                const double2 ax = ex[2 * own[u]], ay = ex[2 * own[u] + 1];
+                w[u].x = expf(static_cast<float>((x[u].x - ax.x) * inv_g));
+                w[u].y = expf(static_cast<float>((ax.y - x[u].x) * inv_g));
+                w[u].z = expf(static_cast<float>((x[u].y - ay.x) * inv_g));
+                w[u].w = expf(static_cast<float>((ay.y - x[u].y) * inv_g));
             }
             __syncthreads();
 #pragma unroll
-            for (int u = 0; u < U; ++u)
-#pragma unroll
-                for (int c = 0; c < 2; ++c) {
-                    es(c, 0)[t + u * kBT] = ep[u][c];
-                    es(c, 1)[t + u * kBT] = em[u][c];
-                }
+            for (int u = 0; u < U; ++u) ew[t + u * kBT] = w[u];
             __syncthreads();
-            double sp[2] = {0, 0}, tp[2] = {0, 0}, sm[2] = {0, 0}, tm[2] = {0, 0};
+            double2 sp = {0, 0}, tp = {0, 0}, sm = {0, 0}, tm = {0, 0};
             if (in_run) {
-                for (int i = a; i < b; ++i)
+                const auto add = [&](const double2& y, const float4& f) {
+                    sp.x += f.x;
+                    tp.x += y.x * f.x;
+                    sm.x += f.y;
+                    tm.x += y.x * f.y;
+                    sp.y += f.z;
+                    tp.y += y.y * f.z;
+                    sm.y += f.w;
+                    tm.y += y.y * f.w;
+                };
+                int i = a;
+#pragma unroll 1
+                for (; i + S <= b; i += S) {               // S pins' reads at once, added in order
+                    double2 y[S];
+                    float4 f[S];
 #pragma unroll
-                    for (int c = 0; c < 2; ++c) {
-                        const double y = xs[c][i], f = es(c, 0)[i], h = es(c, 1)[i];
-                        sp[c] += f;
-                        tp[c] += y * f;
-                        sm[c] += h;
-                        tm[c] += y * h;
+                    for (int u = 0; u < S; ++u) {
+                        y[u] = xy[i + u];
+                        f[u] = ew[i + u];
                     }
-                double w = 0;
 #pragma unroll
-                for (int c = 0; c < 2; ++c) w += tp[c] / sp[c] - tm[c] / sm[c];
+                    for (int u = 0; u < S; ++u) add(y[u], f[u]);
+                }
+#pragma unroll 1
+                for (; i < b; ++i) add(xy[i], ew[i]);
+                const double wa = (0.0 + (tp.x / sp.x - tm.x / sm.x)) + (tp.y / sp.y - tm.y / sm.y);
 #pragma unroll
-                for (int q = 0; q < P; ++q) tot[q] += pr == q ? w : 0.0;
+                for (int q = 0; q < P; ++q) tot[q] += pr == q ? wa : 0.0;
             }
             __syncthreads();
-            if (in_run && pin_g) {
-#pragma unroll
-                for (int c = 0; c < 2; ++c) {
-                    const double rp = 1.0 / sp[c], rm = 1.0 / sm[c];
-                    xs[c][t] = rp;
-                    xs[c][kBT + t] = rm;
-                    xs[c][2 * kBT + t] = tp[c] * rp;
-                    xs[c][3 * kBT + t] = tm[c] * rm;
-                }
+            if constexpr (!Grad) continue;
+            if (in_run) {
+                const double2 rp = {1.0 / sp.x, 1.0 / sp.y}, rm = {1.0 / sm.x, 1.0 / sm.y};
+                xy[4 * t] = make_double2(rp.x, rm.x);
+                xy[4 * t + 1] = make_double2(tp.x * rp.x, tm.x * rm.x);
+                xy[4 * t + 2] = make_double2(rp.y, rm.y);
+                xy[4 * t + 3] = make_double2(tp.y * rp.y, tm.y * rm.y);
             }
             __syncthreads();
-            if (pin_g) {
 #pragma unroll
-                for (int u = 0; u < U; ++u) {
-                    double d[2];
-#pragma unroll
-                    for (int c = 0; c < 2; ++c) {
-                        const double pp = static_cast<double>(ep[u][c]) * xs[c][own[u]];
-                        const double pm = static_cast<double>(em[u][c]) * xs[c][kBT + own[u]];
-                        d[c] = pp * (1.0 + (x[u][c] - xs[c][2 * kBT + own[u]]) * inv_g) -
-                               pm * (1.0 - (x[u][c] - xs[c][3 * kBT + own[u]]) * inv_g);
-                    }
-                    if (t + u * kBT < m)
-                        *reinterpret_cast<double2*>(pin_g + static_cast<int64_t>(at_g[u]) * C + 2 * pr) =
-                            make_double2(d[0], d[1]);
-                }
+            for (int u = 0; u < U; ++u) {
+                const auto d = [&](double y, float fp, float fm, const double2& r, const double2& mean) {
+                    const double pp = static_cast<double>(fp) * r.x, pm = static_cast<double>(fm) * r.y;
+                    return pp * (1.0 + (y - mean.x) * inv_g) - pm * (1.0 - (y - mean.y) * inv_g);
+                };
+                const double2* net = xy + 4 * own[u];
+                const double dx = d(x[u].x, w[u].x, w[u].y, net[0], net[1]), dy = d(x[u].y, w[u].z, w[u].w, net[2], net[3]);
+                if (t + u * kBT < m)
+                    *reinterpret_cast<double2*>(pin_g + static_cast<int64_t>(at_g[u]) * C + 2 * pr) = make_double2(dx, dy);
             }
             __syncthreads();
         }
@@ -400,14 +415,12 @@ __device__ __forceinline__ Run run_merge(Run a, Run b, double sgn_inv_g) {
     return Run{a.m, a.s + b.s * f, a.t + b.t * f};
 }
 
-// The nets above kWave pins, one workgroup each (listed once per index):
-// one pass for the shifted sums of every column, one for the gradients.
 // A net above kWave pins by one workgroup: one pass for the shifted sums of
 // every column, one for the gradients, kBigU pins a lane in flight.
 constexpr int kBigU = 4;
 
 // The lane's pins p, p + kBT, ... (clamped to the net's last): rows and offsets.
-template <int C>
+template <int C, int S>
 __device__ __forceinline__ void big_pins(const float* __restrict__ pos, const int32_t* __restrict__ pin_node,
                                          const float* __restrict__ pin_off, int p, int p1, float (&v)[kBigU][C],
                                          float2 (&off)[kBigU]) {
@@ -419,10 +432,11 @@ __device__ __forceinline__ void big_pins(const float* __restrict__ pos, const in
         off[u] = reinterpret_cast<const float2*>(pin_off)[q];
     }
 #pragma unroll
-    for (int u = 0; u < kBigU; ++u) load_row<C>(pos + static_cast<int64_t>(node[u]) * C, v[u]);
+    for (int u = 0; u < kBigU; ++u) load_row<C>(pos + static_cast<int64_t>(node[u]) * S, v[u]);
 }
 
-template <int P>
+// P column pairs of rows of S columns.
+template <int P, int S>
 __device__ __forceinline__ void wa_big(const float* __restrict__ pos, const int32_t* __restrict__ pin_node,
                                        const float* __restrict__ pin_off, int p0, int p1, double inv_g, double* tot,
                                        const int32_t* __restrict__ place, double* __restrict__ pin_g) {
@@ -437,7 +451,7 @@ __device__ __forceinline__ void wa_big(const float* __restrict__ pos, const int3
         rm[c] = Run{1e300, 0, 0};
     }
     for (int p = p0 + threadIdx.x; p < p1; p += kBigU * kBT) {
-        big_pins<C>(pos, pin_node, pin_off, p, p1, v, off);
+        big_pins<C, S>(pos, pin_node, pin_off, p, p1, v, off);
 #pragma unroll
         for (int u = 0; u < kBigU; ++u) {
             if (p + u * kBT >= p1) break;
@@ -482,11 +496,11 @@ __device__ __forceinline__ void wa_big(const float* __restrict__ pos, const int3
     }
     if (pin_g) {
         for (int p = p0 + threadIdx.x; p < p1; p += kBigU * kBT) {
-            big_pins<C>(pos, pin_node, pin_off, p, p1, v, off);
+            big_pins<C, S>(pos, pin_node, pin_off, p, p1, v, off);
 #pragma unroll
             for (int u = 0; u < kBigU; ++u) {
                 if (p + u * kBT >= p1) break;
-                const int64_t k = static_cast<int64_t>(place[p + u * kBT]) * C;
+                const int64_t k = static_cast<int64_t>(place[p + u * kBT]) * S;
 #pragma unroll
                 for (int c = 0; c < C; ++c) {
                     const ColAcc a{rp[c].m, rm[c].m, rp[c].s, rp[c].t, rm[c].s, rm[c].t};
@@ -506,13 +520,12 @@ __device__ __forceinline__ void wa_big(const float* __restrict__ pos, const int3
 // The net pass: workgroups [0, n_big) take a large net each (first, as the
 // longest of them outlast a batch), the others a batch of kBT nets.
 // Workgroup totals to partial[blockIdx.x].
-template <int P>
-__global__ void __launch_bounds__(kBT) k_wa_nets(const float* __restrict__ pos, const int32_t* __restrict__ net_ptr,
-                                                 int32_t n_nets, const int32_t* __restrict__ big, int32_t n_big,
-                                                 const int32_t* __restrict__ pin_node,
-                                                 const float* __restrict__ pin_off, double inv_g,
-                                                 double* __restrict__ partial,
-                                                 const int32_t* __restrict__ place, double* __restrict__ pin_g) {
+template <int P, bool Grad>
+__global__ void __launch_bounds__(kBT, P == 4 && Grad ? 1 : 4)
+    k_wa_nets(const float* __restrict__ pos, const int32_t* __restrict__ net_ptr, int32_t n_nets,
+              const int32_t* __restrict__ big, int32_t n_big, const int32_t* __restrict__ pin_node,
+              const float* __restrict__ pin_off, double inv_g, double* __restrict__ partial,
+              const int32_t* __restrict__ place, double* __restrict__ pin_g) {
     __shared__ double red[kBT / kWave];
     double tot[P];
 #pragma unroll
@@ -520,9 +533,22 @@ __global__ void __launch_bounds__(kBT) k_wa_nets(const float* __restrict__ pos, 
     const int32_t blk = static_cast<int32_t>(blockIdx.x);
     if (blk < n_big) {
         const int e = big[blk];
-        wa_big<P>(pos, pin_node, pin_off, net_ptr[e], net_ptr[e + 1], inv_g, tot, place, pin_g);
+        // a few column pairs at a time: all four at once take 233 registers, and the
+        // batches beside them run at two waves a SIMD
+        constexpr int T = P < 4 ? P : Grad ? 2 : 1;
+#pragma unroll 1
+        for (int q = 0; q < P; q += T) {
+            if (q) __syncthreads();
+            double part[T] = {};
+            wa_big<T, 2 * P>(pos + 2 * q, pin_node, pin_off, net_ptr[e], net_ptr[e + 1], inv_g, part, place,
+                             Grad ? pin_g + 2 * q : nullptr);
+#pragma unroll
+            for (int c = 0; c < P; ++c)
+#pragma unroll
+                for (int d = 0; d < T; ++d) tot[c] = c == q + d ? part[d] : tot[c];
+        }
     } else {
-        wa_batch<P>(pos, net_ptr, n_nets, blk - n_big, pin_node, pin_off, inv_g, tot, place, pin_g);
+        wa_batch<P, Grad>(pos, net_ptr, n_nets, blk - n_big, pin_node, pin_off, inv_g, tot, place, pin_g);
     }
 #pragma unroll
     for (int q = 0; q < P; ++q) {
@@ -598,8 +624,9 @@ void wa_p(const WlIndex& w, const float* pos, double inv_g, double* wl, float* g
     {
         ProfScope ps(kStageWa, s, bytes);
         if (grid) {
-            hipLaunchKernelGGL(k_wa_nets<P>, dim3(grid), dim3(kBT), 0, s, pos, nl.net_ptr, nl.n_nets, w.big.p, w.n_big,
-                               nl.pin_node, nl.pin_off, inv_g, partial.p, w.place.p, grad ? pin_g.p : nullptr);
+            hipLaunchKernelGGL((grad ? k_wa_nets<P, true> : k_wa_nets<P, false>), dim3(grid), dim3(kBT), 0, s, pos,
+                               nl.net_ptr, nl.n_nets, w.big.p, w.n_big, nl.pin_node, nl.pin_off, inv_g, partial.p,
+                               w.place.p, grad ? pin_g.p : nullptr);
             AHR_LAUNCHED("k_wa_nets");
         }
         if (grad) {
