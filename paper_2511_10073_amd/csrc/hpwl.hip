@@ -17,7 +17,9 @@
 // netlist without big nets).  8 lanes a net, which ran a chain of three
 // dependent loads with most lanes idle (60 % of the nets have 2 pins), and
 // one workgroup after another over the big nets took 61 us at 210k cells and
-// 4 columns (35 now), 158 at 1.1M (134), 390 at 2.2M and 8 columns (286).
+// 4 columns (35 now), 158 at 1.1M (134).  A net's thread reads a pin's pair in
+// one 16-byte read: in arrays an axis, calls with 8 columns took 41 us at 2,000
+// and 20,000 cells (29 now, 34 with the 8 lanes) and 275 at 2.2M (211, 373).
 //
 // ahr_hpwl draws the partial-sum buffer from the library's stream-ordered
 // pool for each call, so calls on different streams share no memory.
@@ -38,8 +40,11 @@ template <int P>
 constexpr int kWindow = P <= 2 ? 1024 : 512;
 
 // Big nets up to this many pins take one wave, longer ones the workgroup, as
-// does a batch's only big net: all of them by the workgroup, one after
-// another, took 42 us at 210k cells (33 with both rules).
+// does a batch's only big net.  At 7,000 and 210,000 cells (53 and 1,025 big
+// nets) and 4 columns a call takes 23 and 41 us; with up to four big nets of a
+// batch by the workgroup, one after another, 27 and 43; with all of them 28 and
+// 48; waves up to 512 pins 23 and 44, up to 8,192 23 and 41.  A batch's only
+// one by a wave is as fast (2,000 to 2.2M cells within 1 %).
 constexpr int kWaveNet = 2048;
 constexpr int kFewBig = 1;
 
@@ -99,7 +104,7 @@ __global__ void __launch_bounds__(kBT, 4) k_hpwl(const float* __restrict__ pos, 
                                               int32_t n_nets, int32_t per, const int32_t* __restrict__ pin_node,
                                               const float* __restrict__ pin_off, double* __restrict__ partial) {
     constexpr int T = kWindow<P>, U = T / kBT;
-    __shared__ double win[2 * P][T];
+    __shared__ double2 win[P][T];
     __shared__ double ext[2 * P][2][kBT / kWave];
     __shared__ double red[kBT / kWave];
     __shared__ int cnt[kBT / kWave];
@@ -162,16 +167,27 @@ __global__ void __launch_bounds__(kBT, 4) k_hpwl(const float* __restrict__ pos, 
 #pragma unroll
             for (int u = 0; u < U; ++u)
 #pragma unroll
-                for (int c = 0; c < 2 * P; ++c)
+                for (int c = 0; c < P; ++c)
                     win[c][threadIdx.x + u * kBT] =
-                        static_cast<double>(g[u][c]) + static_cast<double>((c & 1) ? oy[u] : ox[u]);
+                        make_double2(static_cast<double>(g[u][2 * c]) + static_cast<double>(ox[u]),
+                                     static_cast<double>(g[u][2 * c + 1]) + static_cast<double>(oy[u]));
             __syncthreads();
             const int a = q0 > at ? q0 - at : 0, b = q1 < at + T ? q1 - at : T;
-            for (int i = a; i < b; i += 4)           // four pins' reads at once (the last one repeats)
+            constexpr int R = 4;
+            for (int i = a; i < b; i += R) {         // R pins' reads at once (the last one repeats)
+                double2 x[R][P];
 #pragma unroll
-                for (int u = 0; u < 4; ++u)
+                for (int u = 0; u < R; ++u)
 #pragma unroll
-                    for (int c = 0; c < 2 * P; ++c) bound(win[c][i + u < b ? i + u : b - 1], lo[c], hi[c]);
+                    for (int c = 0; c < P; ++c) x[u][c] = win[c][i + u < b ? i + u : b - 1];
+#pragma unroll
+                for (int u = 0; u < R; ++u)
+#pragma unroll
+                    for (int c = 0; c < P; ++c) {
+                        bound(x[u][c].x, lo[2 * c], hi[2 * c]);
+                        bound(x[u][c].y, lo[2 * c + 1], hi[2 * c + 1]);
+                    }
+            }
             __syncthreads();
         }
         if (q1 > q0) add();
