@@ -170,6 +170,7 @@ class ProfScope {
 constexpr int kLongRow = 128;
 constexpr int kChunk = 2048;
 constexpr int kWholeChunks = 8;      // the most chunks of a row that one workgroup finishes
+constexpr int kFewChunks = 2;        // and as many as it may finish in any graph
 constexpr int kRbRows = 256;
 constexpr int kRbEntries = 1024;
 // Star nodes are averaged over their pins by their row's thread up to
@@ -190,7 +191,7 @@ struct RowClasses {
     int32_t n_long = 0, n_long_inst = 0;      // long rows, those below n_inst
     int32_t n_chunks = 0, n_chunks_inst = 0;  // chunks, those of long rows below n_inst
     int32_t n_chunks_net = 0;                 // those of long rows below the hint nodes
-    int32_t in_parts = 0;                     // chunks summed apart: a row has more than kWholeChunks
+    int32_t in_parts = 0;                     // chunks summed apart (rows_apart in filter.hip)
     int32_t n_rb = 0, n_rb_inst = 0;          // row blocks, those below n_inst
     int32_t has_rb = 0;                       // row blocks built (on first use of the row-block hop)
     int64_t nnz_inst = 0;                     // entries of rows below n_inst (netlist + hints)

@@ -117,9 +117,12 @@ struct LongRowScan {
     int32_t* chunk0;
     int32_t* chunk_row;
     int32_t* counts;       // long rows, those below n_inst, chunks, those below n_inst and below first_hint; and
-                           // whether a row has more than kWholeChunks
+                           // the most chunks of a row (0 where none has more than kFewChunks)
     __device__ Pack<1> first(int64_t r) const {
-        if (r == 0) counts[5] = 0;                  // before any item()
+        if (r == 0) {               // before any item()
+            counts[5] = 0;
+            __threadfence();
+        }
         return again(r);
     }
     __device__ Pack<1> again(int64_t r) const {
@@ -134,7 +137,7 @@ struct LongRowScan {
         }
         if (r == first_hint) counts[4] = c0;
         if (!nc) return;
-        if (nc > kWholeChunks) counts[5] = 1;
+        if (nc > kFewChunks) atomicMax(&counts[5], nc);
         long_rows[k] = static_cast<int32_t>(r);
         chunk0[k] = c0;
         for (int c = 0; c < nc; ++c) chunk_row[c0 + c] = k;
@@ -301,14 +304,31 @@ __device__ __forceinline__ void in_chunk(int n, const F& f) {
 // following ones: all of a row for its first, 0 for its others (whose
 // workgroups have nothing to do); or kApart, where every chunk is summed by a
 // workgroup of its own and the rows are added up by a launch of their own.
-// Whole rows save that launch (5 us a hop) where no row has more than
-// kWholeChunks chunks, 27.8 us for 26.1 + 4.8 a hop at 210k cells; taken
-// together with longer rows in parts they only lengthened the hop (2.2M cells:
-// 258 us for 249, 880k: 114 for 106).
+// Whole rows save that launch (5 us a hop): 27.8 us for 26.1 + 4.8 a hop at 210k
+// cells with hints; taken together with longer rows in parts they only
+// lengthened the hop (2.2M cells: 258 us for 249, 880k: 114 for 106).  But one
+// workgroup takes a row's chunks one after another, 2 to 3 us each, which must
+// not outlast the rest of the hop (rows_apart).
 struct Chunk {
     int nb, net, hb, n, li, take;
 };
 constexpr int kApart = kWholeChunks + 1;
+
+// Whether the long rows are summed in parts: where the longest has more chunks
+// than one workgroup takes, or so many that they are the hop.  Filters of 8
+// hops over one row of 2, 3, 4, 5 and 8 chunks, whole and in parts, at 4 columns:
+//   0.4M entries   78/73  101/74   123/74   131/91   180/96 us
+//   0.8M           87/87  111/88   136/88   159/90   229/93
+//   1.5M          112/130 128/130  157/131  186/130  264/130
+//   2.7M          166/184 167/184  182/184  203/183  282/183
+//   6.3M          335/350 334/349  334/350  335/350  342/349
+// (2 columns: the lines lie alike.)  Below 0.3M entries the launches are the
+// hop: 73/103 and 91/106 with 2 and 3 chunks at 0.23M.
+constexpr int64_t kEntriesPerChunk = 750000;
+
+bool rows_apart(int32_t longest, int64_t entries) {
+    return longest > kFewChunks && (longest > kWholeChunks || longest * kEntriesPerChunk > entries);
+}
 static_assert(kChunk < 1 << 12 && kApart < 1 << 7, "packing of a chunk");
 
 __device__ __forceinline__ int4 pack_chunk(const Chunk& c) {
@@ -320,21 +340,21 @@ __device__ __forceinline__ Chunk unpack_chunk(int4 w) {
 }
 
 __device__ __forceinline__ Chunk chunk_range(int c, const int32_t* long_rows, const int32_t* chunk_row,
-                                             const int32_t* chunk0, const int32_t* counts, const RowRef& m) {
+                                             const int32_t* chunk0, int apart, const RowRef& m) {
     const int li = chunk_row[c], r = long_rows[li];
     const int n0 = m.net_rp[r], ln = m.net_rp[r + 1] - n0, h0 = m.hint_rp[r], len = ln + (m.hint_rp[r + 1] - h0);
     const int at = (c - chunk0[li]) * kChunk, n = at + kChunk < len ? kChunk : len - at;
     const int net = at >= ln ? 0 : at + n < ln ? n : ln - at;
-    const int take = counts[5] ? kApart : at ? 0 : (len + kChunk - 1) / kChunk;
+    const int take = apart ? kApart : at ? 0 : (len + kChunk - 1) / kChunk;
     return {n0 + (at < ln ? at : ln), net, h0 + (at > ln ? at - ln : 0), n, li, take};
 }
 
 // The chunks' entries where no degrees are formed (k_chunk_absdeg).
 __global__ void k_chunk_ranges(RowRef m, int32_t n_chunks, const int32_t* __restrict__ long_rows,
                                const int32_t* __restrict__ chunk_row, const int32_t* __restrict__ chunk0,
-                               const int32_t* __restrict__ counts, int4* __restrict__ chunks) {
+                               int apart, int4* __restrict__ chunks) {
     const int64_t c = static_cast<int64_t>(blockIdx.x) * blockDim.x + threadIdx.x;
-    if (c < n_chunks) chunks[c] = pack_chunk(chunk_range(static_cast<int>(c), long_rows, chunk_row, chunk0, counts, m));
+    if (c < n_chunks) chunks[c] = pack_chunk(chunk_range(static_cast<int>(c), long_rows, chunk_row, chunk0, apart, m));
 }
 
 // One workgroup a chunk: its entries' range, which every later kernel takes
@@ -343,10 +363,10 @@ __global__ void k_chunk_ranges(RowRef m, int32_t n_chunks, const int32_t* __rest
 __global__ void __launch_bounds__(kBT) k_chunk_absdeg(RowRef m, const int32_t* __restrict__ long_rows,
                                                       const int32_t* __restrict__ chunk_row,
                                                       const int32_t* __restrict__ chunk0,
-                                                      const int32_t* __restrict__ counts, int4* __restrict__ chunks,
+                                                      int apart, int4* __restrict__ chunks,
                                                       double* __restrict__ partial) {
     __shared__ double red[2][kBT / kWave];
-    const Chunk d = chunk_range(blockIdx.x, long_rows, chunk_row, chunk0, counts, m);
+    const Chunk d = chunk_range(blockIdx.x, long_rows, chunk_row, chunk0, apart, m);
     if (threadIdx.x == 0) chunks[blockIdx.x] = pack_chunk(d);
     // the lane's hint entries t + u kBT (ascending), all loaded at once: a
     // net entry or a slot past the chunk reads the chunk's first hint slot
@@ -1827,7 +1847,7 @@ static void row_classes_end(int32_t N, int32_t n_inst, int32_t first_hint, RowCl
     rc.n_long_inst = n_inst < N ? v[1] : v[0];
     rc.n_chunks_inst = n_inst < N ? v[3] : v[2];
     rc.n_chunks_net = first_hint < N ? v[8] : v[2];
-    rc.in_parts = v[9];
+    rc.in_parts = rows_apart(v[9], rc.nnz_net_all + rc.nnz_hint_all) ? 1 : 0;
     rc.nnz_inst = static_cast<int64_t>(v[4]) + v[5];
     rc.has_rb = 0;
     rc.partial.ensure(static_cast<size_t>(rc.n_chunks) * 8 + 8, s);
@@ -1841,7 +1861,7 @@ void row_classes(const int32_t* net_rp, const int32_t* hint_rp, int32_t N, int32
     if (!rc.n_chunks) return;
     hipLaunchKernelGGL(k_chunk_ranges, dim3(grid_for(rc.n_chunks, kBT)), dim3(kBT), 0, s,
                        RowRef{net_rp, nullptr, hint_rp, nullptr}, rc.n_chunks, rc.long_rows.p, rc.chunk_row.p,
-                       rc.long_chunk0.p, rc.counts.p, rc.chunks.p);
+                       rc.long_chunk0.p, rc.in_parts, rc.chunks.p);
     AHR_LAUNCHED("k_chunk_ranges");
 }
 
@@ -1999,7 +2019,7 @@ void normalise_degrees(Graph& g, const ahr_filter_spec& spec, hipStream_t s) {
     }
     if (g.rc.n_long) {
         hipLaunchKernelGGL(k_chunk_absdeg, dim3(g.rc.n_chunks), dim3(kBT), 0, s, m, g.rc.long_rows.p, g.rc.chunk_row.p,
-                           g.rc.long_chunk0.p, g.rc.counts.p, g.rc.chunks.p, g.rc.partial.p);
+                           g.rc.long_chunk0.p, g.rc.in_parts, g.rc.chunks.p, g.rc.partial.p);
         AHR_LAUNCHED("k_chunk_absdeg");
         hipLaunchKernelGGL(k_long_deg_final, dim3(grid_for(static_cast<int64_t>(g.rc.n_long) * kWave, kBT)), dim3(kBT), 0, s, g.rc.n_long, g.rc.long_rows.p,
                            g.rc.long_chunk0.p, g.rc.partial.p, g.xqdeg.p, sigma, g.deg.p, g.scale.p, g.hsum.p);
