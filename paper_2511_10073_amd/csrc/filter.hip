@@ -102,6 +102,23 @@ __device__ __forceinline__ Floats<W> load_floats(const float* p) {
 
 // ---------------------------------------------------------------- row classes
 
+// Whether a graph's long rows are summed in parts (Chunk below): where the
+// longest has more chunks than one workgroup takes, or so many that they are
+// the hop.  Filters of 8 hops over one row of 2, 3, 4, 5 and 8 chunks, whole and
+// in parts, at 4 columns:
+//   0.4M entries   78/73  101/74   123/74   131/91   180/96 us
+//   0.8M           87/87  111/88   136/88   159/90   229/93
+//   1.5M          112/130 128/130  157/131  186/130  264/130
+//   2.7M          166/184 167/184  182/184  203/183  282/183
+//   6.3M          335/350 334/349  334/350  335/350  342/349
+// (2 columns: the lines lie alike.)  Below 0.3M entries the launches are the
+// hop: 73/103 and 91/106 with 2 and 3 chunks at 0.23M.
+constexpr int64_t kEntriesPerChunk = 750000;
+
+__device__ __forceinline__ bool rows_apart(int32_t chunks, int64_t entries) {
+    return chunks > kFewChunks && (chunks > kWholeChunks || chunks * kEntriesPerChunk > entries);
+}
+
 // The long rows with their chunks, in row order: long_rows[k] the k-th long
 // row, chunk0[k] its first chunk (the entry past the last row: the total),
 // chunk_row[c] the long row of chunk c; and the counts of those below n_inst.
@@ -112,17 +129,14 @@ struct LongRowScan {
     __device__ Pack<1> pack(const Pack<1>& p) const { return p; }
     const int32_t* net_rp;
     const int32_t* hint_rp;
-    int32_t n_inst, first_hint;
+    int32_t n, n_inst, first_hint;
     int32_t* long_rows;
     int32_t* chunk0;
     int32_t* chunk_row;
     int32_t* counts;       // long rows, those below n_inst, chunks, those below n_inst and below first_hint; and
-                           // the most chunks of a row (0 where none has more than kFewChunks)
+                           // whether the long rows are summed in parts
     __device__ Pack<1> first(int64_t r) const {
-        if (r == 0) {               // before any item()
-            counts[5] = 0;
-            __threadfence();
-        }
+        if (r == 0) counts[5] = 0;                  // before any item()
         return again(r);
     }
     __device__ Pack<1> again(int64_t r) const {
@@ -137,7 +151,7 @@ struct LongRowScan {
         }
         if (r == first_hint) counts[4] = c0;
         if (!nc) return;
-        if (nc > kFewChunks) atomicMax(&counts[5], nc);
+        if (nc > kFewChunks && rows_apart(nc, static_cast<int64_t>(net_rp[n]) + hint_rp[n])) counts[5] = 1;
         long_rows[k] = static_cast<int32_t>(r);
         chunk0[k] = c0;
         for (int c = 0; c < nc; ++c) chunk_row[c0 + c] = k;
@@ -313,22 +327,6 @@ struct Chunk {
     int nb, net, hb, n, li, take;
 };
 constexpr int kApart = kWholeChunks + 1;
-
-// Whether the long rows are summed in parts: where the longest has more chunks
-// than one workgroup takes, or so many that they are the hop.  Filters of 8
-// hops over one row of 2, 3, 4, 5 and 8 chunks, whole and in parts, at 4 columns:
-//   0.4M entries   78/73  101/74   123/74   131/91   180/96 us
-//   0.8M           87/87  111/88   136/88   159/90   229/93
-//   1.5M          112/130 128/130  157/131  186/130  264/130
-//   2.7M          166/184 167/184  182/184  203/183  282/183
-//   6.3M          335/350 334/349  334/350  335/350  342/349
-// (2 columns: the lines lie alike.)  Below 0.3M entries the launches are the
-// hop: 73/103 and 91/106 with 2 and 3 chunks at 0.23M.
-constexpr int64_t kEntriesPerChunk = 750000;
-
-bool rows_apart(int32_t longest, int64_t entries) {
-    return longest > kFewChunks && (longest > kWholeChunks || longest * kEntriesPerChunk > entries);
-}
 static_assert(kChunk < 1 << 12 && kApart < 1 << 7, "packing of a chunk");
 
 __device__ __forceinline__ int4 pack_chunk(const Chunk& c) {
@@ -1823,8 +1821,8 @@ static void row_classes_begin(const int32_t* net_rp, const int32_t* hint_rp, int
     rc.long_chunk0.ensure(static_cast<size_t>(max_long) + 1, s);
     rc.chunk_row.ensure(static_cast<size_t>(max_long + max_entries / kChunk) + 1, s);
     rc.counts.ensure(6, s);
-    run_scans(scan_job(LongRowScan{net_rp, hint_rp, n_inst, first_hint, rc.long_rows.p, rc.long_chunk0.p, rc.chunk_row.p,
-                                   rc.counts.p},
+    run_scans(scan_job(LongRowScan{net_rp, hint_rp, N, n_inst, first_hint, rc.long_rows.p, rc.long_chunk0.p,
+                                   rc.chunk_row.p, rc.counts.p},
                        N),
               scan_tmp, s);
     std::vector<const int32_t*> words{rc.counts.p,     rc.counts.p + 1,  rc.counts.p + 2, rc.counts.p + 3,
@@ -1847,7 +1845,7 @@ static void row_classes_end(int32_t N, int32_t n_inst, int32_t first_hint, RowCl
     rc.n_long_inst = n_inst < N ? v[1] : v[0];
     rc.n_chunks_inst = n_inst < N ? v[3] : v[2];
     rc.n_chunks_net = first_hint < N ? v[8] : v[2];
-    rc.in_parts = rows_apart(v[9], rc.nnz_net_all + rc.nnz_hint_all) ? 1 : 0;
+    rc.in_parts = v[9];
     rc.nnz_inst = static_cast<int64_t>(v[4]) + v[5];
     rc.has_rb = 0;
     rc.partial.ensure(static_cast<size_t>(rc.n_chunks) * 8 + 8, s);
