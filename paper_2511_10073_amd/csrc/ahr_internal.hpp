@@ -365,6 +365,7 @@ struct SortKeys {
     int32_t mask = INT32_MAX;
     int32_t* inverse = nullptr;    // inverse[v] = the position of v in the list
     int32_t* sorted = nullptr;     // sorted[position] = key[i], for a next pass over the list
+    const int32_t* count = nullptr;   // on the device: the elements from *count on have no key either
 };
 // Stable bucket sort: list = the values of the elements with a key, grouped
 // by key, in element order within a key; start[k] = first position of key k

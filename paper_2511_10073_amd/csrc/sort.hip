@@ -36,11 +36,21 @@ constexpr int kLdsWords = 32768;
 constexpr int kSmallIters = 16;
 constexpr int kSmallStep = 2;
 constexpr int kSmallWaves = 16;
+// (key, tile) counters above which the keys are sorted in two passes, by halves
+// of their bits: every counter is a line written, read by the scan and read
+// again.  With 16,384 keys one pass takes 222 us for the counts and 370 for the
+// scatter at 2.2M elements, where the former tile-major table with its
+// transposes took 415 in all; the hints of that placement are rebuilt in 1672
+// us with one pass, 1108 with two, at 1M cells in 1024 and 820.
+constexpr int64_t kMaxTable = int64_t(1) << 21;
 
 __device__ __forceinline__ int sort_key(const SortKeys& k, int64_t i) {
     const int v = k.key[i];
     return v < 0 ? -1 : (v >> k.shift) & k.mask;
 }
+
+// The elements that may have a key.
+__device__ __forceinline__ int32_t sort_count(const SortKeys& k, int32_t n) { return k.count ? *k.count : n; }
 
 __device__ __forceinline__ void wave_lds_order() {
     // LDS serves a wave's accesses in order; the compiler keeps them so
@@ -82,6 +92,7 @@ template <int I>
 __global__ void __launch_bounds__(kMaxWaves * kWave) k_bucket_count(SortKeys k, int32_t n, int nkeys, int32_t ntiles,
                                                                     int32_t* __restrict__ hist) {
     extern __shared__ int32_t h[];
+    const int32_t count = sort_count(k, n);
     for (int b = threadIdx.x; b < nkeys; b += blockDim.x) h[b] = 0;
     __syncthreads();
     const int64_t base = static_cast<int64_t>(blockIdx.x) * I * blockDim.x;
@@ -90,7 +101,7 @@ __global__ void __launch_bounds__(kMaxWaves * kWave) k_bucket_count(SortKeys k, 
     for (int t = 0; t < I; ++t) {
         const int64_t i = base + static_cast<int64_t>(t) * blockDim.x + threadIdx.x;
         key[t] = sort_key(k, i < n ? i : n - 1);
-        if (i >= n) key[t] = -1;
+        if (i >= count) key[t] = -1;
     }
 #pragma unroll
     for (int t = 0; t < I; ++t)
@@ -108,6 +119,7 @@ __global__ void __launch_bounds__(kMaxWaves * kWave) k_bucket_scatter(SortKeys k
                                                                       int32_t* __restrict__ list,
                                                                       int32_t* __restrict__ start) {
     extern __shared__ int32_t run[];     // [wave][key]
+    const int32_t count = sort_count(k, n);
     const int W = blockDim.x / kWave;
     for (int b = threadIdx.x; b < W * nkeys; b += blockDim.x) run[b] = 0;
     __syncthreads();
@@ -119,7 +131,7 @@ __global__ void __launch_bounds__(kMaxWaves * kWave) k_bucket_scatter(SortKeys k
     for (int t = 0; t < I; ++t) {
         const int64_t i = base + t * kWave;
         key[t] = sort_key(k, i < n ? i : n - 1);
-        if (i >= n) key[t] = -1;
+        if (i >= count) key[t] = -1;
     }
 #pragma unroll
     for (int t = 0; t < I; ++t)
@@ -150,6 +162,7 @@ __global__ void __launch_bounds__(kSmallWaves * kWave) k_bucket_small(SortKeys k
     extern __shared__ int32_t run[];     // [wave][key]
     __shared__ int64_t red[kSmallWaves];
     __shared__ int64_t carry;
+    const int32_t count = sort_count(k, n);
     const int W = blockDim.x / kWave;
     for (int b = threadIdx.x; b < W * nkeys; b += blockDim.x) run[b] = 0;
     if (threadIdx.x < kSmallWaves) red[threadIdx.x] = 0;     // (the waves that are not there)
@@ -166,7 +179,7 @@ __global__ void __launch_bounds__(kSmallWaves * kWave) k_bucket_small(SortKeys k
         for (int u = 0; u < kSmallStep; ++u) {
             const int64_t i = base + (t0 + u) * kWave;
             key[u] = sort_key(k, i < n ? i : n - 1);
-            if (i >= n || t0 + u >= per) key[u] = -1;
+            if (i >= count || t0 + u >= per) key[u] = -1;
         }
     };
     for (int t0 = 0; t0 < per; t0 += kSmallStep) {
@@ -221,6 +234,95 @@ void sort_tiles(const SortKeys& k, int32_t n, int nkeys, int bits, int waves, in
     AHR_LAUNCHED("k_bucket_scatter");
 }
 
+int key_bits(int nkeys) {
+    int bits = 0;
+    while ((1 << bits) < nkeys) ++bits;
+    return bits;
+}
+
+// A tile of the longer form: its waves and the 64-element steps of each.  The
+// shortest tile whose (key, tile) table stays within 2^18 counters: short tiles
+// give the scatter more waves, but every tile reads and writes its column of
+// the table with a line an entry (2.2M elements, 1,024 keys: tiles of 8,192,
+// 4,096 and 2,048 take 30, 39 and 74 us in the scatter).
+struct Tile {
+    int waves, iters;
+    int64_t table;       // (key, tile) counters
+};
+
+Tile sort_tile(int32_t n, int nkeys) {
+    Tile t{std::min(kMaxWaves, kLdsWords / nkeys), 2, 0};
+    const auto table = [&]() { return static_cast<int64_t>(nkeys) * grid_for(n, t.iters * t.waves * kWave); };
+    while (t.iters < kMaxIters && table() > (1 << 18)) t.iters *= 2;
+    t.table = table();
+    return t;
+}
+
+// One pass (n > 0; list and start hold n and nkeys + 1 entries).
+void sort_pass(const SortKeys& k, int32_t n, int nkeys, int32_t* list, int32_t* start, DevBuf<int32_t>& i32a,
+               DevBuf<int32_t>& i32b, DevBuf<int64_t>& scan_tmp, hipStream_t s) {
+    const int bits = key_bits(nkeys);
+    const int small_waves =
+        std::min({kSmallWaves, kLdsWords / nkeys, static_cast<int>(std::min(grid_for(n, kWave), 16u))});
+    if (n <= small_waves * kSmallIters * kWave) {
+        hipLaunchKernelGGL(k_bucket_small, dim3(1), dim3(small_waves * kWave),
+                           static_cast<size_t>(small_waves) * nkeys * sizeof(int32_t), s, k, n, nkeys, bits, list, start);
+        AHR_LAUNCHED("k_bucket_small");
+        return;
+    }
+    const Tile t = sort_tile(n, nkeys);
+    auto f = t.iters == 2   ? sort_tiles<2>
+             : t.iters == 4 ? sort_tiles<4>
+             : t.iters == 8 ? sort_tiles<8>
+                            : sort_tiles<16>;
+    f(k, n, nkeys, bits, t.waves, list, start, i32a, i32b, scan_tmp, s);
+}
+
+// start[q] = the first place of a key of q or more, from the keys in sorted
+// order: a thread a place, and one past the last.
+constexpr int kStartBT = 256;
+__global__ void __launch_bounds__(kStartBT) k_key_starts(const int32_t* __restrict__ sorted, int shift, int32_t mask,
+                                                         const int32_t* __restrict__ count, int nkeys,
+                                                         int32_t* __restrict__ start) {
+    const int64_t n = *count, p = static_cast<int64_t>(blockIdx.x) * kStartBT + threadIdx.x;
+    if (p > n) return;
+    const int from = p > 0 ? ((sorted[p - 1] >> shift) & mask) + 1 : 0;
+    const int to = p < n ? (sorted[p] >> shift) & mask : nkeys;
+    for (int q = from; q <= to; ++q) start[q] = static_cast<int32_t>(p);
+}
+
+// The sort in two passes, by the lower and then by the upper half of the key's
+// bits.
+void sort_halves(const SortKeys& k, int32_t n, int nkeys, int32_t* list, int32_t* start, DevBuf<int32_t>& i32a,
+                 DevBuf<int32_t>& i32b, DevBuf<int64_t>& scan_tmp, hipStream_t s) {
+    const int lo_bits = key_bits(nkeys) / 2, nlo = 1 << lo_bits, nhi = ((nkeys - 1) >> lo_bits) + 1;
+    DevBuf<int32_t> first, keys, sorted, lo_start, hi_start;
+    keys.ensure(static_cast<size_t>(n), s);
+    SortKeys lo = k;
+    lo.mask = k.mask & (nlo - 1);
+    lo.inverse = nullptr;
+    lo.sorted = keys.p;
+    first.ensure(static_cast<size_t>(n), s);
+    lo_start.ensure(static_cast<size_t>(nlo) + 1, s);
+    sort_pass(lo, n, nlo, first.p, lo_start.p, i32a, i32b, scan_tmp, s);
+    SortKeys hi = k;
+    hi.key = keys.p;
+    hi.idx = first.p;
+    hi.count = lo_start.p + nlo;
+    hi.shift = k.shift + lo_bits;
+    hi.mask = k.mask >> lo_bits;
+    if (!hi.sorted) {
+        sorted.ensure(static_cast<size_t>(n), s);
+        hi.sorted = sorted.p;
+    }
+    hi_start.ensure(static_cast<size_t>(nhi) + 1, s);
+    sort_pass(hi, n, nhi, list, hi_start.p, i32a, i32b, scan_tmp, s);
+    hipLaunchKernelGGL(k_key_starts, dim3(grid_for(static_cast<int64_t>(n) + 1, kStartBT)), dim3(kStartBT), 0, s,
+                       static_cast<const int32_t*>(hi.sorted), k.shift, k.mask, hi.count, nkeys, start);
+    AHR_LAUNCHED("k_key_starts");
+    for (auto* b : {&first, &keys, &sorted, &lo_start, &hi_start}) b->release(s);
+}
+
 }  // namespace
 
 void bucket_sort(const SortKeys& k, int32_t n, int nkeys, DevBuf<int32_t>& list, DevBuf<int32_t>& start,
@@ -232,26 +334,10 @@ void bucket_sort(const SortKeys& k, int32_t n, int nkeys, DevBuf<int32_t>& list,
         fill_i32(start.p, nkeys + 1, 0, s);
         return;
     }
-    int bits = 0;
-    while ((1 << bits) < nkeys) ++bits;
-    const int small_waves =
-        std::min({kSmallWaves, kLdsWords / nkeys, static_cast<int>(std::min(grid_for(n, kWave), 16u))});
-    if (n <= small_waves * kSmallIters * kWave) {
-        const int waves = small_waves;
-        hipLaunchKernelGGL(k_bucket_small, dim3(1), dim3(waves * kWave),
-                           static_cast<size_t>(waves) * nkeys * sizeof(int32_t), s, k, n, nkeys, bits, list.p, start.p);
-        AHR_LAUNCHED("k_bucket_small");
-        return;
-    }
-    const int waves = std::min(kMaxWaves, kLdsWords / nkeys);
-    // the shortest tile whose (key, tile) table stays within 2^18 counters:
-    // short tiles give the scatter more waves, but every tile reads and writes
-    // its column of the table with a line an entry (2.2M elements, 1,024 keys:
-    // tiles of 8,192, 4,096 and 2,048 take 30, 39 and 74 us in the scatter)
-    int iters = 2;
-    while (iters < kMaxIters && static_cast<int64_t>(nkeys) * grid_for(n, iters * waves * kWave) > (1 << 18)) iters *= 2;
-    auto f = iters == 2 ? sort_tiles<2> : iters == 4 ? sort_tiles<4> : iters == 8 ? sort_tiles<8> : sort_tiles<16>;
-    f(k, n, nkeys, bits, waves, list.p, start.p, i32a, i32b, scan_tmp, s);
+    if (sort_tile(n, nkeys).table > kMaxTable)
+        sort_halves(k, n, nkeys, list.p, start.p, i32a, i32b, scan_tmp, s);
+    else
+        sort_pass(k, n, nkeys, list.p, start.p, i32a, i32b, scan_tmp, s);
 }
 
 void bucket_sort(Graph& g, const SortKeys& k, int32_t n, int nkeys, DevBuf<int32_t>& list, DevBuf<int32_t>& start,
