@@ -490,7 +490,7 @@ struct ChainView {
     const int32_t* chunk0;
     double* partial;
     const int4* rb;
-    int32_t n_tot, n_inst, n_long, n_long_inst, in_parts, n_chunks, n_chunks_inst, n_chunks_net, n_rb, n_rb_inst;
+    int32_t n_tot, n_inst, n_long, n_long_inst, in_parts, n_chunks, n_chunks_inst, n_chunks_net, in_turn, n_rb, n_rb_inst;
     int64_t nnz_inst, nnz_all;
     float* z0;
     float* z1;

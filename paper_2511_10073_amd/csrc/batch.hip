@@ -188,6 +188,7 @@ ChainView batch_view(Batch& b, const ahr_filter_spec& spec) {
     v.n_chunks = b.rc.n_chunks;
     v.n_chunks_inst = b.rc.n_chunks_inst;
     v.n_chunks_net = b.rc.n_chunks_net;
+    v.in_turn = 0;
     v.n_rb = b.rc.n_rb;
     v.n_rb_inst = b.rc.n_rb_inst;
     v.nnz_inst = b.rc.nnz_inst;

@@ -767,6 +767,7 @@ struct HopArgs {
     int32_t n_rows;           // rows of the short path
     int32_t n_chunks;         // chunks of this hop (their workgroups are placed first)
     int32_t n_chunks_net;     // of which the first are netlist nodes' rows
+    int32_t in_turn;          // how they are dealt (dealt_chunk)
     const int32_t* long_rows;
     const int4* chunks;
     const int32_t* chunk0;
@@ -910,6 +911,11 @@ __device__ __forceinline__ void gather_batch(const HopArgs& a, int n0, int ln, i
 // 4.1M.  With this, a chunk's entries found by one load (chunks), as many
 // slots as it has entries (in_chunk) and one pass of sums, a hop takes 92 us
 // for 108 there, 249 for 259 at 2.2M cells and 4 columns, 26 for 28 at 210k.
+// Without hint nodes they are dealt one by one (in_turn): their last eighth is
+// the stars' and has 326k of the 690k entries at 2.2M cells, which kept one
+// XCD busy for longer than the rows do.  8 hops take 1275, 1616 and 1807 us
+// for 1362, 1708 and 1918 at 1, 2 and 4 columns; 192 and 223 for 193 and 220
+// at 210k cells with 2 and 4.
 __host__ __device__ inline int chunk_blocks(const HopArgs& a) {
     const int net = a.n_chunks_net < a.n_chunks ? a.n_chunks_net : a.n_chunks;
     return ((net + kXcds - 1) / kXcds + (a.n_chunks - net + kXcds - 1) / kXcds) * kXcds;
@@ -920,6 +926,7 @@ __device__ __forceinline__ int dealt_chunk(const HopArgs& a, int b) {
     const int net = a.n_chunks_net < a.n_chunks ? a.n_chunks_net : a.n_chunks, hint = a.n_chunks - net;
     const int pn = (net + kXcds - 1) / kXcds, ph = (hint + kXcds - 1) / kXcds;
     const int x = b % kXcds, i = b / kXcds;
+    if (a.in_turn) return b < a.n_chunks ? b : -1;
     if (i < pn) return x * pn + i < net ? x * pn + i : -1;
     const int c = x * ph + i - pn;
     return c < hint ? net + c : -1;
@@ -1566,6 +1573,7 @@ ChainView chain_view(Graph& g, const ahr_filter_spec& spec, hipStream_t s) {
     v.n_chunks = g.rc.n_chunks;
     v.n_chunks_inst = g.rc.n_chunks_inst;
     v.n_chunks_net = g.rc.n_chunks_net;
+    v.in_turn = g.first_mvirt == g.n_tot;
     v.n_rb = g.rc.n_rb;
     v.n_rb_inst = g.rc.n_rb_inst;
     v.nnz_inst = g.rc.nnz_inst;
@@ -1603,6 +1611,7 @@ HopArgs hop_args(const ChainView& v, const float* in, float* out, int ncols) {
     h.n_rows = 0;
     h.n_chunks = 0;
     h.n_chunks_net = v.n_chunks_net;
+    h.in_turn = v.in_turn;
     h.tile_stride = 0;
     h.ldo = ncols;
     h.col0 = 0;
