@@ -932,6 +932,10 @@ __device__ __forceinline__ int dealt_chunk(const HopArgs& a, int b) {
     return c < hint ? net + c : -1;
 }
 
+// One chunk's W sums of each wave, in LDS.
+template <int W>
+using WaveSums = double[W][kBT / kWave];
+
 // A workgroup's chunks of a long row, one after another: value(chunk, acc)
 // adds the chunk's entries to the lane's W sums.  Each wave leaves its sums of
 // every chunk in LDS, and the waves meet once.  Lane c of the first wave then
@@ -940,8 +944,8 @@ __device__ __forceinline__ int dealt_chunk(const HopArgs& a, int b) {
 // order (k_hop1_long).  d is the first chunk; false where the workgroup has
 // none to take.
 template <int W, bool Last, class F>
-__device__ __forceinline__ bool chunk_sums(const HopArgs& a, int chunk, Chunk& d, double& tot, const F& value) {
-    __shared__ double red[kWholeChunks][W][kBT / kWave];
+__device__ __forceinline__ bool chunk_sums(const HopArgs& a, int chunk, Chunk& d, double& tot,
+                                           WaveSums<W>* red, const F& value) {
     d = unpack_chunk(a.chunks[chunk]);
     if (d.take == 0) return false;
     const int take = d.take;
@@ -989,9 +993,10 @@ __device__ __forceinline__ bool chunk_sums(const HopArgs& a, int chunk, Chunk& d
 // Chunks of a long row.  Whole: the row is finished here.  Otherwise the
 // chunk's float64 sums go to partial[chunk], and k_hop_long adds a row's
 // partials after the launch ends (no device-scope fence inside the hop: on
-// this chip that is an L2 write-back).
+// this chip that is an L2 write-back).  red: kWholeChunks of them with Whole,
+// else one.
 template <int C, bool NT, bool Whole>
-__device__ __forceinline__ void hop_chunk(const HopArgs& a) {   // a: tile-adjusted
+__device__ __forceinline__ void hop_chunk(const HopArgs& a, WaveSums<C>* red) {   // a: tile-adjusted
     const int chunk = dealt_chunk(a, blockIdx.x);
     if (chunk < 0) return;
     const auto add = [&](const Chunk& k, double (&acc)[C]) {
@@ -1002,7 +1007,7 @@ __device__ __forceinline__ void hop_chunk(const HopArgs& a) {   // a: tile-adjus
     if constexpr (Whole) {
         Chunk d;
         double tot;
-        if (!chunk_sums<C, false>(a, chunk, d, tot, add) || wave_id() != 0) return;
+        if (!chunk_sums<C, false>(a, chunk, d, tot, red, add) || wave_id() != 0) return;
         Vec<C> sum;
 #pragma unroll
         for (int c = 0; c < C; ++c) sum.v[c] = static_cast<float>(__shfl(tot, c));
@@ -1010,12 +1015,11 @@ __device__ __forceinline__ void hop_chunk(const HopArgs& a) {   // a: tile-adjus
         const int r = a.long_rows[d.li];
         epilogue<C>(a, r, row_ops<C>(a, r), sum);
     } else {
-        __shared__ double red[C][kBT / kWave];
         double acc[C];
 #pragma unroll
         for (int c = 0; c < C; ++c) acc[c] = 0;
         add(unpack_chunk(a.chunks[chunk]), acc);
-        block_sums_f64<kBT>(acc, red);
+        block_sums_f64<kBT>(acc, *red);
         if (threadIdx.x == 0) {
             double* part = a.partial + static_cast<int64_t>(chunk) * 8;
 #pragma unroll
@@ -1055,10 +1059,11 @@ __global__ void __launch_bounds__(kBT) k_hop_long(HopArgs a0, int32_t n_long_row
 
 template <int C, int G, int U, bool NT, bool Whole>
 __global__ void __launch_bounds__(kBT, Whole && C <= 4 && U <= 4 ? 7 : 1) k_hop(HopArgs a0) {
+    __shared__ WaveSums<C> red[Whole ? kWholeChunks : 1];
     const HopArgs a = tile_args<C>(a0);
     const int ncb = chunk_blocks(a);
     if (static_cast<int>(blockIdx.x) < ncb) {
-        hop_chunk<C, NT, Whole>(a);
+        hop_chunk<C, NT, Whole>(a, red);
         return;
     }
     const int64_t nb = static_cast<int64_t>(gridDim.x) - ncb;     // a multiple of kXcds
@@ -1098,8 +1103,7 @@ constexpr int kRbCap = kRbEntries + kLongRow;
 constexpr int kRbUnroll = (kRbCap + kBT - 1) / kBT;
 
 template <int C, bool NT>
-__device__ __forceinline__ void hop_row_block(const HopArgs& a, int blk) {
-    __shared__ __align__(16) float prod[kRbCap * C];
+__device__ __forceinline__ void hop_row_block(const HopArgs& a, int blk, float* prod) {
     __shared__ int32_t nrp[kRbRows + 1], hrp[kRbRows + 1];   // row starts in prod; [nr] = the block's end
     const int4 d0 = a.rb[2 * blk], d1 = a.rb[2 * blk + 1];
     const int r0 = d0.x, nr = d0.y - d0.x;
@@ -1175,16 +1179,20 @@ __device__ __forceinline__ void hop_row_block(const HopArgs& a, int blk) {
 
 template <int C, bool NT, bool Whole>
 __global__ void __launch_bounds__(kBT, Whole && C == 4 ? 6 : 1) k_hop_rb(HopArgs a0) {
+    // The chunks' sums share it: apart, the two pass 40 KB at 8 columns, and a CU
+    // holds 3 workgroups, not 4 (8 hops over 27.5M entries 2739 us for 2316).
+    __shared__ __align__(16) float prod[kRbCap * C];
+    static_assert(sizeof(prod) >= kWholeChunks * sizeof(WaveSums<C>), "a chunk's sums lie in the products' place");
     const HopArgs a = tile_args<C>(a0);
     const int ncb = chunk_blocks(a);
     if (static_cast<int>(blockIdx.x) < ncb) {
-        hop_chunk<C, NT, Whole>(a);
+        hop_chunk<C, NT, Whole>(a, reinterpret_cast<WaveSums<C>*>(prod));
         return;
     }
     const int64_t nb = static_cast<int64_t>(gridDim.x) - ncb;     // a multiple of kXcds
     const int64_t blk = xcd_tile(static_cast<int64_t>(blockIdx.x) - ncb, nb);
     if (blk >= a.n_rb) return;
-    hop_row_block<C, NT>(a, static_cast<int>(blk));
+    hop_row_block<C, NT>(a, static_cast<int>(blk), prod);
 }
 
 // ------------------------------------------------ first hop with lambda_up
@@ -1266,7 +1274,8 @@ __device__ __forceinline__ void hop1_chunk(const HopArgs& a, const float* zpk, c
     if constexpr (Whole) {
         Chunk d;
         double tot;
-        if (!chunk_sums<C + 1, true>(a, chunk, d, tot, add) || wave_id() != 0) return;
+        __shared__ WaveSums<C + 1> red[kWholeChunks];
+        if (!chunk_sums<C + 1, true>(a, chunk, d, tot, red, add) || wave_id() != 0) return;
         Vec<C> sum;
 #pragma unroll
         for (int c = 0; c < C; ++c) sum.v[c] = static_cast<float>(__shfl(tot, c));
