@@ -1057,8 +1057,13 @@ __global__ void __launch_bounds__(kBT) k_hop_long(HopArgs a0, int32_t n_long_row
     epilogue<C>(a, r, ops, sum);
 }
 
+// The second bound is the waves per SIMD that the registers leave room for.
+// Whole keeps 7 with up to 4 columns and 4 entries a lane.  At 4 columns and 8
+// or more lanes a row the compiler's choice is 8, with fewer gathers in
+// flight: with 7 waves 8 hops over 69M entries take 3797 us for 4110 (16
+// lanes) and 8680 for 9671 (64).  With 4 lanes they take 2199 for 2079.
 template <int C, int G, int U, bool NT, bool Whole>
-__global__ void __launch_bounds__(kBT, Whole && C <= 4 && U <= 4 ? 7 : 1) k_hop(HopArgs a0) {
+__global__ void __launch_bounds__(kBT, (Whole && C <= 4 && U <= 4) || (C == 4 && U <= 2) ? 7 : 1) k_hop(HopArgs a0) {
     __shared__ WaveSums<C> red[Whole ? kWholeChunks : 1];
     const HopArgs a = tile_args<C>(a0);
     const int ncb = chunk_blocks(a);
