@@ -1633,9 +1633,25 @@ HopArgs hop_args(const ChainView& v, const float* in, float* out, int ncols) {
 }
 
 // Long rows that a launch after the hop adds up (of the instances' only, or
-// all); -1 where the hop finishes them itself.
-int32_t parts_rows(const ChainView& v, bool inst_only) {
-    return !v.in_parts ? -1 : inst_only ? v.n_long_inst : v.n_long;
+// all); -1 where the hop finishes them itself.  Beside where the graph asks for
+// parts, that is in hops of many entries with 8 columns or 1 or 2 lanes a row:
+// finishing rows costs k_hop registers (94 for 88 with 8 columns, 70 for 63 with
+// 2 and 2 lanes), which its short rows pay for.  8 hops over netlists without
+// hints, longest rows of 3 to 5 chunks, whole and in parts:
+//            8 columns     2 columns, 2 lanes   2 columns, 4 lanes
+//    7.8M    608/613 us        416/396              354/367
+//   13.4M   1012/1007          673/620              576/584
+//   17.8M   1374/1367          925/833              797/795
+//   23.2M   2075/1992         1259/1128            1087/1073
+//   27.5M   2704/2562         1840/1634            1616/1610
+// The row-block form gains nothing (8 columns: 1866/1913 and 2316/2361 us with
+// the last two).
+constexpr int64_t kManyEntries = 12000000;
+
+int32_t parts_rows(const ChainView& v, bool inst_only, int cols, int lanes) {
+    const int32_t rows = inst_only ? v.n_long_inst : v.n_long;
+    const bool apart = v.in_parts || (v.nnz_all > kManyEntries && (cols == 8 || lanes <= 2) && lanes != AHR_HOP_ROW_BLOCK);
+    return rows > 0 && !apart ? -1 : rows;
 }
 
 // Algorithmic bytes of one hop launch over C columns: row pointers,
@@ -1669,7 +1685,7 @@ void hops_c(Graph& g, const ahr_filter_spec& spec, const float* in, int lanes, h
         h.n_rows = inst_only ? v.n_inst : v.n_tot;
         h.n_chunks = inst_only ? v.n_chunks_inst : v.n_chunks;
         h.n_rb = inst_only ? v.n_rb_inst : v.n_rb;
-        hop_dispatch<C>(h, lanes, parts_rows(v, inst_only), hop_bytes(v, h, C), 1, s);
+        hop_dispatch<C>(h, lanes, parts_rows(v, inst_only, C, lanes), hop_bytes(v, h, C), 1, s);
         zin = g.zh[j].p;
     }
 }
@@ -1701,7 +1717,7 @@ void hop1_gersh(const ChainView& v, HopArgs h, const Hop1Gersh& f, hipStream_t s
     constexpr int G = 4, U = 4;
     int64_t tiles = grid_for(static_cast<int64_t>(h.n_rows) * G, kBT);
     tiles = (tiles + kXcds - 1) / kXcds * kXcds;                    // see xcd_tile
-    const int32_t rows = parts_rows(v, false);
+    const int32_t rows = parts_rows(v, false, C, 4);
     hipLaunchKernelGGL((rows >= 0 ? k_hop1_gersh<C, G, U, false> : k_hop1_gersh<C, G, U, true>), dim3(static_cast<unsigned>(chunk_blocks(h) + tiles)), dim3(kBT), 0,
                        s, h, f.zpk, f.deg, f.gmax);
     AHR_LAUNCHED("k_hop1_gersh");
@@ -1754,7 +1770,7 @@ void chain_c(const ChainView& v, const ahr_filter_spec& spec, const float* in, f
                 throw Error{AHR_EINVAL, "first-hop bound needs one column tile of at most 4 columns"};
             }
         } else {
-            hop_dispatch<CT>(h, lanes, parts_rows(v, h.last), hop_bytes(v, h, C), C / CT, s);
+            hop_dispatch<CT>(h, lanes, parts_rows(v, h.last, CT, lanes), hop_bytes(v, h, C), C / CT, s);
         }
         has_acc = has_acc || isb;
         float* t = zin;
