@@ -116,7 +116,7 @@ struct DevWord {
 };
 void read_words(std::initializer_list<DevWord> src, int64_t* out, hipStream_t s);
 // The same read split in two, so that work queued between the halves runs
-// while the host waits: read_scalars_begin gathers up to 8 int32 values on
+// while the host waits: read_scalars_begin gathers up to 12 int32 values on
 // stream s into pinned words of the host; read_scalars_end waits for those
 // words alone and copies the values out.  One split read in flight per host
 // thread.

@@ -616,8 +616,11 @@ __global__ void k_gather_scalars(PtrPack src, int n, uint32_t number, uint64_t* 
 
 namespace {
 
-// One read in flight: its slot of the thread's pinned words (kSlots in turn,
-// so that a read given up by an exception cannot write over the next ones).
+// One read in flight: its slot of the thread's pinned words.  The slots are
+// taken in turn, so that a read given up by an exception and still queued
+// shares none of the thread's next kSlots - 1 reads' words.  A later read may
+// get its slot; on the same stream that runs after it, and on another one a
+// word of its number makes the later read fail, not return a wrong value.
 constexpr int kSlots = 8, kSlotWords = 24;
 
 struct HostRead {
@@ -659,9 +662,12 @@ HostRead begin_read(const PtrPack& pk, int n, hipStream_t s) {
 // Waits for the read's words: watches them for a while, then leaves the
 // waiting (and the report of a failed kernel) to the runtime.
 void end_read(const HostRead& r, int64_t* out) {
+    uint64_t part[kSlotWords];
     auto all_there = [&]() {
-        for (int k = 0; k < 2 * r.n; ++k)
-            if (static_cast<uint32_t>(__atomic_load_n(r.words + k, __ATOMIC_RELAXED) >> 32) != r.number) return false;
+        for (int k = 0; k < 2 * r.n; ++k) {
+            part[k] = __atomic_load_n(r.words + k, __ATOMIC_RELAXED);
+            if (static_cast<uint32_t>(part[k] >> 32) != r.number) return false;
+        }
         return true;
     };
     const auto until = std::chrono::steady_clock::now() + std::chrono::milliseconds(5);
@@ -672,8 +678,7 @@ void end_read(const HostRead& r, int64_t* out) {
         if (!all_there()) throw Error{AHR_EDEVICE, "a read of device counts did not arrive"};
     }
     for (int k = 0; k < r.n; ++k) {
-        const uint64_t lo = __atomic_load_n(r.words + 2 * k, __ATOMIC_RELAXED) & 0xffffffffull;
-        const uint64_t hi = __atomic_load_n(r.words + 2 * k + 1, __ATOMIC_RELAXED) & 0xffffffffull;
+        const uint64_t lo = part[2 * k] & 0xffffffffull, hi = part[2 * k + 1] & 0xffffffffull;
         out[k] = r.wide[k] ? static_cast<int64_t>(lo | (hi << 32)) : static_cast<int64_t>(static_cast<int32_t>(lo));
     }
 }
@@ -694,8 +699,9 @@ void read_scalars_begin(const std::vector<const int32_t*>& src, hipStream_t s) {
 void read_scalars_end(int32_t* host, int n) {
     if (!g_split.words || n > g_split.n) throw Error{AHR_EDEVICE, "read_scalars_end without its begin"};
     int64_t w[12];
-    end_read(g_split, w);
-    g_split.words = nullptr;
+    const HostRead r = g_split;
+    g_split.words = nullptr;       // also where the read fails
+    end_read(r, w);
     for (int k = 0; k < n; ++k) host[k] = static_cast<int32_t>(w[k]);
 }
 

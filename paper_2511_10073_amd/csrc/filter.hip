@@ -2019,6 +2019,13 @@ void normalise_degrees(Graph& g, const ahr_filter_spec& spec, hipStream_t s) {
     // netlist rows' lengths and the hint entries only
     RowRef m{g.xnet_rp.p, nullptr, g.xhint_rp.p, g.xhint_ent.p};
 
+    // (before the split read: no allocation that can fail stands between its halves)
+    g.deg.ensure(static_cast<size_t>(N) + 1, s);
+    g.scale.ensure(static_cast<size_t>(N) + 1, s);
+    g.hsum.ensure(static_cast<size_t>(N) + 1, s);
+    g.lam.ensure(1, s);
+    g.coef.ensure(static_cast<size_t>(N) + 1, s);
+
     // the row classes' counts are read while the short rows' degrees run
     const bool new_rows = g.rows_version != g.hint_version;
     // the layout's locality verdict rides along with the first counts
@@ -2029,11 +2036,6 @@ void normalise_degrees(Graph& g, const ahr_filter_spec& spec, hipStream_t s) {
                           want_loc ? g.loc_flag.p : nullptr);
 
     const double sigma = spec.sigma;
-    g.deg.ensure(static_cast<size_t>(N) + 1, s);
-    g.scale.ensure(static_cast<size_t>(N) + 1, s);
-    g.hsum.ensure(static_cast<size_t>(N) + 1, s);
-    g.lam.ensure(1, s);
-    g.coef.ensure(static_cast<size_t>(N) + 1, s);
     constexpr int G = 4;
     // cell rows from the hint build's sums when it formed them for this
     // hint version, then the other rows from their entries
