@@ -32,6 +32,9 @@
  *   - `stream` is a hipStream_t (NULL = the default stream).  Calls are
  *     asynchronous on it unless documented as synchronous; calls that size
  *     device memory from device-computed counts synchronise the stream.
+ *     "Synchronises `stream`" means that the host waits, during the call,
+ *     until the stream has done the work queued before the call; what the
+ *     call itself queues after that may still run when it returns.
  *   - Every call returns an ahr_status.  Arguments are validated before any
  *     device work is queued, so an AHR_EINVAL return leaves outputs untouched.
  *     ahr_last_error() returns a message for the calling thread's last error.
@@ -277,7 +280,7 @@ ahr_status ahr_gift(ahr_graph* gr, const ahr_gift_spec* spec, const float* in, f
  * g^(r+1) = (1 - gamma) g^(r) + gamma g~ on movable rows (fixed rows keep
  * their input).  g0 and out are [n_inst][ncols] and may be the same
  * buffer.  gamma in [0, 1], T_hint >= 0.  Synchronises `stream` once per
- * round (hint sizes). */
+ * round (hint sizes; none without hint nodes). */
 ahr_status ahr_graph_refine(ahr_graph* gr, const ahr_filter_spec* spec, const float* g0,
                             int32_t ncols, int32_t T_hint, float gamma, float* out,
                             void* stream);
