@@ -14,17 +14,18 @@
 // wavefront, bfloat16 operands, float32 accumulation.  Every layer is
 // computed transposed (hidden x samples): the accumulator of one 16-row
 // output tile leaves lane l with rows 4(l/16)..4(l/16)+3 of sample l%16.
-// Layer 1 (7 features padded to K = 16) uses v_mfma_f32_16x16x16_bf16, whose
-// B operand has exactly that layout.  Layers 2 and 3 contract over the 64
-// hidden units with gfx950's v_mfma_f32_16x16x32_bf16, whose B operand gives
-// lane l eight K slots 8(l/16)..8(l/16)+7: the lane's rows of two output
-// tiles fill them (slots 8g..8g+3 hold hidden units 32p+4g..+3, slots
-// 8g+4..8g+7 hold 32p+16+4g..+3), and the weights are loaded into the A
-// operand with the same permutation of K, so no data moves between lanes.  Training runs forward and
-// backward with the same bfloat16 rounding points (weights, features and
-// hidden activations) and float32 accumulation, gradients straight through
-// the rounding, accumulated per workgroup in a fixed order and reduced in a
-// fixed order.
+// Every layer uses gfx950's v_mfma_f32_16x16x32_bf16, whose B operand gives
+// lane l eight K slots 8(l/16)..8(l/16)+7.  In layer 1 the 7 features, padded
+// to 8, are one lane group's slots and the others' are zeros (mlp_tile).
+// Layers 2 and 3 contract over the 64 hidden units: the lane's rows of two
+// output tiles fill its slots (slots 8g..8g+3 hold hidden units 32p+4g..+3,
+// slots 8g+4..8g+7 hold 32p+16+4g..+3), and the weights are loaded into the A
+// operand with the same permutation of K, so no data moves between lanes.
+//
+// Training runs forward and backward with the same bfloat16 rounding points
+// (weights, features and hidden activations) and float32 accumulation,
+// gradients straight through the rounding, accumulated per workgroup in a
+// fixed order and reduced in a fixed order.
 #include <algorithm>
 
 #include "ahr_internal.hpp"
@@ -491,31 +492,6 @@ constexpr int kTS = 32;           // samples per tile
 constexpr int kGradGrid = 240;    // workgroups of the float32-operand form (fixed: fixes the summation order)
 constexpr int kGradMax = 512;     // most workgroups of the matrix-core form: two per CU, its occupancy
 
-// The gradient with the inference's bfloat16 rounding points, on the matrix
-// cores.  A wave takes 32 samples at a time.  Every product below has
-// operands that are bfloat16 exactly (or float32 on the float32 matrix
-// instruction), so nothing is rounded that the float32 form keeps:
-//   z1, z2, o      weights, features and hidden activations are bfloat16 by
-//                  the rounding points; b1 rides in layer 1's unused K slots
-//                  as its three bfloat16 parts (x = hi + mid + lo holds all
-//                  24 bits of a float32).
-//   dz1            = [z1 > 0] do u,  u = W2^T (w3 [z2 > 0]): w3 masked is bfloat16.
-//   gW2[h][k]      = w3_h sum_s [z2 > 0] do_s a1_sk: do_s as its three
-//                  bfloat16 parts, one product each; gb2 the same without a1,
-//                  gw3 = sum_s do_s a2 likewise.
-//   gW1, gb1       sum over samples of dz1 (float32) times the features and a
-//                  column of ones, with v_mfma_f32_16x16x4_f32.
-// Contractions over hidden units need a lane to hold hidden units of one
-// sample, contractions over samples need samples of one hidden unit.  A tile
-// product gives one or the other by the order of its operands (the same
-// registers), so z1 and z2 are formed both ways and nothing moves between
-// lanes.  The weights' operands sit in LDS in fragment order.
-//
-// What bounds it: the matrix instructions, about 1,450 SIMD cycles per 16
-// samples (three quarters of them in gW2 and gW1), beside about as many
-// cycles of vector work (masks, packing).  1.6M samples take 0.166 ms where
-// the LDS tiles in float32 took 13.28 (5,000: 39 against 89 us with Adam);
-// the gradient's error against 64 bits went from 7.5e-7 to 4.5e-7.
 // bfloat16 of relu(z), NaN -> 0: the median of z, 0 and infinity (inf: a
 // register, since with a constant the compiler takes two instructions).  The
 // empty asm keeps the packed words as they are: the compiler otherwise
@@ -595,6 +571,31 @@ __device__ __forceinline__ void load_grad_tile(const float* __restrict__ feats, 
     T.t = target[s0 + (l < left ? l % kTS : 0)];
 }
 
+// The gradient with the inference's bfloat16 rounding points, on the matrix
+// cores.  A wave takes 32 samples at a time.  Every product below has
+// operands that are bfloat16 exactly (or float32 on the float32 matrix
+// instruction), so nothing is rounded that the float32 form keeps:
+//   z1, z2, o      weights, features and hidden activations are bfloat16 by
+//                  the rounding points; b1 rides in layer 1's unused K slots
+//                  as its three bfloat16 parts (x = hi + mid + lo holds all
+//                  24 bits of a float32).
+//   dz1            = [z1 > 0] do u,  u = W2^T (w3 [z2 > 0]): w3 masked is bfloat16.
+//   gW2[h][k]      = w3_h sum_s [z2 > 0] do_s a1_sk: do_s as its three
+//                  bfloat16 parts, one product each; gb2 the same without a1,
+//                  gw3 = sum_s do_s a2 likewise.
+//   gW1, gb1       sum over samples of dz1 (float32) times the features and a
+//                  column of ones, with v_mfma_f32_16x16x4_f32.
+// Contractions over hidden units need a lane to hold hidden units of one
+// sample, contractions over samples need samples of one hidden unit.  A tile
+// product gives one or the other by the order of its operands (the same
+// registers), so z1 and z2 are formed both ways and nothing moves between
+// lanes.  The weights' operands sit in LDS in fragment order.
+//
+// What bounds it: the matrix instructions, about 1,450 SIMD cycles per 16
+// samples (three quarters of them in gW2 and gW1), beside about as many
+// cycles of vector work (masks, packing).  1.6M samples take 0.161 ms where
+// the LDS tiles in float32 took 13.28 (5,000: 39 against 89 us with Adam);
+// the gradient's error against 64 bits went from 7.5e-7 to 4.5e-7.
 __global__ void __launch_bounds__(kBT, 2) k_mlp_grad_mfma(const float* __restrict__ P, const float* __restrict__ feats,
                                                           const float* __restrict__ target, int64_t n, float inv_n,
                                                           float* __restrict__ part, double* __restrict__ loss_part) {
