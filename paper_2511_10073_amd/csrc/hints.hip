@@ -217,19 +217,15 @@ __global__ void __launch_bounds__(kBT) k_bin_macros(int nbx, const int4* __restr
 
 struct HintArgs {
     Grid gr;
-    const float* pos;
-    int ncols;
     int32_t n_inst, n_macro, nbins;
     int32_t first_mvirt, first_bvirt;
     int macro_hints, bin_hints;
-    const int32_t* perm;          // execution row -> instance
     const int32_t* cell_bin;      // by execution row
     const int32_t* bin_start;
     const int32_t* bin_cells;     // execution rows by bin
     const int32_t* bm_start;
     const int32_t* bm_list;
     const float4* rect;
-    const int4* span;
     const double* phi;
     const float2* xpos;           // by execution row
     const double* xbase_w;        // by execution row
@@ -259,13 +255,13 @@ __device__ __forceinline__ void window(const Grid& gr, int b, int& x0, int& x1, 
     y1 = by + gr.hy >= gr.nby ? gr.nby - 1 : by + gr.hy;
 }
 
-// Per hint cell (execution row): the macros whose footprint holds it and the
-// size of its bin window.  With `pairs`, also lists its (row, macro) pairs
-// at pair_off[r] in ascending macro order.
 // Macros of a bin that a cell tests at a time: one after another, each test
 // waits for two loads (2.2M cells, about ten macros a bin: 31 us against 36).
 constexpr int kBinMacros = 4;
 
+// Per hint cell (execution row): the macros whose footprint holds it and the
+// size of its bin window.  With `pairs`, also lists its (row, macro) pairs
+// at pair_off[r] in ascending macro order.
 __global__ void __launch_bounds__(kBT) k_cell_count(HintArgs a, int32_t* __restrict__ nmac,
                                                     int32_t* __restrict__ nwin, const int32_t* __restrict__ pair_off,
                                                     int32_t* __restrict__ pair_row, int32_t* __restrict__ pair_mac) {
@@ -798,8 +794,6 @@ void build_hints(Graph& g, const float* pos, int32_t ncols, hipStream_t s, bool 
 
     HintArgs a;
     a.gr = gr;
-    a.pos = pos;
-    a.ncols = ncols;
     a.n_inst = n_inst;
     a.n_macro = n_macro;
     a.nbins = nbins;
@@ -807,14 +801,12 @@ void build_hints(Graph& g, const float* pos, int32_t ncols, hipStream_t s, bool 
     a.first_bvirt = g.first_bvirt;
     a.macro_hints = use_macros;
     a.bin_hints = bin_hints;
-    a.perm = g.perm.p;
     a.cell_bin = g.cell_bin.p;
     a.bin_start = g.bin_start.p;
     a.bin_cells = g.bin_cells.p;
     a.bm_start = g.bm_start.p;
     a.bm_list = g.bm_list.p;
     a.rect = g.macro_rect.p;
-    a.span = g.macro_span.p;
     a.phi = g.phi.p;
     a.xpos = g.xpos.p;
     a.xbase_w = g.xbase_w.p;
