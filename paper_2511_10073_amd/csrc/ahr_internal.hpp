@@ -100,9 +100,6 @@ void scan_i32_to_i32(const int32_t* in, int32_t* out, int64_t n, int64_t* tmp, h
 // int32 scan that returns the exact int64 total (one synchronisation); the
 // int32 output is only meaningful when the total is below 2^31.
 int64_t scan_i32_checked(const int32_t* in, int32_t* out, int64_t n, int64_t* tmp, hipStream_t s);
-// The same scan without reading its total: returns the device address of the
-// int64 total (valid until tmp is reused), for a later combined read.
-const int64_t* scan_i32_total(const int32_t* in, int32_t* out, int64_t n, int64_t* tmp, hipStream_t s);
 
 // p[0..n) = v
 void fill_i32(int32_t* p, int64_t n, int32_t v, hipStream_t s);
@@ -125,7 +122,6 @@ void read_scalars_end(int32_t* host, int n);
 // One device scalar (waits for the stream's work so far).
 int32_t read_i32(const int32_t* src, hipStream_t s);
 int64_t read_i64(const int64_t* src, hipStream_t s);
-double read_f64(const double* src, hipStream_t s);
 
 // ---------------------------------------------------------------- profiling
 
@@ -258,8 +254,6 @@ struct Graph {
     DevBuf<int64_t> qdeg;         // [n_tot]
     DevBuf<int32_t> long_nodes;   // nodes of more than 64 raw netlist entries
     int32_t n_long_nodes = 0;
-    DevBuf<int32_t> big_nets;     // nets with more than a wave's worth of pins (HPWL)
-    int32_t n_big_nets = 0;
     DevBuf<int32_t> big_stars;    // star indices (0-based) of nets with more than kStarMid pins
     int32_t n_big_stars = 0;
 

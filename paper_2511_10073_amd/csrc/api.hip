@@ -40,7 +40,7 @@ Graph::~Graph() {
     if (stream_uses > 1) (void)hipDeviceSynchronize();
     if (xnet_ready) (void)hipStreamWaitEvent(s, xnet_ready, 0);   // the side stream's copy
     DevBuf<int32_t>* i32[] = {&pin_node_x, &mpin_owner, &mpin_pin, &star_net, &macro_ids, &net_len, &net_col,
-                              &big_nets, &cell_bin, &bin_start, &bin_cells, &bm_start, &bm_list,
+                              &cell_bin, &bin_start, &bin_cells, &bm_start, &bm_list,
                               &nmac, &nwin, &bin_rank, &wpre, &pair_off, &pair_row, &pair_mac, &mlist, &mstart,
                               &big_stars, &long_nodes, &i32a, &i32b, &counter, &kept, &loc_flag};
     for (auto* b : i32) b->release(s);

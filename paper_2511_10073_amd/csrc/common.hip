@@ -559,19 +559,6 @@ void scan_i32_to_i64(const int32_t* in, int64_t* out, int64_t n, int64_t* tmp, h
     scan_impl<int32_t, int64_t>(in, out, n, tmp, s);
 }
 
-__global__ void k_zero_i64(int64_t* p) { *p = 0; }
-
-const int64_t* scan_i32_total(const int32_t* in, int32_t* out, int64_t n, int64_t* tmp, hipStream_t s) {
-    if (n == 0) {
-        AHR_HIP(hipMemsetAsync(out, 0, sizeof(int32_t), s));
-        hipLaunchKernelGGL(k_zero_i64, dim3(1), dim3(1), 0, s, tmp);
-        AHR_LAUNCHED("k_zero_i64");
-        return tmp;
-    }
-    scan_impl<int32_t, int32_t>(in, out, n, tmp, s);
-    return tmp + (n + kScanTile - 1) / kScanTile;
-}
-
 int64_t scan_i32_checked(const int32_t* in, int32_t* out, int64_t n, int64_t* tmp, hipStream_t s) {
     if (n == 0) {
         AHR_HIP(hipMemsetAsync(out, 0, sizeof(int32_t), s));
@@ -741,13 +728,6 @@ int32_t read_i32(const int32_t* src, hipStream_t s) {
     int32_t v = 0;
     read_scalars({src}, &v, s);
     return v;
-}
-
-double read_f64(const double* src, hipStream_t s) {
-    const int64_t w = read_i64(reinterpret_cast<const int64_t*>(src), s);
-    double d;
-    std::memcpy(&d, &w, sizeof d);
-    return d;
 }
 
 __global__ void k_fill_i32(int32_t* p, int64_t n, int32_t v) {

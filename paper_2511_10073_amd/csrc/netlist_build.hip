@@ -779,7 +779,7 @@ void build_netlist(Graph& g, hipStream_t s) {
     is_mp.release(s);
     g.n_mpin = cnt7[1];
     g.n_star = cnt7[2];
-    g.n_big_nets = cnt7[3];
+    const int32_t n_big_nets = cnt7[3];
     g.n_big_stars = cnt7[4];
     g.n_macro = cnt7[5];
     g.n_movable_macro = cnt7[6];
@@ -806,12 +806,12 @@ void build_netlist(Graph& g, hipStream_t s) {
 
     // the lists, the net of every pin, then entry counts per row (parallel
     // edges counted)
-    DevBuf<int32_t> pin_net, cnt, slot;
+    DevBuf<int32_t> pin_net, cnt, slot, big_nets;
     pin_net.ensure(static_cast<size_t>(n_pins) + 1, s);
     cnt.ensure(static_cast<size_t>(N) + 1, s);
     slot.ensure(static_cast<size_t>(n_pins) + 1, s);
     g.star_net.ensure(static_cast<size_t>(g.n_star) + 1, s);
-    g.big_nets.ensure(static_cast<size_t>(g.n_big_nets) + 1, s);
+    big_nets.ensure(static_cast<size_t>(n_big_nets) + 1, s);
     g.big_stars.ensure(static_cast<size_t>(g.n_big_stars) + 1, s);
     g.macro_ids.ensure(static_cast<size_t>(g.n_macro) + 1, s);
     g.pin_node_x.ensure(static_cast<size_t>(n_pins) + 1, s);
@@ -819,7 +819,7 @@ void build_netlist(Graph& g, hipStream_t s) {
     g.mpin_pin.ensure(static_cast<size_t>(g.n_mpin) + 1, s);
     const ListArgs la{nl.net_ptr,     nl.pin_node,    n_pins,       n_nets,         n_inst,
                       mp_rank.p,      star_rank.p,    big_rank.p,   bs_rank.p,      mac_rank.p,
-                      g.pin_node_x.p, g.mpin_owner.p, g.mpin_pin.p, g.star_net.p,   g.big_nets.p,
+                      g.pin_node_x.p, g.mpin_owner.p, g.mpin_pin.p, g.star_net.p,   big_nets.p,
                       g.big_stars.p,  g.macro_ids.p,  pin_net.p,    cnt.p,          N + 1};
     const int64_t nlist = std::max<int64_t>(std::max<int64_t>(n_pins, n_nets), static_cast<int64_t>(N) + 1);
     hipLaunchKernelGGL(k_build_lists, dim3(grid_for(nlist, kBT)), dim3(kBT), 0, s, la);
@@ -828,10 +828,11 @@ void build_netlist(Graph& g, hipStream_t s) {
     big_rank.release(s);
     bs_rank.release(s);
     mac_rank.release(s);
-    if (g.n_big_nets) {
-        hipLaunchKernelGGL(k_pin_net_big, dim3(g.n_big_nets), dim3(kBT), 0, s, g.big_nets.p, nl.net_ptr, pin_net.p);
+    if (n_big_nets) {
+        hipLaunchKernelGGL(k_pin_net_big, dim3(n_big_nets), dim3(kBT), 0, s, big_nets.p, nl.net_ptr, pin_net.p);
         AHR_LAUNCHED("k_pin_net_big");
     }
+    big_nets.release(s);
     NetArgs a{nl.net_ptr, pin_net.p, g.pin_node_x.p, nl.net_w, star_rank.p, n_nets, n_pins, hp.clique_max,
               g.first_star};
     if (n_pins)
