@@ -35,8 +35,8 @@ HOP_SRCS = [os.path.join(ROOT, "paper_2511_10073_amd", "csrc", f) for f in ("fil
 # (FETCH_SIZE, WRITE_SIZE) scaled by the same counters for a 1 GiB device
 # copy; valid only for the hop and layout sources they were taken with.
 HOP_TRAFFIC = {"workload": "large-2.2M",
-               "sources_sha256": "6aa91018704c471c7880e70a219bee365ec7705d9e9065845790d61969d7a861",
-               "bytes_per_launch": 1270191009,
+               "sources_sha256": "b520d68d05a372353b58fbbcacb026cb132afcda6316991c9a45c0f85748f8cd",
+               "bytes_per_launch": 1270171365,
                "source": "profiles/k_hop_large-2.2M_l2_fabric_traffic.md"}
 
 
