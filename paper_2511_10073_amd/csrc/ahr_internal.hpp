@@ -166,7 +166,7 @@ class ProfScope {
 constexpr int kLongRow = 128;
 constexpr int kChunk = 2048;
 constexpr int kWholeChunks = 8;      // the most chunks of a row that one workgroup finishes
-constexpr int kFewChunks = 2;        // and as many as it may finish in any graph
+constexpr int kFewChunks = 2;        // and as many as it may finish in any graph (rows_apart in filter.hip)
 constexpr int kRbRows = 256;
 constexpr int kRbEntries = 1024;
 // Star nodes are averaged over their pins by their row's thread up to

@@ -111,12 +111,15 @@ __device__ __forceinline__ Floats<W> load_floats(const float* p) {
 //   1.5M          112/130 128/130  157/131  186/130  264/130
 //   2.7M          166/184 167/184  182/184  203/183  282/183
 //   6.3M          335/350 334/349  334/350  335/350  342/349
-// (2 columns: the lines lie alike.)  Below 0.3M entries the launches are the
-// hop: 73/103 and 91/106 with 2 and 3 chunks at 0.23M.
-constexpr int64_t kEntriesPerChunk = 750000;
+// (2 columns: the lines lie alike.)  Below 0.35M entries the launches are the
+// hop, and 3 chunks stay whole: with 2.1 to 2.6 chunks and 0.1M to 0.33M
+// entries 47-61/62-67 us at 2 columns, 57-74/65-73 at 4; 4 chunks 60-70/64-67
+// and 72-90/66-69.
+constexpr int64_t kEntriesPerChunk = 750000, kFewEntries = 350000;
 
 __device__ __forceinline__ bool rows_apart(int32_t chunks, int64_t entries) {
-    return chunks > kFewChunks && (chunks > kWholeChunks || chunks * kEntriesPerChunk > entries);
+    return chunks > kFewChunks + (entries < kFewEntries) &&
+           (chunks > kWholeChunks || chunks * kEntriesPerChunk > entries);
 }
 
 // The long rows with their chunks, in row order: long_rows[k] the k-th long
