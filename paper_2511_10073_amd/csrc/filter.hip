@@ -104,22 +104,34 @@ __device__ __forceinline__ Floats<W> load_floats(const float* p) {
 
 // Whether a graph's long rows are summed in parts (Chunk below): where the
 // longest has more chunks than one workgroup takes, or so many that they are
-// the hop.  Filters of 8 hops over one row of 2, 3, 4, 5 and 8 chunks, whole and
-// in parts, at 4 columns:
+// the hop.  A chunk takes its workgroup 1 to 2 us where its entries are near
+// each other, as a hint node's are, and 3 to 4 where they are anywhere, as a
+// large net's may be; a launch for the parts costs about 2 us a hop.
+// Filters of 8 hops, whole and in parts, with netlist nodes of one row of 2, 3,
+// 4, 5 and 8 chunks, of any cells, at 4 columns (2 columns: the lines lie alike):
 //   0.4M entries   78/73  101/74   123/74   131/91   180/96 us
 //   0.8M           87/87  111/88   136/88   159/90   229/93
 //   1.5M          112/130 128/130  157/131  186/130  264/130
 //   2.7M          166/184 167/184  182/184  203/183  282/183
 //   6.3M          335/350 334/349  334/350  335/350  342/349
-// (2 columns: the lines lie alike.)  Below 0.35M entries the launches are the
-// hop, and 3 chunks stay whole: with 2.1 to 2.6 chunks and 0.1M to 0.33M
-// entries 47-61/62-67 us at 2 columns, 57-74/65-73 at 4; 4 chunks 60-70/64-67
-// and 72-90/66-69.
+// Below 0.35M entries the launches are the hop, and 3 chunks stay whole: with
+// 2.1 to 2.6 chunks and 0.1M to 0.33M entries 47-61/62-67 us at 2 columns,
+// 57-74/65-73 at 4; 4 chunks 60-70/64-67 and 72-90/66-69.
+// With hint nodes, at 2 and 4 columns: up to 4 chunks whole is faster at every
+// size (0.1M entries 55/70 and 68/78, 0.95M 72/90 and 91/100, 4.7M 140/162 and
+// 162/186); 5 chunks 71/77 and 88/81 at 0.3M, 74/85 and 95/93 at 0.7M, 129/142
+// and 159/173 at 2.6M; 6 chunks 93/91 and 120/98 at 0.95M, 98/98 and 128/116 at
+// 1.4M, 148/159 and 189/181 at 4.7M; 8 chunks 110/91 and 144/99 at 0.95M,
+// 145/141 and 197/171 at 2.6M, 174/188 and 229/222 at 4.3M, 313/328 and 357/378
+// at 8.8M.
 constexpr int64_t kEntriesPerChunk = 750000, kFewEntries = 350000;
+constexpr int kFewHintChunks = 4;
+constexpr int64_t kEntriesPerHintChunk = 1000000;      // of those above kFewHintChunks
 
-__device__ __forceinline__ bool rows_apart(int32_t chunks, int64_t entries) {
-    return chunks > kFewChunks + (entries < kFewEntries) &&
-           (chunks > kWholeChunks || chunks * kEntriesPerChunk > entries);
+__device__ __forceinline__ bool rows_apart(int32_t chunks, int64_t entries, bool hint) {
+    if (chunks > kWholeChunks) return true;
+    if (hint) return (chunks - kFewHintChunks) * kEntriesPerHintChunk > entries;
+    return chunks > kFewChunks + (entries < kFewEntries) && chunks * kEntriesPerChunk > entries;
 }
 
 // The long rows with their chunks, in row order: long_rows[k] the k-th long
@@ -154,7 +166,7 @@ struct LongRowScan {
         }
         if (r == first_hint) counts[4] = c0;
         if (!nc) return;
-        if (nc > kFewChunks && rows_apart(nc, static_cast<int64_t>(net_rp[n]) + hint_rp[n])) counts[5] = 1;
+        if (nc > kFewChunks && rows_apart(nc, static_cast<int64_t>(net_rp[n]) + hint_rp[n], r >= first_hint)) counts[5] = 1;
         long_rows[k] = static_cast<int32_t>(r);
         chunk0[k] = c0;
         for (int c = 0; c < nc; ++c) chunk_row[c0 + c] = k;

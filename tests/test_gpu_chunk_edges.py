@@ -1,6 +1,6 @@
 """The longest row's chunks of 2048 entries and the graph's entries decide how
-its hops finish the long rows: inside the hop (up to 2 chunks; in small graphs
-3, in large ones up to 8), or in partial sums that a launch of their own adds up.  Both sides of
+its hops finish the long rows: inside the hop (up to 2 chunks, 3 in small
+graphs, 4 of a hint node; in large graphs up to 8), or in partial sums that a launch of their own adds up.  Both sides of
 those edges, for an instance's row, a star's and a bin's (where no instance has
 a long row), in every column count and both launch forms, within the FP32 bound
 of the oracle; and in batches, which take one form for all members, every
@@ -44,7 +44,7 @@ def longest_row(og):
 
 
 @pytest.mark.parametrize("kind,d", [(k, d) for k in ("hub", "star", "bin")
-                                    for d in (4096, 4097, 6144, 6145, WHOLE - 1, WHOLE, WHOLE + 1, 20000)]
+                                    for d in (4096, 4097, 6144, 6145, 8192, 8193, WHOLE - 1, WHOLE, WHOLE + 1, 20000)]
                          + [("large", 4097), ("large", WHOLE), ("large", WHOLE + 1)])
 def test_longest_row(kind, d):
     nl, p = graph(kind, d)
