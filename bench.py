@@ -35,8 +35,8 @@ HOP_SRCS = [os.path.join(ROOT, "paper_2511_10073_amd", "csrc", f) for f in ("fil
 # (FETCH_SIZE, WRITE_SIZE) scaled by the same counters for a 1 GiB device
 # copy; valid only for the hop and layout sources they were taken with.
 HOP_TRAFFIC = {"workload": "large-2.2M",
-               "sources_sha256": "b520d68d05a372353b58fbbcacb026cb132afcda6316991c9a45c0f85748f8cd",
-               "bytes_per_launch": 1270171365,
+               "sources_sha256": "cf4f92ba80b6321d6a484943cd3faf35a2827d3565a01a3c89bf2a8b60bd4576",
+               "bytes_per_launch": 1270261929,
                "source": "profiles/k_hop_large-2.2M_l2_fabric_traffic.md"}
 
 
